@@ -10,10 +10,14 @@
 //  * 128 x 128 output tile per workgroup of 4 waves (2 x 2, 64 x 64 per wave), K 128 at a time,
 //    v_mfma_f32_16x16x32_bf16 with fp32 accumulators over all of K, one RNE rounding at the store.
 //  * Operands go global -> registers -> LDS in 16-byte pieces of 8 elements along the operand's
-//    contiguous dimension.  A piece that lies wholly inside the matrix at a 16-byte aligned address
-//    is one vector load; any other piece is fetched element by element, and whatever lies outside
+//    contiguous dimension.  A piece that lies wholly inside the matrix is one vector load whatever its
+//    address (the hardware takes 16 bytes at any 2-byte aligned one; fetched element by element where
+//    a leading dimension is odd, 4099^3 ran at 100 TFLOP/s in all modes, now 480-510); any other
+//    piece is fetched element by element, and whatever lies outside
 //    (rows or columns beyond the block, k beyond K) is zero, in BOTH operands, so that nothing
-//    outside the product can reach an accumulator.  The loads of K-step t+1 are in flight while
+//    outside the product can reach an accumulator.  A block of at least a tile in a direction has no
+//    cut-off pieces in it: its last tile is moved back to the block's edge (777 x 1003 x 391 TN
+//    22 -> 13 us).  The loads of K-step t+1 are in flight while
 //    step t is multiplied (one LDS buffer, two barriers per step).  The step is long because an
 //    edge strip is often a single workgroup per compute unit, with nobody to hide the latency of
 //    its loads behind: 32 k a step measured 1 us per step, whatever the step held.
@@ -40,15 +44,15 @@ struct EdgeCfg {
 };
 
 // Eight consecutive elements starting at p, of which the first `nvalid` (0..8) exist; the rest read as 0.
-// The common cases, a whole aligned piece and no piece at all, contain no use of a loaded value and
+// The common cases, a whole piece and no piece at all, contain no use of a loaded value and
 // hence no wait: the vector loads of all pieces of a K-step are in flight together.  (Written as one
 // element-wise path for everything but the whole piece, the waits inside it serialised the pieces of
 // every wave that had an absent piece: an edge strip with a single valid row took twice as long as
 // one with 128.)
 __device__ __forceinline__ u32x4 edge_load8(const uint16_t* p, int nvalid) {
     u32x4 v{0u, 0u, 0u, 0u};
-    if (nvalid == 8 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) {
-        v = *reinterpret_cast<const u32x4*>(p);
+    if (nvalid == 8) {
+        v = *reinterpret_cast<const u32x4_any*>(p);
     } else if (nvalid > 0) {
         uint32_t e[8];
 #pragma unroll
@@ -137,7 +141,11 @@ __global__ __launch_bounds__(256, 2) void gemm_edge_kernel(const uint16_t* __res
     uint8_t* const sa = smem;
     uint8_t* const sb = smem + Cfg::REGION;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, wm = wave >> 1, wn = wave & 1;
-    const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * Cfg::BM, n0 = (int64_t)(blockIdx.x % tiles_n) * Cfg::BN;
+    // the last tile of a row or column of tiles ends at the block's edge (it repeats some outputs of its
+    // neighbour, to the same bits): no piece of it is cut off by that edge
+    int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * Cfg::BM, n0 = (int64_t)(blockIdx.x % tiles_n) * Cfg::BN;
+    if (M >= Cfg::BM && m0 + Cfg::BM > M) m0 = M - Cfg::BM;
+    if (N >= Cfg::BN && n0 + Cfg::BN > N) n0 = N - Cfg::BN;
 
     EdgeOperand<A_KC> oa;
     EdgeOperand<B_KC> ob;
@@ -200,8 +208,8 @@ __global__ __launch_bounds__(256, 2) void gemm_edge_kernel(const uint16_t* __res
             if (n >= N) continue;
             uint16_t* pc = C + m * ldc + n;
             const uint32_t lo = pack2_bf16(acc[i][j][0], acc[i][j][1]), hi = pack2_bf16(acc[i][j][2], acc[i][j][3]);
-            if (n + 4 <= N && (reinterpret_cast<uintptr_t>(pc) & 7) == 0) {
-                *reinterpret_cast<u32x2*>(pc) = u32x2{lo, hi};
+            if (n + 4 <= N) {
+                *reinterpret_cast<u32x2_any*>(pc) = u32x2{lo, hi};
             } else {
                 pc[0] = (uint16_t)(lo & 0xFFFFu);
                 if (n + 1 < N) pc[1] = (uint16_t)(lo >> 16);

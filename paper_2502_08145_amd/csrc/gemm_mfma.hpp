@@ -35,6 +35,8 @@ namespace axonn {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;   // at any 2-byte aligned address: one load or store all the same
+typedef u32x2 __attribute__((aligned(2))) u32x2_any;
 
 constexpr int KB = 32;   // k per LDS stage; K must be a multiple of it
 
