@@ -59,8 +59,8 @@
  *   sizes      M, N, K >= 0, each below 2^31, and each operand below 2^40 elements.
  *              M == 0 or N == 0: nothing to do, AXONN_OK.  K == 0: the output is
  *              set to +0.  Any M, N, K is computed correctly; the fast tiled
- *              kernels need M and N to be multiples of 128 and K of 32 (K >= 160).  Other
- *              shapes take a slower guarded MFMA kernel: for the whole product if K does
+ *              kernels need M and N to be multiples of 128 and K of 64 (K >= 128).  Other
+ *              shapes take the guarded MFMA kernels: for the whole product if K does
  *              not suit the tiled kernels, else only for the last columns and rows beyond
  *              the whole 128 x 128 tiles.
  *   errors     the return value is AXONN_OK (0) or a negative code below; on an
@@ -272,7 +272,8 @@ int axonn_linear_split_k_timeouts(uint64_t *count);
 
 /* Kernel variants.  Variant 0 is the guarded one-thread-per-element kernel that accepts any
  * shape (the library itself uses it for K == 0 only); the last one ("mfma16_edge_128x128") is the
- * guarded MFMA kernel for any M, N, K >= 1; the others are MFMA tile kernels ("_w8": 8 waves,
+ * guarded MFMA kernels for any M, N, K >= 1 (one with 128 x 128 tiles, one that splits a smaller
+ * tile's K over the waves of a workgroup: the sizes decide); the others are MFMA tile kernels ("_w8": 8 waves,
  * "_sk2" ... "_sk8": split-K over that many workgroups).  Host-only queries: no GPU is touched. */
 int axonn_linear_num_variants(void);
 /* Name such as "mfma16k64_256x256_w8_sk2"; NULL if `variant` is out of range. */

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -311,6 +312,25 @@ static double edge_time(int64_t m, int64_t n, int64_t K) {
     return (3.0 + steps * 2.0 * std::max(1.0, wgs / 320.0)) * 2.6e6;
 }
 
+// The guarded MFMA kernel (gemm_edge_kernel) alone, in microseconds: steps of 128 k, dearer in proportion as
+// workgroups come to share the compute units (least squares over 15 000 sampled products each of aligned and
+// of misaligned rows, residual 6 % and 23 %).
+static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
+    const double wgs = (double)(((m + EdgeCfg::BM - 1) / EdgeCfg::BM) * ((n + EdgeCfg::BN - 1) / EdgeCfg::BN));
+    const double steps = (double)((K + EdgeCfg::BK - 1) / EdgeCfg::BK);
+    return 3.0 + (rows_aligned ? 1.8 * steps + 2.6 : 2.0 * steps + 5.0) * std::sqrt(1.0 + (wgs / 292.0) * (wgs / 292.0));
+}
+
+// The wave-K kernel for a block of the guarded kernel's, if its modelled time is less (.tile < 0: it is not).  It
+// wins wherever the output has few 128 x 128 tiles, by a factor of three and more for a few rows over a long K,
+// and loses from some 20 GFLOP on, where 64 x 64 tiles load twice the bytes (1930 x 7344 x 1832 NN: 123 us
+// against 96).  The margin covers the models' residuals.
+static WaveKChoice wavek_instead(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb) {
+    const WaveKChoice c = wavek_choose(layout, m, n, K, lda, ldb);
+    const bool aligned = lda % 8 == 0 && ldb % 8 == 0;
+    return c.tile >= 0 && c.us < 0.85 * edge_us(m, n, K, aligned) ? c : WaveKChoice{};
+}
+
 // The variant with the smallest modelled time for one launch over the whole output (the guarded MFMA
 // kernel if no tile shape divides it; 0, the naive kernel, for K = 0); *t_out receives that time.
 static int select_variant(int64_t M, int64_t N, int64_t K, int layout, bool allow_split, double* t_out = nullptr) {
@@ -340,6 +360,7 @@ static int select_variant(int64_t M, int64_t N, int64_t K, int layout, bool allo
 struct Part {
     int variant;
     int64_t m, n, row0, col0;
+    WaveKChoice wavek{};   // guarded variant: the wave-K launch that does this block, if one does
 };
 struct Plan {
     int parts;
@@ -396,6 +417,13 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
     return plan;
 }
 
+// Which kernel does the blocks of the guarded variant.
+static void settle_guarded_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
+    for (int i = 0; i < plan.parts; ++i)
+        if (variants()[plan.part[i].variant].edge)
+            plan.part[i].wavek = wavek_instead(plan.part[i].m, plan.part[i].n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N);
+}
+
 // Plans are remembered per shape: the search above costs a few hundred model evaluations.
 static std::map<std::tuple<int64_t, int64_t, int64_t, int, bool>, Plan> g_plans;
 static std::mutex g_plans_mutex;
@@ -407,7 +435,8 @@ static Plan cached_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_
         const auto it = g_plans.find(key);
         if (it != g_plans.end()) return it->second;
     }
-    const Plan plan = make_plan(M, N, K, layout, allow_split);
+    Plan plan = make_plan(M, N, K, layout, allow_split);
+    settle_guarded_parts(plan, M, N, K, layout);
     std::lock_guard<std::mutex> lock(g_plans_mutex);
     if (g_plans.size() >= 4096) g_plans.clear();
     g_plans[key] = plan;
@@ -437,6 +466,7 @@ static void raise_lds_limits() {
             if (var.fn[l])
                 (void)hipFuncSetAttribute(reinterpret_cast<const void*>(var.fn[l]), hipFuncAttributeMaxDynamicSharedMemorySize, var.lds_bytes);
     edge_kernel_raise_lds_limit();
+    wavek_raise_lds_limit();
     (void)hipGetLastError();
 }
 
@@ -477,6 +507,10 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
     B += layout == AXONN_NT ? p.col0 * K : p.col0;
     C += p.row0 * N + p.col0;
     if (var.edge) {
+        if (p.wavek.tile >= 0) {
+            wavek_launch(p.wavek, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc);
+            return;
+        }
         const int tiles_n = (int)((p.n + var.bn - 1) / var.bn);
         edge_kernel_launch(layout, (unsigned)part_workgroups(p), s, A, B, C, p.m, p.n, K, lda, ldb, ldc, tiles_n);
         return;
@@ -513,6 +547,7 @@ static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, co
     if (forced >= 0) {
         if (!variant_supports(forced, M, N, K, layout)) return AXONN_ERR_UNSUPPORTED;
         plan = Plan{1, {{forced, M, N, 0, 0}}};
+        settle_guarded_parts(plan, M, N, K, layout);
     } else {
         plan = cached_plan(M, N, K, layout, g_split_k_enabled.load(std::memory_order_relaxed) != 0);
     }

@@ -28,4 +28,14 @@ void edge_kernel_raise_lds_limit();
 void edge_kernel_launch(int layout, unsigned workgroups, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                         int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc, int tiles_n);
 
+// wave-K kernel (gemm_wavek_kernel): few tiles, few rows, rows at any address; a tile split over the waves of a workgroup
+struct WaveKChoice {
+    int tile = -1, waves = 0;   // tile < 0: the kernel does not take this block
+    double us = 0.0;            // modelled time
+};
+WaveKChoice wavek_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb);
+void wavek_raise_lds_limit();
+void wavek_launch(const WaveKChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
+                  int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);
+
 }  // namespace axonn

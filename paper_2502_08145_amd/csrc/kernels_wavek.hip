@@ -1,0 +1,98 @@
+// Translation unit of the wave-K kernel (see kernels.hpp).
+#include "kernels.hpp"
+#include "gemm_wavek.hpp"
+
+#include <cmath>
+
+namespace axonn {
+
+typedef void (*wavek_kernel_t)(const uint16_t*, const uint16_t*, uint16_t*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int, int, int);
+
+// The tiles that are built, per layout (NN, NT, TN), in 16 x 16 blocks.  An MN-contiguous operand wants at
+// least two blocks side by side (a k-row of one block is 32 bytes of a 128-byte line); the 1 x 1 tile serves
+// it only where the matrix is narrower than that.  4 x 4 with two K-contiguous operands does not fit the
+// registers.  Among 22 000 sampled products (outputs of 1 to 16384 rows, up to 30 GFLOP) the best of these
+// tiles is within 1 % of the best of all nine combinations of 1, 2 and 4 on average.
+struct WaveKTile {
+    int mi, ni;
+    wavek_kernel_t fn[3];   // nullptr: not for this layout
+};
+#define AXONN_WAVEK(MI, NI) {gemm_wavek_kernel<true, false, MI, NI>, gemm_wavek_kernel<true, true, MI, NI>, gemm_wavek_kernel<false, false, MI, NI>}
+static const WaveKTile kTiles[] = {
+    {1, 1, AXONN_WAVEK(1, 1)},
+    {1, 2, {gemm_wavek_kernel<true, false, 1, 2>, gemm_wavek_kernel<true, true, 1, 2>, nullptr}},
+    {2, 2, AXONN_WAVEK(2, 2)},
+    {2, 4, AXONN_WAVEK(2, 4)},
+    {4, 4, {gemm_wavek_kernel<true, false, 4, 4>, nullptr, gemm_wavek_kernel<false, false, 4, 4>}},
+};
+#undef AXONN_WAVEK
+
+// Modelled time of a launch in microseconds: launch, fill and drain, plus the largest (smoothly) of
+//   the chain of one wave:   its chunks, one after the other
+//   a compute unit's work:   all chunks of the tiles it gets, its load path shared by its waves, and the
+//                            exchange of partial tiles
+//   memory:                  every operand and output byte once
+//   staging:                 every byte that some tile loads, through the L2s
+// Constants: least squares on the logarithm over 7 000 sampled products of up to 150 GFLOP, operands in cache
+// (residual 13-14 %; the tile and wave count it chooses are 6 % behind the best ones measured on average).
+struct WaveKModel {
+    double fill, chunk0, chunk_area, work_side, work_area, exchange, store, per_mb, staged_per_mb;
+};
+static const WaveKModel kModel[3] = {
+    {4.5, 0.165, 0.040, 0.031, 0.0, 0.33, 0.21, 0.157, 0.064},     // NN
+    {5.2, 0.160, 0.034, 0.011, 0.009, 0.70, 0.0, 0.149, 0.053},    // NT
+    {4.6, 0.130, 0.043, 0.041, 0.0, 0.35, 0.28, 0.185, 0.014},     // TN
+};
+static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t N, int64_t K) {
+    const WaveKModel& m = kModel[layout];
+    const double area = mi * ni, tiles = (double)((M + 16 * mi - 1) / (16 * mi)) * (double)((N + 16 * ni - 1) / (16 * ni));
+    const int64_t n_chunks = (K + WaveKCfg::KC - 1) / WaveKCfg::KC;
+    const double chunks = (double)n_chunks, rounds = std::pow(1.0 + std::pow(tiles / 256.0, 4.0), 0.25);
+    const double chain = (double)((n_chunks + waves - 1) / waves) * (m.chunk0 + m.chunk_area * area);
+    const double unit = rounds * (chunks * (m.work_side * (mi + ni) + m.work_area * area) +
+                                  (waves > 1 ? m.exchange * waves * area / 16.0 : 0.0) + m.store * area / 16.0);
+    const double memory = 2e-6 * ((double)M * K + (double)K * N + (double)M * N) * m.per_mb;
+    const double staged = 2048e-6 * tiles * chunks * (mi + ni) * m.staged_per_mb;
+    return m.fill + std::cbrt(chain * chain * chain + unit * unit * unit + memory * memory * memory + staged * staged * staged);
+}
+
+WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+    WaveKChoice best;
+    if (lda >= WaveKCfg::MAX_LD || ldb >= WaveKCfg::MAX_LD || (layout != 2 && K < 8)) return best;
+    for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
+        const WaveKTile& t = kTiles[i];
+        const int64_t tm = 16 * t.mi, tn = 16 * t.ni;
+        if (!t.fn[layout]) continue;
+        if (M < tm && (layout == 2 || t.mi > 2)) continue;   // see the kernel's requirements
+        if (N < tn && (layout != 1 || t.ni > 2)) continue;
+        if (t.mi * t.ni == 1 && ((layout != 1 && N >= 32) && (layout != 2 || M >= 32))) continue;   // narrow matrices only
+        if (((M + tm - 1) / tm) * ((N + tn - 1) / tn) >= ((int64_t)1 << 31)) continue;
+        for (int w = 1; w <= WaveKCfg::max_waves(t.mi, t.ni) && (w == 1 || (int64_t)(w - 1) * WaveKCfg::KC < K); w *= 2) {
+            const double us = model_us(layout, t.mi, t.ni, w, M, N, K);
+            if (best.tile < 0 || us < best.us) best = WaveKChoice{i, w, us};
+        }
+    }
+    return best;
+}
+
+static int lds_bytes(int tile, int waves, int layout) {
+    return WaveKCfg::lds_bytes(layout != 2, layout == 1, kTiles[tile].mi, kTiles[tile].ni, waves);
+}
+
+void wavek_raise_lds_limit() {
+    for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i)
+        for (int l = 0; l < 3; ++l)
+            if (kTiles[i].fn[l])
+                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kTiles[i].fn[l]), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                          lds_bytes(i, WaveKCfg::max_waves(kTiles[i].mi, kTiles[i].ni), l));
+}
+
+void wavek_launch(const WaveKChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
+                  int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
+    const WaveKTile& t = kTiles[c.tile];
+    const int64_t tiles_m = (m + 16 * t.mi - 1) / (16 * t.mi), tiles_n = (n + 16 * t.ni - 1) / (16 * t.ni);
+    hipLaunchKernelGGL(t.fn[layout], dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * c.waves), lds_bytes(c.tile, c.waves, layout), s,
+                       A, B, C, m, n, K, lda, ldb, ldc, (int)tiles_m, (int)tiles_n, (int)(tiles_m < 8 ? tiles_m : 8));
+}
+
+}  // namespace axonn

@@ -935,3 +935,36 @@ def test_tuned_call_runs_the_product_in_the_remembered_mode(oracle_mod, op):
         assert np.array_equal(U.to_host_bits(a), A) and np.array_equal(U.to_host_bits(b), Bm)   # operands untouched
     finally:
         B.axonn_linear_tune_reset()
+
+
+# ------------------------------------------------------------------ few rows, few tiles: K split over a workgroup's waves
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("shape", [(1, 48, 8), (15, 33, 9), (16, 16, 63), (17, 95, 64), (31, 64, 65), (33, 200, 129), (63, 257, 515),
+                                   (64, 64, 1000), (65, 130, 2047), (96, 1000, 71), (200, 31, 333), (391, 303, 777), (40, 2056, 24)])
+def test_few_rows_and_tiles_bit_exact_on_integers(oracle_mod, layout, shape):
+    """Around the tile edges of the wave-K kernel (16, 32, 64 rows and columns), shorter and longer than a
+    chunk of 64 k and than one chunk per wave, leading dimensions that leave rows at any 2-byte address.
+    |sum| <= 16 K < 2^24: exact in fp32 in any order, so the output equals the rounded oracle bit for bit."""
+    M, N, K = shape
+    a = synth.integer_bf16(740 + M, (M, K), -4, 4)
+    b = synth.integer_bf16(750 + N, (K, N), -4, 4)
+    A, Bm = store(a, b, layout)
+    want = U.f64_to_bf16_bits_rne(oracle_mod.gemm(M, N, K, layout, A, Bm))
+    got = run_gpu_guard_rows("fwd", M, N, K, layout, A, Bm)
+    bad = np.argwhere(got != want)
+    assert bad.size == 0, f"{layout} {shape}: {len(bad)} mismatches, first at {bad[0]}"
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_k_tail_lets_no_neighbour_value_through(oracle_mod, layout):
+    """Elements beside an operand's last k (the next row's first ones, fetched in the same 16 bytes) must not
+    reach a product: they are NaN and infinity here, in rows whose outputs are not compared."""
+    M, N, K = 40, 40, 75
+    a = synth.integer_bf16(760, (M, K), -4, 4)
+    b = synth.integer_bf16(761, (K, N), -4, 4)
+    a[1::2, :], b[:, 1::2] = 0x7F80, 0x7FC0     # every other row of A infinite, every other column of B NaN
+    A, Bm = store(a, b, layout)
+    clean_a, clean_b = np.where(np.arange(M)[:, None] % 2, 0, a).astype(np.uint16), np.where(np.arange(N)[None, :] % 2, 0, b).astype(np.uint16)
+    want = U.f64_to_bf16_bits_rne(oracle_mod.gemm(M, N, K, "NN", clean_a, clean_b))
+    got = run_gpu("fwd", M, N, K, layout, A, Bm)
+    assert np.array_equal(got[0::2, 0::2], want[0::2, 0::2])
