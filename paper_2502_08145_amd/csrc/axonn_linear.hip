@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -70,6 +71,9 @@ struct Variant {
     // do not: neither condition alone describes both), so these stand.
     double eff[3];
     tile_kernel_t fn[3];             // per layout
+    // Microseconds per 64 k of a full round of workgroups, per layout, operands in cache (block_us); 0: not used there.
+    double us64[3] = {0.0, 0.0, 0.0};
+    tile_kernel_t fn_tail[3] = {nullptr, nullptr, nullptr};   // for a K that is no multiple of 64
     bool edge = false;               // the guarded MFMA kernel: any shape, launched through edge_kernel_launch
     int resident = 0;                // > 0: a grid of at most this many workgroups walks the tiles (one per compute unit)
 };
@@ -140,6 +144,21 @@ static std::vector<Variant> make_variants() {
                                          "mfma16k64_256x256_w8_sk6", "mfma16k64_256x256_w8_sk7", "mfma16k64_256x256_w8_sk8"};
     for (int sp = 2; sp <= 8; ++sp) k64(k64_sk[sp - 2], sp);
     // guarded MFMA kernel: ragged shapes and the edge strips of ragged outputs
+    // fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %)
+    static const struct { const char* name; double us64[3]; } measured[] = {
+        {"mfma16_128x128", {0.530, 0.565, 0.557}},       {"mfma16_128x256", {0.927, 0.887, 0.950}},
+        {"mfma16_128x256_w8", {0.773, 0.818, 0.852}},    {"mfma16_256x128", {0.885, 0.888, 0.951}},
+        {"mfma16k64_128x256", {0.0, 0.817, 0.0}},        {"mfma16k64_256x128", {0.0, 0.819, 0.0}},
+        {"mfma16k64_256x256_w8", {1.284, 1.219, 1.263}},
+    };
+    for (Variant& x : v)
+        for (const auto& q : measured)
+            if (std::strcmp(x.name, q.name) == 0) {
+                std::copy(q.us64, q.us64 + 3, x.us64);
+                for (int l = 0; l < 3; ++l)
+                    x.fn_tail[l] = !x.k64 ? ring_kernel_small(x.bm, x.bn, x.threads / 128, false, l, true)
+                                   : x.bm * x.bn == 256 * 256 ? k64_kernel(false, l, true) : k64_kernel_half(x.bm, x.bn, false, l, true);
+            }
     Variant e{"mfma16_edge_128x128", EdgeCfg::BM, EdgeCfg::BN, EdgeCfg::NT, EdgeCfg::LDS_BYTES, 1, 1, 1, false, {0, 0, 0}, {nullptr, nullptr, nullptr}};
     e.edge = true;
     v.push_back(e);
@@ -227,6 +246,10 @@ static Scratch static_scratch() {
 static std::atomic<int> g_forced{-1};
 static std::once_flag g_attr_once[kMaxDevices];   // the LDS limits are a per-device property of a kernel
 
+// per-lane address offsets are 32 bits: up to 16 rows of a K-contiguous operand, 4 (64-k kernel: 36)
+// k-rows of an MN-contiguous one, plus the K window of a K-contiguous one
+constexpr int64_t kMaxTileDim = (int64_t)1 << 24;
+
 static bool variant_supports(int v, int64_t M, int64_t N, int64_t K, int layout) {
     if (v < 0 || v >= num_variants() || layout < 0 || layout > 2) return false;
     const Variant& var = variants()[v];
@@ -234,9 +257,6 @@ static bool variant_supports(int v, int64_t M, int64_t N, int64_t K, int layout)
     if (M <= 0 || N <= 0 || K <= 0) return false;
     if (var.edge) return ((M + var.bm - 1) / var.bm) * ((N + var.bn - 1) / var.bn) < ((int64_t)1 << 31);
     if (!var.fn[layout]) return false;   // a kernel for one layout only
-    // per-lane address offsets are 32 bits: up to 16 rows of a K-contiguous operand, 4 (64-k kernel: 36)
-    // k-rows of an MN-contiguous one, plus the K window of a K-contiguous one
-    constexpr int64_t kMaxTileDim = (int64_t)1 << 24;
     if (M > kMaxTileDim || N > kMaxTileDim || K > kMaxTileDim) return false;
     if (M % var.bm != 0 || N % var.bn != 0 || K % (var.kstep * var.splits) != 0 || K / var.splits < var.min_k) return false;
     if (var.splits == 1) return true;
@@ -301,16 +321,8 @@ static double model_time(int v, int64_t M, int64_t N, int64_t K, int layout, boo
     return rounds * var.bm * var.bn * k_cost / e;
 }
 
-// What the guarded MFMA kernel takes for an m x n block, in the model's units (2.6e6 to the
-// microsecond: a 256 x 256 tile over K = 4096 is 2.7e8 and takes about 100 us).  Its K-steps of
-// 128 are a chain of load, barrier, LDS store, barrier, multiply: measured 1.9 us per step for a
-// workgroup that has a compute unit to itself, 1.6 us with the chip full (two to a CU, 205 us for
-// 4096^3 in 1024 workgroups), plus launch and epilogue.
-static double edge_time(int64_t m, int64_t n, int64_t K) {
-    const double wgs = (double)(((m + EdgeCfg::BM - 1) / EdgeCfg::BM) * ((n + EdgeCfg::BN - 1) / EdgeCfg::BN));
-    const double steps = (double)((K + EdgeCfg::BK - 1) / EdgeCfg::BK);
-    return (3.0 + steps * 2.0 * std::max(1.0, wgs / 320.0)) * 2.6e6;
-}
+// model_time's units to the microsecond: a 256 x 256 tile over K = 4096 is 2.7e8 and takes about 100 us
+constexpr double kUnitsPerUs = 2.6e6;
 
 // The guarded MFMA kernel (gemm_edge_kernel) alone, in microseconds: steps of 128 k, dearer in proportion as
 // workgroups come to share the compute units (least squares over 15 000 sampled products each of aligned and
@@ -321,14 +333,64 @@ static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
     return 3.0 + (rows_aligned ? 1.8 * steps + 2.6 : 2.0 * steps + 5.0) * std::sqrt(1.0 + (wgs / 292.0) * (wgs / 292.0));
 }
 
-// The wave-K kernel for a block of the guarded kernel's, if its modelled time is less (.tile < 0: it is not).  It
-// wins wherever the output has few 128 x 128 tiles, by a factor of three and more for a few rows over a long K,
-// and loses from some 20 GFLOP on, where 64 x 64 tiles load twice the bytes (1930 x 7344 x 1832 NN: 123 us
-// against 96).  The margin covers the models' residuals.
-static WaveKChoice wavek_instead(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb) {
-    const WaveKChoice c = wavek_choose(layout, m, n, K, lda, ldb);
-    const bool aligned = lda % 8 == 0 && ldb % 8 == 0;
-    return c.tile >= 0 && c.us < 0.85 * edge_us(m, n, K, aligned) ? c : WaveKChoice{};
+// How a block of the output that is no whole number of tiles is computed (guarded variant).
+struct GuardedChoice {
+    int tile = -1;           // >= 0: this tile variant, its last tiles moved back to the block's edge (TileGrid)
+    WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel; else the guarded MFMA kernel
+    int lead_m = 0, lead_n = 0;   // rows and columns before the block that the launch covers as well
+    double us = 0.0;         // modelled time, operands in cache
+};
+
+// A tile variant over an m x n block, in microseconds; < 0: it cannot run there.
+static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
+    const Variant& x = variants()[v];
+    const int64_t k_padded = (K + 63) / 64 * 64;   // every tile kernel takes K 64 at a time
+    if (x.us64[layout] <= 0.0 || m < x.bm || n < x.bn || k_padded < x.min_k || K <= 64) return -1.0;
+    if (K != k_padded && !x.fn_tail[layout]) return -1.0;
+    if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0) return -1.0;   // 16-byte direct loads and stores
+    if (std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return -1.0;
+    const int64_t tiles = ((m + x.bm - 1) / x.bm) * ((n + x.bn - 1) / x.bn), rest = tiles % 256;
+    const double rounds = (double)(tiles / 256) + (rest ? 0.76 + 0.24 * (double)rest / 256.0 : 0.0);
+    const double fixed = x.bm * x.bn <= 128 * 128 ? 1.9 : x.bm * x.bn < 256 * 256 ? 3.6 : 5.6;   // per round
+    return 3.0 + rounds * ((double)(k_padded / 64) * x.us64[layout] + fixed);
+}
+
+// The kernel with the smallest modelled time.  The tile kernels win as soon as their tiles fill a good part of the
+// chip (1064 x 4168 x 1608 NN: 23 us against 39 for the guarded kernel and 43 for the wave-K one), the wave-K kernel
+// wherever the output has few 128 x 128 tiles (by a factor of three and more for a few rows over a long K; it
+// loses from some 20 GFLOP on, where 64 x 64 tiles load twice the bytes: 1930 x 7344 x 1832 NN 123 us against
+// 96 for the guarded kernel).  The margin between those two covers their models' residuals.
+static GuardedChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
+    GuardedChoice best;
+    best.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
+    const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb);
+    if (wk.tile >= 0 && wk.us < 0.85 * best.us) {
+        best.wavek = wk;
+        best.us = wk.us;
+    }
+    for (int v = 1; v < edge_variant(); ++v) {
+        const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
+        if (us >= 0.0 && us < best.us) {
+            best = GuardedChoice{};
+            best.tile = v;
+            best.us = us;
+        }
+    }
+    return best;
+}
+// The same for the block at (row0, col0) of the M x N product.  An edge strip of fewer than 16 rows or columns of
+// an MN-contiguous operand is too narrow for the wave-K kernel and would take the guarded one, element by element
+// (2048 x 8 over K = 4096: 60 us against 12); it takes the 16 last ones instead, some of which the launch over the
+// whole tiles, which comes first, has written before.
+static GuardedChoice guarded_choice(int64_t row0, int64_t col0, int64_t m, int64_t n, int64_t M, int64_t N, int64_t K, int layout) {
+    const int lead_m = (layout == AXONN_TN && m < 16 && row0 >= 16) ? (int)(16 - m) : 0;
+    const int lead_n = (layout != AXONN_NT && n < 16 && col0 >= 16) ? (int)(16 - n) : 0;
+    GuardedChoice g = guarded_choice(m + lead_m, n + lead_n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N, N);
+    if (g.tile < 0 && g.wavek.tile >= 0) {
+        g.lead_m = lead_m;
+        g.lead_n = lead_n;
+    }
+    return g;
 }
 
 // The variant with the smallest modelled time for one launch over the whole output (the guarded MFMA
@@ -345,7 +407,7 @@ static int select_variant(int64_t M, int64_t N, int64_t K, int layout, bool allo
     }
     if (best == 0 && variant_supports(edge_variant(), M, N, K, layout)) {
         best = edge_variant();
-        best_t = edge_time(M, N, K);
+        best_t = guarded_choice(0, 0, M, N, M, N, K, layout).us * kUnitsPerUs;
     }
     if (t_out) *t_out = best_t;
     return best;
@@ -360,7 +422,7 @@ static int select_variant(int64_t M, int64_t N, int64_t K, int layout, bool allo
 struct Part {
     int variant;
     int64_t m, n, row0, col0;
-    WaveKChoice wavek{};   // guarded variant: the wave-K launch that does this block, if one does
+    GuardedChoice guarded{};   // guarded variant: how
 };
 struct Plan {
     int parts;
@@ -368,27 +430,40 @@ struct Plan {
 };
 static_assert(AXONN_MAX_PLAN_PARTS >= 4, "two launches over whole tiles and two edge strips");
 
-static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_split) {
+static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_split, double* t_out = nullptr) {
     double t_one = 0;
     Plan plan{1, {{select_variant(M, N, K, layout, allow_split, &t_one), M, N, 0, 0}}};
+    if (t_out) *t_out = t_one;
     if (is_guarded(plan.part[0].variant)) {
-        // Ragged output of some size: the whole 128 x 128 tiles go to the tile kernels (if K suits
-        // them), the last columns and the last rows to the guarded kernel, as strips of their own.
+        // Ragged output: one launch (guarded_choice: on tile kernels the last tiles overlap their
+        // neighbours), or the whole 128 x 128 tiles to the tile kernels (if K suits them) and the last
+        // columns and the last rows as strips of their own.  Strips pay where the overlapping tiles would
+        // start another round: 2049 x 8192 x 2048 NN is one round of 256 large tiles and a strip of one row
+        // (62 us), or 288 tiles in one launch (87 us).
         const int64_t mm = M - M % 128, nm = N - N % 128;
         // the tile kernels move 16 bytes at a time: every row of the operands and of the output, as
         // stored in the whole matrices, has to start on a 16-byte boundary (K is a multiple of 32 here)
         const bool rows_aligned = N % 8 == 0 && (layout != AXONN_TN || M % 8 == 0);
         if (mm > 0 && nm > 0 && (mm != M || nm != N) && rows_aligned) {
-            constexpr double kNextLaunch = 8.0e6;   // about 3 us, as for the two-launch plans below
+            constexpr double kLaunch = 3.0;
+            // A ragged product of up to 640 whole tiles never touches the scratch area, so calls of that size
+            // may overlap on several streams; the whole tiles of a larger one may be split as any whole output.
+            const bool split = allow_split && (mm / 128) * (nm / 128) > 640;
             double t_tiles = 0;
-            const int v_tiles = select_variant(mm, nm, K, layout, allow_split, &t_tiles);
-            const double t_strips = (nm != N ? edge_time(mm, N - nm, K) + kNextLaunch : 0.0) +
-                                    (mm != M ? edge_time(M - mm, N, K) + kNextLaunch : 0.0);
-            if (!is_guarded(v_tiles) && t_tiles + t_strips < t_one) {
-                const Plan inner = make_plan(mm, nm, K, layout, allow_split);
-                plan = inner;
-                if (nm != N) plan.part[plan.parts++] = Part{edge_variant(), mm, N - nm, 0, nm};
-                if (mm != M) plan.part[plan.parts++] = Part{edge_variant(), M - mm, N, mm, 0};
+            const int v_tiles = select_variant(mm, nm, K, layout, split, &t_tiles);
+            if (!is_guarded(v_tiles)) {
+                const Plan inner = make_plan(mm, nm, K, layout, split, &t_tiles);
+                double t = t_tiles / kUnitsPerUs + kLaunch;
+                if (nm != N) t += guarded_choice(0, nm, mm, N - nm, M, N, K, layout).us;
+                if (mm != M) t += guarded_choice(mm, 0, M - mm, N, M, N, K, layout).us;
+                // beside two rounds and more the strips' share is small and so is what the models can tell
+                // apart: strips then, whose tiled part is a whole product's plan
+                const double favour = (mm / 128) * (nm / 128) >= 4 * 256 ? 1.4 : 1.0;
+                if (t < favour * t_one / kUnitsPerUs) {
+                    plan = inner;
+                    if (nm != N) plan.part[plan.parts++] = Part{edge_variant(), mm, N - nm, 0, nm};
+                    if (mm != M) plan.part[plan.parts++] = Part{edge_variant(), M - mm, N, mm, 0};
+                }
             }
         }
         return plan;
@@ -408,6 +483,7 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
         const int v2 = select_variant(m2, n2, K, layout, allow_split, &t2);
         if (is_guarded(v1) || is_guarded(v2) || t1 + t2 + kSecondLaunch >= best_t) return;
         best_t = t1 + t2 + kSecondLaunch;
+        if (t_out) *t_out = best_t;
         plan = Plan{2, {{v1, m1, n1, 0, 0}, {v2, m2, n2, along_n ? 0 : m1, along_n ? n1 : 0}}};
     };
     // second blocks of up to half a round of large tiles, in steps of one tile column / row
@@ -417,11 +493,12 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
     return plan;
 }
 
-// Which kernel does the blocks of the guarded variant.
+// Which kernels do the blocks of the guarded variant.
 static void settle_guarded_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
-    for (int i = 0; i < plan.parts; ++i)
-        if (variants()[plan.part[i].variant].edge)
-            plan.part[i].wavek = wavek_instead(plan.part[i].m, plan.part[i].n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N);
+    for (int i = 0; i < plan.parts; ++i) {
+        Part& p = plan.part[i];
+        if (variants()[p.variant].edge) p.guarded = guarded_choice(p.row0, p.col0, p.m, p.n, M, N, K, layout);
+    }
 }
 
 // Plans are remembered per shape: the search above costs a few hundred model evaluations.
@@ -463,8 +540,8 @@ static int check_args(int64_t M, int64_t N, int64_t K, int layout, const void* a
 static void raise_lds_limits() {
     for (const Variant& var : variants())
         for (int l = 0; l < 3; ++l)
-            if (var.fn[l])
-                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(var.fn[l]), hipFuncAttributeMaxDynamicSharedMemorySize, var.lds_bytes);
+            for (const tile_kernel_t fn : {var.fn[l], var.fn_tail[l]})
+                if (fn) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, var.lds_bytes);
     edge_kernel_raise_lds_limit();
     wavek_raise_lds_limit();
     (void)hipGetLastError();
@@ -498,24 +575,10 @@ static int64_t part_workgroups(const Part& p) {
     return ((p.m + var.bm - 1) / var.bm) * ((p.n + var.bn - 1) / var.bn) * var.splits;
 }
 
-// One kernel launch over the block `p` of the M x N output.
-static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layout, const uint16_t* A, const uint16_t* B,
-                        uint16_t* C, const Scratch& scratch, hipStream_t s) {
-    const Variant& var = variants()[p.variant];
-    const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N, ldc = N;
-    A += layout == AXONN_TN ? p.row0 : p.row0 * K;
-    B += layout == AXONN_NT ? p.col0 * K : p.col0;
-    C += p.row0 * N + p.col0;
-    if (var.edge) {
-        if (p.wavek.tile >= 0) {
-            wavek_launch(p.wavek, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc);
-            return;
-        }
-        const int tiles_n = (int)((p.n + var.bn - 1) / var.bn);
-        edge_kernel_launch(layout, (unsigned)part_workgroups(p), s, A, B, C, p.m, p.n, K, lda, ldb, ldc, tiles_n);
-        return;
-    }
-    const int tiles_m = (int)(p.m / var.bm), tiles_n = (int)(p.n / var.bn);
+// A tile kernel over the m x n block that starts at A, B, C.
+static void launch_tiles(const Variant& var, int64_t m, int64_t n, int64_t K, int layout, const uint16_t* A, const uint16_t* B,
+                         uint16_t* C, int64_t lda, int64_t ldb, int64_t ldc, const Scratch& scratch, hipStream_t s) {
+    const int tiles_m = (int)((m + var.bm - 1) / var.bm), tiles_n = (int)((n + var.bn - 1) / var.bn);
     const int64_t tiles = (int64_t)tiles_m * tiles_n;
     const int group_m = tiles_m < 8 ? tiles_m : 8;
     SplitK sk{nullptr, nullptr, nullptr, 0u, 1, 0};
@@ -528,8 +591,32 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
         sk = SplitK{scratch.partials, scratch.flags, scratch.timeouts(), epoch, var.splits, skew};
     }
     const int64_t grid = var.resident > 0 ? std::min<int64_t>(tiles, var.resident) : tiles * var.splits;
-    hipLaunchKernelGGL(var.fn[layout], dim3((unsigned)grid), dim3(var.threads), var.lds_bytes, s,
-                       A, B, C, (int)K, (int)lda, (int)ldb, (int)ldc, tiles_m, tiles_n, group_m, sk);
+    const int k_tail = (int)(K % 64);
+    hipLaunchKernelGGL(k_tail ? var.fn_tail[layout] : var.fn[layout], dim3((unsigned)grid), dim3(var.threads), var.lds_bytes, s,
+                       A, B, C, (int)(K - k_tail + (k_tail ? 64 : 0)), (int)lda, (int)ldb, (int)ldc,
+                       TileGrid{tiles_m, tiles_n, (int)(m - var.bm), (int)(n - var.bn), k_tail}, group_m, sk);
+}
+
+// One kernel launch over the block `p` of the M x N output.
+static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layout, const uint16_t* A, const uint16_t* B,
+                        uint16_t* C, const Scratch& scratch, hipStream_t s) {
+    const Variant& var = variants()[p.variant];
+    const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N, ldc = N;
+    A += layout == AXONN_TN ? p.row0 : p.row0 * K;
+    B += layout == AXONN_NT ? p.col0 * K : p.col0;
+    C += p.row0 * N + p.col0;
+    if (var.edge && p.guarded.tile < 0) {
+        if (p.guarded.wavek.tile >= 0) {
+            const int64_t dm = p.guarded.lead_m, dn = p.guarded.lead_n;
+            wavek_launch(p.guarded.wavek, layout, s, A - (layout == AXONN_TN ? dm : dm * K), B - (layout == AXONN_NT ? dn * K : dn),
+                         C - dm * N - dn, p.m + dm, p.n + dn, K, lda, ldb, ldc);
+            return;
+        }
+        const int tiles_n = (int)((p.n + var.bn - 1) / var.bn);
+        edge_kernel_launch(layout, (unsigned)part_workgroups(p), s, A, B, C, p.m, p.n, K, lda, ldb, ldc, tiles_n);
+        return;
+    }
+    launch_tiles(var.edge ? variants()[p.guarded.tile] : var, p.m, p.n, K, layout, A, B, C, lda, ldb, ldc, scratch, s);
 }
 
 // Where a call's split-K kernels find their scratch area.

@@ -77,6 +77,18 @@ __device__ __forceinline__ void direct_load16(uint32_t lds_dst, const uint8_t* b
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(voff), "s"(base), "s"(lds_dst) : "memory", "m0");
 }
+// The same with an address per lane.
+__device__ __forceinline__ void direct_load16_from(uint32_t lds_dst, const uint8_t* lane_src) {
+    lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(lane_src), "s"(lds_dst) : "memory", "m0");
+}
+// What a lane fetches in place of a piece beyond the last k: direct loads write LDS, so a zero has to come
+// from memory too.
+static __device__ const u32x4 g_zero_piece = {0u, 0u, 0u, 0u};
+__device__ __forceinline__ const uint8_t* piece_or_zero(const uint8_t* piece, bool exists) {
+    return exists ? piece : reinterpret_cast<const uint8_t*>(&g_zero_piece);
+}
 // LDS reads.  An LDS read completes asynchronously and the compiler does not know that: to it the
 // asm statement has produced its result at once.  The destination is therefore declared read-write
 // ("+v"), which pins a fragment to ONE set of registers for the whole kernel: the compiler can then
@@ -213,6 +225,13 @@ struct OperandKContig {   // global P[row * ld + k]
         else
             direct_load16(lds_dst[C] + stage_off, base[C], voff[0]);
     }
+    // The same load for K-step STEP (0 or 1) of a shorter last 64 k taken first: `delta` bytes beyond the window's
+    // address, zero for the pieces behind the `left` (1 .. 63) k that exist (whole pieces: rows are 16-byte aligned).
+    template <int C, int AHEAD, int STEP>
+    __device__ __forceinline__ void issue_tail(uint32_t stage_off, size_t delta, int left, int lane, int /*wave*/) const {
+        const int k = 32 * STEP + 8 * ((lane & 3) ^ ((lane >> (2 + SWZ)) & 3));
+        direct_load16_from(lds_dst[C] + stage_off + (PAIR ? lds_par : 0u), piece_or_zero(base[C] + voff[PAIR ? AHEAD : 0] + delta, k < left));
+    }
     // next K-step: window one step on and, PAIR, the other row groups
     __device__ __forceinline__ void advance() {
         if constexpr (PAIR) {
@@ -310,6 +329,11 @@ struct OperandMNContig {   // global P[k * ld + row]
         static_assert(AHEAD == 0, "loaded one K-step at a time");
         direct_load16(lds_dst[C] + stage_off, base, voff[C]);
     }
+    template <int C, int AHEAD, int STEP>
+    __device__ __forceinline__ void issue_tail(uint32_t stage_off, size_t delta, int left, int lane, int wave) const {
+        const int k = 32 * STEP + KR * (QL * wave + C) + lane / CPR;
+        direct_load16_from(lds_dst[C] + stage_off, piece_or_zero(base + voff[C] + delta, k < left));
+    }
     // One K-step on.  The window moves in the (64-bit, scalar) base pointers, not in the 32-bit
     // per-lane offsets: a panel of more than 4 GB (K * ld * 2 bytes) would wrap those.
     __device__ __forceinline__ void advance() { base += kstep_bytes; }
@@ -364,6 +388,18 @@ constexpr int kSplitRangePerXcdK = 32768;        // four K ranges: from this K o
 // much; measured 17-20 % faster at K = 65536 for NN and NT).  The readers then sit on two XCDs only,
 // which makes the exchange slower by some 10 us: not for short K.  Writers keep the lower ids there
 // too (same pid >> 3, lower XCD).
+// The tiles of an output block.  An extent that is no whole number of tiles is covered all the same: the last
+// tile of a row or column of tiles is moved back to end at the block's edge (first row m_last, first column
+// n_last).  It computes some outputs of its neighbour a second time, from the same operands in the same
+// order: both store the same bits.  Needs an extent of at least one tile.
+// A K that is no multiple of 64 is handed to a kernel's KTAIL form as the next multiple: the k_tail (1 .. 63) k
+// beyond the last whole 64 are taken FIRST, as an iteration of their own whose missing pieces are zeros.  Only
+// the prologue knows about it, where there are registers to spare; the loop is the same.
+struct TileGrid {
+    int tiles_m, tiles_n;
+    int m_last, n_last;
+    int k_tail;
+};
 struct TileWork {
     int tile_id;          // index into the tile sequence (= split-K slot index within a range)
     int tile_m, tile_n;

@@ -225,11 +225,11 @@ __device__ __forceinline__ void store_block_row16(f32x4 (&row)[NI], uint8_t* epi
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Requires M % BM == 0, N % BN == 0, K % 64 == 0, K >= TileCfg16::MIN_K (per K range when split).
-template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, bool SPLITK>
+// Requires M >= BM, N >= BN, K % 64 == 0, K >= TileCfg16::MIN_K (per K range when split), and 16-byte aligned rows.
+template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, bool SPLITK, bool KTAIL = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
-    int K, int lda, int ldb, int ldc, int tiles_m, int tiles_n, int group_m, SplitK sk) {
+    int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
     using Cfg = TileCfg16<BM, BN, WM, WN>;
     constexpr int NW = Cfg::NW;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, MI = Cfg::MI, NI = Cfg::NI, NS = Cfg::NS, NTAIL = Cfg::NTAIL;
@@ -251,14 +251,16 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     const int wm = wave / WN, wn = wave % WN;
 
     // ---- workgroup -> output tile and K range ------------------------------------------------
-    const TileWork work = map_workgroup<SPLITK, BM * BN == 256 * 256>(blockIdx.x, gridDim.x, K, tiles_m, tiles_n, group_m, sk);
-    const int tile_m = work.tile_m, tile_n = work.tile_n, krange = work.krange, ktotal = work.ktotal;
-    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+    const TileWork work = map_workgroup<SPLITK, BM * BN == 256 * 256>(blockIdx.x, gridDim.x, K, grid.tiles_m, grid.tiles_n, group_m, sk);
+    const int krange = work.krange, ktotal = work.ktotal;
+    const int64_t m0 = min(work.tile_m * BM, grid.m_last), n0 = min(work.tile_n * BN, grid.n_last);
 
     const uint32_t lds0 = lds_address(smem);
     OpA opa;
     OpB opb;
-    const int64_t k0 = (int64_t)krange * ktotal;
+    static_assert(!(SPLITK && KTAIL), "a shorter last 64 k belongs to no range");
+    // KTAIL: K-steps 0 and 1 are the shorter last 64 k, K-step s the k from 32 (s - 2) on: the window starts 64 k early
+    const int64_t k0 = KTAIL ? -64 : (int64_t)krange * ktotal;
     // the load schedule starts NS K-steps before K-step 0
     constexpr bool FIRST_ODD = NS % 2 == 1;
     opa.init(A + (A_KC ? k0 : k0 * lda), m0, 2u * (uint32_t)lda, lane, wave, lds0, wm * TM, FIRST_ODD);
@@ -335,6 +337,16 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     auto next_stage = [&](uint32_t off) __attribute__((always_inline)) -> uint32_t { return off + SB == RING ? 0u : off + SB; };
 
     // ---- prologue: the loads "steps -NS .. -1" would have issued: K-steps 0 .. NS-1 ---------------
+    auto first_load = [&](auto& op, auto x_c, auto ahead_c, auto step_c, bool is_a, uint32_t stage) __attribute__((always_inline)) {
+        constexpr int X = decltype(x_c)::value, AHEAD = decltype(ahead_c)::value, STEP = decltype(step_c)::value;
+        using Op = typename std::remove_reference<decltype(op)>::type;
+        if constexpr (KTAIL && STEP < 2) {
+            const size_t elements = is_a ? (A_KC ? (size_t)ktotal : (size_t)ktotal * lda) : (B_KC ? (size_t)ktotal : (size_t)ktotal * ldb);
+            op.template issue_tail<X, Op::PAIR ? AHEAD : 0, STEP>(stage, 2 * elements, grid.k_tail, lane, wave);
+        } else {
+            op.template issue<X, Op::PAIR ? AHEAD : 0>(stage);
+        }
+    };
     static_for<NS>([&](auto v) __attribute__((always_inline)) {
         constexpr int T = decltype(v)::value - NS;                // virtual step
         constexpr uint32_t FAR = (T + NS) * SB;                   // stage of K-step T+NS
@@ -344,12 +356,14 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
             auto& op = [&]() __attribute__((always_inline)) -> auto& { if constexpr (IS_A) return opa; else return opb; }();
             if constexpr (Op::PAIR && T == -NS) {
                 // K-step -1 does not exist: only the K-step 0 half of the pair, window stays
-                static_for<Op::NBASE>([&](auto d) __attribute__((always_inline)) { op.template issue<decltype(d)::value, 0>(FAR); });
+                static_for<Op::NBASE>([&](auto d) __attribute__((always_inline)) { first_load(op, d, Int<0>{}, Int<0>{}, IS_A, FAR); });
                 op.flip();
             } else {
                 constexpr uint32_t NEAR = Op::PAIR ? FAR - SB : 0u;
-                issue_loads(op_c, Int<2>{}, Int<0>{}, NEAR, FAR);
-                issue_loads(op_c, Int<2>{}, Int<1>{}, NEAR, FAR);
+                static_for<Op::NBASE>([&](auto d) __attribute__((always_inline)) {
+                    if constexpr (Op::PAIR) first_load(op, d, Int<0>{}, Int<T + NS - 1>{}, IS_A, NEAR);
+                    first_load(op, d, Int<1>{}, Int<T + NS>{}, IS_A, FAR);
+                });
                 op.advance();
             }
         });
@@ -444,7 +458,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     __syncthreads();   // every wave is done with the ring before the epilogue reuses LDS
 
     if constexpr (SPLITK) {
-        if (split_k_exchange16<BM, BN, MI, NI>(acc, sk, krange, work.tile_id, tiles_m * tiles_n, wave, lane, t)) return;
+        if (split_k_exchange16<BM, BN, MI, NI>(acc, sk, krange, work.tile_id, grid.tiles_m * grid.tiles_n, wave, lane, t)) return;
     }
     store_tile16<TM, TN, MI, NI>(acc, smem, C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN, ldc, wave, lane);
 #undef AXONN_FENCE

@@ -85,6 +85,12 @@ struct OperandK64KContig {   // global P[row * ld + k]; LDS [row][64 k], chunks 
     __device__ __forceinline__ void issue(uint32_t buf) const {
         direct_load16(lds_dst + buf + X * 1024u, base[X], voff[X & 1]);
     }
+    // load X of a shorter last 64 k, `delta` bytes beyond the window: zero for the pieces behind the `left` k that exist
+    template <int X>
+    __device__ __forceinline__ void issue_tail(uint32_t buf, size_t delta, int left, int lane, int /*wave*/) const {
+        const int k = 8 * ((lane & 7) ^ (4 * (X & 1) + (lane >> 4)));
+        direct_load16_from(lds_dst + buf + X * 1024u, piece_or_zero(base[X] + voff[X & 1] + delta, k < left));
+    }
     __device__ __forceinline__ void advance() {
         voff[0] += 128;
         voff[1] += 128;
@@ -132,6 +138,12 @@ struct OperandK64MNContig {   // global P[k * ld + row]; the buffer holds two 32
         else
             direct_load16(in.lds_dst[C] + buf + HALF, in.base, voff_hi[C]);
     }
+    template <int X>
+    __device__ __forceinline__ void issue_tail(uint32_t buf, size_t delta, int left, int lane, int wave) const {
+        constexpr int C = X % QH, H = X / QH;
+        const int k = KB * H + Inner::KR * (QH * wave + C) + lane / Inner::CPR;
+        direct_load16_from(in.lds_dst[C] + buf + H * HALF, piece_or_zero(in.base + (H ? voff_hi[C] : in.voff[C]) + delta, k < left));
+    }
     __device__ __forceinline__ void advance() {
         in.base += 2 * in.kstep_bytes;   // 64-bit: panels may exceed 4 GB
     }
@@ -162,11 +174,11 @@ constexpr int k64_lds_bytes(int bm, int bn, int sched) {
     return ring > epi ? ring : epi;
 }
 
-// Requires M % BM == 0, N % BN == 0, K % 64 == 0, K >= 128 (per K range when split).
-template <int BM, int BN, int WN, bool A_KC, bool B_KC, bool SPLITK, int SCHED>
+// Requires M >= BM, N >= BN, K % 64 == 0, K >= 128 (per K range when split), and 16-byte aligned rows.
+template <int BM, int BN, int WN, bool A_KC, bool B_KC, bool SPLITK, int SCHED, bool KTAIL = false>
 __global__ __launch_bounds__(128 * WN) void gemm_tile_kernel_k64(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
-    int K, int lda, int ldb, int ldc, int tiles_m, int tiles_n, int group_m, SplitK sk) {
+    int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
     using Cfg = TileCfgK64;
     static_assert(WN == 2 || WN == 4, "2 x 2 or 2 x 4 waves");
     static_assert((BM == 128 || BM == 256) && (BN == 128 || BN == 256), "tile extents are 128 or 256");
@@ -185,9 +197,9 @@ __global__ __launch_bounds__(128 * WN) void gemm_tile_kernel_k64(
     const int wm = wave / WN, wn = wave % WN;
 
     // ---- workgroup -> output tile and K range ------------------------------------------------
-    const TileWork work = map_workgroup<SPLITK, BM * BN == 256 * 256>(blockIdx.x, gridDim.x, K, tiles_m, tiles_n, group_m, sk);
-    const int tile_m = work.tile_m, tile_n = work.tile_n, krange = work.krange;
-    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+    const TileWork work = map_workgroup<SPLITK, BM * BN == 256 * 256>(blockIdx.x, gridDim.x, K, grid.tiles_m, grid.tiles_n, group_m, sk);
+    const int krange = work.krange;
+    const int64_t m0 = min(work.tile_m * BM, grid.m_last), n0 = min(work.tile_n * BN, grid.n_last);
     int ktotal = work.ktotal;
     int64_t k0 = (int64_t)krange * ktotal;
     if constexpr (SPLITK) {
@@ -284,10 +296,21 @@ __global__ __launch_bounds__(128 * WN) void gemm_tile_kernel_k64(
     };
 
     // ---- prologue: iterations 0 and 1 into the first two buffers of each operand ---------------------
-    static_for<QLA>([&](auto x) __attribute__((always_inline)) { issue_a(x, 0u); });
-    static_for<QLB>([&](auto x) __attribute__((always_inline)) { issue_b(x, 0u); });
-    opa.advance();
-    opb.advance();
+    static_assert(!(SPLITK && KTAIL), "a shorter last 64 k belongs to no range");
+    if constexpr (KTAIL) {   // the shorter last 64 k is iteration 0; the window stays at k = 0 for iteration 1
+        const size_t whole = (size_t)(ktotal - Cfg::KS);
+        static_for<QLA>([&](auto x) __attribute__((always_inline)) {
+            opa.template issue_tail<decltype(x)::value>(0u, 2 * (A_KC ? whole : whole * lda), grid.k_tail, lane, wave);
+        });
+        static_for<QLB>([&](auto x) __attribute__((always_inline)) {
+            opb.template issue_tail<decltype(x)::value>(0u, 2 * (B_KC ? whole : whole * ldb), grid.k_tail, lane, wave);
+        });
+    } else {
+        static_for<QLA>([&](auto x) __attribute__((always_inline)) { issue_a(x, 0u); });
+        static_for<QLB>([&](auto x) __attribute__((always_inline)) { issue_b(x, 0u); });
+        opa.advance();
+        opb.advance();
+    }
     static_for<QLA>([&](auto x) __attribute__((always_inline)) { issue_a(x, ABUF); });
     static_for<QLB>([&](auto x) __attribute__((always_inline)) { issue_b(x, BBUF); });
     opa.advance();
@@ -420,7 +443,7 @@ __global__ __launch_bounds__(128 * WN) void gemm_tile_kernel_k64(
     if constexpr (!OVERLAP_EPI) {
         __syncthreads();   // every wave is done with the buffers before the epilogue reuses LDS
         if constexpr (SPLITK) {
-            if (split_k_exchange16<BM, BN, MI, NI>(acc, sk, krange, work.tile_id, tiles_m * tiles_n, wave, lane, t)) return;
+            if (split_k_exchange16<BM, BN, MI, NI>(acc, sk, krange, work.tile_id, grid.tiles_m * grid.tiles_n, wave, lane, t)) return;
         }
         store_tile16<TM, TN, MI, NI>(acc, smem, C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN, ldc, wave, lane);
     }

@@ -34,12 +34,12 @@ struct TileCfgK64P {
     static constexpr int MAX_WORKGROUPS = 256;                      // one per compute unit
 };
 
-// Requires M % 256 == 0, N % 256 == 0, K % 64 == 0, K >= 128; gridDim.x <= tiles, and a multiple of 8
+// Requires M >= 256, N >= 256, K % 64 == 0, K >= 128, 16-byte aligned rows; gridDim.x <= tiles, and a multiple of 8
 // whenever the number of tiles is one (keeps a workgroup's tiles on the XCD that map_workgroup means them for).
 template <bool A_KC, bool B_KC>
 __global__ __launch_bounds__(512) void gemm_tile_kernel_k64p(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
-    int K, int lda, int ldb, int ldc, int tiles_m, int tiles_n, int group_m, SplitK sk) {
+    int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
     using Cfg = TileCfgK64;
     constexpr int WN = 4, BM = Cfg::BM, BN = Cfg::BN, NW = 8;
     constexpr int TM = BM / 2, TN = BN / WN, MI = TM / 16, NI = TN / 16, NM = MI * NI;
@@ -52,11 +52,11 @@ __global__ __launch_bounds__(512) void gemm_tile_kernel_k64p(
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int total = tiles_m * tiles_n;
+    const int total = grid.tiles_m * grid.tiles_n;
     const int stride = (int)gridDim.x;
 
     int pid = (int)blockIdx.x;
-    TileWork work = map_workgroup<false, true>(pid, total, K, tiles_m, tiles_n, group_m, sk);
+    TileWork work = map_workgroup<false, true>(pid, total, K, grid.tiles_m, grid.tiles_n, group_m, sk);
 
     using OpA = typename std::conditional<A_KC, OperandK64KContig<BM, 0, NW>, OperandK64MNContig<BM, 0, NW, MI / 2>>::type;
     using OpB = typename std::conditional<B_KC, OperandK64KContig<BN, REGION_B, NW>, OperandK64MNContig<BN, REGION_B, NW, NI / 2>>::type;
@@ -64,8 +64,10 @@ __global__ __launch_bounds__(512) void gemm_tile_kernel_k64p(
     const uint32_t lds0 = lds_address(smem);
     OpA opa;
     OpB opb;
-    opa.init(A, (int64_t)work.tile_m * BM, 2u * (uint32_t)lda, lane, wave, lds0, wm * TM);
-    opb.init(B, (int64_t)work.tile_n * BN, 2u * (uint32_t)ldb, lane, wave, lds0, wn * TN);
+    auto row_of = [&](const TileWork& w) __attribute__((always_inline)) -> int64_t { return min(w.tile_m * BM, grid.m_last); };
+    auto col_of = [&](const TileWork& w) __attribute__((always_inline)) -> int64_t { return min(w.tile_n * BN, grid.n_last); };
+    opa.init(A, row_of(work), 2u * (uint32_t)lda, lane, wave, lds0, wm * TM);
+    opb.init(B, col_of(work), 2u * (uint32_t)ldb, lane, wave, lds0, wn * TN);
     auto issue = [&](auto x_c, uint32_t buf) __attribute__((always_inline)) {
         constexpr int X = decltype(x_c)::value;
         if constexpr (X < QL)
@@ -229,17 +231,17 @@ __global__ __launch_bounds__(512) void gemm_tile_kernel_k64p(
         const bool has_next = next < total;
         // the tile whose panels the loads turn to two iterations before this one ends: the next tile,
         // or, behind the last one, this tile once more (valid addresses, nobody multiplies them)
-        const TileWork nw = has_next ? map_workgroup<false, true>(next, total, K, tiles_m, tiles_n, group_m, sk) : work;
+        const TileWork nw = has_next ? map_workgroup<false, true>(next, total, K, grid.tiles_m, grid.tiles_n, group_m, sk) : work;
         for (int it = 0; it < KI - 1; ++it) {
             if (it == KI - 2) {
-                opa.retarget(A, (int64_t)nw.tile_m * BM, 2u * (uint32_t)lda, wave, 2u * (uint32_t)K);
-                opb.retarget(B, (int64_t)nw.tile_n * BN, 2u * (uint32_t)ldb, wave, 2u * (uint32_t)K);
+                opa.retarget(A, row_of(nw), 2u * (uint32_t)lda, wave, 2u * (uint32_t)K);
+                opb.retarget(B, col_of(nw), 2u * (uint32_t)ldb, wave, 2u * (uint32_t)K);
             }
             substep(Int<0>{});
             substep(Int<1>{});
         }
         substep(Int<0>{});
-        last_substep(C + ((int64_t)work.tile_m * BM + wm * TM) * (int64_t)ldc + (int64_t)work.tile_n * BN + wn * TN);
+        last_substep(C + (row_of(work) + wm * TM) * (int64_t)ldc + col_of(work) + wn * TN);
         if (!has_next) break;
         pid = next;
         work = nw;

@@ -11,7 +11,13 @@ namespace axonn {
 // makes no difference (NN) or costs 2-5 % (TN, either operand triple-buffered), so those keep two buffers each.
 constexpr int kSchedNN = 0, kSchedNT = 1, kSchedTN = 0;
 
-tile_kernel_t k64_kernel(bool split, int layout) {
+tile_kernel_t k64_kernel(bool split, int layout, bool k_tail) {
+    if (k_tail) {
+        static const tile_kernel_t tail[3] = {gemm_tile_kernel_k64<256, 256, 4, true, false, false, kSchedNN, true>,
+                                              gemm_tile_kernel_k64<256, 256, 4, true, true, false, kSchedNT, true>,
+                                              gemm_tile_kernel_k64<256, 256, 4, false, false, false, kSchedTN, true>};
+        return (!split && layout >= 0 && layout < 3) ? tail[layout] : nullptr;
+    }
     static const tile_kernel_t fn[2][3] = {
         {gemm_tile_kernel_k64<256, 256, 4, true, false, false, kSchedNN>, gemm_tile_kernel_k64<256, 256, 4, true, true, false, kSchedNT>,
          gemm_tile_kernel_k64<256, 256, 4, false, false, false, kSchedTN>},
@@ -26,8 +32,10 @@ tile_kernel_t k64_kernel(bool split, int layout) {
 // tiles (2048 x 4096 x 4096: 1018 against 794 TFLOP/s; 4096^3: 1141 against 949); with an MN-contiguous
 // operand it is 15-30 % BEHIND the ring (NN 743 against 990, TN 704 against 904), like every schedule
 // tried that issues such an operand's loads anywhere but straight after the barrier.
-tile_kernel_t k64_kernel_half(int bm, int bn, bool split, int layout) {
-    if (layout != 1) return nullptr;
+tile_kernel_t k64_kernel_half(int bm, int bn, bool split, int layout, bool k_tail) {
+    if (layout != 1 || (split && k_tail)) return nullptr;
+    if (k_tail && bm == 256 && bn == 128) return gemm_tile_kernel_k64<256, 128, 2, true, true, false, 3, true>;
+    if (k_tail && bm == 128 && bn == 256) return gemm_tile_kernel_k64<128, 256, 2, true, true, false, 3, true>;
     if (bm == 256 && bn == 128)
         return split ? gemm_tile_kernel_k64<256, 128, 2, true, true, true, 3> : gemm_tile_kernel_k64<256, 128, 2, true, true, false, 3>;
     if (bm == 128 && bn == 256)

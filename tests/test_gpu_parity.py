@@ -937,6 +937,29 @@ def test_tuned_call_runs_the_product_in_the_remembered_mode(oracle_mod, op):
         B.axonn_linear_tune_reset()
 
 
+# ------------------------------------------------------------------ tile kernels on outputs and K that are no whole tiles
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("shape", [(1064, 4168, 1608), (1608, 4168, 1064), (264, 8200, 1032), (8200, 264, 1000), (2056, 2312, 456),
+                                   (1304, 1800, 200), (520, 5128, 2048 + 56), (3080, 3336, 264), (2056, 2056, 320), (5128, 3080, 136)])
+def test_overlapping_tiles_and_k_tails_bit_exact_on_integers(oracle_mod, layout, shape):
+    """Sizes that are multiples of 8 and of nothing larger: the last tiles end at the output's edge, and the
+    last K mod 64 (8 to 56 here; any number for TN, whose operands both have their rows along k) is an iteration
+    of its own.  Every element, exact in fp32 in any order: |sum| <= 16 K < 2^24."""
+    M, N, K = shape
+    for K in (K, K + 3) if layout == "TN" else (K,):
+        a = synth.integer_bf16(770 + M, (M, K), -4, 4)
+        b = synth.integer_bf16(780 + N, (K, N), -4, 4)
+        A, Bm = store(a, b, layout)
+        # |sum| < 2^24: fp32 products on the device are exact too, and are checked against the oracle below
+        ref = U.to_device(a).float() @ U.to_device(b).float()
+        ii, jj = _sample_positions(M, N, seed=M + K, n_rows=2, n_cols=2)
+        at = oracle_mod.gemm_at(M, N, K, layout, A, Bm, ii, jj)
+        assert np.array_equal(ref[torch.from_numpy(ii).cuda(), torch.from_numpy(jj).cuda()].cpu().numpy(), at)
+        got = run_gpu_guard_rows("fwd", M, N, K, layout, A, Bm)
+        bad = np.argwhere(got != U.to_host_bits(ref.to(torch.bfloat16)))
+        assert bad.size == 0, f"{layout} {(M, N, K)}: {len(bad)} mismatches, first at {bad[0]}"
+
+
 # ------------------------------------------------------------------ few rows, few tiles: K split over a workgroup's waves
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("shape", [(1, 48, 8), (15, 33, 9), (16, 16, 63), (17, 95, 64), (31, 64, 65), (33, 200, 129), (63, 257, 515),
