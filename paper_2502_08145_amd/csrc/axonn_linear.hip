@@ -973,15 +973,16 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     if (!src || !dst || (s & 1) || (d & 1) || (s < d + bytes && d < s + bytes)) return AXONN_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
-    if (rows % axonn::TR_TILE == 0 && cols % axonn::TR_TILE == 0 && !(s & 15) && !(d & 15)) {
-        const int64_t tiles = (rows / axonn::TR_TILE) * (cols / axonn::TR_TILE);
-        if (tiles >= kMaxDim) return AXONN_ERR_UNSUPPORTED;
-        hipLaunchKernelGGL(axonn::transpose_tile_kernel, dim3((unsigned)tiles), dim3(256), 0, st,
-                           static_cast<const uint16_t*>(src), static_cast<uint16_t*>(dst), rows, cols,
-                           (int)(cols / axonn::TR_TILE));
+    const bool whole = rows % axonn::TR_TILE == 0 && cols % axonn::TR_TILE == 0 && !(s & 15) && !(d & 15);
+    const dim3 grid((unsigned)((rows + 63) / 64), (unsigned)((cols + 3) / 4));
+    if (!whole && grid.y > 65535u) return AXONN_ERR_UNSUPPORTED;
+    const int64_t tiles_r = (rows + axonn::TR_TILE - 1) / axonn::TR_TILE, tiles_c = (cols + axonn::TR_TILE - 1) / axonn::TR_TILE;
+    if (whole || (rows >= axonn::TR_TILE && cols >= axonn::TR_TILE && rows * cols >= axonn::tr_ragged_from(std::min(rows, cols)))) {
+        const int64_t tiles = tiles_r * tiles_c;   // fewer than 2^29: rows * cols < 2^40
+        hipLaunchKernelGGL(tiles >= axonn::TR_BANDS_FROM ? axonn::transpose_tile_kernel<true> : axonn::transpose_tile_kernel<false>,
+                           dim3((unsigned)tiles), dim3(256), 0, st, static_cast<const uint16_t*>(src), static_cast<uint16_t*>(dst),
+                           rows, cols, (int)tiles_r, (int)tiles_c);
     } else {
-        const dim3 grid((unsigned)((rows + 63) / 64), (unsigned)((cols + 3) / 4));
-        if (grid.y > 65535u) return AXONN_ERR_UNSUPPORTED;
         hipLaunchKernelGGL(axonn::transpose_naive_kernel, grid, dim3(256), 0, st, static_cast<const uint16_t*>(src),
                            static_cast<uint16_t*>(dst), rows, cols);
     }

@@ -8,6 +8,19 @@
 // four consecutive rows -- twice per lane for eight consecutive rows, i.e. 16 bytes of one output
 // row, stored with one 16-byte global store.  A wave writes 16 output rows x 64 bytes per store and
 // the two stores of a wave complete each 128-byte line.
+//
+// Any size of at least a tile: the last tiles are moved back to the matrix' edge (what they repeat is stored
+// twice, the same bits), and loads and stores take any 2-byte aligned address.  One element per thread, as
+// before, 2049 x 4100 took 29 us; now 16 (floor at the rate of a large copy: 6.5; the rest is lines that two tiles
+// write a part of).
+//
+// Order of the tiles: each XCD works on a contiguous chunk of them, four tiles deep along the shorter side of the
+// matrix, so that both the 128-byte pieces read and those written have their neighbours in flight behind the
+// same L2; and each such band starts 5 tiles further along, because a stride of a power of two sends
+// the same column of tiles to the same memory channels.  Operands from HBM, us, row-major order -> this one:
+// 4096 x 12288 50 -> 43, 8192 x 8192 67 -> 53, 4096 x 16384 66 -> 53 (floors 39, 52, 52).  Tiles of 64 x 128, 128 x 64 and
+// 128 x 128 were no faster in this order; non-temporal stores 5 % faster from 128 MB on, slower below, and half
+// as fast where rows are not whole lines.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -15,22 +28,48 @@
 namespace axonn {
 
 typedef uint32_t tr_u32x4 __attribute__((ext_vector_type(4)));
+typedef tr_u32x4 __attribute__((aligned(2))) tr_u32x4_any;   // at any 2-byte aligned address
 typedef short tr_v4i16 __attribute__((ext_vector_type(4)));
 
 constexpr int TR_TILE = 64;          // rows and columns per workgroup
+constexpr int TR_BAND = 4;           // tiles across a band
+constexpr int TR_BANDS_FROM = 1024;  // tiles
+// A ragged matrix takes the tile kernel from this many elements on: below, the launch is all that counts, and a
+// narrow one still gives the element kernel the more workgroups (4589 x 193: 3.6 us against 4.2; 1000 x 1000: 4.0
+// against 3.0).
+constexpr int64_t tr_ragged_from(int64_t narrow) { return narrow < 256 ? 3 << 19 : 1 << 18; }
 constexpr int TR_LDS_STRIDE = 144;   // bytes per tile row in LDS (128 + 16)
 
-// Requires rows % 64 == 0, cols % 64 == 0, both pointers 16-byte aligned.  grid = tiles, block = 256.
+// Requires rows >= 64, cols >= 64.  grid = tiles, block = 256.  BANDS: the order of tiles described above, else row by
+// row: up to 1023 tiles all fit the chip side by side, and the order's index arithmetic would cost them 0.4 us of 3.
+template <bool BANDS>
 __global__ __launch_bounds__(256) void transpose_tile_kernel(const uint16_t* __restrict__ src,
                                                              uint16_t* __restrict__ dst, int64_t rows,
-                                                             int64_t cols, int tiles_c) {
+                                                             int64_t cols, int tiles_r, int tiles_c) {
     __shared__ __attribute__((aligned(16))) uint8_t tile[TR_TILE * TR_LDS_STRIDE];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int64_t r0 = (int64_t)(blockIdx.x / tiles_c) * TR_TILE, c0 = (int64_t)(blockIdx.x % tiles_c) * TR_TILE;
+    uint32_t tr, tc;
+    if constexpr (BANDS) {
+        // XCD x runs the workgroups x, x + 8, ...: a contiguous chunk of the sequence
+        const uint32_t x = blockIdx.x & 7, rem = gridDim.x & 7;
+        const uint32_t id = x * (gridDim.x >> 3) + min(x, rem) + (blockIdx.x >> 3);
+        const bool tall = tiles_r > tiles_c;   // bands of four tile columns, else of four tile rows
+        const uint32_t across = tall ? tiles_c : tiles_r, along = tall ? tiles_r : tiles_c;
+        const uint32_t band = id / (TR_BAND * along), in_band = id - band * (TR_BAND * along);
+        const uint32_t depth = min(across - band * TR_BAND, (uint32_t)TR_BAND);
+        const uint32_t in_line = in_band / depth;
+        const uint32_t a = band * TR_BAND + in_band - in_line * depth, l = (in_line + band * 5) % along;
+        tr = tall ? l : a;
+        tc = tall ? a : l;
+    } else {
+        tr = blockIdx.x / (uint32_t)tiles_c;
+        tc = blockIdx.x - tr * tiles_c;
+    }
+    const int64_t r0 = min((int64_t)tr * TR_TILE, rows - TR_TILE), c0 = min((int64_t)tc * TR_TILE, cols - TR_TILE);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int q = t + 256 * u, row = q >> 3, ch = q & 7;   // 16-byte chunk ch of tile row `row`
-        const tr_u32x4 v = *reinterpret_cast<const tr_u32x4*>(src + (r0 + row) * cols + c0 + ch * 8);
+        const tr_u32x4 v = *reinterpret_cast<const tr_u32x4_any*>(src + (r0 + row) * cols + c0 + ch * 8);
         *reinterpret_cast<tr_u32x4*>(tile + row * TR_LDS_STRIDE + ch * 16) = v;
     }
     __syncthreads();
@@ -49,11 +88,12 @@ __global__ __launch_bounds__(256) void transpose_tile_kernel(const uint16_t* __r
         out[1] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(lo, lo, 2, 3));
         out[2] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(hi, hi, 0, 1));
         out[3] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(hi, hi, 2, 3));
-        *reinterpret_cast<tr_u32x4*>(dst + (c0 + 16 * wave + s) * rows + r0 + rb * 32 + 8 * g) = out;
+        *reinterpret_cast<tr_u32x4_any*>(dst + (c0 + 16 * wave + s) * rows + r0 + rb * 32 + 8 * g) = out;
     }
 }
 
-// Any rows, cols >= 1: one element per thread (stores coalesced along the output rows).
+// Any rows, cols >= 1 (used below a tile in either direction and for small ragged matrices): one element per thread, stores coalesced along
+// the output rows.
 __global__ __launch_bounds__(256) void transpose_naive_kernel(const uint16_t* __restrict__ src,
                                                               uint16_t* __restrict__ dst, int64_t rows,
                                                               int64_t cols) {

@@ -843,6 +843,26 @@ def test_transpose_matches_oracle_bit_for_bit(oracle_mod, shape):
     assert np.array_equal(U.to_host_bits(s), src)   # the source is untouched
 
 
+@pytest.mark.parametrize("shape", [(64, 65), (65, 64), (63, 200), (200, 63), (127, 129), (321, 1087), (1087, 321), (260, 1009), (64, 24577),
+                                   (24577, 64), (300, 5001), (2085, 2050), (2050, 2085)])
+@pytest.mark.parametrize("offset", [0, 1, 7])
+def test_transpose_of_any_size_and_address(oracle_mod, shape, offset):
+    """One tile and a bit in either direction, the element kernel just below a tile, more than one band of
+    tiles, and buffers that start `offset` elements off a 16-byte boundary; nothing around the output is written."""
+    rows, cols = shape
+    src = synth.normal_bf16(78 + rows, (rows, cols))
+    want = oracle_mod.transpose(src)
+    s = torch.empty((rows * cols + 16,), dtype=torch.bfloat16, device="cuda")
+    s[offset:offset + rows * cols] = U.to_device(src).reshape(-1)
+    d = torch.empty((rows * cols + 32,), dtype=torch.bfloat16, device="cuda")
+    d.view(torch.int16).fill_(0x7FC0)
+    B.axonn_transpose_bf16(rows, cols, s[offset:offset + rows * cols], d[16 - offset:16 - offset + rows * cols])
+    torch.cuda.synchronize()
+    got = U.to_host_bits(d)
+    assert np.array_equal(got[16 - offset:16 - offset + rows * cols].reshape(cols, rows), want)
+    assert (got[:16 - offset] == 0x7FC0).all() and (got[16 - offset + rows * cols:] == 0x7FC0).all()
+
+
 def test_transposed_weight_runs_the_forward_product_in_another_mode(oracle_mod):
     # Sec. IV-C in one piece: Y = X W computed as NN on (X, W) and as NT on (X, transpose(W))
     T, d_in, d_out = 512, 768, 1024
