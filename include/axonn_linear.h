@@ -273,7 +273,8 @@ int axonn_linear_split_k_timeouts(uint64_t *count);
 /* Kernel variants.  Variant 0 is the guarded one-thread-per-element kernel that accepts any
  * shape (the library itself uses it for K == 0 only); the last one ("mfma16_edge_128x128") is the
  * guarded MFMA kernels for any M, N, K >= 1 (one with 128 x 128 tiles, one that splits a smaller
- * tile's K over the waves of a workgroup: the sizes decide); the others are MFMA tile kernels ("_w8": 8 waves,
+ * tile's K over the waves of a workgroup, the tile kernels with their last tiles moved back to the output's
+ * edge: the sizes decide); the others are MFMA tile kernels ("_w8": 8 waves,
  * "_sk2" ... "_sk8": split-K over that many workgroups).  Host-only queries: no GPU is touched. */
 int axonn_linear_num_variants(void);
 /* Name such as "mfma16k64_256x256_w8_sk2"; NULL if `variant` is out of range. */
@@ -304,7 +305,10 @@ int axonn_linear_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_pa
  * larger scratch area than the one registered there (or none is registered), in which case it is
  * the plan without split-K that the call would fall back to.  Host logic plus one hipGetDevice. */
 int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_part_t parts[AXONN_MAX_PLAN_PARTS]);
-/* Override the choice for all later calls in this process; -1 restores automatic selection.
+/* A plan names the variants its blocks are planned with.  Where the smallest outputs are concerned (a few dozen
+ * tiles of 128 x 128) the block of a tile variant may run on the kernel that splits K over a workgroup's waves,
+ * which needs no scratch area; a FORCED tile variant is always that very kernel.
+ * Override the choice for all later calls in this process; -1 restores automatic selection.
  * Returns AXONN_OK or AXONN_ERR_INVALID_ARG.  For tests, tuning and the benchmark. */
 int axonn_linear_force_variant(int variant);
 

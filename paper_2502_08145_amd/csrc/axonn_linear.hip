@@ -153,9 +153,11 @@ static std::vector<Variant> make_variants() {
     };
     for (Variant& x : v)
         for (const auto& q : measured)
-            if (std::strcmp(x.name, q.name) == 0) {
+            // a split-K variant's name is the plain one's and "_sk<ranges>"
+            if (std::strncmp(x.name, q.name, std::strlen(q.name)) == 0 && (x.splits > 1) == (std::strstr(x.name, "_sk") == x.name + std::strlen(q.name)) &&
+                (x.splits > 1 || std::strlen(x.name) == std::strlen(q.name))) {
                 std::copy(q.us64, q.us64 + 3, x.us64);
-                for (int l = 0; l < 3; ++l)
+                for (int l = 0; l < 3 && x.splits == 1; ++l)
                     x.fn_tail[l] = !x.k64 ? ring_kernel_small(x.bm, x.bn, x.threads / 128, false, l, true)
                                    : x.bm * x.bn == 256 * 256 ? k64_kernel(false, l, true) : k64_kernel_half(x.bm, x.bn, false, l, true);
             }
@@ -333,26 +335,35 @@ static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
     return 3.0 + (rows_aligned ? 1.8 * steps + 2.6 : 2.0 * steps + 5.0) * std::sqrt(1.0 + (wgs / 292.0) * (wgs / 292.0));
 }
 
-// How a block of the output that is no whole number of tiles is computed (guarded variant).
-struct GuardedChoice {
+// How a block of the output is computed where it is not simply the tile variant of its part.
+struct BlockChoice {
     int tile = -1;           // >= 0: this tile variant, its last tiles moved back to the block's edge (TileGrid)
     WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel; else the guarded MFMA kernel
     int lead_m = 0, lead_n = 0;   // rows and columns before the block that the launch covers as well
     double us = 0.0;         // modelled time, operands in cache
 };
 
-// A tile variant over an m x n block, in microseconds; < 0: it cannot run there.
+// A tile variant over an m x n block, in microseconds; < 0: it cannot run there, or there is no model of it.
+// Full rounds of 256 workgroups and 0.76 + 0.24 f of one for a last round that fills a fraction f of the compute
+// units; split-K variants also exchange partial tiles, which costs a trip to memory and back per range and
+// some of its bandwidth per tile.  Fitted over 36 000 sampled products, residual 3-8 %.
 static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
     const Variant& x = variants()[v];
     const int64_t k_padded = (K + 63) / 64 * 64;   // every tile kernel takes K 64 at a time
-    if (x.us64[layout] <= 0.0 || m < x.bm || n < x.bn || k_padded < x.min_k || K <= 64) return -1.0;
+    if (x.us64[layout] <= 0.0 || m < x.bm || n < x.bn || k_padded / x.splits < x.min_k || K <= 64) return -1.0;
     if (K != k_padded && !x.fn_tail[layout]) return -1.0;
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0) return -1.0;   // 16-byte direct loads and stores
     if (std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return -1.0;
-    const int64_t tiles = ((m + x.bm - 1) / x.bm) * ((n + x.bn - 1) / x.bn), rest = tiles % 256;
-    const double rounds = (double)(tiles / 256) + (rest ? 0.76 + 0.24 * (double)rest / 256.0 : 0.0);
-    const double fixed = x.bm * x.bn <= 128 * 128 ? 1.9 : x.bm * x.bn < 256 * 256 ? 3.6 : 5.6;   // per round
-    return 3.0 + rounds * ((double)(k_padded / 64) * x.us64[layout] + fixed);
+    const int64_t tiles = ((m + x.bm - 1) / x.bm) * ((n + x.bn - 1) / x.bn), wgs = tiles * x.splits, rest = wgs % 256;
+    const double rounds = (double)(wgs / 256) + (rest ? 0.76 + 0.24 * (double)rest / 256.0 : 0.0);
+    const int area = x.bm * x.bn, more = x.splits - 2;
+    const double fixed = area <= 128 * 128 ? 1.9 : area < 256 * 256 ? 3.6 : 5.6;   // per round
+    double exchange = 0.0;
+    if (x.splits > 1)
+        exchange = area <= 128 * 128  ? 4.1 + 1.35 * more + (0.030 + 0.022 * more) * (double)tiles
+                   : area < 256 * 256 ? 5.4 + 2.3 * more + (0.044 + 0.030 * more) * (double)tiles
+                                      : 6.8 + 2.7 * more + (0.060 + 0.040 * more) * (double)tiles;
+    return 3.0 + rounds * ((double)(k_padded / 64 / x.splits) * x.us64[layout] + fixed) + exchange;
 }
 
 // The kernel with the smallest modelled time.  The tile kernels win as soon as their tiles fill a good part of the
@@ -360,8 +371,8 @@ static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64
 // wherever the output has few 128 x 128 tiles (by a factor of three and more for a few rows over a long K; it
 // loses from some 20 GFLOP on, where 64 x 64 tiles load twice the bytes: 1930 x 7344 x 1832 NN 123 us against
 // 96 for the guarded kernel).  The margin between those two covers their models' residuals.
-static GuardedChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
-    GuardedChoice best;
+static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
+    BlockChoice best;
     best.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
     const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb);
     if (wk.tile >= 0 && wk.us < 0.85 * best.us) {
@@ -369,9 +380,10 @@ static GuardedChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout,
         best.us = wk.us;
     }
     for (int v = 1; v < edge_variant(); ++v) {
+        if (variants()[v].splits > 1) continue;   // ragged outputs never touch the scratch area
         const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
         if (us >= 0.0 && us < best.us) {
-            best = GuardedChoice{};
+            best = BlockChoice{};
             best.tile = v;
             best.us = us;
         }
@@ -382,10 +394,10 @@ static GuardedChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout,
 // an MN-contiguous operand is too narrow for the wave-K kernel and would take the guarded one, element by element
 // (2048 x 8 over K = 4096: 60 us against 12); it takes the 16 last ones instead, some of which the launch over the
 // whole tiles, which comes first, has written before.
-static GuardedChoice guarded_choice(int64_t row0, int64_t col0, int64_t m, int64_t n, int64_t M, int64_t N, int64_t K, int layout) {
+static BlockChoice guarded_choice(int64_t row0, int64_t col0, int64_t m, int64_t n, int64_t M, int64_t N, int64_t K, int layout) {
     const int lead_m = (layout == AXONN_TN && m < 16 && row0 >= 16) ? (int)(16 - m) : 0;
     const int lead_n = (layout != AXONN_NT && n < 16 && col0 >= 16) ? (int)(16 - n) : 0;
-    GuardedChoice g = guarded_choice(m + lead_m, n + lead_n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N, N);
+    BlockChoice g = guarded_choice(m + lead_m, n + lead_n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N, N);
     if (g.tile < 0 && g.wavek.tile >= 0) {
         g.lead_m = lead_m;
         g.lead_n = lead_n;
@@ -422,7 +434,7 @@ static int select_variant(int64_t M, int64_t N, int64_t K, int layout, bool allo
 struct Part {
     int variant;
     int64_t m, n, row0, col0;
-    GuardedChoice guarded{};   // guarded variant: how
+    BlockChoice how{};   // what the guarded variant runs here; a tile variant may leave the block to the wave-K kernel
 };
 struct Plan {
     int parts;
@@ -493,11 +505,21 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
     return plan;
 }
 
-// Which kernels do the blocks of the guarded variant.
-static void settle_guarded_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
+// Which kernels do the blocks of the guarded variant, and which of a tile variant's blocks are small enough for
+// the wave-K kernel: outputs of a few dozen 128 x 128 tiles (512 x 1024 x 2048 NT: 32 tiles, 15.6 us against 9.6; 640 x 640 x
+// 2048 TN 17 -> 10).  On 3 700 sampled products of 0.1 to 30 GFLOP with whole tiles the rule picks it for a
+// third, which run 1.36 times as fast, 2 % of them slower than before (0.77 at worst).
+static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
+    const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
     for (int i = 0; i < plan.parts; ++i) {
         Part& p = plan.part[i];
-        if (variants()[p.variant].edge) p.guarded = guarded_choice(p.row0, p.col0, p.m, p.n, M, N, K, layout);
+        if (variants()[p.variant].edge) {
+            p.how = guarded_choice(p.row0, p.col0, p.m, p.n, M, N, K, layout);
+        } else if (p.variant > 0) {
+            const double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);
+            const WaveKChoice wk = wavek_choose(layout, p.m, p.n, K, lda, ldb);
+            if (us > 0.0 && wk.tile >= 0 && wk.us < 0.9 * us) p.how.wavek = wk;
+        }
     }
 }
 
@@ -513,7 +535,7 @@ static Plan cached_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_
         if (it != g_plans.end()) return it->second;
     }
     Plan plan = make_plan(M, N, K, layout, allow_split);
-    settle_guarded_parts(plan, M, N, K, layout);
+    settle_parts(plan, M, N, K, layout);
     std::lock_guard<std::mutex> lock(g_plans_mutex);
     if (g_plans.size() >= 4096) g_plans.clear();
     g_plans[key] = plan;
@@ -605,18 +627,18 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
     A += layout == AXONN_TN ? p.row0 : p.row0 * K;
     B += layout == AXONN_NT ? p.col0 * K : p.col0;
     C += p.row0 * N + p.col0;
-    if (var.edge && p.guarded.tile < 0) {
-        if (p.guarded.wavek.tile >= 0) {
-            const int64_t dm = p.guarded.lead_m, dn = p.guarded.lead_n;
-            wavek_launch(p.guarded.wavek, layout, s, A - (layout == AXONN_TN ? dm : dm * K), B - (layout == AXONN_NT ? dn * K : dn),
-                         C - dm * N - dn, p.m + dm, p.n + dn, K, lda, ldb, ldc);
-            return;
-        }
+    if (p.how.wavek.tile >= 0) {
+        const int64_t dm = p.how.lead_m, dn = p.how.lead_n;
+        wavek_launch(p.how.wavek, layout, s, A - (layout == AXONN_TN ? dm : dm * K), B - (layout == AXONN_NT ? dn * K : dn),
+                     C - dm * N - dn, p.m + dm, p.n + dn, K, lda, ldb, ldc);
+        return;
+    }
+    if (var.edge && p.how.tile < 0) {
         const int tiles_n = (int)((p.n + var.bn - 1) / var.bn);
         edge_kernel_launch(layout, (unsigned)part_workgroups(p), s, A, B, C, p.m, p.n, K, lda, ldb, ldc, tiles_n);
         return;
     }
-    launch_tiles(var.edge ? variants()[p.guarded.tile] : var, p.m, p.n, K, layout, A, B, C, lda, ldb, ldc, scratch, s);
+    launch_tiles(var.edge ? variants()[p.how.tile] : var, p.m, p.n, K, layout, A, B, C, lda, ldb, ldc, scratch, s);
 }
 
 // Where a call's split-K kernels find their scratch area.
@@ -634,7 +656,7 @@ static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, co
     if (forced >= 0) {
         if (!variant_supports(forced, M, N, K, layout)) return AXONN_ERR_UNSUPPORTED;
         plan = Plan{1, {{forced, M, N, 0, 0}}};
-        settle_guarded_parts(plan, M, N, K, layout);
+        if (variants()[forced].edge) settle_parts(plan, M, N, K, layout);   // any other: that very kernel
     } else {
         plan = cached_plan(M, N, K, layout, g_split_k_enabled.load(std::memory_order_relaxed) != 0);
     }

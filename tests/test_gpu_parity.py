@@ -999,6 +999,26 @@ def test_few_rows_and_tiles_bit_exact_on_integers(oracle_mod, layout, shape):
 
 
 @pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("shape", [(128, 128, 128), (256, 384, 192), (640, 640, 2048), (1024, 512, 2048), (512, 512, 4096), (128, 256, 16384)])
+def test_small_whole_outputs_bit_exact_with_and_without_scratch(oracle_mod, layout, shape):
+    """Outputs of whole tiles, but few of them: planned on small tiles and split-K, run on the wave-K kernel where
+    its modelled time is less.  |sum| <= 9 K < 2^24: exact in any order; the same with no scratch area registered
+    (another plan) and through the static one."""
+    M, N, K = shape
+    a = synth.integer_bf16(790 + M, (M, K), -3, 3)
+    b = synth.integer_bf16(800 + N, (K, N), -3, 3)
+    A, Bm = store(a, b, layout)
+    want = U.f64_to_bf16_bits_rne(oracle_mod.gemm(M, N, K, layout, A, Bm))
+    assert np.array_equal(run_gpu_guard_rows("fwd", M, N, K, layout, A, Bm), want)
+    c = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    B.axonn_linear_gemm_static(M, N, K, layout, U.to_device(A), U.to_device(Bm), c)
+    torch.cuda.synchronize()
+    assert np.array_equal(U.to_host_bits(c), want)
+    B.axonn_linear_set_workspace(None)
+    assert np.array_equal(run_gpu("fwd", M, N, K, layout, A, Bm), want)
+
+
+@pytest.mark.parametrize("layout", LAYOUTS)
 def test_k_tail_lets_no_neighbour_value_through(oracle_mod, layout):
     """Elements beside an operand's last k (the next row's first ones, fetched in the same 16 bytes) must not
     reach a product: they are NaN and infinity here, in rows whose outputs are not compared."""
