@@ -81,14 +81,17 @@ struct Variant {
 // Kernel families: the 64-k-stage kernel (256 x 256, eight waves: the default wherever the output has
 // whole large tiles), the 32-k ring (the same tile for NT at very long K and TN with four and more K
 // ranges; the smaller tiles for outputs of few tiles), the guarded kernel.  Split-K variants of one
-// tile share one kernel (the number of K ranges is a run-time argument).
+// tile share one kernel (the number of K ranges is a run-time argument).  128 x 128 tiles are the ring's for NN and TN and
+// the 64-k kernel's for NT, under one name.
 static std::vector<Variant> make_variants() {
     std::vector<Variant> v;
     v.push_back({"naive", 0, 0, 256, 0, 0, 1, 1, false, {0, 0, 0}, {nullptr, nullptr, nullptr}});
     auto ring = [&](const char* name, int bm, int bn, int wn, int splits, int lds, int min_k, double nn, double nt, double tn) {
         Variant x{name, bm, bn, 128 * wn, lds, min_k, 2 * KB, splits, false, {nn, nt, tn}, {nullptr, nullptr, nullptr}};
         for (int l = 0; l < 3; ++l)
-            x.fn[l] = (bm == 256 && bn == 256) ? ring_kernel_large(splits > 1, l) : ring_kernel_small(bm, bn, wn, splits > 1, l);
+            x.fn[l] = (bm == 256 && bn == 256)              ? ring_kernel_large(splits > 1, l)
+                      : (bm == 128 && bn == 128 && l == AXONN_NT) ? k64_kernel_half(bm, bn, splits > 1, l)
+                                                              : ring_kernel_small(bm, bn, wn, splits > 1, l);
         v.push_back(x);
     };
     auto k64 = [&](const char* name, int splits) {
@@ -146,7 +149,7 @@ static std::vector<Variant> make_variants() {
     // guarded MFMA kernel: ragged shapes and the edge strips of ragged outputs
     // fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %)
     static const struct { const char* name; double us64[3]; } measured[] = {
-        {"mfma16_128x128", {0.530, 0.565, 0.557}},       {"mfma16_128x256", {0.927, 0.887, 0.950}},
+        {"mfma16_128x128", {0.530, 0.525, 0.557}},       {"mfma16_128x256", {0.927, 0.887, 0.950}},
         {"mfma16_128x256_w8", {0.773, 0.818, 0.852}},    {"mfma16_256x128", {0.885, 0.888, 0.951}},
         {"mfma16k64_128x256", {0.0, 0.817, 0.0}},        {"mfma16k64_256x128", {0.0, 0.819, 0.0}},
         {"mfma16k64_256x256_w8", {1.284, 1.219, 1.263}},
@@ -158,8 +161,9 @@ static std::vector<Variant> make_variants() {
                 (x.splits > 1 || std::strlen(x.name) == std::strlen(q.name))) {
                 std::copy(q.us64, q.us64 + 3, x.us64);
                 for (int l = 0; l < 3 && x.splits == 1; ++l)
-                    x.fn_tail[l] = !x.k64 ? ring_kernel_small(x.bm, x.bn, x.threads / 128, false, l, true)
-                                   : x.bm * x.bn == 256 * 256 ? k64_kernel(false, l, true) : k64_kernel_half(x.bm, x.bn, false, l, true);
+                    x.fn_tail[l] = x.bm * x.bn == 256 * 256                                   ? k64_kernel(false, l, true)
+                                   : x.k64 || (x.bm * x.bn == 128 * 128 && l == AXONN_NT) ? k64_kernel_half(x.bm, x.bn, false, l, true)
+                                                                                    : ring_kernel_small(x.bm, x.bn, x.threads / 128, false, l, true);
             }
     Variant e{"mfma16_edge_128x128", EdgeCfg::BM, EdgeCfg::BN, EdgeCfg::NT, EdgeCfg::LDS_BYTES, 1, 1, 1, false, {0, 0, 0}, {nullptr, nullptr, nullptr}};
     e.edge = true;

@@ -1,5 +1,5 @@
 // The tile kernel with LDS stages of 64 k and one barrier per 64 k, four or eight waves, tiles of 256 x 256,
-// 256 x 128 and 128 x 256.
+// 256 x 128, 128 x 256 and 128 x 128.
 //
 // Why a kernel of its own.  In gemm_tile_kernel16 a K-contiguous operand is staged 32 k at a time:
 // a row of a stage is 64 bytes, half a cache line, so every direct load asks the L1 for sixteen
@@ -165,7 +165,7 @@ struct OperandK64MNContig {   // global P[k * ld + row]; the buffer holds two 32
 //   0  two buffers per operand; all loads of an iteration in sub-step 1, into the running buffers
 //   1  three A buffers, A's loads in sub-step 0; B as in 0
 //   2  three B buffers, B's loads in sub-step 0; A as in 0
-//   3  three buffers each (fits for the 128 x 256 and 256 x 128 tiles); half of an iteration's loads in
+//   3  three buffers each (fits for the smaller tiles); half of an iteration's loads in
 //      either sub-step
 constexpr int k64_a_buffers(int sched) { return (sched == 1 || sched == 3) ? 3 : 2; }
 constexpr int k64_b_buffers(int sched) { return (sched == 2 || sched == 3) ? 3 : 2; }

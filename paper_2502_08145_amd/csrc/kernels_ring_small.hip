@@ -8,17 +8,21 @@ namespace axonn {
     {gemm_tile_kernel16<BM, BN, 2, WN, true, false, __VA_ARGS__>, gemm_tile_kernel16<BM, BN, 2, WN, true, true, __VA_ARGS__>, \
      gemm_tile_kernel16<BM, BN, 2, WN, false, false, __VA_ARGS__>}
 
+#define AXONN_RING2(BM, BN, WN, ...)                                                        \
+    {gemm_tile_kernel16<BM, BN, 2, WN, true, false, __VA_ARGS__>, nullptr, gemm_tile_kernel16<BM, BN, 2, WN, false, false, __VA_ARGS__>}
+
 tile_kernel_t ring_kernel_small(int bm, int bn, int wn, bool split, int layout, bool k_tail) {
     static const tile_kernel_t k256x128[3] = AXONN_RING3(256, 128, 2, false);
     static const tile_kernel_t k128x256[3] = AXONN_RING3(128, 256, 2, false);
     static const tile_kernel_t k128x256_w8[3] = AXONN_RING3(128, 256, 4, false);
     static const tile_kernel_t k256x128_sk[3] = AXONN_RING3(256, 128, 2, true);
     static const tile_kernel_t k128x256_sk[3] = AXONN_RING3(128, 256, 2, true);
-    static const tile_kernel_t k128x128[3] = AXONN_RING3(128, 128, 2, false);
-    static const tile_kernel_t k128x128_sk[3] = AXONN_RING3(128, 128, 2, true);
+    // two K-contiguous operands (NT): the 64-k kernel has that tile (k64_kernel_half)
+    static const tile_kernel_t k128x128[3] = AXONN_RING2(128, 128, 2, false);
+    static const tile_kernel_t k128x128_sk[3] = AXONN_RING2(128, 128, 2, true);
     static const tile_kernel_t k256x128_tail[3] = AXONN_RING3(256, 128, 2, false, true);
     static const tile_kernel_t k128x256_w8_tail[3] = AXONN_RING3(128, 256, 4, false, true);
-    static const tile_kernel_t k128x128_tail[3] = AXONN_RING3(128, 128, 2, false, true);
+    static const tile_kernel_t k128x128_tail[3] = AXONN_RING2(128, 128, 2, false, true);
     if (layout < 0 || layout > 2) return nullptr;
     if (k_tail) {
         if (split) return nullptr;
