@@ -379,7 +379,7 @@ static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, i
     BlockChoice best;
     best.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
     const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb);
-    if (wk.tile >= 0 && wk.us < 0.85 * best.us) {
+    if (wk.tile >= 0 && wk.us < 0.93 * best.us) {
         best.wavek = wk;
         best.us = wk.us;
     }
@@ -522,7 +522,7 @@ static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout
         } else if (p.variant > 0) {
             const double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);
             const WaveKChoice wk = wavek_choose(layout, p.m, p.n, K, lda, ldb);
-            if (us > 0.0 && wk.tile >= 0 && wk.us < 0.9 * us) p.how.wavek = wk;
+            if (us > 0.0 && wk.tile >= 0 && wk.us < 0.97 * us) p.how.wavek = wk;
         }
     }
 }

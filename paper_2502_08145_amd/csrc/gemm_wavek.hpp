@@ -8,8 +8,8 @@
 // of K through barriers, so a small output leaves most compute units idle behind a serial chain.  Here
 // the chain is cut inside the workgroup: its waves all own the SAME output tile (16 MI x 16 NI), and wave w
 // takes the 64-k chunks w, w + WK, w + 2 WK, ... of the reduction.  A wave shares nothing with the others
-// until the end, so there is no barrier in the loop, and the loads of two chunks per wave are in flight
-// all the time.  At the end the partial accumulators go through LDS once and are added in the order of
+// until the end, so there is no barrier in the loop, and the loads of a chunk per wave are in flight all the
+// time.  At the end the partial accumulators go through LDS once and are added in the order of
 // the waves (the result does not depend on timing).  No scratch memory is needed.
 //
 //  * A K-contiguous operand (A of NN/NT, B of NT) goes from global memory straight into the registers of
@@ -209,15 +209,17 @@ __global__ __launch_bounds__(64 * WaveKCfg::max_waves(MI, NI)) void gemm_wavek_k
         typename OpA::Regs a;
         typename OpB::Regs b;
     };
-    Regs r0, r1;
-    auto load = [&](Regs& r, int64_t k0) __attribute__((always_inline)) {
+    Regs r;
+    auto load = [&](int64_t k0) __attribute__((always_inline)) {
         opa.load(r.a, k0);
         opb.load(r.b, k0);
     };
-    auto multiply = [&](const Regs& r) __attribute__((always_inline)) {
+    auto stage = [&]() __attribute__((always_inline)) {
         opa.stage(r.a, la);
         opb.stage(r.b, lb);
         wave_order();
+    };
+    auto multiply = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             bf16x8 fa[MI], fb[NI];
@@ -240,20 +242,19 @@ __global__ __launch_bounds__(64 * WaveKCfg::max_waves(MI, NI)) void gemm_wavek_k
     const bool tail = left != 0 && wave == (int)((Kw / WaveKCfg::KC) % waves);
     int64_t k0 = (int64_t)wave * WaveKCfg::KC;
     if (tail) {
-        opa.load_tail(r0.a, Kw, left, lane);
-        opb.load_tail(r0.b, Kw, left, lane);
+        opa.load_tail(r.a, Kw, left, lane);
+        opb.load_tail(r.b, Kw, left, lane);
         k0 -= step;   // counts as the chunk before the first
     } else if (k0 < Kw) {
-        load(r0, k0);
+        load(k0);
     }
-    if (k0 + step < Kw) load(r1, k0 + step);
-    for (; k0 < Kw; k0 += 2 * step) {
-        multiply(r0);
-        if (k0 + 2 * step < Kw) load(r0, k0 + 2 * step);
-        if (k0 + step < Kw) {
-            multiply(r1);
-            if (k0 + 3 * step < Kw) load(r1, k0 + 3 * step);
-        }
+    // Staged, its registers refilled, multiplied: the next chunk's loads are in flight under this one's MFMAs and
+    // the other waves'.  (Two register sets, two chunks ahead, were 5-12 % slower on every product tried and did
+    // not fit the 4 x 4 tile of two K-contiguous operands.)
+    for (; k0 < Kw; k0 += step) {
+        stage();
+        if (k0 + step < Kw) load(k0 + step);
+        multiply();
     }
 
     // this lane's four outputs of block (i, j): C[m][n .. n + 3]

@@ -8,11 +8,10 @@ namespace axonn {
 
 typedef void (*wavek_kernel_t)(const uint16_t*, const uint16_t*, uint16_t*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t, int, int, int);
 
-// The tiles that are built, per layout (NN, NT, TN), in 16 x 16 blocks.  An MN-contiguous operand wants at
+// The tiles that are built, in 16 x 16 blocks, per layout (NN, NT, TN).  An MN-contiguous operand wants at
 // least two blocks side by side (a k-row of one block is 32 bytes of a 128-byte line); the 1 x 1 tile serves
-// it only where the matrix is narrower than that.  4 x 4 with two K-contiguous operands does not fit the
-// registers.  Among 22 000 sampled products (outputs of 1 to 16384 rows, up to 30 GFLOP) the best of these
-// tiles is within 1 % of the best of all nine combinations of 1, 2 and 4 on average.
+// it only where the matrix is narrower than that.  Among 22 000 sampled products (outputs of 1 to 16384 rows, up to
+// 30 GFLOP) the best of these tiles is within 1 % of the best of all nine combinations of 1, 2 and 4 on average.
 struct WaveKTile {
     int mi, ni;
     wavek_kernel_t fn[3];   // nullptr: not for this layout
@@ -23,7 +22,7 @@ static const WaveKTile kTiles[] = {
     {1, 2, {gemm_wavek_kernel<true, false, 1, 2>, gemm_wavek_kernel<true, true, 1, 2>, nullptr}},
     {2, 2, AXONN_WAVEK(2, 2)},
     {2, 4, AXONN_WAVEK(2, 4)},
-    {4, 4, {gemm_wavek_kernel<true, false, 4, 4>, nullptr, gemm_wavek_kernel<false, false, 4, 4>}},
+    {4, 4, AXONN_WAVEK(4, 4)},
 };
 #undef AXONN_WAVEK
 
@@ -33,15 +32,17 @@ static const WaveKTile kTiles[] = {
 //                            exchange of partial tiles
 //   memory:                  every operand and output byte once
 //   staging:                 every byte that some tile loads, through the L2s
-// Constants: least squares on the logarithm over 7 000 sampled products of up to 150 GFLOP, operands in cache
-// (residual 13-14 %; the tile and wave count it chooses are 6 % behind the best ones measured on average).
+// Constants: least squares on the logarithm over 5 700 sampled products of up to 150 GFLOP, operands in cache
+// (residual 16-18 %; the tile and wave count it chooses are 6 % behind the best ones measured on average).  The
+// smallest of some twenty estimates is an optimistic one: what is chosen takes 1.10 of it.
+constexpr double kChosen = 1.10;
 struct WaveKModel {
     double fill, chunk0, chunk_area, work_side, work_area, exchange, store, per_mb, staged_per_mb;
 };
 static const WaveKModel kModel[3] = {
-    {4.5, 0.165, 0.040, 0.031, 0.0, 0.33, 0.21, 0.157, 0.064},     // NN
-    {5.2, 0.160, 0.034, 0.011, 0.009, 0.70, 0.0, 0.149, 0.053},    // NT
-    {4.6, 0.130, 0.043, 0.041, 0.0, 0.35, 0.28, 0.185, 0.014},     // TN
+    {4.0, 0.110, 0.045, 0.029, 0.0, 0.30, 0.20, 0.153, 0.044},       // NN
+    {5.3, 0.141, 0.032, 0.010, 0.0076, 0.45, 0.14, 0.148, 0.038},    // NT
+    {4.0, 0.105, 0.044, 0.033, 0.0, 0.31, 0.21, 0.153, 0.044},       // TN
 };
 static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t N, int64_t K) {
     const WaveKModel& m = kModel[layout];
@@ -72,6 +73,7 @@ WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t ld
             if (best.tile < 0 || us < best.us) best = WaveKChoice{i, w, us};
         }
     }
+    best.us *= kChosen;
     return best;
 }
 
