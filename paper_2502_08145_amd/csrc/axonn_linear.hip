@@ -1005,7 +1005,7 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     const int64_t tiles_r = (rows + axonn::TR_TILE - 1) / axonn::TR_TILE, tiles_c = (cols + axonn::TR_TILE - 1) / axonn::TR_TILE;
     if (whole || (rows >= axonn::TR_TILE && cols >= axonn::TR_TILE && rows * cols >= axonn::tr_ragged_from(std::min(rows, cols)))) {
         const int64_t tiles = tiles_r * tiles_c;   // fewer than 2^29: rows * cols < 2^40
-        hipLaunchKernelGGL(tiles >= axonn::TR_BANDS_FROM ? axonn::transpose_tile_kernel<true> : axonn::transpose_tile_kernel<false>,
+        hipLaunchKernelGGL(axonn::tr_bands(rows, cols, tiles, whole) ? axonn::transpose_tile_kernel<true> : axonn::transpose_tile_kernel<false>,
                            dim3((unsigned)tiles), dim3(256), 0, st, static_cast<const uint16_t*>(src), static_cast<uint16_t*>(dst),
                            rows, cols, (int)tiles_r, (int)tiles_c);
     } else {

@@ -14,13 +14,16 @@
 // before, 2049 x 4100 took 29 us; now 16 (floor at the rate of a large copy: 6.5; the rest is lines that two tiles
 // write a part of).
 //
-// Order of the tiles: each XCD works on a contiguous chunk of them, four tiles deep along the shorter side of the
-// matrix, so that both the 128-byte pieces read and those written have their neighbours in flight behind the
-// same L2; and each such band starts 5 tiles further along, because a stride of a power of two sends
-// the same column of tiles to the same memory channels.  Operands from HBM, us, row-major order -> this one:
-// 4096 x 12288 50 -> 43, 8192 x 8192 67 -> 53, 4096 x 16384 66 -> 53 (floors 39, 52, 52).  Tiles of 64 x 128, 128 x 64 and
-// 128 x 128 were no faster in this order; non-temporal stores 5 % faster from 128 MB on, slower below, and half
-// as fast where rows are not whole lines.
+// Order of the tiles.  Row by row for whole tiles.  BANDS, for large matrices whose rows are no whole lines or whose
+// both strides are multiples of 4 KB: each XCD works on a contiguous chunk of the tiles, four deep along the
+// shorter side of the matrix (with output rows that are no whole lines: always along those; 3000 x 9000 from HBM 34 ->
+// 30 us), and each such band starts 5 tiles further along.  In the first case two tiles
+// that write parts of one line then do it behind the same L2 (2049 x 4100 from HBM 19 -> 16 us); in the second, the
+// lines of a tile fall on few memory channels, and it is the neighbouring tiles that use the others (from HBM:
+// 4096 x 12288 50 -> 43 us, 8192 x 8192 67 -> 53, 4096 x 16384 66 -> 53; floors 39, 52, 52).  Anywhere else it is 3-10 % behind
+// (3136 x 15872 47.6 -> 50.0, 11904 x 1280 16.4 -> 18.3), and below 1024 tiles, which all fit the chip side by side, its
+// index arithmetic costs 0.4 us of 3.  Tiles of 64 x 128, 128 x 64 and 128 x 128 were no faster; non-temporal stores 5 % faster
+// from 128 MB on, slower below, and half as fast where rows are not whole lines.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -33,15 +36,16 @@ typedef short tr_v4i16 __attribute__((ext_vector_type(4)));
 
 constexpr int TR_TILE = 64;          // rows and columns per workgroup
 constexpr int TR_BAND = 4;           // tiles across a band
-constexpr int TR_BANDS_FROM = 1024;  // tiles
+inline bool tr_bands(int64_t rows, int64_t cols, int64_t tiles, bool whole) {
+    return tiles >= 1024 && (!whole || (rows % 2048 == 0 && cols % 2048 == 0));
+}
 // A ragged matrix takes the tile kernel from this many elements on: below, the launch is all that counts, and a
 // narrow one still gives the element kernel the more workgroups (4589 x 193: 3.6 us against 4.2; 1000 x 1000: 4.0
 // against 3.0).
 constexpr int64_t tr_ragged_from(int64_t narrow) { return narrow < 256 ? 3 << 19 : 1 << 18; }
 constexpr int TR_LDS_STRIDE = 144;   // bytes per tile row in LDS (128 + 16)
 
-// Requires rows >= 64, cols >= 64.  grid = tiles, block = 256.  BANDS: the order of tiles described above, else row by
-// row: up to 1023 tiles all fit the chip side by side, and the order's index arithmetic would cost them 0.4 us of 3.
+// Requires rows >= 64, cols >= 64.  grid = tiles, block = 256.
 template <bool BANDS>
 __global__ __launch_bounds__(256) void transpose_tile_kernel(const uint16_t* __restrict__ src,
                                                              uint16_t* __restrict__ dst, int64_t rows,
@@ -53,7 +57,7 @@ __global__ __launch_bounds__(256) void transpose_tile_kernel(const uint16_t* __r
         // XCD x runs the workgroups x, x + 8, ...: a contiguous chunk of the sequence
         const uint32_t x = blockIdx.x & 7, rem = gridDim.x & 7;
         const uint32_t id = x * (gridDim.x >> 3) + min(x, rem) + (blockIdx.x >> 3);
-        const bool tall = tiles_r > tiles_c;   // bands of four tile columns, else of four tile rows
+        const bool tall = tiles_r > tiles_c || (rows & (TR_TILE - 1));   // bands of four tile columns, else of four tile rows
         const uint32_t across = tall ? tiles_c : tiles_r, along = tall ? tiles_r : tiles_c;
         const uint32_t band = id / (TR_BAND * along), in_band = id - band * (TR_BAND * along);
         const uint32_t depth = min(across - band * TR_BAND, (uint32_t)TR_BAND);
