@@ -146,12 +146,14 @@ struct WaveMNContig {
     __device__ __forceinline__ void load_tail(Regs& x, int64_t k0, int left, int /*lane*/) const {
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            // a load's k-rows that lie behind K: the lane takes its piece from the last k-row, and drops it
-            const int over = j * KR + kr - (left - 1);
-            const uint8_t* const p = base + (k0 + (j * KR < left ? j * KR : left - 1)) * ld_bytes;
-            const uint32_t back = over > 0 ? (uint32_t)(j * KR < left ? over : kr) * (uint32_t)ld_bytes : 0u;
-            const u32x4 v = *reinterpret_cast<const u32x4_any*>(p + (piece - back));
-            x.v[j] = over > 0 ? u32x4{0u, 0u, 0u, 0u} : v;
+            x.v[j] = u32x4{0u, 0u, 0u, 0u};
+            if (j * KR < left) {   // uniform
+                // k-rows behind K: the lane takes its piece from the last one that exists, and drops it
+                const int over = j * KR + kr - (left - 1);
+                const uint32_t back = over > 0 ? (uint32_t)over * (uint32_t)ld_bytes : 0u;
+                const u32x4 v = *reinterpret_cast<const u32x4_any*>(base + (k0 + j * KR) * ld_bytes + (piece - back));
+                if (over <= 0) x.v[j] = v;
+            }
         }
     }
     __device__ __forceinline__ void stage(const Regs& x, uint8_t* lds) const {
@@ -219,21 +221,17 @@ __global__ __launch_bounds__(64 * WaveKCfg::max_waves(MI, NI)) void gemm_wavek_k
         opb.stage(r.b, lb);
         wave_order();
     };
-    auto multiply = [&]() __attribute__((always_inline)) {
+    auto multiply_half = [&](int h) __attribute__((always_inline)) {
+        bf16x8 fa[MI], fb[NI];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            bf16x8 fa[MI], fb[NI];
+        for (int i = 0; i < MI; ++i) fa[i] = opa.fragment(la, i, h);
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[i] = opa.fragment(la, i, h);
+        for (int j = 0; j < NI; ++j) fb[j] = opb.fragment(lb, j, h);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) fb[j] = opb.fragment(lb, j, h);
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
-        }
-        wave_order();
+            for (int j = 0; j < NI; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
     };
     // whole chunks: wave, wave + waves, ...; a shorter one at the end is the first of the wave that has the
     // fewest (its loads need the extra code in one place only then)
@@ -254,7 +252,9 @@ __global__ __launch_bounds__(64 * WaveKCfg::max_waves(MI, NI)) void gemm_wavek_k
     for (; k0 < Kw; k0 += step) {
         stage();
         if (k0 + step < Kw) load(k0 + step);
-        multiply();
+        multiply_half(0);
+        if (k0 >= 0 || left > 32) multiply_half(1);   // the second half of a tail of up to 32 k is zeros
+        wave_order();
     }
 
     // this lane's four outputs of block (i, j): C[m][n .. n + 3]

@@ -67,8 +67,9 @@ WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t ld
         if (M < tm && (layout == 2 || t.mi > 2)) continue;   // see the kernel's requirements
         if (N < tn && (layout != 1 || t.ni > 2)) continue;
         if (t.mi * t.ni == 1 && ((layout != 1 && N >= 32) && (layout != 2 || M >= 32))) continue;   // narrow matrices only
-        if (((M + tm - 1) / tm) * ((N + tn - 1) / tn) >= ((int64_t)1 << 31)) continue;
+        const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
         for (int w = 1; w <= WaveKCfg::max_waves(t.mi, t.ni) && (w == 1 || (int64_t)(w - 1) * WaveKCfg::KC < K); w *= 2) {
+            if (tiles * 64 * w >= ((int64_t)1 << 32)) continue;   // threads of a launch
             const double us = model_us(layout, t.mi, t.ni, w, M, N, K);
             if (best.tile < 0 || us < best.us) best = WaveKChoice{i, w, us};
         }
