@@ -16,8 +16,8 @@
 //
 // Order of the tiles.  Row by row for whole tiles.  BANDS, for large matrices whose rows are no whole lines or whose
 // both strides are multiples of 4 KB: each XCD works on a contiguous chunk of the tiles, four deep along the
-// shorter side of the matrix (with output rows that are no whole lines: always along those; 3000 x 9000 from HBM 34 ->
-// 30 us), and each such band starts 5 tiles further along.  In the first case two tiles
+// shorter side of the matrix (with output rows that are no whole lines but whole 16-byte pieces: always along those; 3000 x
+// 9000 from HBM 34 -> 30 us), and each such band starts 5 tiles further along.  In the first case two tiles
 // that write parts of one line then do it behind the same L2 (2049 x 4100 from HBM 19 -> 16 us); in the second, the
 // lines of a tile fall on few memory channels, and it is the neighbouring tiles that use the others (from HBM:
 // 4096 x 12288 50 -> 43 us, 8192 x 8192 67 -> 53, 4096 x 16384 66 -> 53; floors 39, 52, 52).  Anywhere else it is 3-10 % behind
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void transpose_tile_kernel(const uint16_t* __r
         // XCD x runs the workgroups x, x + 8, ...: a contiguous chunk of the sequence
         const uint32_t x = blockIdx.x & 7, rem = gridDim.x & 7;
         const uint32_t id = x * (gridDim.x >> 3) + min(x, rem) + (blockIdx.x >> 3);
-        const bool tall = tiles_r > tiles_c || (rows & (TR_TILE - 1));   // bands of four tile columns, else of four tile rows
+        const bool tall = tiles_r > tiles_c || ((rows & (TR_TILE - 1)) && !(rows & 7));   // bands of four tile columns, else of four tile rows
         const uint32_t across = tall ? tiles_c : tiles_r, along = tall ? tiles_r : tiles_c;
         const uint32_t band = id / (TR_BAND * along), in_band = id - band * (TR_BAND * along);
         const uint32_t depth = min(across - band * TR_BAND, (uint32_t)TR_BAND);
