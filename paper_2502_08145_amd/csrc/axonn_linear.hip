@@ -371,9 +371,9 @@ static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64
 }
 
 // The kernel with the smallest modelled time.  The tile kernels win as soon as their tiles fill a good part of the
-// chip (1064 x 4168 x 1608 NN: 23 us against 39 for the guarded kernel and 43 for the wave-K one), the wave-K kernel
+// chip (1064 x 4168 x 1608 NN: 25 us against 39 for the guarded kernel and 43 for the wave-K one), the wave-K kernel
 // wherever the output has few 128 x 128 tiles (by a factor of three and more for a few rows over a long K; it
-// loses from some 20 GFLOP on, where 64 x 64 tiles load twice the bytes: 1930 x 7344 x 1832 NN 123 us against
+// loses from some 20 GFLOP on, where its 64 x 64 tiles load twice the bytes: 1930 x 7344 x 1832 NN 123 us against
 // 96 for the guarded kernel).  The margin between those two covers their models' residuals.
 static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
     BlockChoice best;
@@ -455,7 +455,7 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
         // neighbours), or the whole 128 x 128 tiles to the tile kernels (if K suits them) and the last
         // columns and the last rows as strips of their own.  Strips pay where the overlapping tiles would
         // start another round: 2049 x 8192 x 2048 NN is one round of 256 large tiles and a strip of one row
-        // (62 us), or 288 tiles in one launch (87 us).
+        // (59 us), or 288 tiles in one launch (87 us).
         const int64_t mm = M - M % 128, nm = N - N % 128;
         // the tile kernels move 16 bytes at a time: every row of the operands and of the output, as
         // stored in the whole matrices, has to start on a 16-byte boundary (K is a multiple of 32 here)
