@@ -175,7 +175,7 @@ def main():
             gemms.append(dict(name=f"square{n}.{layout}", op="fwd", layout=layout, M=n, N=n, K=n,
                               a=[up(a_h) for _ in range(sets)], b=[up(b_h) for _ in range(sets)],
                               c=[torch.empty((n, n), dtype=torch.bfloat16, device=dev) for _ in range(sets)],
-                              flops=2.0 * n ** 3, host=(a_h, b_h), variant=B.plan_name(n, n, n, layout)))
+                              flops=2.0 * n ** 3, host=(a_h, b_h), variant=B.kernel_name(n, n, n, layout, now=True)))
     else:
         seed = synth.BASE_SEED + 100 * sorted(LAYERS).index(args.workload)
         step_bytes = sum(2 * (tk * di + di * do + tk * do) + 2 * (tk * do + tk * di + di * do)
@@ -191,7 +191,7 @@ def main():
                 g["c"] = [torch.empty((g["M"], g["N"]), dtype=torch.bfloat16, device=dev) for _ in range(sets)]
                 g["flops"] = 2.0 * g["M"] * g["N"] * g["K"]
                 g["host"] = (t[first], t[second])
-                g["variant"] = B.plan_name(g["M"], g["N"], g["K"], g["layout"])   # "a+b": two launches
+                g["variant"] = B.kernel_name(g["M"], g["N"], g["K"], g["layout"], now=True)   # "a+b": two launches
                 gemms.append(g)
     step_flops = sum(g["flops"] for g in gemms)
     log(f"workload {args.workload}: {len(gemms)} GEMMs, {step_flops / 1e12:.3f} TFLOP per step, {step_bytes / 1e6:.0f} MB of "

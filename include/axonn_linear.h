@@ -308,7 +308,15 @@ int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_pl
 /* A plan names the variants its blocks are planned with.  Where the smallest outputs are concerned (a few dozen
  * tiles of 128 x 128) the block of a tile variant may run on the kernel that splits K over a workgroup's waves,
  * which needs no scratch area; a FORCED tile variant is always that very kernel.
- * Override the choice for all later calls in this process; -1 restores automatic selection.
+ * axonn_linear_part_kernel tells what runs: it writes the name of the kernel behind launch `part` (0, 1, ...) to
+ * `name` (HOST memory, `name_bytes` bytes, 64 are enough, zero-terminated) and returns the number of launches, or a
+ * negative error code.  now = 0: of axonn_linear_plan; now = 1: of a call made now on the current device, a forced
+ * variant included.  Names: a tile variant's, with "_ktail" behind it for a K that is no multiple of 64 (the
+ * 128 x 128 tiles of NT are the 64-k kernel's: "mfma16k64_128x128"); "wavek_<rows>x<columns>_w<waves>" where the
+ * waves of a workgroup split K; "edge_128x128" for the guarded kernel; "naive".  Host logic, now = 1 plus one
+ * hipGetDevice. */
+int axonn_linear_part_kernel(int64_t M, int64_t N, int64_t K, int layout, int now, int part, char *name, size_t name_bytes);
+/* Override the choice for all later calls in this process; -1 restores automatic selection.
  * Returns AXONN_OK or AXONN_ERR_INVALID_ARG.  For tests, tuning and the benchmark. */
 int axonn_linear_force_variant(int variant);
 

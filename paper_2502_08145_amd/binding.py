@@ -24,7 +24,7 @@ EXPORTS = (
     "axonn_linear_gemm_static", "axonn_linear_static_scratch_bytes",
     "axonn_status_string", "axonn_linear_version", "axonn_linear_num_variants",
     "axonn_linear_variant_name", "axonn_linear_variant_supports", "axonn_linear_select_variant",
-    "axonn_linear_plan", "axonn_linear_call_plan",
+    "axonn_linear_plan", "axonn_linear_call_plan", "axonn_linear_part_kernel",
     "axonn_linear_force_variant",
     "axonn_linear_init", "axonn_linear_set_split_k", "axonn_linear_split_k_timeouts",
     "axonn_linear_workspace_bytes", "axonn_linear_set_workspace", "axonn_transpose_bf16",
@@ -105,6 +105,8 @@ def lib() -> ctypes.CDLL:
         L.axonn_linear_plan.restype = ci
         L.axonn_linear_call_plan.argtypes = [i64, i64, i64, ci, ctypes.POINTER(PlanPart)]
         L.axonn_linear_call_plan.restype = ci
+        L.axonn_linear_part_kernel.argtypes = [i64, i64, i64, ci, ci, ci, ctypes.c_char_p, ctypes.c_size_t]
+        L.axonn_linear_part_kernel.restype = ci
         L.axonn_linear_force_variant.argtypes = [ci]
         L.axonn_linear_force_variant.restype = ci
         L.axonn_linear_workspace_bytes.argtypes = [i64, i64, i64, ci]
@@ -193,6 +195,24 @@ def call_plan(M: int, N: int, K: int, layout) -> list:
 def plan_name(M: int, N: int, K: int, layout, now: bool = False) -> str:
     """Variant names of the launches of plan() (now=True: of call_plan()), joined by '+'."""
     return "+".join(variant_name(p["variant"]) for p in (call_plan if now else plan)(M, N, K, layout))
+
+
+def kernels(M: int, N: int, K: int, layout, now: bool = False) -> list:
+    """Names of the kernels that the launches of plan() run; now=True: those of a call made now, a forced variant
+    included."""
+    name = ctypes.create_string_buffer(64)
+    names, launches = [], 1
+    while len(names) < launches:
+        launches = lib().axonn_linear_part_kernel(M, N, K, _layout(layout), int(now), len(names), name, len(name))
+        if launches < 0:
+            raise AxonnError(launches, "axonn_linear_part_kernel")
+        names.append(name.value.decode())
+    return names
+
+
+def kernel_name(M: int, N: int, K: int, layout, now: bool = False) -> str:
+    """kernels(), joined by '+'."""
+    return "+".join(kernels(M, N, K, layout, now))
 
 
 def force_variant(v: int) -> None:

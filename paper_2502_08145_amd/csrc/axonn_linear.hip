@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdio>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -648,15 +649,9 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
 // Where a call's split-K kernels find their scratch area.
 enum class ScratchFrom { Registered, Static };
 
-static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, const void* b, void* c,
-                  int fp32_accumulate, void* stream, ScratchFrom from = ScratchFrom::Registered) {
-    const int rc = check_args(M, N, K, layout, a, b, c, fp32_accumulate);
-    if (rc != AXONN_OK) return rc;
-    if (M == 0 || N == 0) return AXONN_OK;
-
+// The launches of a call made now on the current device, and the scratch area that its split-K kernels use.
+static int plan_call(int64_t M, int64_t N, int64_t K, int layout, ScratchFrom from, Plan& plan, Scratch& scratch) {
     const int forced = g_forced.load(std::memory_order_relaxed);
-    Plan plan;
-    Scratch scratch;
     if (forced >= 0) {
         if (!variant_supports(forced, M, N, K, layout)) return AXONN_ERR_UNSUPPORTED;
         plan = Plan{1, {{forced, M, N, 0, 0}}};
@@ -673,6 +668,36 @@ static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, co
             plan = cached_plan(M, N, K, layout, false);   // no area, or too small a one: the kernels that need none
         }
     }
+    return AXONN_OK;
+}
+
+// The kernel behind one launch, named as profile_summary.short() names its symbol (plus the number of K ranges
+// or of waves per tile, which are run-time arguments).  A plan names variants: what runs is more than that.
+static int part_kernel_name(const Part& p, int64_t K, int layout, char* name, size_t bytes) {
+    const Variant& planned = variants()[p.variant];
+    if (p.how.wavek.tile >= 0) {
+        int rows = 0, cols = 0;
+        wavek_tile(p.how.wavek, &rows, &cols);
+        return std::snprintf(name, bytes, "wavek_%dx%d_w%d", rows, cols, p.how.wavek.waves);
+    }
+    if (planned.edge && p.how.tile < 0) return std::snprintf(name, bytes, "edge_%dx%d", planned.bm, planned.bn);
+    const Variant& var = planned.edge ? variants()[p.how.tile] : planned;
+    // two K-contiguous operands (NT) on 128 x 128 tiles: the 64-k kernel under the ring variant's name
+    const bool k64_under_ring_name = layout == AXONN_NT && !var.k64 && var.bm == 128 && var.bn == 128;
+    return std::snprintf(name, bytes, "%s%s%s", k64_under_ring_name ? "mfma16k64_" : "",
+                         var.name + (k64_under_ring_name ? std::strlen("mfma16_") : 0), var.bm && K % 64 ? "_ktail" : "");
+}
+
+static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, const void* b, void* c,
+                  int fp32_accumulate, void* stream, ScratchFrom from = ScratchFrom::Registered) {
+    const int rc = check_args(M, N, K, layout, a, b, c, fp32_accumulate);
+    if (rc != AXONN_OK) return rc;
+    if (M == 0 || N == 0) return AXONN_OK;
+
+    Plan plan;
+    Scratch scratch;
+    const int planned = plan_call(M, N, K, layout, from, plan, scratch);
+    if (planned != AXONN_OK) return planned;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const uint16_t* A = static_cast<const uint16_t*>(a);
     const uint16_t* B = static_cast<const uint16_t*>(b);
@@ -925,6 +950,22 @@ int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_pl
     for (int i = 0; i < plan.parts; ++i)
         parts[i] = axonn_plan_part_t{plan.part[i].variant, plan.part[i].m, plan.part[i].n, plan.part[i].row0, plan.part[i].col0};
     return plan.parts;
+}
+
+int axonn_linear_part_kernel(int64_t M, int64_t N, int64_t K, int layout, int now, int part, char* name, size_t name_bytes) {
+    if (M <= 0 || N <= 0 || K < 0 || layout < 0 || layout > 2 || (now != 0 && now != 1) || part < 0 || !name || name_bytes == 0)
+        return AXONN_ERR_INVALID_ARG;
+    axonn::Plan plan;
+    if (now) {
+        axonn::Scratch scratch;
+        const int rc = axonn::plan_call(M, N, K, layout, axonn::ScratchFrom::Registered, plan, scratch);
+        if (rc != AXONN_OK) return rc;
+    } else {
+        plan = axonn::cached_plan(M, N, K, layout, axonn::g_split_k_enabled.load(std::memory_order_relaxed) != 0);
+    }
+    if (part >= plan.parts) return AXONN_ERR_INVALID_ARG;
+    const int n = axonn::part_kernel_name(plan.part[part], K, layout, name, name_bytes);
+    return n > 0 && (size_t)n < name_bytes ? plan.parts : AXONN_ERR_INVALID_ARG;
 }
 
 int axonn_linear_init(void) {

@@ -78,6 +78,11 @@ WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t ld
     return best;
 }
 
+void wavek_tile(const WaveKChoice& c, int* rows, int* cols) {
+    *rows = 16 * kTiles[c.tile].mi;
+    *cols = 16 * kTiles[c.tile].ni;
+}
+
 static int lds_bytes(int tile, int waves, int layout) {
     return WaveKCfg::lds_bytes(layout != 2, layout == 1, kTiles[tile].mi, kTiles[tile].ni, waves);
 }

@@ -67,7 +67,7 @@ def peak_curve(args):
             reps = int(max(4, min(100, 2000.0 / max(est, 1e-3))))
             ms = time_gemm("fwd", n, n, n, layout, a, b, c, reps)
             tf = 2.0 * n ** 3 / ms / 1e9
-            v = B.plan_name(n, n, n, layout)
+            v = B.kernel_name(n, n, n, layout)
             print(f"{n:6d} {layout:>4s} {v:<22s} {reps:4d} {ms:10.4f} {tf:9.1f} {tf / PEAK * 100:6.1f}%", flush=True)
         del a, b, c
         n *= 2
@@ -101,9 +101,9 @@ def model_zoo(args):
                         flops_sum += fl
                         ms_sum += ms
                         if worst is None or tf < worst[0]:
-                            worst = (tf, f"{name}.{op} {lay} M={M} N={N} K={K} {B.plan_name(M, N, K, lay)}")
+                            worst = (tf, f"{name}.{op} {lay} M={M} N={N} K={K} {B.kernel_name(M, N, K, lay)}")
                         if args.verbose:
-                            print(f"   {h} {name}.{op} {lay} M={M} N={N} K={K} {B.plan_name(M, N, K, lay)} {ms * 1e3:.1f} us {tf:.0f}", flush=True)
+                            print(f"   {h} {name}.{op} {lay} M={M} N={N} K={K} {B.kernel_name(M, N, K, lay)} {ms * 1e3:.1f} us {tf:.0f}", flush=True)
                     del X, W, dY
         rates.sort()
         print(f"{h:6d} {len(rates):5d} {guarded:7d} {rates[0]:8.1f} {rates[len(rates) // 2]:8.1f} {rates[-1]:8.1f} "

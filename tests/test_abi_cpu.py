@@ -339,3 +339,28 @@ def test_planner_choices_that_the_design_notes_describe():
     assert name(2048, 2048, 65536, "NT").startswith("mfma16k64_256x256_w8_sk")
     # one and a half rounds of large tiles: two launches
     assert "+" in name(2048, 12288, 4096, "NN")
+
+
+# ------------------------------------------------------------------ what a call really runs
+@pytest.mark.parametrize("shape,layout,planned,runs", [
+    ((640, 640, 2048), "TN", "mfma16_128x128", "wavek_"),                              # few tiles: K split over the waves
+    ((128, 128, 8192), "NT", "mfma16_128x128_sk", "wavek_"),
+    ((1064, 4168, 1608), "NT", "mfma16_edge_128x128", "mfma16k64_128x256_ktail"),      # overlapping tiles, a K tail
+    ((1064, 4168, 1664), "NN", "mfma16_edge_128x128", "mfma16_128x256_w8"),            # overlapping tiles
+    ((4099, 4099, 4099), "TN", "mfma16_edge_128x128", "edge_128x128"),
+    ((1024, 3072, 3072), "NT", "mfma16_128x128", "mfma16k64_128x128"),                  # the 64-k kernel under the ring's name
+    ((128, 128, 0), "NN", "naive", "naive"),
+])
+def test_kernel_names_are_those_of_the_kernels_that_run(shape, layout, planned, runs):
+    assert B.plan_name(*shape, layout).startswith(planned)
+    got = B.kernel_name(*shape, layout, now=True)
+    assert got.startswith(runs) and ("_ktail" in got) == ("_ktail" in runs), got
+    assert len(B.kernels(*shape, layout)) == len(B.plan(*shape, layout))
+
+
+def test_kernel_name_query_refuses_bad_arguments():
+    L, name = B.lib(), ctypes.create_string_buffer(64)
+    assert L.axonn_linear_part_kernel(0, 8, 8, 0, 0, 0, name, 64) == B.AXONN_ERR_INVALID_ARG
+    assert L.axonn_linear_part_kernel(256, 256, 256, 0, 0, 1, name, 64) == B.AXONN_ERR_INVALID_ARG   # one launch only
+    assert L.axonn_linear_part_kernel(256, 256, 256, 0, 0, 0, name, 4) == B.AXONN_ERR_INVALID_ARG    # no room
+    assert L.axonn_linear_part_kernel(256, 256, 256, 0, 0, 0, None, 64) == B.AXONN_ERR_INVALID_ARG
