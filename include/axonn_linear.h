@@ -307,7 +307,8 @@ int axonn_linear_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_pa
 int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_part_t parts[AXONN_MAX_PLAN_PARTS]);
 /* A plan names the variants its blocks are planned with.  Where the smallest outputs are concerned (a few dozen
  * tiles of 128 x 128) the block of a tile variant may run on the kernel that splits K over a workgroup's waves,
- * which needs no scratch area; a FORCED tile variant is always that very kernel.
+ * which needs no scratch area.  A FORCED variant is always that very kernel (the last one: the guarded kernel with
+ * 128 x 128 tiles).
  * axonn_linear_part_kernel tells what runs: it writes the name of the kernel behind launch `part` (0, 1, ...) to
  * `name` (HOST memory, `name_bytes` bytes, 64 are enough, zero-terminated) and returns the number of launches, or a
  * negative error code.  now = 0: of axonn_linear_plan; now = 1: of a call made now on the current device, a forced

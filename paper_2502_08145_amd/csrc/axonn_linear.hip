@@ -654,8 +654,7 @@ static int plan_call(int64_t M, int64_t N, int64_t K, int layout, ScratchFrom fr
     const int forced = g_forced.load(std::memory_order_relaxed);
     if (forced >= 0) {
         if (!variant_supports(forced, M, N, K, layout)) return AXONN_ERR_UNSUPPORTED;
-        plan = Plan{1, {{forced, M, N, 0, 0}}};
-        if (variants()[forced].edge) settle_parts(plan, M, N, K, layout);   // any other: that very kernel
+        plan = Plan{1, {{forced, M, N, 0, 0}}};   // that very kernel (for the last variant: gemm_edge_kernel)
     } else {
         plan = cached_plan(M, N, K, layout, g_split_k_enabled.load(std::memory_order_relaxed) != 0);
     }

@@ -364,3 +364,19 @@ def test_kernel_name_query_refuses_bad_arguments():
     assert L.axonn_linear_part_kernel(256, 256, 256, 0, 0, 1, name, 64) == B.AXONN_ERR_INVALID_ARG   # one launch only
     assert L.axonn_linear_part_kernel(256, 256, 256, 0, 0, 0, name, 4) == B.AXONN_ERR_INVALID_ARG    # no room
     assert L.axonn_linear_part_kernel(256, 256, 256, 0, 0, 0, None, 64) == B.AXONN_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
+@pytest.mark.parametrize("shape", [(1, 1, 1), (130, 257, 96), (24, 2048, 8192), (1064, 4168, 1608), (1031, 520, 1000), (4096, 4096, 4096)])
+def test_a_forced_variant_is_that_very_kernel(shape, layout):
+    """The guarded variant among them: forced, it is the guarded kernel and not what the sizes would decide."""
+    forced = [B.num_variants() - 1] + [v for v in range(1, B.num_variants() - 1)
+                                       if "_sk" not in B.variant_name(v) and B.variant_supports(v, *shape, layout)]
+    for v in forced:
+        B.force_variant(v)
+        try:
+            got = B.kernel_name(*shape, layout, now=True)
+        finally:
+            B.force_variant(-1)
+        assert got.split("_", 1)[1] in B.variant_name(v) and not got.startswith("wavek") and "_ktail" not in got, (v, got)
+    assert "wavek" in B.kernel_name(24, 2048, 8192, layout, now=True)   # not forced any more
