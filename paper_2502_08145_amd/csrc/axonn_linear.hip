@@ -385,7 +385,7 @@ static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, i
         best.us = wk.us;
     }
     for (int v = 1; v < edge_variant(); ++v) {
-        if (variants()[v].splits > 1) continue;   // ragged outputs never touch the scratch area
+        if (variants()[v].splits > 1) continue;   // overlapping tiles and strips never touch the scratch area
         const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
         if (us >= 0.0 && us < best.us) {
             best = BlockChoice{};
@@ -447,6 +447,25 @@ struct Plan {
 };
 static_assert(AXONN_MAX_PLAN_PARTS >= 4, "two launches over whole tiles and two edge strips");
 
+// Whether the whole tiles of a ragged product (mm x nm of its M x N) may use the scratch area.  Products that may
+// not can overlap on several streams and are never refused by the static entry, so the set is part of the
+// interface: it is fixed by the rates below (a guarded strip's, in microseconds) and does not follow what a ragged
+// product's kernels have become since.  Without it 311 of 90 000 sampled products would exchange partial tiles
+// through the area that other plans leave alone, twelve of them more than the static area holds.
+static bool ragged_may_split(int64_t M, int64_t N, int64_t mm, int64_t nm, int64_t K, int layout) {
+    constexpr double kLaunch = 3.0, kStep = 2.0, kSideBySide = 320.0;   // a launch; 128 k; workgroups at that rate
+    auto guarded = [&](int64_t m, int64_t n) {
+        const double wgs = (double)(((m + 127) / 128) * ((n + 127) / 128));
+        return kLaunch + (double)((K + 127) / 128) * kStep * std::max(1.0, wgs / kSideBySide);
+    };
+    double t = 0.0;
+    if (is_guarded(select_variant(mm, nm, K, layout, true, &t))) return false;
+    // a strip is a further launch of 8e6 units
+    if (nm != N) t += guarded(mm, N - nm) * kUnitsPerUs + 8.0e6;
+    if (mm != M) t += guarded(M - mm, N) * kUnitsPerUs + 8.0e6;
+    return t < guarded(M, N) * kUnitsPerUs;
+}
+
 static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_split, double* t_out = nullptr) {
     double t_one = 0;
     Plan plan{1, {{select_variant(M, N, K, layout, allow_split, &t_one), M, N, 0, 0}}};
@@ -463,9 +482,8 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
         const bool rows_aligned = N % 8 == 0 && (layout != AXONN_TN || M % 8 == 0);
         if (mm > 0 && nm > 0 && (mm != M || nm != N) && rows_aligned) {
             constexpr double kLaunch = 3.0;
-            // A ragged product of up to 640 whole tiles never touches the scratch area, so calls of that size
-            // may overlap on several streams; the whole tiles of a larger one may be split as any whole output.
-            const bool split = allow_split && (mm / 128) * (nm / 128) > 640;
+            // Up to 640 whole tiles the plans that split took as long as the one launch or longer, which needs no scratch.
+            const bool split = allow_split && (mm / 128) * (nm / 128) > 640 && ragged_may_split(M, N, mm, nm, K, layout);
             double t_tiles = 0;
             const int v_tiles = select_variant(mm, nm, K, layout, split, &t_tiles);
             if (!is_guarded(v_tiles)) {

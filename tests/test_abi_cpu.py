@@ -380,3 +380,17 @@ def test_a_forced_variant_is_that_very_kernel(shape, layout):
             B.force_variant(-1)
         assert got.split("_", 1)[1] in B.variant_name(v) and not got.startswith("wavek") and "_ktail" not in got, (v, got)
     assert "wavek" in B.kernel_name(24, 2048, 8192, layout, now=True)   # not forced any more
+
+
+@pytest.mark.parametrize("shape,layouts", [((1624, 13616, 5952), ("NN", "NT", "TN")), ((8200, 2624, 13568), ("NN", "NT")),
+                                           ((3856, 5232, 9280), ("NT",)), ((14120, 1576, 6144), ("NN", "NT")),
+                                           ((1320, 13488, 4352), ("NN", "NT", "TN")), ((2648, 8496, 10368), ("NN", "NT", "TN")),
+                                           ((6736, 3080, 16256), ("NT",)), ((13304, 1360, 8960), ("NN", "NT", "TN"))])
+def test_ragged_products_that_need_no_scratch(shape, layouts):
+    """Ragged products that one launch without scratch serves: calls may overlap on several streams, and
+    the static entry takes them whatever their size."""
+    for lay in layouts:
+        assert B.axonn_linear_workspace_bytes(*shape, lay) == 0, lay
+        assert "_sk" not in B.kernel_name(*shape, lay)
+    # what splits is the whole tiles of a product that is large beside its strips
+    assert B.axonn_linear_workspace_bytes(2048 + 8, 12288, 8192, "NT") == B.axonn_linear_workspace_bytes(2048, 12288, 8192, "NT") > 0
