@@ -241,9 +241,10 @@ const char *axonn_status_string(int status);
 /* Library version, major * 10000 + minor * 100 + patch. */
 int axonn_linear_version(void);
 
-/* Caller-owned split-K scratch.  axonn_linear_workspace_bytes: what the launches the library would
- * make for this problem need (0: none; otherwise at least the 4 KiB + 256 KiB that
- * axonn_linear_set_workspace accepts).  axonn_linear_set_workspace: use `bytes` bytes at the
+/* Caller-owned split-K scratch.  axonn_linear_workspace_bytes: what the variants that this problem is planned with
+ * need (0: none; otherwise at least the 4 KiB + 256 KiB that axonn_linear_set_workspace accepts).  A block that
+ * runs on a kernel without scratch all the same (axonn_linear_part_kernel) touches none of it, registered or not.
+ * axonn_linear_set_workspace: use `bytes` bytes at the
  * DEVICE pointer `dev_ptr` (256-byte aligned) as the current device's scratch area from now on; the
  * first 4 KiB are cleared (hipMemset, then a device synchronisation: this call is synchronous).  The
  * caller keeps ownership and must keep the memory alive, and untouched, while it is registered;
@@ -301,7 +302,7 @@ typedef struct {
     int64_t m, n, row0, col0;
 } axonn_plan_part_t;
 int axonn_linear_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_part_t parts[AXONN_MAX_PLAN_PARTS]);
-/* The same for a call made NOW on the current device: as axonn_linear_plan unless the plan needs a
+/* The same for a call made NOW on the current device: as axonn_linear_plan unless its launches need a
  * larger scratch area than the one registered there (or none is registered), in which case it is
  * the plan without split-K that the call would fall back to.  Host logic plus one hipGetDevice. */
 int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_part_t parts[AXONN_MAX_PLAN_PARTS]);

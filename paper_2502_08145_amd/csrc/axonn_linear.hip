@@ -614,6 +614,14 @@ static size_t split_bytes(const Plan& plan) {
     return bytes;   // the launches of a plan run one after the other and share the area
 }
 
+// What the launches touch of it: nothing for a block planned with split-K that runs on the wave-K kernel.
+static size_t split_bytes_run(const Plan& plan) {
+    size_t bytes = 0;
+    for (int i = 0; i < plan.parts; ++i)
+        if (plan.part[i].how.wavek.tile < 0) bytes = std::max(bytes, split_bytes(plan.part[i]));
+    return bytes;
+}
+
 // workgroups of the launch over block `p`
 static int64_t part_workgroups(const Part& p) {
     const Variant& var = variants()[p.variant];
@@ -676,7 +684,7 @@ static int plan_call(int64_t M, int64_t N, int64_t K, int layout, ScratchFrom fr
     } else {
         plan = cached_plan(M, N, K, layout, g_split_k_enabled.load(std::memory_order_relaxed) != 0);
     }
-    if (const size_t need = split_bytes(plan)) {
+    if (const size_t need = split_bytes_run(plan)) {
         if (from == ScratchFrom::Static) {
             // the static area has one size: a product whose plan needs more is refused, not re-planned
             if (need > kStaticSlots * kSlotBytes || !(scratch = static_scratch()).partials) return AXONN_ERR_WORKSPACE;
@@ -962,7 +970,7 @@ int axonn_linear_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_pa
 int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_part_t parts[AXONN_MAX_PLAN_PARTS]) {
     if (M <= 0 || N <= 0 || K < 0 || layout < 0 || layout > 2 || !parts) return AXONN_ERR_INVALID_ARG;
     axonn::Plan plan = axonn::cached_plan(M, N, K, layout, axonn::g_split_k_enabled.load(std::memory_order_relaxed) != 0);
-    if (const size_t need = axonn::split_bytes(plan))
+    if (const size_t need = axonn::split_bytes_run(plan))
         if (!axonn::registered_scratch(need).partials) plan = axonn::cached_plan(M, N, K, layout, false);
     for (int i = 0; i < plan.parts; ++i)
         parts[i] = axonn_plan_part_t{plan.part[i].variant, plan.part[i].m, plan.part[i].n, plan.part[i].row0, plan.part[i].col0};

@@ -394,3 +394,15 @@ def test_ragged_products_that_need_no_scratch(shape, layouts):
         assert "_sk" not in B.kernel_name(*shape, lay)
     # what splits is the whole tiles of a product that is large beside its strips
     assert B.axonn_linear_workspace_bytes(2048 + 8, 12288, 8192, "NT") == B.axonn_linear_workspace_bytes(2048, 12288, 8192, "NT") > 0
+
+
+@pytest.mark.parametrize("shape", [(1280, 1152, 3072), (1792, 896, 4096), (1536, 896, 3264), (1536, 128, 3456), (128, 128, 8192)])
+def test_a_block_on_the_wave_k_kernel_asks_for_no_scratch(shape):
+    """Planned with split-K, run on the kernel that needs no scratch: the call is the same with and without a
+    registered area (there is none here)."""
+    assert "_sk" in B.plan_name(*shape, "NT") and B.axonn_linear_workspace_bytes(*shape, "NT") > 0
+    assert B.kernel_name(*shape, "NT").startswith("wavek_")
+    assert B.kernels(*shape, "NT", now=True) == B.kernels(*shape, "NT")
+    assert B.call_plan(*shape, "NT") == B.plan(*shape, "NT")
+    # one that does exchange partial tiles falls back
+    assert "_sk" in B.kernel_name(1024, 1024, 4096, "NT") and "_sk" not in B.kernel_name(1024, 1024, 4096, "NT", now=True)
