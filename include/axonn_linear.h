@@ -142,6 +142,9 @@ size_t axonn_linear_static_scratch_bytes(void);
  * `stream` and returns.  AXONN_OK, AXONN_ERR_INVALID_ARG, AXONN_ERR_UNSUPPORTED or
  * AXONN_ERR_LAUNCH; nothing launched on error. */
 int axonn_transpose_bf16(int64_t rows, int64_t cols, const void *src, void *dst, void *stream);
+/* Name of the kernel that re-stores a matrix of this size, both buffers 16-byte aligned or not; NULL if the size is
+ * refused.  Host only. */
+const char *axonn_transpose_kernel(int64_t rows, int64_t cols, int aligned);
 
 /* Mode tuner (Sec. IV-C: time each product in the three modes during the first batch and keep the
  * fastest).  `op` is 0 (fwd), 1 (bwd_data) or 2 (bwd_weight); `first`, `second` are that product's

@@ -1063,22 +1063,31 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     const uintptr_t s = reinterpret_cast<uintptr_t>(src), d = reinterpret_cast<uintptr_t>(dst);
     const uintptr_t bytes = (uintptr_t)rows * (uintptr_t)cols * 2;
     if (!src || !dst || (s & 1) || (d & 1) || (s < d + bytes && d < s + bytes)) return AXONN_ERR_INVALID_ARG;
+    const axonn::TrKernel kernel = axonn::tr_choose(rows, cols, !((s | d) & 15));
+    if (kernel == axonn::TrKernel::Refused) return AXONN_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const uint16_t* from = static_cast<const uint16_t*>(src);
+    uint16_t* to = static_cast<uint16_t*>(dst);
     (void)hipGetLastError();
-    const bool whole = rows % axonn::TR_TILE == 0 && cols % axonn::TR_TILE == 0 && !(s & 15) && !(d & 15);
-    const dim3 grid((unsigned)((rows + 63) / 64), (unsigned)((cols + 3) / 4));
-    if (!whole && grid.y > 65535u) return AXONN_ERR_UNSUPPORTED;
-    const int64_t tiles_r = (rows + axonn::TR_TILE - 1) / axonn::TR_TILE, tiles_c = (cols + axonn::TR_TILE - 1) / axonn::TR_TILE;
-    if (whole || (rows >= axonn::TR_TILE && cols >= axonn::TR_TILE && rows * cols >= axonn::tr_ragged_from(std::min(rows, cols)))) {
-        const int64_t tiles = tiles_r * tiles_c;   // fewer than 2^29: rows * cols < 2^40
-        hipLaunchKernelGGL(axonn::tr_bands(rows, cols, tiles, whole) ? axonn::transpose_tile_kernel<true> : axonn::transpose_tile_kernel<false>,
-                           dim3((unsigned)tiles), dim3(256), 0, st, static_cast<const uint16_t*>(src), static_cast<uint16_t*>(dst),
-                           rows, cols, (int)tiles_r, (int)tiles_c);
+    if (kernel == axonn::TrKernel::Element) {
+        hipLaunchKernelGGL(axonn::transpose_naive_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)((cols + 3) / 4)), dim3(256), 0, st,
+                           from, to, rows, cols);
     } else {
-        hipLaunchKernelGGL(axonn::transpose_naive_kernel, grid, dim3(256), 0, st, static_cast<const uint16_t*>(src),
-                           static_cast<uint16_t*>(dst), rows, cols);
+        const int64_t tiles_r = axonn::tr_tiles(rows), tiles_c = axonn::tr_tiles(cols);   // product below 2^29: rows * cols < 2^40
+        hipLaunchKernelGGL(kernel == axonn::TrKernel::TileBands ? axonn::transpose_tile_kernel<true> : axonn::transpose_tile_kernel<false>,
+                           dim3((unsigned)(tiles_r * tiles_c)), dim3(256), 0, st, from, to, rows, cols, (int)tiles_r, (int)tiles_c);
     }
     return hipGetLastError() == hipSuccess ? AXONN_OK : AXONN_ERR_LAUNCH;
+}
+
+const char* axonn_transpose_kernel(int64_t rows, int64_t cols, int aligned) {
+    if (rows <= 0 || cols <= 0) return nullptr;
+    switch (axonn::tr_choose(rows, cols, aligned != 0)) {
+        case axonn::TrKernel::Element: return "transpose_naive";
+        case axonn::TrKernel::Tile: return "transpose_tile";
+        case axonn::TrKernel::TileBands: return "transpose_tile_bands";
+        default: return nullptr;
+    }
 }
 
 static bool comm_args_ok(const int* grid, int g_node, double beta_inter, double bytes_per_element) {

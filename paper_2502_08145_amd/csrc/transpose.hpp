@@ -28,6 +28,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace axonn {
 
 typedef uint32_t tr_u32x4 __attribute__((ext_vector_type(4)));
@@ -43,6 +45,18 @@ inline bool tr_bands(int64_t rows, int64_t cols, int64_t tiles, bool whole) {
 // narrow one still gives the element kernel the more workgroups (4589 x 193: 3.6 us against 4.2; 1000 x 1000: 4.0
 // against 3.0).
 constexpr int64_t tr_ragged_from(int64_t narrow) { return narrow < 256 ? 3 << 19 : 1 << 18; }
+inline int64_t tr_tiles(int64_t extent) { return (extent + TR_TILE - 1) / TR_TILE; }
+enum class TrKernel { Refused, Element, Tile, TileBands };
+// `aligned`: both pointers on 16-byte boundaries.
+inline TrKernel tr_choose(int64_t rows, int64_t cols, bool aligned) {
+    const bool whole = rows % TR_TILE == 0 && cols % TR_TILE == 0 && aligned;
+    if (!whole && (cols + 3) / 4 > 65535) return TrKernel::Refused;   // the element kernel's grid, whichever kernel runs
+    const int64_t tiles = tr_tiles(rows) * tr_tiles(cols);
+    // 256 threads a tile, and a launch holds fewer than 2^32 in one dimension: the element kernel has two
+    const bool ragged_tiles = std::min(rows, cols) >= TR_TILE && rows * cols >= tr_ragged_from(std::min(rows, cols)) && tiles < ((int64_t)1 << 24);
+    if (!whole && !ragged_tiles) return TrKernel::Element;
+    return tr_bands(rows, cols, tiles, whole) ? TrKernel::TileBands : TrKernel::Tile;
+}
 constexpr int TR_LDS_STRIDE = 144;   // bytes per tile row in LDS (128 + 16)
 
 // Requires rows >= 64, cols >= 64.  grid = tiles, block = 256.

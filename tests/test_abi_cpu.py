@@ -406,3 +406,19 @@ def test_a_block_on_the_wave_k_kernel_asks_for_no_scratch(shape):
     assert B.call_plan(*shape, "NT") == B.plan(*shape, "NT")
     # one that does exchange partial tiles falls back
     assert "_sk" in B.kernel_name(1024, 1024, 4096, "NT") and "_sk" not in B.kernel_name(1024, 1024, 4096, "NT", now=True)
+
+
+@pytest.mark.parametrize("rows,cols,aligned,kernel", [
+    (64, 64, True, "transpose_tile"), (64, 64, False, "transpose_naive"), (63, 9000, True, "transpose_naive"),
+    (2049, 4100, True, "transpose_tile_bands"), (4096, 12288, True, "transpose_tile_bands"), (4096, 12224, True, "transpose_tile"),
+    # 2^24 tiles and more would be 2^32 threads in one dimension, which no launch holds: the element kernel has two
+    (262139 * 64, 64 * 64, False, "transpose_tile_bands"), (2 ** 24, 64 * 64, False, "transpose_naive"),
+    (2 ** 28 + 1, 256, True, "transpose_naive"), (262144 + 1, 262140, True, "transpose_naive"),
+    (8, 262141, True, None), (2049, 300001, True, None), (64, 64 * 5000, True, "transpose_tile"),
+])
+def test_transpose_kernel_by_size(rows, cols, aligned, kernel):
+    got = B.transpose_kernel(rows, cols, aligned)
+    assert got == kernel, (rows, cols, got)
+    if got and got.startswith("transpose_tile"):
+        tiles = -(-rows // 64) * -(-cols // 64)
+        assert tiles * 256 < 2 ** 32
