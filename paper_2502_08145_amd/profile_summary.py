@@ -21,27 +21,44 @@ import re
 import sys
 
 
+_LAYOUT = {("true", "false"): "NN", ("true", "true"): "NT", ("false", "false"): "TN"}   # (A, B) K-contiguous
+_BOOL = "(true|false)"
+
+
 def short(name: str) -> str:
-    m = re.search(r"gemm_tile_kernel(16)?<(\d+), (\d+), (\d+), (\d+), (true|false), (true|false), (true|false)>", name)
+    """The name of a kernel symbol: the library's (axonn_linear_part_kernel) without what is a run-time argument (the
+    number of K ranges, the waves per wave-K tile), and the mode; kernel_key() gives the same from the library's side."""
+    m = re.search(rf"gemm_tile_kernel16<(\d+), (\d+), (\d+), (\d+), {_BOOL}, {_BOOL}, {_BOOL}, {_BOOL}>", name)
     if m:
-        k16, bm, bn, wm, wn, akc, bkc, split = m.groups()
-        lay = {("true", "false"): "NN", ("true", "true"): "NT", ("false", "false"): "TN"}.get((akc, bkc), "??")
+        bm, bn, wm, wn, akc, bkc, split, tail = m.groups()
         waves = "_w8" if int(wm) * int(wn) == 8 else ""
-        return f"mfma{k16 or ''}_{bm}x{bn}{waves}{'_sk' if split == 'true' else ''}/{lay}"
-    m = re.search(r"gemm_tile_kernel_k64<(\d+), (\d+), (\d+), (true|false), (true|false), (true|false), \d+>", name)
+        return f"mfma16_{bm}x{bn}{waves}{'_sk' if split == 'true' else ''}{'_ktail' if tail == 'true' else ''}/{_LAYOUT.get((akc, bkc), '??')}"
+    m = re.search(rf"gemm_tile_kernel_k64<(\d+), (\d+), (\d+), {_BOOL}, {_BOOL}, {_BOOL}, \d+, {_BOOL}>", name)
     if m:
-        bm, bn, wn, akc, bkc, split = m.groups()
-        lay = {("true", "false"): "NN", ("true", "true"): "NT", ("false", "false"): "TN"}.get((akc, bkc), "??")
-        return f"mfma16k64_{bm}x{bn}{'_w8' if wn == '4' else ''}{'_sk' if split == 'true' else ''}/{lay}"
-    m = re.search(r"gemm_tile_kernel_k64p<(true|false), (true|false)>", name)
+        bm, bn, wn, akc, bkc, split, tail = m.groups()
+        waves = "_w8" if wn == "4" else ""
+        return f"mfma16k64_{bm}x{bn}{waves}{'_sk' if split == 'true' else ''}{'_ktail' if tail == 'true' else ''}/{_LAYOUT.get((akc, bkc), '??')}"
+    m = re.search(rf"gemm_tile_kernel_k64p<{_BOOL}, {_BOOL}>", name)
     if m:
-        lay = {("true", "false"): "NN", ("true", "true"): "NT", ("false", "false"): "TN"}.get(m.groups(), "??")
-        return f"mfma16k64p_256x256_w8/{lay}"
-    if "transpose_tile_kernel" in name:
+        return f"mfma16k64p_256x256_w8/{_LAYOUT.get(m.groups(), '??')}"
+    m = re.search(rf"gemm_wavek_kernel<{_BOOL}, {_BOOL}, (\d+), (\d+)>", name)
+    if m:
+        akc, bkc, mi, ni = m.groups()
+        return f"wavek_{16 * int(mi)}x{16 * int(ni)}/{_LAYOUT.get((akc, bkc), '??')}"
+    m = re.search(rf"gemm_edge_kernel<{_BOOL}, {_BOOL}>", name)
+    if m:
+        return f"edge_128x128/{_LAYOUT.get(m.groups(), '??')}"
+    m = re.search(r"gemm_naive_kernel<(\d)>", name)
+    if m:
+        return f"naive/{('NN', 'NT', 'TN')[int(m.group(1))]}"
+    if "transpose_tile_kernel" in name:   # in rows or in bands of tiles: the same traffic
         return "transpose_tile"
-    if "gemm_naive_kernel" in name:
-        return "naive"
+    if "transpose_naive_kernel" in name:
+        return "transpose_naive"
     return re.sub(r"\(.*", "", name)[:60]
+
+
+GEMMS = ("mfma", "wavek", "edge", "naive")   # what the names of the product kernels start with
 
 
 def summarize(d: str, out=sys.stdout):
@@ -56,7 +73,7 @@ def summarize(d: str, out=sys.stdout):
         for r in csv.DictReader(open(f)):
             ctr[short(r["Kernel_Name"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
     print(f"== {d}", file=out)
-    keys = [k for k in dur if k.startswith(("mfma", "transpose_tile", "naive"))]
+    keys = [k for k in dur if k.startswith(GEMMS + ("transpose",))]
     for k in sorted(keys, key=lambda k: -sum(dur[k])):
         v = dur[k]
         print(f"{k:<22s} calls {len(v):5d}  mean {sum(v) / len(v) / 1e3:9.2f} us  min {min(v) / 1e3:9.2f}  "
@@ -74,10 +91,11 @@ def summarize(d: str, out=sys.stdout):
     return dur, ctr
 
 
-def kernel_key(variant: str, layout: str) -> str:
-    """The name this module gives the kernel behind a library variant (split-K variants of 2 and
-    4 K ranges are one kernel)."""
-    return re.sub(r"_sk\d+$", "_sk", variant) + "/" + layout
+def kernel_key(kernel: str, layout: str) -> str:
+    """The name short() gives the symbol behind a kernel name of the library (binding.kernel_name): split-K over any
+    number of K ranges, and wave-K tiles over any number of waves, are one kernel."""
+    kernel = re.sub(r"^(wavek_\d+x\d+)_w\d+$", r"\1", kernel)
+    return re.sub(r"_sk\d+$", "_sk", kernel) + "/" + layout
 
 
 def traffic(workload: str, copy_mib: float, fetch_dir: str, write_dir: str) -> dict:
@@ -90,7 +108,7 @@ def traffic(workload: str, copy_mib: float, fetch_dir: str, write_dir: str) -> d
     w_scale = kib / mean(write["transpose_tile"]["WRITE_SIZE"])
     out = {}
     for k in fetch:
-        if k.startswith("mfma") and k in write:
+        if k.startswith(GEMMS) and k in write:
             out[k] = int(round(1024.0 * (mean(fetch[k]["FETCH_SIZE"]) * f_scale + mean(write[k]["WRITE_SIZE"]) * w_scale)))
     from .build import source_id
     return {workload: out, "_scale": {"FETCH_SIZE": round(f_scale, 4), "WRITE_SIZE": round(w_scale, 4)},
