@@ -33,7 +33,7 @@ static const WaveKTile kTiles[] = {
 //   memory:                  every operand and output byte once
 //   staging:                 every byte that some tile loads, through the L2s
 // Constants: least squares on the logarithm over 5 700 sampled products of up to 150 GFLOP, operands in cache
-// (residual 16-18 %; the tile and wave count it chooses are 6 % behind the best ones measured on average).  The
+// (residual 16-18 %; the tile and wave count it chooses are 4 % behind the best ones measured on average).  The
 // smallest of some twenty estimates is an optimistic one: what is chosen takes 1.10 of it.
 constexpr double kChosen = 1.10;
 struct WaveKModel {
@@ -48,7 +48,11 @@ static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t
     const WaveKModel& m = kModel[layout];
     const double area = mi * ni, tiles = (double)((M + 16 * mi - 1) / (16 * mi)) * (double)((N + 16 * ni - 1) / (16 * ni));
     const int64_t n_chunks = (K + WaveKCfg::KC - 1) / WaveKCfg::KC;
-    const double chunks = (double)n_chunks, rounds = std::pow(1.0 + std::pow(tiles / 256.0, 4.0), 0.25);
+    // Beyond one tile per compute unit a round more is a whole one: smoothed there as well, the model was 16-18 % short
+    // just above 256, 512 and 768 tiles, and 2816 x 128 x 9856 TN went to 352 tiles of 32 x 32 (53.5 us) from split-K
+    // (39.6).
+    const double chunks = (double)n_chunks, full = tiles / 256.0;
+    const double rounds = full > 1.0 ? std::ceil(full) : std::pow(1.0 + std::pow(full, 4.0), 0.25);
     const double chain = (double)((n_chunks + waves - 1) / waves) * (m.chunk0 + m.chunk_area * area);
     const double unit = rounds * (chunks * (m.work_side * (mi + ni) + m.work_area * area) +
                                   (waves > 1 ? m.exchange * waves * area / 16.0 : 0.0) + m.store * area / 16.0);
