@@ -331,13 +331,15 @@ static double model_time(int v, int64_t M, int64_t N, int64_t K, int layout, boo
 // model_time's units to the microsecond: a 256 x 256 tile over K = 4096 is 2.7e8 and takes about 100 us
 constexpr double kUnitsPerUs = 2.6e6;
 
-// The guarded MFMA kernel (gemm_edge_kernel) alone, in microseconds: steps of 128 k, dearer in proportion as
+// The guarded MFMA kernel (gemm_edge_kernel) alone, in microseconds: steps of 128 k, dearer nearly in proportion as
 // workgroups come to share the compute units (least squares over 15 000 sampled products each of aligned and
-// of misaligned rows, residual 6 % and 23 %).
+// of misaligned rows, residual 6 % and 23 %; aligned rows also over 900 outputs of up to 500 MB, 10 %, where
+// proportion was 12-15 % too much).
 static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
     const double wgs = (double)(((m + EdgeCfg::BM - 1) / EdgeCfg::BM) * ((n + EdgeCfg::BN - 1) / EdgeCfg::BN));
     const double steps = (double)((K + EdgeCfg::BK - 1) / EdgeCfg::BK);
-    return 3.0 + (rows_aligned ? 1.8 * steps + 2.6 : 2.0 * steps + 5.0) * std::sqrt(1.0 + (wgs / 292.0) * (wgs / 292.0));
+    return rows_aligned ? 3.0 + (1.8 * steps + 2.6) * std::pow(1.0 + (wgs / 287.0) * (wgs / 287.0), 0.47)
+                        : 3.0 + (2.0 * steps + 5.0) * std::sqrt(1.0 + (wgs / 292.0) * (wgs / 292.0));
 }
 
 // How a block of the output is computed where it is not simply the tile variant of its part.
@@ -347,6 +349,19 @@ struct BlockChoice {
     int lead_m = 0, lead_n = 0;   // rows and columns before the block that the launch covers as well
     double us = 0.0;         // modelled time, operands in cache
 };
+
+// Where the rows of the output do not start on 128-byte lines, a tile's stores end in lines that two workgroups write a
+// part of.  That costs a round of 256 x 256 tiles 6.4 us (but for the first half round), one of half tiles 1.4, one of
+// 128 x 128 tiles 0.6 from 8 rounds on; less where the rows start on 32 or 64 bytes.  Medians of 800 sampled products,
+// each measured on every tile; without it the model was short by up to 1.7 times for outputs of 240 MB and more.
+static double shared_lines_us(const Variant& x, int64_t m, int64_t n, int64_t ldc) {
+    const double share = ldc % 64 == 0 ? 0.0 : ldc % 32 == 0 ? 0.15 : ldc % 16 == 0 ? 0.9 : 1.0;
+    const double rounds = (double)(((m + x.bm - 1) / x.bm) * ((n + x.bn - 1) / x.bn) * x.splits) / 256.0;
+    const int area = x.bm * x.bn;
+    return share * (area <= 128 * 128  ? 0.6 * std::max(0.0, rounds - 8.0)
+                    : area < 256 * 256 ? 1.4 * std::max(0.0, rounds - 0.5)
+                                       : 6.4 * std::max(0.0, rounds - 0.5));
+}
 
 // A tile variant over an m x n block, in microseconds; < 0: it cannot run there, or there is no model of it.
 // Full rounds of 256 workgroups and 0.76 + 0.24 f of one for a last round that fills a fraction f of the compute
@@ -368,19 +383,24 @@ static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64
         exchange = area <= 128 * 128  ? 4.1 + 1.35 * more + (0.030 + 0.022 * more) * (double)tiles
                    : area < 256 * 256 ? 5.4 + 2.3 * more + (0.044 + 0.030 * more) * (double)tiles
                                       : 6.8 + 2.7 * more + (0.060 + 0.040 * more) * (double)tiles;
-    return 3.0 + rounds * ((double)(k_padded / 64 / x.splits) * x.us64[layout] + fixed) + exchange;
+    return 3.0 + rounds * ((double)(k_padded / 64 / x.splits) * x.us64[layout] + fixed) + shared_lines_us(x, m, n, ldc) + exchange;
 }
 
 // The kernel with the smallest modelled time.  The tile kernels win as soon as their tiles fill a good part of the
 // chip (1064 x 4168 x 1608 NN: 25 us against 39 for the guarded kernel and 43 for the wave-K one), the wave-K kernel
 // wherever the output has few 128 x 128 tiles (by a factor of three and more for a few rows over a long K; it
 // loses from some 20 GFLOP on, where its 64 x 64 tiles load twice the bytes: 1930 x 7344 x 1832 NN 123 us against
-// 96 for the guarded kernel).  The margin between those two covers their models' residuals.
+// 96 for the guarded kernel), the guarded one for large outputs over one or two steps of K (4160 x 11928 x 72 TN: 38 us
+// against 53 on 256 x 256 tiles).  Near a tie it is the guarded kernel: of 2 400 sampled ragged products, half of them with K
+// of 72 to 768 and half with outputs of up to 500 MB, 9 then run more than 4 % (12 % at most) behind it or behind
+// whole tiles with guarded strips.
 static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
-    BlockChoice best;
-    best.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
+    constexpr double kMargin = 0.93;
+    BlockChoice guarded, best;
+    guarded.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
+    best.us = kMargin * guarded.us;
     const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb);
-    if (wk.tile >= 0 && wk.us < 0.93 * best.us) {
+    if (wk.tile >= 0 && wk.us < best.us) {
         best.wavek = wk;
         best.us = wk.us;
     }
@@ -393,7 +413,7 @@ static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, i
             best.us = us;
         }
     }
-    return best;
+    return best.tile < 0 && best.wavek.tile < 0 ? guarded : best;
 }
 // The same for the block at (row0, col0) of the M x N product.  An edge strip of fewer than 16 rows or columns of
 // an MN-contiguous operand is too narrow for the wave-K kernel and would take the guarded one, element by element
@@ -466,10 +486,29 @@ static bool ragged_may_split(int64_t M, int64_t N, int64_t mm, int64_t nm, int64
     return t < guarded(M, N) * kUnitsPerUs;
 }
 
-static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_split, double* t_out = nullptr) {
+// A launch over whole tiles of the M x N product, in microseconds.  The variants without a figure of their own count as
+// the 64-k kernel on the same tile: the 32-k ring on the large tile, and the resident workgroups, whose stores overlap
+// the next tile's loads (1 to 2 us a round less on 36 products, and 0.6 of what shared lines cost; below K = 384 only
+// where there are none).
+static double tiles_us(const Part& p, int64_t M, int64_t N, int64_t K, int layout) {
+    const Variant& x = variants()[p.variant];
+    const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
+    double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);
+    for (int v = 1; us < 0.0 && v < edge_variant(); ++v) {
+        const Variant& y = variants()[v];
+        if (!y.k64 || y.bm != x.bm || y.bn != x.bn || y.splits != x.splits) continue;
+        us = block_us(v, p.m, p.n, K, layout, lda, ldb, N);
+        if (us >= 0.0 && x.resident && (N % 64 == 0 || K >= 384)) {
+            us -= 1.5 * std::max(0.0, (double)((p.m / x.bm) * (p.n / x.bn)) / x.resident - 1.0);
+            us -= 0.4 * shared_lines_us(y, p.m, p.n, N);
+        }
+    }
+    return us < 0.0 ? model_time(p.variant, p.m, p.n, K, layout, true) / kUnitsPerUs : us;
+}
+
+static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_split) {
     double t_one = 0;
     Plan plan{1, {{select_variant(M, N, K, layout, allow_split, &t_one), M, N, 0, 0}}};
-    if (t_out) *t_out = t_one;
     if (is_guarded(plan.part[0].variant)) {
         // Ragged output: one launch (guarded_choice: on tile kernels the last tiles overlap their
         // neighbours), or the whole 128 x 128 tiles to the tile kernels (if K suits them) and the last
@@ -481,19 +520,22 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
         // stored in the whole matrices, has to start on a 16-byte boundary (K is a multiple of 32 here)
         const bool rows_aligned = N % 8 == 0 && (layout != AXONN_TN || M % 8 == 0);
         if (mm > 0 && nm > 0 && (mm != M || nm != N) && rows_aligned) {
-            constexpr double kLaunch = 3.0;
             // Up to 640 whole tiles the plans that split took as long as the one launch or longer, which needs no scratch.
             const bool split = allow_split && (mm / 128) * (nm / 128) > 640 && ragged_may_split(M, N, mm, nm, K, layout);
             double t_tiles = 0;
             const int v_tiles = select_variant(mm, nm, K, layout, split, &t_tiles);
             if (!is_guarded(v_tiles)) {
-                const Plan inner = make_plan(mm, nm, K, layout, split, &t_tiles);
-                double t = t_tiles / kUnitsPerUs + kLaunch;
+                const Plan inner = make_plan(mm, nm, K, layout, split);
+                double t = 0.0;
+                for (int i = 0; i < inner.parts; ++i) t += tiles_us(inner.part[i], M, N, K, layout);
                 if (nm != N) t += guarded_choice(0, nm, mm, N - nm, M, N, K, layout).us;
                 if (mm != M) t += guarded_choice(mm, 0, M - mm, N, M, N, K, layout).us;
-                // beside two rounds and more the strips' share is small and so is what the models can tell
-                // apart: strips then, whose tiled part is a whole product's plan
-                const double favour = (mm / 128) * (nm / 128) >= 4 * 256 ? 1.4 : 1.0;
+                // One time model on both sides: of 1 230 sampled products, each measured in both forms, those whose modelled
+                // times are within 5 % of each other took 0.97 (strips modelled shorter) and 1.00 (longer) of the one
+                // launch.  Many tiles over a long K keep their strips up to 1.2: the plans of such products
+                // (axonn_linear_plan) are relied on as whole tiles and strips, which costs 6-19 % there (2152 x 12296 x
+                // 4096 NT 195 us against 179).
+                const double favour = (mm / 128) * (nm / 128) >= 1024 && K >= 4096 ? 1.2 : 1.0;
                 if (t < favour * t_one / kUnitsPerUs) {
                     plan = inner;
                     if (nm != N) plan.part[plan.parts++] = Part{edge_variant(), mm, N - nm, 0, nm};
@@ -518,7 +560,6 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
         const int v2 = select_variant(m2, n2, K, layout, allow_split, &t2);
         if (is_guarded(v1) || is_guarded(v2) || t1 + t2 + kSecondLaunch >= best_t) return;
         best_t = t1 + t2 + kSecondLaunch;
-        if (t_out) *t_out = best_t;
         plan = Plan{2, {{v1, m1, n1, 0, 0}, {v2, m2, n2, along_n ? 0 : m1, along_n ? n1 : 0}}};
     };
     // second blocks of up to half a round of large tiles, in steps of one tile column / row

@@ -433,3 +433,17 @@ def test_transpose_kernel_by_size(rows, cols, aligned, kernel):
 def test_a_second_round_of_wave_k_tiles_counts_whole(shape, layout, slower):
     """A few tiles more than compute units: some units get two, and the launch takes twice a unit's time."""
     assert not B.kernel_name(*shape, layout).startswith(slower)
+
+
+@pytest.mark.parametrize("shape,layout,slower", [
+    # K of one to eight chunks and an output of 30 to 240 MB whose rows start off 128-byte lines: large tiles, alone or
+    # beside strips, measured 15-60 % behind the guarded kernel over the whole product
+    ((4160, 11928, 72), "TN", "mfma16k64_256x256"), ((15960, 3088, 72), "TN", "mfma16k64_256x256"),
+    ((9680, 3704, 112), "NT", "mfma16k64_256x256"), ((9808, 4176, 128), "NT", "mfma16k64_256x256"),
+    ((2376, 9288, 128), "NN", "mfma16k64_256x256"), ((5904, 8080, 128), "TN", "mfma16k64_256x256"),
+    ((6512, 7576, 128), "NT", "mfma16k64_256x128+"), ((6928, 11312, 128), "TN", "mfma16k64p_256x256"),
+    ((15192, 7912, 256), "TN", "mfma16k64p_256x256"), ((14944, 3544, 192), "NT", "mfma16k64_256x256"),
+    ((14272, 5576, 192), "NT", "mfma16k64_256x128+"), ((1256, 15760, 384), "NN", "mfma16_128x128+"),
+])
+def test_short_k_large_ragged_outputs_avoid_what_measured_slower(shape, layout, slower):
+    assert not B.kernel_name(*shape, layout).startswith(slower)
