@@ -20,8 +20,9 @@ tile_kernel_t ring_kernel_small(int bm, int bn, int wn, bool split, int layout, 
     // two K-contiguous operands (NT): the 64-k kernel has that tile (k64_kernel_half)
     static const tile_kernel_t k128x128[3] = AXONN_RING2(128, 128, 2, false);
     static const tile_kernel_t k128x128_sk[3] = AXONN_RING2(128, 128, 2, true);
-    static const tile_kernel_t k256x128_tail[3] = AXONN_RING3(256, 128, 2, false, true);
-    static const tile_kernel_t k128x256_w8_tail[3] = AXONN_RING3(128, 256, 4, false, true);
+    // ... and is ahead on the half tiles, so no plan of a ragged K leaves NT here
+    static const tile_kernel_t k256x128_tail[3] = AXONN_RING2(256, 128, 2, false, true);
+    static const tile_kernel_t k128x256_w8_tail[3] = AXONN_RING2(128, 256, 4, false, true);
     static const tile_kernel_t k128x128_tail[3] = AXONN_RING2(128, 128, 2, false, true);
     if (layout < 0 || layout > 2) return nullptr;
     if (k_tail) {

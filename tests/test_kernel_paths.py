@@ -1,0 +1,145 @@
+"""Every wave-K tile, every K-tail form and the guarded kernel, each on products that the library itself sends there.
+
+Which sizes run on which kernel is up to the time models and may change with them; so the products are searched for
+here (host logic only) by the names of the kernels that would run, and a kernel that no product reaches fails."""
+import math
+import random
+import re
+import shutil
+import subprocess
+from functools import lru_cache
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_08145_amd import binding as B
+from paper_2502_08145_amd import synth
+from paper_2502_08145_amd.profile_summary import kernel_key, short
+
+LAYOUTS = ["NN", "NT", "TN"]
+
+
+def _log_int(rng, lo, hi, step):
+    return max(step, round(math.exp(rng.uniform(math.log(lo), math.log(hi))) / step) * step)
+
+
+@lru_cache(maxsize=None)
+def reached():
+    """{(kernel name with its wave count, layout): [the two smallest sampled products of one launch on it]}"""
+    rng = random.Random(20250208)
+    found = {}
+    for _ in range(30000):
+        step = rng.choice([1, 8, 8, 8])
+        M, N, K = (_log_int(rng, lo, 4200, step) for lo in (16, 16, 24))
+        if not 2e6 < M * N * K < 6e9:
+            continue
+        for layout in LAYOUTS:
+            names = B.kernels(M, N, K, layout)
+            if len(names) == 1 and (names[0].startswith(("wavek", "edge")) or names[0].endswith("_ktail")):
+                best = found.setdefault((names[0], layout), [])
+                best.append((M, N, K))
+                best.sort(key=lambda s: s[0] * s[1] * s[2])
+                del best[2:]
+    return found
+
+
+def test_every_such_kernel_of_the_library_is_reached():
+    nm = shutil.which("nm")
+    if not nm:
+        pytest.skip("nm is missing")
+    out = subprocess.run([nm, "-C", B.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    built = {short(m.group(1)) for m in re.finditer(r"axonn::__device_stub__(.*)", out)}
+    built = {n for n in built if n.startswith(("wavek", "edge")) or "_ktail" in n}
+    have = {kernel_key(name, layout) for name, layout in reached()}
+    assert built == have, (built - have, have - built)
+
+
+def _bits(bits):
+    return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).cuda().view(torch.bfloat16)
+
+
+def _check(oracle_mod, M, N, K, layout, kernels):
+    """Integers of |value| <= 4 are exact in fp32 in any order (|sum| <= 16 K < 2^24): every element, and nothing
+    behind the output.  The device's fp32 product that they are compared with is checked against the oracle."""
+    a, b = synth.integer_bf16(910 + M, (M, K), -4, 4), synth.integer_bf16(920 + N, (K, N), -4, 4)
+    A = synth.transpose_bits(a) if layout == "TN" else a
+    Bm = synth.transpose_bits(b) if layout == "NT" else b
+    ref = _bits(a).float() @ _bits(b).float()
+    rng = np.random.default_rng(M + N + K)
+    ii, jj = rng.integers(0, M, 64), rng.integers(0, N, 64)
+    ii[:4], jj[:4] = (0, 0, M - 1, M - 1), (0, N - 1, 0, N - 1)
+    at = oracle_mod.gemm_at(M, N, K, layout, A, Bm, ii, jj)
+    assert np.array_equal(ref[torch.from_numpy(ii).cuda(), torch.from_numpy(jj).cuda()].cpu().numpy(), at)
+    assert B.kernels(M, N, K, layout, now=True) == kernels
+    c = torch.empty((M + 2, N), dtype=torch.bfloat16, device="cuda")
+    c.view(torch.int16).fill_(0x7FC0)
+    x, y = _bits(A), _bits(Bm)
+    B.axonn_linear_fwd(M, N, K, layout, x, y, c[:M])
+    torch.cuda.synchronize()
+    got = c[:M].clone()
+    assert torch.equal(got.view(torch.int16), ref.to(torch.bfloat16).view(torch.int16)), (kernels, layout, (M, N, K))
+    assert bool((c[M:].view(torch.int16) == 0x7FC0).all())
+    for _ in range(2):   # the same bits again
+        B.axonn_linear_fwd(M, N, K, layout, x, y, c[:M])
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), c[:M].view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("family", ["wavek_16x16", "wavek_16x32", "wavek_32x32", "wavek_32x64", "wavek_64x64", "ktail", "edge"])
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_kernels_on_products_that_reach_them(oracle_mod, layout, family):
+    B.register_workspace()
+    cases = [(name, s) for (name, lay), shapes in sorted(reached().items()) if lay == layout and family in name for s in shapes]
+    for name, (M, N, K) in cases:
+        print(f"  {name} {layout} {(M, N, K)}", flush=True)
+        _check(oracle_mod, M, N, K, layout, [name])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("shape", [(300, 700, 5), (300, 700, 7), (515, 1031, 3), (2047, 2303, 4093), (3001, 1999, 2049)])
+def test_guarded_kernel_on_misaligned_rows(oracle_mod, layout, shape):
+    """Odd leading dimensions, several tiles, a ragged K: tiles moved back to the edge, whole pieces at any address."""
+    edge = B.num_variants() - 1
+    B.force_variant(edge)
+    try:
+        _check(oracle_mod, *shape, layout, ["edge_128x128"])
+    finally:
+        B.force_variant(-1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout,shape", [("NN", (2048, 2056, 4096)), ("TN", (2048, 2056, 4096)), ("NT", (2048, 2056, 4096)),
+                                          ("TN", (2056, 8192, 2048)), ("NN", (2049, 8192, 2048)), ("TN", (4104, 8200, 2048))])
+def test_strips_narrower_than_sixteen(oracle_mod, layout, shape):
+    """Strips of fewer than 16 rows or columns of an operand contiguous along them take the 16 last ones, some of which
+    the launch over the whole tiles has written before."""
+    B.register_workspace()
+    M, N, K = shape
+    kernels = B.kernels(M, N, K, layout)
+    assert len(kernels) >= 2 and all(k.startswith("wavek") for k in kernels[1:]), kernels
+    _check(oracle_mod, M, N, K, layout, kernels)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout,shape,kernel", [("NN", (1024, 3072, 3072), "mfma16_128x128"), ("NT", (1024, 3072, 3072), "mfma16k64_128x128"),
+                                                 ("NN", (4099, 4099, 4099), "edge"), ("NN", (1000, 520, 1031), "wavek")])
+def test_same_inputs_same_bits_on_the_kernel_named(layout, shape, kernel):
+    B.register_workspace()
+    M, N, K = shape
+    assert B.kernel_name(M, N, K, layout, now=True).startswith(kernel)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    y = torch.randn((N, K) if layout == "NT" else (K, N), generator=gen, device="cuda").to(torch.bfloat16)
+    outs = [torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    for c in outs[:2]:
+        B.axonn_linear_fwd(M, N, K, layout, x, y, c)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        B.axonn_linear_fwd(M, N, K, layout, x, y, outs[2], stream=side)
+    torch.cuda.synchronize()
+    for c in outs[1:]:
+        assert torch.equal(c.view(torch.int16), outs[0].view(torch.int16))
