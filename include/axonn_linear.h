@@ -58,11 +58,12 @@
  *              0 is never less accurate than 1.  Other values: INVALID_ARG.
  *   sizes      M, N, K >= 0, each below 2^31, and each operand below 2^40 elements.
  *              M == 0 or N == 0: nothing to do, AXONN_OK.  K == 0: the output is
- *              set to +0.  Any M, N, K is computed correctly; the fast tiled
- *              kernels need M and N to be multiples of 128 and K of 64 (K >= 128).  Other
- *              shapes take the guarded MFMA kernels: for the whole product if K does
- *              not suit the tiled kernels, else only for the last columns and rows beyond
- *              the whole 128 x 128 tiles.
+ *              set to +0.  Any M, N, K is computed correctly.  The tile kernels, fastest for
+ *              large products, want every row of the three matrices as stored to start on a
+ *              16-byte boundary (N, and K or M as the mode has it, multiples of 8), M and N
+ *              of at least a tile (128) and K > 64; they need no multiples beyond that, but
+ *              multiples of 256 of M and N and of 64 of K waste nothing.  Small products and
+ *              misaligned rows have kernels of their own.
  *   errors     the return value is AXONN_OK (0) or a negative code below; on an
  *              error nothing has been launched.  No exceptions, no aborts.
  *   threads    callable from any thread; the process-wide state is the kernel
@@ -275,11 +276,11 @@ int axonn_linear_set_split_k(int enable);
 int axonn_linear_split_k_timeouts(uint64_t *count);
 
 /* Kernel variants.  Variant 0 is the guarded one-thread-per-element kernel that accepts any
- * shape (the library itself uses it for K == 0 only); the last one ("mfma16_edge_128x128") is the
- * guarded MFMA kernels for any M, N, K >= 1 (one with 128 x 128 tiles, one that splits a smaller
- * tile's K over the waves of a workgroup, the tile kernels with their last tiles moved back to the output's
- * edge: the sizes decide); the others are MFMA tile kernels ("_w8": 8 waves,
- * "_sk2" ... "_sk8": split-K over that many workgroups).  Host-only queries: no GPU is touched. */
+ * shape (the library itself uses it for K == 0 only); the last one ("mfma16_edge_128x128") takes
+ * any M, N, K >= 1: forced, it is the guarded MFMA kernel with 128 x 128 tiles; in a plan it stands for that one, the
+ * kernel that splits a smaller tile's K over the waves of a workgroup, or a tile kernel with its last tiles moved back
+ * to the output's edge, as the sizes decide (axonn_linear_part_kernel).  The others are MFMA tile kernels ("_w8":
+ * 8 waves, "_sk2" ... "_sk8": split-K over that many workgroups).  Host-only queries: no GPU is touched. */
 int axonn_linear_num_variants(void);
 /* Name such as "mfma16k64_256x256_w8_sk2"; NULL if `variant` is out of range. */
 const char *axonn_linear_variant_name(int variant);
@@ -293,10 +294,9 @@ int axonn_linear_select_variant(int64_t M, int64_t N, int64_t K, int layout);
  * into two blocks (the second holds the last rows or the last columns), each with the variant
  * that suits it, e.g. the large tile for the first and split-K for the second.  Block i covers
  * rows row0 .. row0+m-1 and columns col0 .. col0+n-1 of the M x N output; the blocks are
- * disjoint and cover it.  A ragged output (M or N not a multiple of 128) whose K suits the tile
- * kernels, and whose rows start on 16-byte boundaries in all three matrices (N, and for TN also M,
- * a multiple of 8), is planned over its whole tiles as above where that pays, and the last columns
- * and the last rows follow as up to two blocks of the guarded MFMA kernel.  Writes parts[0 .. return value - 1] (HOST
+ * disjoint and cover it.  A ragged output (M or N not a multiple of 128) is one launch, or, where that pays, K is a
+ * multiple of 64 and the rows of all three matrices start on 16-byte boundaries, its whole tiles are planned as above
+ * and the last columns and the last rows follow as up to two blocks of the last variant.  Writes parts[0 .. return value - 1] (HOST
  * memory, caller-owned, room for AXONN_MAX_PLAN_PARTS) and returns the number of launches, 1 to
  * AXONN_MAX_PLAN_PARTS; negative error code on bad arguments.  Pure host logic. */
 #define AXONN_MAX_PLAN_PARTS 4

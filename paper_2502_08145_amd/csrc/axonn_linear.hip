@@ -110,6 +110,8 @@ static std::vector<Variant> make_variants() {
     ring("mfma16_128x256", 128, 256, 2, 1, TileCfg16<128, 256, 2, 2>::LDS_BYTES, TileCfg16<128, 256, 2, 2>::MIN_K, 0.95, 0.74, 0.92);
     ring("mfma16_128x256_w8", 128, 256, 4, 1, TileCfg16<128, 256, 2, 4>::LDS_BYTES, TileCfg16<128, 256, 2, 4>::MIN_K, 0.93, 0.72, 0.97);
     using S = TileCfg16<128, 128, 2, 2>;
+    // NT runs the 64-k kernel with three buffers on this tile, under the same variants
+    static_assert(S::LDS_BYTES >= k64_lds_bytes(128, 128, 3) && S::MIN_K >= TileCfgK64::MIN_K, "one LDS size and shortest K for both kernels");
     ring("mfma16_128x128", 128, 128, 2, 1, S::LDS_BYTES, S::MIN_K, 0.85, 0.72, 0.90);
     ring("mfma16_128x128_sk2", 128, 128, 2, 2, S::LDS_BYTES, S::MIN_K, 0.85, 0.72, 0.90);
     ring("mfma16_128x128_sk4", 128, 128, 2, 4, S::LDS_BYTES, S::MIN_K, 0.85, 0.72, 0.90);
@@ -147,8 +149,7 @@ static std::vector<Variant> make_variants() {
     static const char* const k64_sk[] = {"mfma16k64_256x256_w8_sk2", "mfma16k64_256x256_w8_sk3", "mfma16k64_256x256_w8_sk4", "mfma16k64_256x256_w8_sk5",
                                          "mfma16k64_256x256_w8_sk6", "mfma16k64_256x256_w8_sk7", "mfma16k64_256x256_w8_sk8"};
     for (int sp = 2; sp <= 8; ++sp) k64(k64_sk[sp - 2], sp);
-    // guarded MFMA kernel: ragged shapes and the edge strips of ragged outputs
-    // fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %)
+    // us64: fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %)
     static const struct { const char* name; double us64[3]; } measured[] = {
         {"mfma16_128x128", {0.530, 0.525, 0.557}},       {"mfma16_128x256", {0.927, 0.887, 0.950}},
         {"mfma16_128x256_w8", {0.773, 0.818, 0.852}},    {"mfma16_256x128", {0.885, 0.888, 0.951}},
@@ -166,6 +167,7 @@ static std::vector<Variant> make_variants() {
                                    : x.k64 || (x.bm * x.bn == 128 * 128 && l == AXONN_NT) ? k64_kernel_half(x.bm, x.bn, false, l, true)
                                                                                     : ring_kernel_small(x.bm, x.bn, x.threads / 128, false, l, true);
             }
+    // guarded MFMA kernel: any shape; a plan's blocks under this name run on what guarded_choice takes for them
     Variant e{"mfma16_edge_128x128", EdgeCfg::BM, EdgeCfg::BN, EdgeCfg::NT, EdgeCfg::LDS_BYTES, 1, 1, 1, false, {0, 0, 0}, {nullptr, nullptr, nullptr}};
     e.edge = true;
     v.push_back(e);

@@ -3,8 +3,9 @@
 //   C[M,N] = sum_k a(i,k) b(k,j)      (the local matrix multiply of Algorithm 1 lines 3, 11, 13)
 //
 // for ANY M, N, K >= 1 and any leading dimensions: ragged edges in all three directions, operand
-// rows that are not 16-byte aligned.  It serves the shapes the tile kernels do not take (they want
-// whole tiles and K in whole K-steps) and the edge strips that a plan cuts off a ragged output.
+// rows that are not 16-byte aligned.  Ragged products mostly run on the tile kernels (rows on 16-byte boundaries) or
+// the wave-K kernel (few tiles); what is left here is large products of misaligned rows, large outputs over one or
+// two K-steps, K below 8 with a K-contiguous operand, and matrices narrower than the wave-K tiles.
 //
 // Built for being right at every shape rather than for the last per cent:
 //  * 128 x 128 output tile per workgroup of 4 waves (2 x 2, 64 x 64 per wave), K 128 at a time,
@@ -25,8 +26,8 @@
 //    ds_read_b128 fragments) and an MN-contiguous operand as it is in memory, one row per k (256
 //    bytes, padded to 288), read with the transposing ds_read_b64_tr_b16.  No inline asm: the
 //    compiler places the waits.
-//  * Stores are guarded per element; four consecutive n of a row go out as one 8-byte store where
-//    the address allows.
+//  * Four consecutive n of a row go out as one 8-byte store at any address; only those across the block's last
+//    column are guarded per element.
 #pragma once
 #include "gemm_mfma.hpp"
 #include "gemm_mfma16.hpp"

@@ -377,17 +377,6 @@ struct SplitK {
 constexpr uint32_t kSplitSpinLimit = 1u << 19;   // x ~1 us per probe
 constexpr int kSplitRangePerXcdK = 32768;        // four K ranges: from this K on, one range per pair of XCDs
 
-// Workgroup -> output tile and K range.  The hardware hands workgroup b to XCD b % 8, in order of b
-// on each XCD, and every XCD has a private L2: ids are remapped so that an XCD works on a contiguous
-// chunk of the tile sequence, and tiles are then grouped `group_m` along m, which makes the tiles
-// running side by side behind one L2 a compact patch of the output (they share operand panels).
-// Split-K: the workgroups of a tile sit on the same XCD, last K range first (writers get the lower
-// ids) -- except with four ranges of a large tile at long K, where XCDs 0-1 take the last K range,
-// ..., XCDs 6-7 range 0, each a contiguous chunk of the tiles, so the 32 workgroups that share an L2
-// read the same K slices (with all four ranges of a tile on one XCD they would share a quarter as
-// much; measured 17-20 % faster at K = 65536 for NN and NT).  The readers then sit on two XCDs only,
-// which makes the exchange slower by some 10 us: not for short K.  Writers keep the lower ids there
-// too (same pid >> 3, lower XCD).
 // The tiles of an output block.  An extent that is no whole number of tiles is covered all the same: the last
 // tile of a row or column of tiles is moved back to end at the block's edge (first row m_last, first column
 // n_last).  It computes some outputs of its neighbour a second time, from the same operands in the same
@@ -400,6 +389,18 @@ struct TileGrid {
     int m_last, n_last;
     int k_tail;
 };
+
+// Workgroup -> output tile and K range.  The hardware hands workgroup b to XCD b % 8, in order of b
+// on each XCD, and every XCD has a private L2: ids are remapped so that an XCD works on a contiguous
+// chunk of the tile sequence, and tiles are then grouped `group_m` along m, which makes the tiles
+// running side by side behind one L2 a compact patch of the output (they share operand panels).
+// Split-K: the workgroups of a tile sit on the same XCD, last K range first (writers get the lower
+// ids) -- except with four ranges of a large tile at long K, where XCDs 0-1 take the last K range,
+// ..., XCDs 6-7 range 0, each a contiguous chunk of the tiles, so the 32 workgroups that share an L2
+// read the same K slices (with all four ranges of a tile on one XCD they would share a quarter as
+// much; measured 17-20 % faster at K = 65536 for NN and NT).  The readers then sit on two XCDs only,
+// which makes the exchange slower by some 10 us: not for short K.  Writers keep the lower ids there
+// too (same pid >> 3, lower XCD).
 struct TileWork {
     int tile_id;          // index into the tile sequence (= split-K slot index within a range)
     int tile_m, tile_n;

@@ -12,11 +12,13 @@
 // time.  At the end the partial accumulators go through LDS once and are added in the order of
 // the waves (the result does not depend on timing).  No scratch memory is needed.
 //
-//  * A K-contiguous operand (A of NN/NT, B of NT) goes from global memory straight into the registers of
-//    the MFMA operand: lane l loads row l%16, k = 8 (l/16) .. +7 of a block (and the same 32 k on).  No LDS.
-//  * An MN-contiguous operand (A of TN, B of NN/TN) goes through a region of LDS that belongs to the wave
-//    alone, [64 k][16 NI], padded by 16 bytes a row, and is read with the transposing ds_read_b64_tr_b16.
-//    A wave's LDS operations execute in order, so its region needs no barrier either.
+//  * Either kind of operand goes through a region of LDS that belongs to the wave alone.  A wave's LDS operations
+//    execute in order, so its region needs no barrier.
+//  * A K-contiguous operand (A of NN/NT, B of NT) is loaded 8 rows x 128 bytes, whole lines, at a time, kept as
+//    [16 MI][64 k], padded by 16 bytes a row, and read with ds_read_b128.  (Loaded straight into the registers of the
+//    MFMA operand, sixteen half lines at a time, 24 x 2048 x 8192 NT took 18 us where this takes 11.)
+//  * An MN-contiguous operand (A of TN, B of NN/TN) is kept as in memory, [64 k][16 NI], padded likewise, and read
+//    with the transposing ds_read_b64_tr_b16.
 //  * Loads are 16 bytes at 2-byte alignment: the hardware takes them at any address, a little slower where
 //    a line is crossed (fetched element by element, as a guarded kernel would, the same product is ten times
 //    slower).  Nothing outside the operands is read: the last tile of a row or column of tiles is moved
