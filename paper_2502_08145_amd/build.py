@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 # one translation unit per kernel family (the compile time is the kernels'), compiled side by side
-UNITS = ["axonn_linear.hip", "kernels_k64.hip", "kernels_ring_large.hip", "kernels_ring_small.hip", "kernels_edge.hip", "kernels_wavek.hip"]
+UNITS = ["axonn_linear.hip", "kernels_k64.hip", "kernels_k64g.hip", "kernels_ring_large.hip", "kernels_ring_small.hip", "kernels_edge.hip", "kernels_wavek.hip"]
 LIB_DIR = os.path.join(HERE, "lib")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(LIB_DIR, "libaxonn_linear.so")

@@ -77,13 +77,14 @@ struct Variant {
     tile_kernel_t fn_tail[3] = {nullptr, nullptr, nullptr};   // for a K that is no multiple of 64
     bool edge = false;               // the guarded MFMA kernel: any shape, launched through edge_kernel_launch
     int resident = 0;                // > 0: a grid of at most this many workgroups walks the tiles (one per compute unit)
+    bool group = false;              // the eight-wave kernel (gemm_tile_kernel_k64g), which has a time model of its own
 };
 
 // Kernel families: the 64-k-stage kernel (256 x 256, eight waves: the default wherever the output has
 // whole large tiles), the 32-k ring (the same tile for NT at very long K and TN with four and more K
-// ranges; the smaller tiles for outputs of few tiles), the guarded kernel.  Split-K variants of one
-// tile share one kernel (the number of K ranges is a run-time argument).  128 x 128 tiles are the ring's for NN and TN and
-// the 64-k kernel's for NT, under one name.
+// ranges; the smaller tiles with split-K), the eight-wave kernel (128 x 128 and half tiles without split-K), the guarded kernel.
+// Split-K variants of one tile share one kernel (the number of K ranges is a run-time argument).  128 x 128 tiles with split-K
+// are the ring's for NN and TN and the four-wave 64-k kernel's for NT, under one name.
 static std::vector<Variant> make_variants() {
     std::vector<Variant> v;
     v.push_back({"naive", 0, 0, 256, 0, 0, 1, 1, false, {0, 0, 0}, {nullptr, nullptr, nullptr}});
@@ -91,8 +92,18 @@ static std::vector<Variant> make_variants() {
         Variant x{name, bm, bn, 128 * wn, lds, min_k, 2 * KB, splits, false, {nn, nt, tn}, {nullptr, nullptr, nullptr}};
         for (int l = 0; l < 3; ++l)
             x.fn[l] = (bm == 256 && bn == 256)              ? ring_kernel_large(splits > 1, l)
-                      : (bm == 128 && bn == 128 && l == AXONN_NT) ? k64_kernel_half(bm, bn, splits > 1, l)
-                                                              : ring_kernel_small(bm, bn, wn, splits > 1, l);
+                      : (bm == 128 && bn == 128 && l == AXONN_NT) ? k64_kernel_half(bm, bn, l)
+                                                              : ring_kernel_small(bm, bn, splits > 1, l);
+        v.push_back(x);
+    };
+    auto group = [&](const char* name, int bm, int bn, int min_k, bool k64, double nn, double nt, double tn) {
+        Variant x{name, bm, bn, 512, group_lds_bytes(bm, bn, 1), min_k, TileCfgK64::KS, 1, k64, {nn, nt, tn}, {nullptr, nullptr, nullptr}};
+        x.group = true;
+        for (int l = 0; l < 3; ++l)
+            if (!k64 || l == AXONN_NT) {
+                x.fn[l] = group_kernel(bm, bn, 1, l, false);
+                x.fn_tail[l] = group_kernel(bm, bn, 1, l, true);
+            }
         v.push_back(x);
     };
     auto k64 = [&](const char* name, int splits) {
@@ -106,13 +117,13 @@ static std::vector<Variant> make_variants() {
     static const char* const ring_sk[] = {"mfma16_256x256_w8_sk2", "mfma16_256x256_w8_sk3", "mfma16_256x256_w8_sk4", "mfma16_256x256_w8_sk5",
                                           "mfma16_256x256_w8_sk6", "mfma16_256x256_w8_sk7", "mfma16_256x256_w8_sk8"};
     for (int sp = 2; sp <= 8; ++sp) ring(ring_sk[sp - 2], 256, 256, 4, sp, L::LDS_BYTES, L::MIN_K, 1.13, 1.06, 1.12);
-    ring("mfma16_256x128", 256, 128, 2, 1, TileCfg16<256, 128, 2, 2>::LDS_BYTES, TileCfg16<256, 128, 2, 2>::MIN_K, 0.86, 0.78, 0.91);
+    group("mfma16_256x128", 256, 128, TileCfg16<256, 128, 2, 2>::MIN_K, false, 0.86, 0.78, 0.91);
     ring("mfma16_128x256", 128, 256, 2, 1, TileCfg16<128, 256, 2, 2>::LDS_BYTES, TileCfg16<128, 256, 2, 2>::MIN_K, 0.95, 0.74, 0.92);
-    ring("mfma16_128x256_w8", 128, 256, 4, 1, TileCfg16<128, 256, 2, 4>::LDS_BYTES, TileCfg16<128, 256, 2, 4>::MIN_K, 0.93, 0.72, 0.97);
+    group("mfma16_128x256_w8", 128, 256, TileCfg16<128, 256, 2, 4>::MIN_K, false, 0.93, 0.72, 0.97);
     using S = TileCfg16<128, 128, 2, 2>;
-    // NT runs the 64-k kernel with three buffers on this tile, under the same variants
+    group("mfma16_128x128", 128, 128, S::MIN_K, false, 0.85, 0.72, 0.90);
+    // with split-K NT runs the 64-k kernel with three buffers on this tile, under the same variants
     static_assert(S::LDS_BYTES >= k64_lds_bytes(128, 128, 3) && S::MIN_K >= TileCfgK64::MIN_K, "one LDS size and shortest K for both kernels");
-    ring("mfma16_128x128", 128, 128, 2, 1, S::LDS_BYTES, S::MIN_K, 0.85, 0.72, 0.90);
     ring("mfma16_128x128_sk2", 128, 128, 2, 2, S::LDS_BYTES, S::MIN_K, 0.85, 0.72, 0.90);
     ring("mfma16_128x128_sk4", 128, 128, 2, 4, S::LDS_BYTES, S::MIN_K, 0.85, 0.72, 0.90);
     k64("mfma16k64_256x256_w8", 1);
@@ -123,15 +134,15 @@ static std::vector<Variant> make_variants() {
         x.resident = TileCfgK64P::MAX_WORKGROUPS;
         v.push_back(x);
     }
-    // half tiles with 64-k stages: NT only (eff from 2048 x 4096 x 4096 and 4096^3 against the ring's half tiles)
+    // half tiles of two K-contiguous operands (eff from 2048 x 4096 x 4096 and 4096^3 against the ring's half tiles)
     auto k64h = [&](const char* name, int bm, int bn, int splits, double nt) {
         Variant x{name, bm, bn, 256, k64_lds_bytes(bm, bn, 3), TileCfgK64::MIN_K, TileCfgK64::KS, splits, true,
                   {0.0, nt, 0.0}, {nullptr, nullptr, nullptr}};
-        for (int l = 0; l < 3; ++l) x.fn[l] = k64_kernel_half(bm, bn, splits > 1, l);
+        for (int l = 0; l < 3; ++l) x.fn[l] = k64_kernel_half(bm, bn, l);
         v.push_back(x);
     };
-    k64h("mfma16k64_256x128", 256, 128, 1, 0.95);
-    k64h("mfma16k64_128x256", 128, 256, 1, 0.94);
+    group("mfma16k64_256x128", 256, 128, TileCfgK64::MIN_K, true, 0.0, 0.95, 0.0);
+    group("mfma16k64_128x256", 128, 256, TileCfgK64::MIN_K, true, 0.0, 0.94, 0.0);
     // split-K on the half tiles, for outputs that are narrow in one direction (2048 x 1152, 640 x 15360 ...) over a
     // long K: the 64-k kernel for NT, the 32-k ring for NN and TN
     // (two and three ranges only: with four and more the reader's turn at the slots costs more than the large
@@ -152,20 +163,16 @@ static std::vector<Variant> make_variants() {
     // us64: fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %)
     static const struct { const char* name; double us64[3]; } measured[] = {
         {"mfma16_128x128", {0.530, 0.525, 0.557}},       {"mfma16_128x256", {0.927, 0.887, 0.950}},
-        {"mfma16_128x256_w8", {0.773, 0.818, 0.852}},    {"mfma16_256x128", {0.885, 0.888, 0.951}},
-        {"mfma16k64_128x256", {0.0, 0.817, 0.0}},        {"mfma16k64_256x128", {0.0, 0.819, 0.0}},
+        {"mfma16_256x128", {0.885, 0.888, 0.951}},       {"mfma16k64_128x256", {0.0, 0.817, 0.0}},        {"mfma16k64_256x128", {0.0, 0.819, 0.0}},
         {"mfma16k64_256x256_w8", {1.284, 1.219, 1.263}},
     };
     for (Variant& x : v)
         for (const auto& q : measured)
             // a split-K variant's name is the plain one's and "_sk<ranges>"
-            if (std::strncmp(x.name, q.name, std::strlen(q.name)) == 0 && (x.splits > 1) == (std::strstr(x.name, "_sk") == x.name + std::strlen(q.name)) &&
+            if (!x.group && std::strncmp(x.name, q.name, std::strlen(q.name)) == 0 && (x.splits > 1) == (std::strstr(x.name, "_sk") == x.name + std::strlen(q.name)) &&
                 (x.splits > 1 || std::strlen(x.name) == std::strlen(q.name))) {
                 std::copy(q.us64, q.us64 + 3, x.us64);
-                for (int l = 0; l < 3 && x.splits == 1; ++l)
-                    x.fn_tail[l] = x.bm * x.bn == 256 * 256                                   ? k64_kernel(false, l, true)
-                                   : x.k64 || (x.bm * x.bn == 128 * 128 && l == AXONN_NT) ? k64_kernel_half(x.bm, x.bn, false, l, true)
-                                                                                    : ring_kernel_small(x.bm, x.bn, x.threads / 128, false, l, true);
+                for (int l = 0; l < 3 && x.splits == 1 && x.bm * x.bn == 256 * 256; ++l) x.fn_tail[l] = k64_kernel(false, l, true);
             }
     // guarded MFMA kernel: any shape; a plan's blocks under this name run on what guarded_choice takes for them
     Variant e{"mfma16_edge_128x128", EdgeCfg::BM, EdgeCfg::BN, EdgeCfg::NT, EdgeCfg::LDS_BYTES, 1, 1, 1, false, {0, 0, 0}, {nullptr, nullptr, nullptr}};
@@ -334,8 +341,8 @@ static double model_time(int v, int64_t M, int64_t N, int64_t K, int layout, boo
 constexpr double kUnitsPerUs = 2.6e6;
 
 // The guarded MFMA kernel (gemm_edge_kernel) alone, in microseconds: steps of 128 k, dearer nearly in proportion as
-// workgroups come to share the compute units (least squares over 15 000 sampled products each of aligned and
-// of misaligned rows, residual 6 % and 23 %; aligned rows also over 900 outputs of up to 500 MB, 10 %, where
+// workgroups come to share the compute units (least squares over 15 000 sampled products each of aligned and of
+// misaligned rows, residual 6 % and 23 %; aligned rows also over 900 outputs of up to 500 MB, 10 %, where
 // proportion was 12-15 % too much).
 static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
     const double wgs = (double)(((m + EdgeCfg::BM - 1) / EdgeCfg::BM) * ((n + EdgeCfg::BN - 1) / EdgeCfg::BN));
@@ -347,7 +354,8 @@ static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
 // How a block of the output is computed where it is not simply the tile variant of its part.
 struct BlockChoice {
     int tile = -1;           // >= 0: this tile variant, its last tiles moved back to the block's edge (TileGrid)
-    WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel; else the guarded MFMA kernel
+    GroupChoice group{};     // else, .tile >= 0: one of the eight-wave kernel's small tiles
+    WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel; else what the part's variant says
     int lead_m = 0, lead_n = 0;   // rows and columns before the block that the launch covers as well
     double us = 0.0;         // modelled time, operands in cache
 };
@@ -366,18 +374,26 @@ static double shared_lines_us(const Variant& x, int64_t m, int64_t n, int64_t ld
 }
 
 // A tile variant over an m x n block, in microseconds; < 0: it cannot run there, or there is no model of it.
-// Full rounds of 256 workgroups and 0.76 + 0.24 f of one for a last round that fills a fraction f of the compute
+// The eight-wave kernel has a model of its own.  Full rounds of 256 workgroups and 0.76 + 0.24 f of one for a last round that fills a fraction f of the compute
 // units; split-K variants also exchange partial tiles, which costs a trip to memory and back per range and
 // some of its bandwidth per tile.  Fitted over 36 000 sampled products, residual 3-8 %.
 static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
     const Variant& x = variants()[v];
     const int64_t k_padded = (K + 63) / 64 * 64;   // every tile kernel takes K 64 at a time
-    if (x.us64[layout] <= 0.0 || m < x.bm || n < x.bn || k_padded / x.splits < x.min_k || K <= 64) return -1.0;
+    if ((x.us64[layout] <= 0.0 && !x.group) || !x.fn[layout] || m < x.bm || n < x.bn || K <= 64) return -1.0;
+    if (k_padded / x.splits < x.min_k && !x.group) return -1.0;   // the eight-wave kernel takes any K
     if (K != k_padded && !x.fn_tail[layout]) return -1.0;
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0) return -1.0;   // 16-byte direct loads and stores
     if (std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return -1.0;
+    if (x.group) return group_us(x.bm, x.bn, 1, layout, m, n, K, lda, ldb, ldc);
     const int64_t tiles = ((m + x.bm - 1) / x.bm) * ((n + x.bn - 1) / x.bn), wgs = tiles * x.splits, rest = wgs % 256;
     const double rounds = (double)(wgs / 256) + (rest ? 0.76 + 0.24 * (double)rest / 256.0 : 0.0);
+    if (x.splits == 1 && x.bm * x.bn == 256 * 256) {
+        // fitted by itself over 1 500 products of 4 to 600 GFLOP, the mean of operands in cache and from memory (residual 4 %; 8 %
+        // with the split forms' figures, which were up to 25 % too much for K of one to four steps)
+        static const double step[3] = {1.444, 1.333, 1.411};
+        return rounds * ((double)(k_padded / 64) * step[layout] + 6.4) + shared_lines_us(x, m, n, ldc);
+    }
     const int area = x.bm * x.bn, more = x.splits - 2;
     const double fixed = area <= 128 * 128 ? 1.9 : area < 256 * 256 ? 3.6 : 5.6;   // per round
     double exchange = 0.0;
@@ -386,6 +402,35 @@ static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64
                    : area < 256 * 256 ? 5.4 + 2.3 * more + (0.044 + 0.030 * more) * (double)tiles
                                       : 6.8 + 2.7 * more + (0.060 + 0.040 * more) * (double)tiles;
     return 3.0 + rounds * ((double)(k_padded / 64 / x.splits) * x.us64[layout] + fixed) + shared_lines_us(x, m, n, ldc) + exchange;
+}
+
+// The tile kernel without split-K (overlapping tiles and strips never touch the scratch area) of the smallest modelled time, if
+// that is below best.us.
+static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, BlockChoice& best) {
+    bool found = false;
+    for (int v = 1; v < edge_variant(); ++v) {
+        if (variants()[v].splits > 1) continue;
+        const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
+        if (us >= 0.0 && us < best.us) {
+            best = BlockChoice{};
+            best.tile = v;
+            best.us = us;
+            found = true;
+        }
+    }
+    if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
+    // Near a tie the wave-K kernel stays: either model is good to 6 %, and where operands come from memory (12 MB and more) its
+    // waves, eight chunks of a row in flight between them, suffer less (698 x 968 x 7144 NT: 35 us in cache, 40 from memory; 64 x 64
+    // tiles 34 and 51).
+    const GroupChoice g = group_choose(layout, m, n, K, lda, ldb, ldc);
+    const double near = best.wavek.tile < 0 ? 1.0 : m * K + K * n > (int64_t)6000000 ? 0.88 : 0.96;
+    if (g.tile >= 0 && g.us < near * best.us) {
+        best = BlockChoice{};
+        best.group = g;
+        best.us = g.us;
+        found = true;
+    }
+    return found;
 }
 
 // The kernel with the smallest modelled time.  The tile kernels win as soon as their tiles fill a good part of the
@@ -406,16 +451,8 @@ static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, i
         best.wavek = wk;
         best.us = wk.us;
     }
-    for (int v = 1; v < edge_variant(); ++v) {
-        if (variants()[v].splits > 1) continue;   // overlapping tiles and strips never touch the scratch area
-        const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
-        if (us >= 0.0 && us < best.us) {
-            best = BlockChoice{};
-            best.tile = v;
-            best.us = us;
-        }
-    }
-    return best.tile < 0 && best.wavek.tile < 0 ? guarded : best;
+    if (tiles_choice(m, n, K, layout, lda, ldb, ldc, best)) return best;
+    return best.wavek.tile < 0 ? guarded : best;
 }
 // The same for the block at (row0, col0) of the M x N product.  An edge strip of fewer than 16 rows or columns of
 // an MN-contiguous operand is too narrow for the wave-K kernel and would take the guarded one, element by element
@@ -425,7 +462,7 @@ static BlockChoice guarded_choice(int64_t row0, int64_t col0, int64_t m, int64_t
     const int lead_m = (layout == AXONN_TN && m < 16 && row0 >= 16) ? (int)(16 - m) : 0;
     const int lead_n = (layout != AXONN_NT && n < 16 && col0 >= 16) ? (int)(16 - n) : 0;
     BlockChoice g = guarded_choice(m + lead_m, n + lead_n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N, N);
-    if (g.tile < 0 && g.wavek.tile >= 0) {
+    if (g.tile < 0 && g.group.tile < 0 && g.wavek.tile >= 0) {
         g.lead_m = lead_m;
         g.lead_n = lead_n;
     }
@@ -537,7 +574,9 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
                 // launch.  Many tiles over a long K keep their strips up to 1.2: the plans of such products
                 // (axonn_linear_plan) are relied on as whole tiles and strips, which costs 6-19 % there (2152 x 12296 x
                 // 4096 NT 195 us against 179).
-                const double favour = (mm / 128) * (nm / 128) >= 1024 && K >= 4096 ? 1.2 : 1.0;
+                // Below K = 512 the strips have to be clearly shorter: what shared lines cost the whole tiles is the larger
+                // part of the time there.
+                const double favour = (mm / 128) * (nm / 128) >= 1024 && K >= 4096 ? 1.2 : K < 512 ? 0.9 : 1.0;
                 if (t < favour * t_one / kUnitsPerUs) {
                     plan = inner;
                     if (nm != N) plan.part[plan.parts++] = Part{edge_variant(), mm, N - nm, 0, nm};
@@ -575,6 +614,9 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
 // the wave-K kernel: outputs of a few dozen 128 x 128 tiles (512 x 1024 x 2048 NT: 32 tiles, 15.6 us against 9.6; 640 x 640 x
 // 2048 TN 17 -> 10).  1 500 sampled products of 0.1 to 40 GFLOP that the rule gives it run 1.89 times as fast as the tile variant
 // of their plan (geometric mean, operands in cache), the slowest 0.98 times.
+// A block planned without split-K also goes to whatever other tile kernel without it is modelled faster: the plans are made
+// with efficiencies from before the eight-wave kernel, which do not know its smaller tiles.  One planned with split-K
+// leaves it for the wave-K kernel only, and only where that is far ahead: callers bring a scratch area for it.
 static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
     const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
     for (int i = 0; i < plan.parts; ++i) {
@@ -582,9 +624,19 @@ static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout
         if (variants()[p.variant].edge) {
             p.how = guarded_choice(p.row0, p.col0, p.m, p.n, M, N, K, layout);
         } else if (p.variant > 0) {
-            const double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);
+            const bool split = variants()[p.variant].splits > 1;
+            const double margin = split ? 0.815 : 0.98;
+            const double us = split ? block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N) : tiles_us(p, M, N, K, layout);
+            if (us <= 0.0) continue;
+            BlockChoice best;
+            best.us = margin * us;
             const WaveKChoice wk = wavek_choose(layout, p.m, p.n, K, lda, ldb);
-            if (us > 0.0 && wk.tile >= 0 && wk.us < 0.97 * us) p.how.wavek = wk;
+            if (wk.tile >= 0 && wk.us < best.us) {
+                best.wavek = wk;
+                best.us = wk.us;
+            }
+            if (!split) tiles_choice(p.m, p.n, K, layout, lda, ldb, N, best);
+            if (best.tile != p.variant) p.how = best;
         }
     }
 }
@@ -632,6 +684,7 @@ static void raise_lds_limits() {
                 if (fn) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, var.lds_bytes);
     edge_kernel_raise_lds_limit();
     wavek_raise_lds_limit();
+    group_raise_lds_limit();
     (void)hipGetLastError();
 }
 
@@ -657,11 +710,11 @@ static size_t split_bytes(const Plan& plan) {
     return bytes;   // the launches of a plan run one after the other and share the area
 }
 
-// What the launches touch of it: nothing for a block planned with split-K that runs on the wave-K kernel.
+// What the launches touch of it: nothing for a block planned with split-K that runs on a kernel without it.
 static size_t split_bytes_run(const Plan& plan) {
     size_t bytes = 0;
     for (int i = 0; i < plan.parts; ++i)
-        if (plan.part[i].how.wavek.tile < 0) bytes = std::max(bytes, split_bytes(plan.part[i]));
+        if (plan.part[i].how.wavek.tile < 0 && plan.part[i].how.group.tile < 0 && plan.part[i].how.tile < 0) bytes = std::max(bytes, split_bytes(plan.part[i]));
     return bytes;
 }
 
@@ -707,12 +760,16 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
                      C - dm * N - dn, p.m + dm, p.n + dn, K, lda, ldb, ldc);
         return;
     }
+    if (p.how.group.tile >= 0) {
+        group_launch(p.how.group, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc);
+        return;
+    }
     if (var.edge && p.how.tile < 0) {
         const int tiles_n = (int)((p.n + var.bn - 1) / var.bn);
         edge_kernel_launch(layout, (unsigned)part_workgroups(p), s, A, B, C, p.m, p.n, K, lda, ldb, ldc, tiles_n);
         return;
     }
-    launch_tiles(var.edge ? variants()[p.how.tile] : var, p.m, p.n, K, layout, A, B, C, lda, ldb, ldc, scratch, s);
+    launch_tiles(p.how.tile >= 0 ? variants()[p.how.tile] : var, p.m, p.n, K, layout, A, B, C, lda, ldb, ldc, scratch, s);
 }
 
 // Where a call's split-K kernels find their scratch area.
@@ -748,12 +805,20 @@ static int part_kernel_name(const Part& p, int64_t K, int layout, char* name, si
         wavek_tile(p.how.wavek, &rows, &cols);
         return std::snprintf(name, bytes, "wavek_%dx%d_w%d", rows, cols, p.how.wavek.waves);
     }
+    const char* const tail = planned.bm && K % 64 ? "_ktail" : "";
+    if (p.how.group.tile >= 0) {
+        // two groups of waves on a 64 x 64 tile are K split over waves, like the wave-K kernel's tiles
+        int rows = 0, cols = 0, groups = 0;
+        group_tile(p.how.group, &rows, &cols, &groups);
+        return std::snprintf(name, bytes, "%s_%dx%d%s%s", rows * cols == 64 * 64 ? "wavek" : "mfma16", rows, cols, groups == 2 ? "_g2" : "", tail);
+    }
     if (planned.edge && p.how.tile < 0) return std::snprintf(name, bytes, "edge_%dx%d", planned.bm, planned.bn);
-    const Variant& var = planned.edge ? variants()[p.how.tile] : planned;
-    // two K-contiguous operands (NT) on 128 x 128 tiles: the 64-k kernel under the ring variant's name
+    const Variant& var = p.how.tile >= 0 ? variants()[p.how.tile] : planned;
+    // two K-contiguous operands (NT): one kernel behind the variants of a tile, under the 64-k one's name
+    if (layout == AXONN_NT && var.group) return std::snprintf(name, bytes, "mfma16k64_%dx%d%s", var.bm, var.bn, tail);
     const bool k64_under_ring_name = layout == AXONN_NT && !var.k64 && var.bm == 128 && var.bn == 128;
     return std::snprintf(name, bytes, "%s%s%s", k64_under_ring_name ? "mfma16k64_" : "",
-                         var.name + (k64_under_ring_name ? std::strlen("mfma16_") : 0), var.bm && K % 64 ? "_ktail" : "");
+                         var.name + (k64_under_ring_name ? std::strlen("mfma16_") : 0), tail);
 }
 
 static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, const void* b, void* c,

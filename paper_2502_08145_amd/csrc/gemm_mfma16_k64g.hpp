@@ -1,0 +1,393 @@
+// The tile kernel for outputs of up to a few hundred tiles: eight waves on one output tile from 64 x 64 to 256 x 128, a ring
+// of 64-k stages, one barrier per 64 k.
+//
+// What bounds such products is the way from the L2 into LDS.  A compute unit receives 150 bytes/ns while every line hits
+// in the L2 and 95-125 where a good part of them comes from the memory side (loads alone, 32 KB and more in flight, one
+// workgroup on the chip or 256; to LDS or to registers alike); 64 k of a 128 x 128 tile are 32 KB: 0.3 us, where its MFMAs
+// take 0.21.  So that path has to be kept busy all the time, with the fewest bytes per flop that leave no unit idle, and
+// little else may stand in a row with it:
+//
+//  * Two waves per SIMD, which cover each other's LDS reads, loads and waits, share one stage and one barrier per 64 k.
+//    (The 128 x 128 tile on four waves, one per SIMD, took 0.48-0.53 us per 64 k; here 0.40-0.47.)
+//  * At the barrier every wave has its last fragments of a stage in registers and the loads of the next stage have landed;
+//    after it the next stage is read and the released one refilled, NS - 1 iterations ahead of its use.  NS: three stages
+//    of the larger tiles are enough (a fourth and fifth gained nothing and lengthen the prologue); 64 x 128 has four (1024 x
+//    1600 x 4160 NN 21.5 -> 19.7 us), 64 x 64 five (512 x 512 x 8192 NT 30.6 -> 23.1), two workgroups on a unit.
+//  * G = 1: the waves divide the tile and each multiplies both 32-k halves of a stage.  G = 2: two groups of 2 x 2 waves own
+//    the whole tile each, group g multiplies half g, and at the end each hands half of its sums to the other through LDS.
+//    That costs 0.5 (64 x 64) to 2 us per tile and saves a third of the LDS reads: it is the better form of the 64 x 64 tile
+//    (G = 1: 2-7 % slower) and, where an operand is read with the transposing reads, of the 128 x 128 tile over a long K
+//    (NN 3-7 %, TN 8-11 % from K = 6000 on; 9-11 % slower below K = 1536); half tiles lose by it.
+//  * Loads are whole 128-byte lines of a K-contiguous operand (a stage row), and whole k-rows of the tile of an
+//    MN-contiguous one; both LDS layouts are free of bank conflicts for their reads.
+//
+// Measured against the kernels that served these products (us, operands in cache, NN / NT / TN):
+//   2048 x 4096 x 4096 (256 x 128 tiles) 57 / 54 / 58 -> 51 / 52 / 54;  2048 x 2048 x 8192 (128 x 128) 66 / 66 / 68 -> 58 / 57 / 60;
+//   1024 x 1600 x 4160 (64 x 128) 30 / 31 / 30 -> 20 / 20 / 22;  640 x 640 x 2048 (64 x 64) 8.1 / 8.2 / 8.7 -> 6.6 / 6.1 / 7.3;
+// and on equal tiles, over 9 000 sampled products, 1.03 (half tiles) to 1.24 times (128 x 128, K >= 3072) as fast as the 32-k
+// ring and the four-wave 64-k kernel, none slower by more than 4 %.
+//
+// MFMA order, accumulator layout and the XCD-aware tile order are those of gemm_tile_kernel16.
+#pragma once
+#include "gemm_mfma16.hpp"
+
+namespace axonn {
+
+// Operand policies: one stage holds ROWS x 64 k of the operand and is filled by all NW waves.
+//   issue<X>(stage)           the X-th of this wave's QL direct loads, at the window, into the stage at `stage`
+//   issue_tail<X>(...)        the same for a shorter last 64 k
+//   advance()                 the window 64 k on
+//   cursor<H>(stage), read<I>() fragment of 16-row block I: the 32 k of this wave's group (H = 0), or the other half (H = 1)
+template <int ROWS, int REGION, int NW, int NB>
+struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chunks swizzled by (row >> 1) & 7
+    static constexpr int QL = ROWS / 8 / NW;   // a load is 8 rows x 128 bytes
+    static_assert(QL >= 1 && (QL == 1 || QL % 2 == 0), "loads per wave");
+    const uint8_t* base;     // uniform: the wave's first row, at the window
+    uint32_t voff[QL];       // per lane
+    uint32_t lds_dst;        // uniform
+    uint32_t raddr[2];       // read address of block 0 in stage 0, for half 0 (the wave's own) and half 1
+
+    __device__ __forceinline__ void init(const uint16_t* P, int64_t row0, uint32_t ld_bytes, int lane, int wave, int group,
+                                         uint32_t lds0, int wave_row) {
+        base = reinterpret_cast<const uint8_t*>(P) + (size_t)(row0 + 8 * QL * wave) * ld_bytes;
+#pragma unroll
+        for (int x = 0; x < QL; ++x) {
+            const uint32_t row = 8 * (QL * wave + x) + (lane >> 3);
+            voff[x] = (uint32_t)(8 * x + (lane >> 3)) * ld_bytes + ((((uint32_t)lane & 7u) ^ ((row >> 1) & 7u)) << 4);
+        }
+        lds_dst = lds0 + REGION + (uint32_t)(QL * wave) * 1024u;
+        const uint32_t r16 = lane & 15, quad = lane >> 4;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            raddr[h] = lds0 + REGION + (uint32_t)(wave_row + r16) * 128u + (((4u * (group ^ h) + quad) ^ (r16 >> 1)) << 4);
+    }
+    template <int X>
+    __device__ __forceinline__ void issue(uint32_t stage) const {
+        direct_load16(lds_dst + stage + X * 1024u, base, voff[X]);
+    }
+    template <int X>
+    __device__ __forceinline__ void issue_tail(uint32_t stage, size_t delta, int left, int lane, int wave) const {
+        const uint32_t row = 8 * (QL * wave + X) + (lane >> 3);
+        const int k = 8 * (int)((lane & 7) ^ ((row >> 1) & 7));
+        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, k < left));
+    }
+    __device__ __forceinline__ void advance() { base += 128; }
+    struct Cursor {
+        uint32_t a;
+    };
+    template <int H>
+    __device__ __forceinline__ Cursor cursor(uint32_t stage) const { return Cursor{raddr[H] + stage}; }
+    template <int I>
+    __device__ __forceinline__ bf16x8 read(const Cursor& c) const {
+        typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<lds_u32x4*>(c.a + I * 2048u));
+    }
+};
+
+template <int ROWS, int REGION, int NW, int NB>
+struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte chunks swizzled by k
+    static constexpr int ROWB = ROWS * 2, CPR = ROWB / 16;
+    static constexpr int KR = 1024 / ROWB;     // k-rows per load
+    static constexpr int QL = 64 / KR / NW;
+    static_assert(QL >= 1, "loads per wave");
+    const uint8_t* base;     // uniform: the wave's first k-row, at the window
+    size_t step_bytes;       // 64 k-rows
+    uint32_t voff[QL];
+    uint32_t lds_dst;
+    uint32_t raddr[NB];      // read address of block I in stage 0
+
+    // The transposing read serves its four 16-lane groups (k blocks of eight) two at a time; the eight 32-byte pieces of
+    // a pair fall into eight different eighths of the 64 banks.
+    static __device__ __forceinline__ uint32_t swizzle(uint32_t k) {
+        return ROWS >= 128 ? (2u * (k & 3u)) ^ (8u * ((k >> 3) & 1u)) : (2u * ((k >> 1) & 1u)) ^ (4u * ((k >> 3) & 1u));
+    }
+    __device__ __forceinline__ void init(const uint16_t* P, int64_t row0, uint32_t ld_bytes, int lane, int wave, int group,
+                                         uint32_t lds0, int wave_row) {
+        base = reinterpret_cast<const uint8_t*>(P) + (size_t)row0 * 2 + (size_t)(KR * QL * wave) * ld_bytes;
+        step_bytes = (size_t)64 * ld_bytes;
+        const uint32_t kr = lane / CPR, pos = lane % CPR;
+#pragma unroll
+        for (int x = 0; x < QL; ++x) voff[x] = (KR * x + kr) * ld_bytes + ((pos ^ swizzle(KR * (QL * wave + x) + kr)) << 4);
+        lds_dst = lds0 + REGION + (uint32_t)(QL * wave) * 1024u;
+        const uint32_t s = lane & 15, k = 32u * group + 8u * (lane >> 4) + (s >> 2);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const uint32_t m = wave_row + 16 * i + 4 * (s & 3);
+            raddr[i] = lds0 + REGION + k * ROWB + (((m >> 3) ^ swizzle(k)) << 4) + (m & 4) * 2;
+        }
+    }
+    template <int X>
+    __device__ __forceinline__ void issue(uint32_t stage) const {
+        direct_load16(lds_dst + stage + X * 1024u, base, voff[X]);
+    }
+    template <int X>
+    __device__ __forceinline__ void issue_tail(uint32_t stage, size_t delta, int left, int lane, int wave) const {
+        const int k = KR * (QL * wave + X) + lane / CPR;
+        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, k < left));
+    }
+    __device__ __forceinline__ void advance() { base += step_bytes; }
+    struct Cursor {
+        uint32_t a;
+    };
+    template <int H>
+    __device__ __forceinline__ Cursor cursor(uint32_t stage) const { return Cursor{stage + H * 32u * ROWB}; }
+    template <int I>
+    __device__ __forceinline__ bf16x8 read(const Cursor& c) const {
+        typedef short i16x4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+        const uint32_t a = raddr[I] + c.a;
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>(a));
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<lds_i16x4*>(a + 4u * ROWB));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
+
+template <int BM, int BN, int G>
+struct GroupCfg {
+    static constexpr int NW = 8, NT = 512;
+    static constexpr int WN = G == 2 || BM > BN || BN == 64 ? 2 : 4, WM = NW / G / WN;
+    static constexpr int STAGE = (BM + BN) * 128;                // 64 k of both operands
+    static constexpr int NS = BM + BN <= 128 ? 5 : BM + BN <= 192 ? 4 : 3;
+    static constexpr int EXCHANGE = G == 2 ? BM * BN * 4 : 0;   // half of either group's fp32 tile
+    static constexpr int LDS_BYTES = NS * STAGE > EXCHANGE ? NS * STAGE : EXCHANGE;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
+    // 128 registers, so that two workgroups share a compute unit, where LDS has room for two
+    static constexpr int WAVES_PER_SIMD = 2 * LDS_BYTES <= 160 * 1024 ? 4 : 2;
+};
+
+// Requires M >= BM, N >= BN, K % 64 == 0 (KTAIL: see TileGrid), and 16-byte aligned rows.
+template <int BM, int BN, int G, bool A_KC, bool B_KC, bool KTAIL = false>
+__global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void gemm_tile_kernel_k64g(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
+    int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
+    using Cfg = GroupCfg<BM, BN, G>;
+    constexpr int NW = Cfg::NW, NS = Cfg::NS;
+    constexpr uint32_t STAGE = Cfg::STAGE;
+    constexpr int TM = BM / Cfg::WM, TN = BN / Cfg::WN, MI = TM / 16, NI = TN / 16, NM = MI * NI;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+
+    const int t = threadIdx.x;
+    int lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int group = G == 2 ? wave >> 2 : 0, wm = (G == 2 ? wave & 3 : wave) / Cfg::WN, wn = wave % Cfg::WN;
+
+    const TileWork work = map_workgroup<false, false>(blockIdx.x, gridDim.x, K, grid.tiles_m, grid.tiles_n, group_m, sk);
+    const int64_t m0 = min(work.tile_m * BM, grid.m_last), n0 = min(work.tile_n * BN, grid.n_last);
+
+    using OpA = typename std::conditional<A_KC, GroupKContig<BM, 0, NW, MI>, GroupMNContig<BM, 0, NW, MI>>::type;
+    using OpB = typename std::conditional<B_KC, GroupKContig<BN, BM * 128, NW, NI>, GroupMNContig<BN, BM * 128, NW, NI>>::type;
+    constexpr int QLA = OpA::QL, QLB = OpB::QL, QL = QLA + QLB;
+    const uint32_t lds0 = lds_address(smem);
+    OpA opa;
+    OpB opb;
+    opa.init(A, m0, 2u * (uint32_t)lda, lane, wave, group, lds0, wm * TM);
+    opb.init(B, n0, 2u * (uint32_t)ldb, lane, wave, group, lds0, wn * TN);
+
+    f32x4 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    struct Frags {
+        bf16x8 a[MI], b[NI];
+    };
+    Frags f[2];
+
+#define AXONN_FENCE() __builtin_amdgcn_sched_barrier(0)
+    auto issue_stage = [&](uint32_t stage) __attribute__((always_inline)) {
+        static_for<QLA>([&](auto x) __attribute__((always_inline)) { opa.template issue<decltype(x)::value>(stage); });
+        static_for<QLB>([&](auto x) __attribute__((always_inline)) { opb.template issue<decltype(x)::value>(stage); });
+        opa.advance();
+        opb.advance();
+    };
+    auto read_range = [&](Frags& x, uint32_t stage, auto h_c, auto lo_c, auto hi_c) __attribute__((always_inline)) {
+        constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;
+        constexpr int H = decltype(h_c)::value;
+        const auto ca = opa.template cursor<H>(stage);
+        const auto cb = opb.template cursor<H>(stage);
+        static_for<HI - LO>([&](auto d) __attribute__((always_inline)) {
+            constexpr int X = LO + decltype(d)::value;
+            if constexpr (X < MI)
+                x.a[X] = opa.template read<X>(ca);
+            else
+                x.b[X - MI] = opb.template read<X - MI>(cb);
+        });
+    };
+    auto mfma_range = [&](const Frags& x, auto lo_c, auto hi_c) __attribute__((always_inline)) {
+        constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;
+        static_for<HI - LO>([&](auto d) __attribute__((always_inline)) {
+            constexpr int I = (LO + decltype(d)::value) / NI, J0 = (LO + decltype(d)::value) % NI;
+            constexpr int J = (I & 1) ? NI - 1 - J0 : J0;
+            acc[I][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.b[J], x.a[I], acc[I][J], 0, 0, 0);
+        });
+    };
+
+    // ---- prologue: the first stages
+    const int KI = K / 64;
+    const int fill = KI < NS ? KI : NS;
+    {
+        int s = 0;
+        if constexpr (KTAIL) {
+            const size_t whole = (size_t)(K - 64);
+            static_for<QLA>([&](auto x) __attribute__((always_inline)) {
+                opa.template issue_tail<decltype(x)::value>(0u, 2 * (A_KC ? whole : whole * lda), grid.k_tail, lane, wave);
+            });
+            static_for<QLB>([&](auto x) __attribute__((always_inline)) {
+                opb.template issue_tail<decltype(x)::value>(0u, 2 * (B_KC ? whole : whole * ldb), grid.k_tail, lane, wave);
+            });
+            s = 1;
+        }
+        for (; s < fill; ++s) issue_stage(s * STAGE);
+    }
+    if (KI < NS) {   // all of K is in LDS
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        for (int i = 0; i < KI; ++i) {
+            static_for<2 / G>([&](auto h) __attribute__((always_inline)) {
+                read_range(f[0], i * STAGE, h, Int<0>{}, Int<MI + NI>{});
+                mfma_range(f[0], Int<0>{}, Int<NM>{});
+            });
+        }
+    } else {
+        constexpr int P = NM < 4 ? 0 : 2;   // MFMAs before the barrier
+        // clusters of reads and loads: no difference in time, but other numbers make the compiler spill
+        constexpr int NC = BM * BN <= 64 * 128 ? 3 : 2;
+        uint32_t st = 0;                // stage of the running iteration
+        auto next = [&](uint32_t s) __attribute__((always_inline)) { return s + STAGE == NS * STAGE ? 0u : s + STAGE; };
+        // MFMAs on `cur`, among them the reads of `nxt` from half H of stage `from` and the loads LF .. LL-1 of a stage
+        // into `to`.  VM >= 0: a barrier first, at which this wave's fragments are in registers and all its loads but the
+        // last VM have landed.
+        auto substep = [&](const Frags& cur, Frags& nxt, auto vm_c, auto read_c, auto h_c, auto lf_c, auto ll_c, uint32_t from, uint32_t to) __attribute__((always_inline)) {
+            constexpr bool READ = decltype(read_c)::value;
+            constexpr int VM = decltype(vm_c)::value, LF = decltype(lf_c)::value, NL = decltype(ll_c)::value - LF;
+            AXONN_FENCE();
+            mfma_range(cur, Int<0>{}, Int<P>{});
+            AXONN_FENCE();
+            if constexpr (VM >= 0) {
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(VM < 0 ? 0 : VM) : "memory");
+                AXONN_FENCE();
+            }
+            constexpr int R = NM - P;
+            static_for<NC>([&](auto q_c) __attribute__((always_inline)) {
+                constexpr int Q = decltype(q_c)::value;
+                if constexpr (READ) read_range(nxt, from, h_c, Int<Q * (MI + NI) / NC>{}, Int<(Q + 1) * (MI + NI) / NC>{});
+                static_for<(Q + 1) * NL / NC - Q * NL / NC>([&](auto d) __attribute__((always_inline)) {
+                    constexpr int X = LF + Q * NL / NC + decltype(d)::value;
+                    if constexpr (X < QLA)
+                        opa.template issue<X>(to);
+                    else
+                        opb.template issue<X - QLA>(to);
+                });
+                AXONN_FENCE();
+                __builtin_amdgcn_s_setprio(1);
+                mfma_range(cur, Int<P + Q * R / NC>{}, Int<P + (Q + 1) * R / NC>{});
+                __builtin_amdgcn_s_setprio(0);
+                AXONN_FENCE();
+            });
+        };
+        using Yes = std::true_type;
+        using No = std::false_type;
+        wait_vmcnt<(NS - 1) * QL>();
+        __builtin_amdgcn_s_barrier();
+        AXONN_FENCE();
+        constexpr int VM = (NS - 2) * QL;
+        if constexpr (G == 2) {
+            // one iteration: multiplies `cur`, reads the next iteration's fragments, refills the stage behind the barrier
+            auto step = [&](const Frags& cur, Frags& nxt, auto vm_c, auto read_c, auto load_c) __attribute__((always_inline)) {
+                const uint32_t ns = next(st);
+                substep(cur, nxt, vm_c, read_c, Int<0>{}, Int<0>{}, Int<decltype(load_c)::value ? QL : 0>{}, ns, st);
+                if constexpr (decltype(load_c)::value) {
+                    opa.advance();
+                    opb.advance();
+                }
+                st = ns;
+            };
+            int n = KI - NS;   // iterations with a load; the register buffers alternate, and the ones without a load start on f[0]
+            if (n & 1) {
+                read_range(f[1], 0u, Int<0>{}, Int<0>{}, Int<MI + NI>{});
+                step(f[1], f[0], Int<VM>{}, Yes{}, Yes{});
+            } else {
+                read_range(f[0], 0u, Int<0>{}, Int<0>{}, Int<MI + NI>{});
+            }
+            for (n >>= 1; n > 0; --n) {
+                step(f[0], f[1], Int<VM>{}, Yes{}, Yes{});
+                step(f[1], f[0], Int<VM>{}, Yes{}, Yes{});
+            }
+            static_for<NS>([&](auto j_c) __attribute__((always_inline)) {
+                constexpr int J = decltype(j_c)::value;
+                constexpr int V = J == NS - 1 ? -1 : J < NS - 2 ? (NS - 2 - J) * QL : 0;
+                step(f[J & 1], f[1 - (J & 1)], Int<V>{}, std::bool_constant<(J < NS - 1)>{}, No{});
+            });
+        } else {
+            // one iteration: both halves.  The stage is released at the barrier in the second one; its loads go out there
+            // and in the next iteration's first half.
+            constexpr int QH = QL / 2;
+            uint32_t to = 0;
+            auto step = [&](auto vm_c, auto last_c, auto load0_c, auto load1_c) __attribute__((always_inline)) {
+                constexpr bool LAST = decltype(last_c)::value, L0 = decltype(load0_c)::value, L1 = decltype(load1_c)::value;
+                const uint32_t ns = next(st);
+                substep(f[0], f[1], Int<-1>{}, Yes{}, Int<1>{}, Int<QH>{}, Int<L0 ? QL : QH>{}, st, to);
+                if constexpr (L0) {
+                    opa.advance();
+                    opb.advance();
+                }
+                substep(f[1], f[0], vm_c, std::bool_constant<!LAST>{}, Int<0>{}, Int<0>{}, Int<L1 ? QH : 0>{}, ns, st);
+                to = st;
+                st = ns;
+            };
+            read_range(f[0], 0u, Int<0>{}, Int<0>{}, Int<MI + NI>{});
+            int n = KI - NS;
+            if (n > 0) {
+                step(Int<VM>{}, No{}, No{}, Yes{});
+                for (; n > 1; --n) step(Int<VM>{}, No{}, Yes{}, Yes{});
+                step(Int<VM>{}, No{}, Yes{}, No{});
+            } else {
+                step(Int<VM>{}, No{}, No{}, No{});
+            }
+            static_for<NS - 1>([&](auto j_c) __attribute__((always_inline)) {
+                constexpr int J = decltype(j_c)::value + 1;
+                constexpr int V = J == NS - 1 ? -1 : J < NS - 2 ? (NS - 2 - J) * QL : 0;
+                step(Int<V>{}, std::bool_constant<(J == NS - 1)>{}, No{}, No{});
+            });
+        }
+    }
+    __syncthreads();   // the stages are free
+    asm volatile("" : "+v"(lane));   // see split_k_exchange16: keeps the epilogue's addresses out of the K loop's registers
+    if constexpr (G == 1) {
+        uint8_t* const epi = smem + wave * (32 * TN);
+        uint16_t* const pc = C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) store_block_row16<TN, NI>(acc[i], epi, pc + (int64_t)(16 * i) * ldc, ldc, lane);
+    } else {
+        // the groups' sums: group 0 keeps the first half of the block rows, group 1 the second
+        constexpr int MH = MI / 2;
+        f32x4* const slots = reinterpret_cast<f32x4*>(smem);
+        f32x4* const mine = slots + wave * (MH * NI * 64) + lane;
+        const f32x4* const other = slots + (wave ^ 4) * (MH * NI * 64) + lane;
+        f32x4 out[MH][NI];
+        auto give = [&](auto first_c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < MH; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) mine[(i * NI + j) * 64] = acc[decltype(first_c)::value + i][j];
+        };
+        auto take = [&](auto first_c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < MH; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) out[i][j] = acc[decltype(first_c)::value + i][j] + other[(i * NI + j) * 64];
+        };
+        if (group == 0) give(Int<MH>{});
+        else give(Int<0>{});
+        __syncthreads();
+        if (group == 0) take(Int<0>{});
+        else take(Int<MH>{});
+        // staged through the slot that this wave alone has read
+        uint8_t* const epi = smem + (wave ^ 4) * (MH * NI * 1024);
+        uint16_t* const pc = C + (m0 + wm * TM + group * (TM / 2)) * (int64_t)ldc + n0 + wn * TN;
+#pragma unroll
+        for (int i = 0; i < MH; ++i) store_block_row16<TN, NI>(out[i], epi, pc + (int64_t)(16 * i) * ldc, ldc, lane);
+    }
+#undef AXONN_FENCE
+}
+
+}  // namespace axonn

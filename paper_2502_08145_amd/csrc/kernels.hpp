@@ -15,13 +15,28 @@ typedef void (*tile_kernel_t)(const uint16_t*, const uint16_t*, uint16_t*, int, 
 // layout: 0 NN, 1 NT, 2 TN.  k_tail: the form for a K that is no multiple of 64 (TileGrid).  nullptr: no such kernel.
 // 32-k LDS ring (gemm_tile_kernel16): tile bm x bn, 2 x wn waves, with or without split-K
 tile_kernel_t ring_kernel_large(bool split, int layout);                          // 256 x 256, 2 x 4 waves
-tile_kernel_t ring_kernel_small(int bm, int bn, int wn, bool split, int layout, bool k_tail = false);  // 256x128, 128x256 (wn 2; wn 4 without split-K), 128x128 (not NT)
+tile_kernel_t ring_kernel_small(int bm, int bn, bool split, int layout);          // 2 x 2 waves: 256x128, 128x256, 128x128 (not NT) with split-K; 128x256 without
 // 64-k stages (gemm_tile_kernel_k64): 256 x 256, 2 x 4 waves
 tile_kernel_t k64_kernel(bool split, int layout, bool k_tail = false);
-// the same on 256 x 128, 128 x 256 and 128 x 128 tiles, 2 x 2 waves, three LDS buffers per operand (NT only)
-tile_kernel_t k64_kernel_half(int bm, int bn, bool split, int layout, bool k_tail = false);
+// the same on 256 x 128, 128 x 256 and 128 x 128 tiles, 2 x 2 waves, three LDS buffers per operand (NT with split-K only)
+tile_kernel_t k64_kernel_half(int bm, int bn, int layout);
 // the same with one resident workgroup per compute unit walking a list of tiles (gemm_tile_kernel_k64p)
 tile_kernel_t k64p_kernel(int layout);
+
+// eight waves on tiles from 64 x 64 to 256 x 128 (gemm_tile_kernel_k64g), no split-K
+tile_kernel_t group_kernel(int bm, int bn, int groups, int layout, bool k_tail);
+int group_lds_bytes(int bm, int bn, int groups);
+double group_us(int bm, int bn, int groups, int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);   // modelled time; < 0: not there
+void group_raise_lds_limit();
+// the tiles that are no variants: 64 x 64, 64 x 128, 128 x 64, and 128 x 128 in two groups
+struct GroupChoice {
+    int tile = -1;              // < 0: none of them takes this block
+    double us = 0.0;            // modelled time
+};
+GroupChoice group_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);
+void group_tile(const GroupChoice& c, int* rows, int* cols, int* groups);
+void group_launch(const GroupChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
+                  int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);
 
 // guarded MFMA kernel (gemm_edge_kernel): any m, n, K >= 1 and any leading dimensions
 void edge_kernel_raise_lds_limit();

@@ -27,27 +27,15 @@ tile_kernel_t k64_kernel(bool split, int layout, bool k_tail) {
     return (layout >= 0 && layout < 3) ? fn[split ? 1 : 0][layout] : nullptr;
 }
 
-// The 64-k kernel on the half tiles: four waves (2 x 2), three buffers per operand (144 KB), half of an
-// iteration's loads in either sub-step.  NT only: there it measures 28 % over the 32-k ring on the same
-// tiles (2048 x 4096 x 4096: 1018 against 794 TFLOP/s; 4096^3: 1141 against 949); with an MN-contiguous
-// operand it is 15-30 % BEHIND the ring (NN 743 against 990, TN 704 against 904), like every schedule
-// tried that issues such an operand's loads anywhere but straight after the barrier.  128 x 128 tiles (96 KB, four
-// waves) gain less, but gain at every size: alternating runs against the ring, one product of 2048 x 2048 x 8192
-// 73.0 -> 65.8 us (operands from HBM 87 -> 81), 1024 x 3072 x 3072 29.6 -> 27.1 (39.2 -> 37.4), 2048 x 640 x 640 from HBM 9.0 ->
-// 8.0: every load is a whole line and there is one barrier per 64 k; their bytes in flight do not matter (the
-// ring with eight stages instead of six: no change).
-tile_kernel_t k64_kernel_half(int bm, int bn, bool split, int layout, bool k_tail) {
-    if (layout != 1 || (split && k_tail)) return nullptr;
-    if (bm == 128 && bn == 128)
-        return split    ? gemm_tile_kernel_k64<128, 128, 2, true, true, true, 3>
-               : k_tail ? gemm_tile_kernel_k64<128, 128, 2, true, true, false, 3, true>
-                        : gemm_tile_kernel_k64<128, 128, 2, true, true, false, 3>;
-    if (k_tail && bm == 256 && bn == 128) return gemm_tile_kernel_k64<256, 128, 2, true, true, false, 3, true>;
-    if (k_tail && bm == 128 && bn == 256) return gemm_tile_kernel_k64<128, 256, 2, true, true, false, 3, true>;
-    if (bm == 256 && bn == 128)
-        return split ? gemm_tile_kernel_k64<256, 128, 2, true, true, true, 3> : gemm_tile_kernel_k64<256, 128, 2, true, true, false, 3>;
-    if (bm == 128 && bn == 256)
-        return split ? gemm_tile_kernel_k64<128, 256, 2, true, true, true, 3> : gemm_tile_kernel_k64<128, 256, 2, true, true, false, 3>;
+// The 64-k kernel on the smaller tiles: four waves (2 x 2), three buffers per operand, half of an iteration's loads in either
+// sub-step.  NT only: there it is 28 % ahead of the 32-k ring on the half tiles (2048 x 4096 x 4096: 1018 against 794 TFLOP/s);
+// with an MN-contiguous operand it is 15-30 % BEHIND it, like every schedule tried that issues such an operand's loads
+// anywhere but straight after the barrier.  Split-K only: without it the eight-wave kernel (gemm_mfma16_k64g.hpp) has these tiles.
+tile_kernel_t k64_kernel_half(int bm, int bn, int layout) {
+    if (layout != 1) return nullptr;
+    if (bm == 128 && bn == 128) return gemm_tile_kernel_k64<128, 128, 2, true, true, true, 3>;
+    if (bm == 256 && bn == 128) return gemm_tile_kernel_k64<256, 128, 2, true, true, true, 3>;
+    if (bm == 128 && bn == 256) return gemm_tile_kernel_k64<128, 256, 2, true, true, true, 3>;
     return nullptr;
 }
 

@@ -26,39 +26,42 @@ static const WaveKTile kTiles[] = {
 };
 #undef AXONN_WAVEK
 
-// Modelled time of a launch in microseconds: launch, fill and drain, plus the largest (smoothly) of
+// Modelled time of a launch in microseconds: launch, fill and drain, the adding up of partial tiles, plus the largest (smoothly) of
 //   the chain of one wave:   its chunks, one after the other
 //   a compute unit's work:   all chunks of the tiles it gets, its load path shared by its waves, and the
 //                            exchange of partial tiles
 //   memory:                  every operand and output byte once
 //   staging:                 every byte that some tile loads, through the L2s
-// Constants: least squares on the logarithm over 5 700 sampled products of up to 150 GFLOP, operands in cache
-// (residual 16-18 %; the tile and wave count it chooses are 4 % behind the best ones measured on average).  The
-// smallest of some twenty estimates is an optimistic one: what is chosen takes 1.10 of it.
-constexpr double kChosen = 1.10;
+// Rows of an operand that do not start on 128-byte lines, or not on 16 bytes, make its loads touch more lines.
+// Constants: least squares on the logarithm over 8 500 sampled products (1 to 16384 rows) on the four tiles and wave counts
+// modelled shortest and two others each, the mean of operands in cache and from memory (residual 7-9 % near the best).  The smallest
+// of some twenty estimates is an optimistic one: what is chosen takes 1.02 of it.
+constexpr double kChosen = 1.02;
 struct WaveKModel {
-    double fill, chunk0, chunk_area, work_side, work_area, exchange, store, per_mb, staged_per_mb;
+    double fill, chunk0, chunk_area, work_side, work_area, exchange, store, per_mb, staged_per_mb, off_line, off_piece, chain_lines, add_up;
 };
 static const WaveKModel kModel[3] = {
-    {4.0, 0.110, 0.045, 0.029, 0.0, 0.30, 0.20, 0.153, 0.044},       // NN
-    {5.3, 0.141, 0.032, 0.010, 0.0076, 0.45, 0.14, 0.148, 0.038},    // NT
-    {4.0, 0.105, 0.044, 0.033, 0.0, 0.31, 0.21, 0.153, 0.044},       // TN
+    {2.75, 0.205, 0.0289, 0.0245, 0.0, 0.260, 0.270, 0.224, 0.0308, 0.358, 0.147, 0.311, 0.79},      // NN
+    {2.70, 0.178, 0.0345, 0.0188, 0.0021, 0.160, 0.406, 0.191, 0.0263, 0.399, 0.271, 0.299, 1.18},   // NT
+    {3.01, 0.194, 0.0307, 0.0238, 0.0, 0.206, 0.235, 0.271, 0.0417, 0.274, 0.184, 0.340, 0.83},      // TN
 };
-static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t N, int64_t K) {
+static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
     const WaveKModel& m = kModel[layout];
     const double area = mi * ni, tiles = (double)((M + 16 * mi - 1) / (16 * mi)) * (double)((N + 16 * ni - 1) / (16 * ni));
     const int64_t n_chunks = (K + WaveKCfg::KC - 1) / WaveKCfg::KC;
+    auto more_lines = [&](int64_t ld) { return (ld % 64 ? m.off_line : 0.0) + (ld % 8 ? m.off_piece : 0.0); };
+    const double more = (more_lines(lda) * mi + more_lines(ldb) * ni) / (mi + ni);
     // Beyond one tile per compute unit a round more is a whole one: smoothed there as well, the model was 16-18 % short
     // just above 256, 512 and 768 tiles, and 2816 x 128 x 9856 TN went to 352 tiles of 32 x 32 (53.5 us) from split-K
     // (39.6).
     const double chunks = (double)n_chunks, full = tiles / 256.0;
     const double rounds = full > 1.0 ? std::ceil(full) : std::pow(1.0 + std::pow(full, 4.0), 0.25);
-    const double chain = (double)((n_chunks + waves - 1) / waves) * (m.chunk0 + m.chunk_area * area);
-    const double unit = rounds * (chunks * (m.work_side * (mi + ni) + m.work_area * area) +
+    const double chain = (double)((n_chunks + waves - 1) / waves) * (m.chunk0 + m.chunk_area * area) * (1.0 + m.chain_lines * more);
+    const double unit = rounds * (chunks * (m.work_side * (mi + ni) * (1.0 + more) + m.work_area * area) +
                                   (waves > 1 ? m.exchange * waves * area / 16.0 : 0.0) + m.store * area / 16.0);
     const double memory = 2e-6 * ((double)M * K + (double)K * N + (double)M * N) * m.per_mb;
-    const double staged = 2048e-6 * tiles * chunks * (mi + ni) * m.staged_per_mb;
-    return m.fill + std::cbrt(chain * chain * chain + unit * unit * unit + memory * memory * memory + staged * staged * staged);
+    const double staged = 2048e-6 * tiles * chunks * (mi + ni) * m.staged_per_mb * (1.0 + more);
+    return m.fill + (waves > 1 ? m.add_up * area / 16.0 : 0.0) + std::cbrt(chain * chain * chain + unit * unit * unit + memory * memory * memory + staged * staged * staged);
 }
 
 WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
@@ -74,7 +77,7 @@ WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t ld
         const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
         for (int w = 1; w <= WaveKCfg::max_waves(t.mi, t.ni) && (w == 1 || (int64_t)(w - 1) * WaveKCfg::KC < K); w *= 2) {
             if (tiles * 64 * w >= ((int64_t)1 << 32)) continue;   // threads of a launch
-            const double us = model_us(layout, t.mi, t.ni, w, M, N, K);
+            const double us = model_us(layout, t.mi, t.ni, w, M, N, K, lda, ldb);
             if (best.tile < 0 || us < best.us) best = WaveKChoice{i, w, us};
         }
     }

@@ -97,6 +97,39 @@ def test_kernels_on_products_that_reach_them(oracle_mod, layout, family):
         _check(oracle_mod, M, N, K, layout, [name])
 
 
+@lru_cache(maxsize=None)
+def small_tile_products(kernel, layout):
+    """Products of one launch on `kernel`: up to one each of the shortest K (all of it in LDS), of one to six steps more (either
+    parity, the ring once around) and of some dozens, on outputs of whole and of ragged tiles.  (The 128 x 128 tile in two
+    groups is taken for a long K only.)"""
+    rng = random.Random(f"{kernel} {layout}")
+    found = {}
+    long_k = "128x128" in kernel
+    for _ in range(40000):
+        steps = rng.choice([32, 33, 47, 48, 65] if long_k else [2, 3, 4, 5, 6, 7, 8, 9, 24, 25, 33])
+        step = rng.choice([8, 64])
+        M, N, K = _log_int(rng, 1024 if long_k else 64, 2304, step), _log_int(rng, 1024 if long_k else 64, 2304, step), 64 * steps
+        if B.kernels(M, N, K, layout) == [kernel]:
+            key = (steps, M % 64 == 0 and N % 64 == 0)
+            if key not in found or M * N < found[key][0] * found[key][1]:
+                found[key] = (M, N, K)
+    return sorted(found.values())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("kernel", ["wavek_64x64_g2", "mfma16_64x128", "mfma16_128x64", "mfma16_128x128_g2"])
+def test_small_tiles_of_the_eight_wave_kernel(oracle_mod, layout, kernel):
+    if kernel == "mfma16_128x128_g2" and layout == "NT":
+        pytest.skip("not built: one group is as fast there")
+    B.register_workspace()
+    shapes = small_tile_products(kernel, layout)
+    assert shapes
+    for shape in shapes:
+        print(f"  {kernel} {layout} {shape}", flush=True)
+        _check(oracle_mod, *shape, layout, [kernel])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("shape", [(300, 700, 5), (300, 700, 7), (515, 1031, 3), (2047, 2303, 4093), (3001, 1999, 2049)])
