@@ -144,7 +144,8 @@ size_t axonn_linear_static_scratch_bytes(void);
  * AXONN_ERR_LAUNCH; nothing launched on error. */
 int axonn_transpose_bf16(int64_t rows, int64_t cols, const void *src, void *dst, void *stream);
 /* Name of the kernel that re-stores a matrix of this size, both buffers 16-byte aligned or not; NULL if the size is
- * refused.  Host only. */
+ * refused.  Larger matrices whose output rows start off 128-byte lines run on the form of the tile kernels that follows those
+ * lines, under the same names.  Host only. */
 const char *axonn_transpose_kernel(int64_t rows, int64_t cols, int aligned);
 
 /* Mode tuner (Sec. IV-C: time each product in the three modes during the first batch and keep the

@@ -1180,6 +1180,10 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     if (kernel == axonn::TrKernel::Element) {
         hipLaunchKernelGGL(axonn::transpose_naive_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)((cols + 3) / 4)), dim3(256), 0, st,
                            from, to, rows, cols);
+    } else if (axonn::tr_window(rows, cols, d)) {
+        const int64_t tiles_r = axonn::tr_windows(rows), tiles_c = axonn::tr_tiles(cols);
+        hipLaunchKernelGGL(axonn::transpose_window_kernel, dim3((unsigned)(tiles_r * tiles_c)), dim3(axonn::TR_WINDOW_THREADS), 0, st,
+                           from, to, rows, cols, (int)tiles_r, (int)tiles_c);
     } else {
         const int64_t tiles_r = axonn::tr_tiles(rows), tiles_c = axonn::tr_tiles(cols);   // product below 2^29: rows * cols < 2^40
         hipLaunchKernelGGL(kernel == axonn::TrKernel::TileBands ? axonn::transpose_tile_kernel<true> : axonn::transpose_tile_kernel<false>,

@@ -11,14 +11,13 @@
 //
 // Any size of at least a tile: the last tiles are moved back to the matrix' edge (what they repeat is stored
 // twice, the same bits), and loads and stores take any 2-byte aligned address.  One element per thread, as
-// before, 2049 x 4100 took 29 us; now 16 (floor at the rate of a large copy: 6.5; the rest is lines that two tiles
-// write a part of).
+// before, 2049 x 4100 took 29 us; on this kernel 16 (floor at the rate of a large copy: 6.5; the rest is lines that two
+// tiles write a part of: see transpose_window_kernel).
 //
 // Order of the tiles.  Row by row for whole tiles.  BANDS, for large matrices whose rows are no whole lines or whose
 // both strides are multiples of 4 KB: each XCD works on a contiguous chunk of the tiles, four deep along the
-// shorter side of the matrix (with output rows that are no whole lines but whole 16-byte pieces: always along those; 3000 x
-// 9000 from HBM 34 -> 30 us), and each such band starts 5 tiles further along.  In the first case two tiles
-// that write parts of one line then do it behind the same L2 (2049 x 4100 from HBM 19 -> 16 us); in the second, the
+// shorter side of the matrix (with output rows that are no whole lines but whole 16-byte pieces: always along those, 3-10 %), and each such band starts 5 tiles further along.  In the first case two tiles
+// that write parts of one line then do it behind the same L2 (2049 x 4100 from HBM 19 -> 16 us; matrices of that size have gone to transpose_window_kernel since); in the second, the
 // lines of a tile fall on few memory channels, and it is the neighbouring tiles that use the others (from HBM:
 // 4096 x 12288 50 -> 43 us, 8192 x 8192 67 -> 53, 4096 x 16384 66 -> 53; floors 39, 52, 52).  Anywhere else it is 3-10 % behind
 // (3136 x 15872 47.6 -> 50.0, 11904 x 1280 16.4 -> 18.3), and below 1024 tiles, which all fit the chip side by side, its
@@ -38,6 +37,12 @@ typedef short tr_v4i16 __attribute__((ext_vector_type(4)));
 
 constexpr int TR_TILE = 64;          // rows and columns per workgroup
 constexpr int TR_BAND = 4;           // tiles across a band
+// transpose_window_kernel: output elements along an output row per workgroup, threads, tile columns across a band
+constexpr int TR_WINDOW = 128;
+constexpr int TR_WINDOW_THREADS = 512;
+constexpr int TR_WINDOW_BAND = 8;
+constexpr int TR_WINDOW_STRIDE = 33;          // dwords per src row in LDS
+inline int64_t tr_windows(int64_t rows) { return (rows + 63 + TR_WINDOW - 1) / TR_WINDOW; }   // a window starts up to 63 early
 inline bool tr_bands(int64_t rows, int64_t cols, int64_t tiles, bool whole) {
     return tiles >= 1024 && (!whole || (rows % 2048 == 0 && cols % 2048 == 0));
 }
@@ -56,6 +61,14 @@ inline TrKernel tr_choose(int64_t rows, int64_t cols, bool aligned) {
     const bool ragged_tiles = std::min(rows, cols) >= TR_TILE && rows * cols >= tr_ragged_from(std::min(rows, cols)) && tiles < ((int64_t)1 << 24);
     if (!whole && !ragged_tiles) return TrKernel::Element;
     return tr_bands(rows, cols, tiles, whole) ? TrKernel::TileBands : TrKernel::Tile;
+}
+// Whether the tile kernels leave a matrix to transpose_window_kernel.  Where output rows start at odd addresses it is ahead from
+// some 600 tiles on (1001 x 3000, 752 tiles: 4.8 -> 4.2 us; 1001 x 2000, 512 tiles: 3.3 -> 3.7); where at even ones, from some 2500
+// on (2008 x 5000, 2528 tiles: 7.8 -> 7.5 us; 1608 x 4168, 1716 tiles: 5.4 -> 5.9).
+// A launch of 512 threads per window and tile column holds fewer than 2^32.
+inline bool tr_window(int64_t rows, int64_t cols, uintptr_t dst) {
+    if ((rows % 64 == 0 && dst % 128 == 0) || tr_windows(rows) * tr_tiles(cols) >= ((int64_t)1 << 23)) return false;
+    return tr_tiles(rows) * tr_tiles(cols) >= ((rows % 2 || dst % 4) ? 640 : 2560);
 }
 constexpr int TR_LDS_STRIDE = 144;   // bytes per tile row in LDS (128 + 16)
 
@@ -107,6 +120,72 @@ __global__ __launch_bounds__(256) void transpose_tile_kernel(const uint16_t* __r
         out[2] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(hi, hi, 0, 1));
         out[3] = __builtin_bit_cast(uint32_t, __builtin_shufflevector(hi, hi, 2, 3));
         *reinterpret_cast<tr_u32x4_any*>(dst + (c0 + 16 * wave + s) * rows + r0 + rb * 32 + 8 * g) = out;
+    }
+}
+
+// Output rows that do not start on 128-byte lines (rows no multiple of 64, or dst off a line): the stores of a 64 x 64 tile
+// end in lines that another tile writes the rest of, and at odd addresses each is several accesses.  Here the window of a
+// workgroup follows the lines: of output row c it writes TR_WINDOW elements from the line boundary at or before r0 on, so
+// that every store is an aligned 16-byte piece and a wave's store eight whole lines; only the first and last pieces of an
+// output row go element by element.  The window starts up to 63 elements earlier from one output row to the next, so a
+// workgroup reads TR_WINDOW + 63 rows of src (the compute units of an XCD work on a band of tiles side by side, and what
+// two of them read comes from its L2).  The shift differs per output row, so the transposing LDS read does not fit; 16-bit reads
+// from rows of an odd number of dwords do, spread over the banks.
+// us, operands in cache / from HBM: 2049 x 4100 12.4 / 15.4 -> 7.1 / 10.7 (as a copy: 6.5), 8191 x 8193 72 / 87 -> 42 / 56,
+// 701 x 9001 8.2 / 10.3 -> 6.0 / 8.4, 4104 x 4104 12.5 / 18.9 -> 11.7 / 16.9.  Windows of 192 elements: 2-8 % slower up to
+// 2000 tiles, level above; 256: 10 %; 192 on four waves: another 5 %; 448: 20 %.  Bands of 4 or 16: +-3 %.
+// Requires rows >= 1, cols >= 64.  grid = tr_windows(rows) x tr_tiles(cols).
+__global__ __launch_bounds__(TR_WINDOW_THREADS) void transpose_window_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst, int64_t rows,
+                                                               int64_t cols, int tiles_r, int tiles_c) {
+    constexpr int NT = TR_WINDOW_THREADS, IN_ROWS = TR_WINDOW + 64;
+    __shared__ uint32_t tile[IN_ROWS * TR_WINDOW_STRIDE];
+    const int t = threadIdx.x;
+    // XCD x runs the workgroups x, x + 8, ...: a contiguous chunk of the sequence
+    const uint32_t x = blockIdx.x & 7, rem = gridDim.x & 7;
+    const uint32_t id = x * (gridDim.x >> 3) + min(x, rem) + (blockIdx.x >> 3);
+    const uint32_t band = id / (TR_WINDOW_BAND * (uint32_t)tiles_r), in_band = id - band * (TR_WINDOW_BAND * (uint32_t)tiles_r);
+    const uint32_t depth = min((uint32_t)tiles_c - band * TR_WINDOW_BAND, (uint32_t)TR_WINDOW_BAND), tr = in_band / depth;
+    const int64_t r0 = (int64_t)tr * TR_WINDOW;
+    const int64_t c0 = min((int64_t)(band * TR_WINDOW_BAND + in_band - tr * depth) * 64, cols - 64);
+
+    constexpr int LOADS = IN_ROWS * 8 / NT;
+    static_assert(IN_ROWS * 8 % NT == 0 && TR_WINDOW % 64 == 0 && TR_WINDOW * 8 % NT == 0, "whole passes");
+    tr_u32x4 v[LOADS];
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+        const int q = t + NT * u;
+        const int64_t r = min(max(r0 - 64 + (q >> 3), (int64_t)0), rows - 1);   // a row outside is never stored
+        v[u] = *reinterpret_cast<const tr_u32x4_any*>(src + r * cols + c0 + (q & 7) * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) {
+        const int q = t + NT * u;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) tile[(q >> 3) * TR_WINDOW_STRIDE + (q & 7) * 4 + d] = v[u][d];
+    }
+    __syncthreads();
+    const uint16_t* const halves = reinterpret_cast<const uint16_t*>(tile);
+    const uint32_t phase = (uint32_t)(reinterpret_cast<uintptr_t>(dst) >> 1);
+#pragma unroll 2
+    for (int u = 0; u < TR_WINDOW * 8 / NT; ++u) {
+        const int q = t + NT * u, c = (q >> 3) & 63, p = 64 * (q >> 9) + 8 * (q & 7);   // output row c0 + c, p elements into the window
+        const uint32_t shift = (phase + (uint32_t)(c0 + c) * (uint32_t)rows) & 63u;
+        const int64_t r = r0 + p - (int)shift;
+        const uint16_t* const from = halves + (64 + p - (int)shift) * (2 * TR_WINDOW_STRIDE) + c;
+        uint32_t e[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = from[i * (2 * TR_WINDOW_STRIDE)];
+        uint16_t* const to = dst + (c0 + c) * rows + r;
+        if (r >= 0 && r + 8 <= rows) {
+            tr_u32x4 out;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out[i] = e[2 * i] | e[2 * i + 1] << 16;
+            *reinterpret_cast<tr_u32x4*>(to) = out;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (r + i >= 0 && r + i < rows) to[i] = (uint16_t)e[i];
+        }
     }
 }
 

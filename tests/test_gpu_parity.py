@@ -863,6 +863,27 @@ def test_transpose_of_any_size_and_address(oracle_mod, shape, offset):
     assert (got[:16 - offset] == 0x7FC0).all() and (got[16 - offset + rows * cols:] == 0x7FC0).all()
 
 
+# rows at and around whole windows of 128 less the 63 that a line boundary can lie back, narrower than a window, one more than whole
+# tiles in either direction; even rows from 2560 tiles on; whole rows whose output starts off a line (offset 1, 8)
+@pytest.mark.parametrize("shape", [(65, 24581), (129, 14000), (193, 10311), (319, 8257), (321, 6977), (577, 4097), (1001, 3000), (2049, 2049),
+                                   (24583, 65), (14001, 129), (2008, 5130), (2050, 5001), (4096, 2561)])
+@pytest.mark.parametrize("offset", [0, 1, 8])
+def test_transpose_in_windows_along_the_lines(oracle_mod, shape, offset):
+    """Every element once, whatever line its output row starts in; nothing around the output is written."""
+    rows, cols = shape
+    assert B.transpose_kernel(rows, cols, offset == 0).startswith("transpose_tile")
+    src = synth.normal_bf16(79 + rows, (rows, cols))
+    s = torch.empty((rows * cols + 8,), dtype=torch.bfloat16, device="cuda")
+    s[8 - offset:8 - offset + rows * cols] = U.to_device(src).reshape(-1)
+    d = torch.empty((rows * cols + 128,), dtype=torch.bfloat16, device="cuda")
+    d.view(torch.int16).fill_(0x7FC0)
+    B.axonn_transpose_bf16(rows, cols, s[8 - offset:8 - offset + rows * cols], d[64 + offset:64 + offset + rows * cols])
+    torch.cuda.synchronize()
+    got = U.to_host_bits(d)
+    assert np.array_equal(got[64 + offset:64 + offset + rows * cols].reshape(cols, rows), oracle_mod.transpose(src))
+    assert (got[:64 + offset] == 0x7FC0).all() and (got[64 + offset + rows * cols:] == 0x7FC0).all()
+
+
 def test_transposed_weight_runs_the_forward_product_in_another_mode(oracle_mod):
     # Sec. IV-C in one piece: Y = X W computed as NN on (X, W) and as NT on (X, transpose(W))
     T, d_in, d_out = 512, 768, 1024
