@@ -316,4 +316,90 @@ __global__ __launch_bounds__(64 * WaveKCfg::max_waves(MI, NI)) void gemm_wavek_k
     }
 }
 
+// The weight gradient of a few tokens: two MN-contiguous operands over K <= 32 H (H = 1, 2), M >= 64, N >= 64.  All of K is one
+// chunk, so what counts is the output, written once, and how many waves are there to write it.  A workgroup of
+// four waves takes 64 rows and, SPAN times, 4 x 64 columns; a wave's region of LDS holds 32 H k-rows (wave-K kernel: 64 of
+// both operands), the fragments of the rows stay in registers, the next columns' loads are in flight while 16 rows at a time
+// are multiplied, rounded and stored as whole lines.  Products and sums are the wave-K kernel's, to the bit.
+// What bounds it is the output's way to memory.  On the wave-K kernel eight waves fit a compute unit's LDS (18 KB each) and
+// each lived for one tile: load, multiply, store.  us, before / here: 2048 x 8192 x 24 11.8 / 8.9 (clearing the output: 7.6), x 64
+// 11.5 / 9.9, 4096 x 16384 x 48 from HBM 53 / 31, 1024 x 4096 x 24 6.2 / 4.7, 2001 x 8191 x 31 12.5 / 10.1.
+struct ShortKCfg {
+    static constexpr int ROWB = 32 * 4 + WaveKCfg::PAD;            // bytes per k-row, or output row, in LDS
+    static constexpr int COLS = 4 * 64;                             // per workgroup and step
+    static constexpr int wave_bytes(int H) { return 32 * H * ROWB + 16 * ROWB; }
+};
+template <int H>
+__global__ __launch_bounds__(256, (H == 1 ? 4 : 3)) void gemm_shortk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
+                                                          int64_t M, int64_t N, int K, int64_t lda, int64_t ldb, int64_t ldc, int tiles_n, int span) {
+    constexpr int ROWB = ShortKCfg::ROWB, NL = 4 * H;
+    __shared__ __attribute__((aligned(16))) uint8_t smem[4 * ShortKCfg::wave_bytes(H)];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t* const region = smem + wave * ShortKCfg::wave_bytes(H);
+    uint8_t* const rows16 = region + 32 * H * ROWB;
+    const int spans = (tiles_n + span - 1) / span;   // tiles_n: steps of COLS columns
+    const int tile_m = blockIdx.x / spans, first = (blockIdx.x - tile_m * spans) * span, last = min(first + span, tiles_n);
+    const int64_t m0 = min((int64_t)tile_m * 64, M - 64);
+
+    // a load is 8 k-rows x 128 bytes; k-rows behind K: the last one again, dropped
+    const int kr = lane >> 3, ch = lane & 7;
+    const auto load = [&](u32x4 (&x)[NL], const uint16_t* P, int64_t ld) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j)
+            if (8 * j < K) x[j] = *reinterpret_cast<const u32x4_any*>(P + min(8 * j + kr, K - 1) * ld + 8 * ch);
+    };
+    const auto stage = [&](const u32x4 (&x)[NL]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j)
+            *reinterpret_cast<u32x4*>(region + (8 * j + kr) * ROWB + 16 * ch) = 8 * j + kr < K ? x[j] : u32x4{0u, 0u, 0u, 0u};
+        wave_order();
+    };
+    const auto fragments = [&](bf16x8 (&f)[4][H]) __attribute__((always_inline)) {
+        typedef short i16x4 __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+        const int s = lane & 15, g = lane >> 4;
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const uint8_t* const p = region + (32 * h + 8 * g + (s >> 2)) * ROWB + 8 * (s & 3) + 32 * b;
+                const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p));
+                const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p + 4 * ROWB));
+                f[b][h] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        wave_order();
+    };
+    const auto column = [&](int tile) __attribute__((always_inline)) { return min((int64_t)tile * ShortKCfg::COLS + 64 * wave, N - 64); };
+
+    u32x4 xa[NL] = {}, xb[NL] = {};
+    bf16x8 fa[4][H], fb[4][H];
+    load(xa, A + m0, lda);
+    load(xb, B + column(first), ldb);
+    stage(xa);
+    fragments(fa);
+    for (int tile = first; tile < last; ++tile) {
+        const int64_t n0 = column(tile);
+        stage(xb);
+        if (tile + 1 < last) load(xb, B + column(tile + 1), ldb);
+        fragments(fb);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                f32x4 acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int h = 0; h < H; ++h) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j][h], fa[i][h], acc, 0, 0, 0);
+                *reinterpret_cast<u32x2*>(rows16 + (lane & 15) * ROWB + 32 * j + 8 * (lane >> 4)) = u32x2{pack2_bf16(acc[0], acc[1]), pack2_bf16(acc[2], acc[3])};
+            }
+            wave_order();
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const u32x4 v = *reinterpret_cast<const u32x4*>(rows16 + (8 * it + kr) * ROWB + 16 * ch);
+                *reinterpret_cast<u32x4_any*>(C + (m0 + 16 * i + 8 * it + kr) * ldc + n0 + 8 * ch) = v;
+            }
+            wave_order();
+        }
+    }
+}
+
 }  // namespace axonn

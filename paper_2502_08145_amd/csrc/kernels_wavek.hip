@@ -90,6 +90,11 @@ void wavek_tile(const WaveKChoice& c, int* rows, int* cols) {
     *cols = 16 * kTiles[c.tile].ni;
 }
 
+// One wave over all of K on the 64 x 64 tile of two MN-contiguous operands: all of K is one chunk there.
+bool wavek_short(const WaveKChoice& c, int layout, int64_t K) {
+    return layout == 2 && c.waves == 1 && kTiles[c.tile].mi == 4 && kTiles[c.tile].ni == 4 && K <= 64;
+}
+
 static int lds_bytes(int tile, int waves, int layout) {
     return WaveKCfg::lds_bytes(layout != 2, layout == 1, kTiles[tile].mi, kTiles[tile].ni, waves);
 }
@@ -105,6 +110,15 @@ void wavek_raise_lds_limit() {
 void wavek_launch(const WaveKChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                   int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const WaveKTile& t = kTiles[c.tile];
+    if (wavek_short(c, layout, K)) {
+        const int64_t tm = (m + 63) / 64, tn = (n + ShortKCfg::COLS - 1) / ShortKCfg::COLS;
+        // from three workgroups a compute unit on, each takes two steps of columns: 3000 x 5000 x 24 8.9 -> 8.6 us, 8192 x 8192 x 40 33.9 ->
+        // 28.7; 600 x 16384 x 7 (640 steps) 6.4 -> 6.9.  Four steps: 14 % slower on 2048 x 8192 x 24.
+        const int64_t span = tm * tn >= 768 ? 2 : 1;
+        hipLaunchKernelGGL(K <= 32 ? gemm_shortk_kernel<1> : gemm_shortk_kernel<2>, dim3((unsigned)(tm * ((tn + span - 1) / span))), dim3(256), 0, s,
+                           A, B, C, m, n, (int)K, lda, ldb, ldc, (int)tn, (int)span);
+        return;
+    }
     const int64_t tiles_m = (m + 16 * t.mi - 1) / (16 * t.mi), tiles_n = (n + 16 * t.ni - 1) / (16 * t.ni);
     hipLaunchKernelGGL(t.fn[layout], dim3((unsigned)(tiles_m * tiles_n)), dim3(64 * c.waves), lds_bytes(c.tile, c.waves, layout), s,
                        A, B, C, m, n, K, lda, ldb, ldc, (int)tiles_m, (int)tiles_n, (int)(tiles_m < 8 ? tiles_m : 8));

@@ -131,6 +131,15 @@ def test_small_tiles_of_the_eight_wave_kernel(oracle_mod, layout, kernel):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(2048, 8192, 24), (1024, 4096, 32), (1025, 4099, 31), (600, 16384, 7), (3000, 5000, 1), (16384, 1024, 33),
+                                   (2001, 8191, 64), (2000, 8200, 40), (65, 40001, 9), (4099, 2303, 63), (9000, 900, 8)])
+def test_weight_gradient_of_a_few_tokens(oracle_mod, shape):
+    """All of K in one chunk: K at the ends of the 8-row loads and of the 32-k halves, one step of columns a workgroup and two, ragged edges."""
+    M, N, K = shape
+    _check(oracle_mod, M, N, K, "TN", [f"wavek_64x64_k{32 if K <= 32 else 64}"])
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("layout", LAYOUTS)
 @pytest.mark.parametrize("shape", [(300, 700, 5), (300, 700, 7), (515, 1031, 3), (2047, 2303, 4093), (3001, 1999, 2049)])
 def test_guarded_kernel_on_misaligned_rows(oracle_mod, layout, shape):
