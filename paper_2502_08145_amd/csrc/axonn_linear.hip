@@ -160,16 +160,18 @@ static std::vector<Variant> make_variants() {
     static const char* const k64_sk[] = {"mfma16k64_256x256_w8_sk2", "mfma16k64_256x256_w8_sk3", "mfma16k64_256x256_w8_sk4", "mfma16k64_256x256_w8_sk5",
                                          "mfma16k64_256x256_w8_sk6", "mfma16k64_256x256_w8_sk7", "mfma16k64_256x256_w8_sk8"};
     for (int sp = 2; sp <= 8; ++sp) k64(k64_sk[sp - 2], sp);
-    // us64: fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %)
+    // us64: fitted over 36 000 sampled products (residual 3-4 %, 128 x 128 tiles 7-8 %).  The eight-wave kernel's are those of
+    // the kernels that had its tiles when the rule for the scratch area was made (Figures::Area); nothing else reads them.
     static const struct { const char* name; double us64[3]; } measured[] = {
         {"mfma16_128x128", {0.530, 0.525, 0.557}},       {"mfma16_128x256", {0.927, 0.887, 0.950}},
-        {"mfma16_256x128", {0.885, 0.888, 0.951}},       {"mfma16k64_128x256", {0.0, 0.817, 0.0}},        {"mfma16k64_256x128", {0.0, 0.819, 0.0}},
+        {"mfma16_128x256_w8", {0.773, 0.818, 0.852}},    {"mfma16_256x128", {0.885, 0.888, 0.951}},
+        {"mfma16k64_128x256", {0.0, 0.817, 0.0}},        {"mfma16k64_256x128", {0.0, 0.819, 0.0}},
         {"mfma16k64_256x256_w8", {1.284, 1.219, 1.263}},
     };
     for (Variant& x : v)
         for (const auto& q : measured)
             // a split-K variant's name is the plain one's and "_sk<ranges>"
-            if (!x.group && std::strncmp(x.name, q.name, std::strlen(q.name)) == 0 && (x.splits > 1) == (std::strstr(x.name, "_sk") == x.name + std::strlen(q.name)) &&
+            if (std::strncmp(x.name, q.name, std::strlen(q.name)) == 0 && (x.splits > 1) == (std::strstr(x.name, "_sk") == x.name + std::strlen(q.name)) &&
                 (x.splits > 1 || std::strlen(x.name) == std::strlen(q.name))) {
                 std::copy(q.us64, q.us64 + 3, x.us64);
                 for (int l = 0; l < 3 && x.splits == 1 && x.bm * x.bn == 256 * 256; ++l) x.fn_tail[l] = k64_kernel(false, l, true);
@@ -351,13 +353,22 @@ static double edge_us(int64_t m, int64_t n, int64_t K, bool rows_aligned) {
                         : 3.0 + (2.0 * steps + 5.0) * std::sqrt(1.0 + (wgs / 292.0) * (wgs / 292.0));
 }
 
+// Whose figures a modelled time is made of.
+// Area: the ones that decide which products exchange partial tiles through the scratch area.  That set is part of the
+// interface -- other products can overlap on several streams, and the static entry never refuses them -- so it does
+// not follow the kernels: these figures stay, and compare whole tiles and split-K, and the wave-K kernel, in one unit (operands
+// in cache).  While it did follow the refitted ones, which are the mean of operands in cache and from memory but for split-K,
+// 1 % of sampled ragged products went from one launch without scratch to whole tiles with split-K and strips: thirty of those, in
+// one launch and so, 0.88 times as fast (6984 x 6056 x 9856 NN 615 us and 762).
+enum class Figures { Current, Area };
+
 // How a block of the output is computed where it is not simply the tile variant of its part.
 struct BlockChoice {
     int tile = -1;           // >= 0: this tile variant, its last tiles moved back to the block's edge (TileGrid)
     GroupChoice group{};     // else, .tile >= 0: one of the eight-wave kernel's small tiles
     WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel; else what the part's variant says
     int lead_m = 0, lead_n = 0;   // rows and columns before the block that the launch covers as well
-    double us = 0.0;         // modelled time, operands in cache
+    double us = 0.0;         // modelled time
 };
 
 // Where the rows of the output do not start on 128-byte lines, a tile's stores end in lines that two workgroups write a
@@ -377,18 +388,19 @@ static double shared_lines_us(const Variant& x, int64_t m, int64_t n, int64_t ld
 // The eight-wave kernel has a model of its own.  Full rounds of 256 workgroups and 0.76 + 0.24 f of one for a last round that fills a fraction f of the compute
 // units; split-K variants also exchange partial tiles, which costs a trip to memory and back per range and
 // some of its bandwidth per tile.  Fitted over 36 000 sampled products, residual 3-8 %.
-static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
+static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, Figures figures = Figures::Current) {
     const Variant& x = variants()[v];
+    const bool group = x.group && figures == Figures::Current;
     const int64_t k_padded = (K + 63) / 64 * 64;   // every tile kernel takes K 64 at a time
-    if ((x.us64[layout] <= 0.0 && !x.group) || !x.fn[layout] || m < x.bm || n < x.bn || K <= 64) return -1.0;
-    if (k_padded / x.splits < x.min_k && !x.group) return -1.0;   // the eight-wave kernel takes any K
+    if ((x.us64[layout] <= 0.0 && !group) || !x.fn[layout] || m < x.bm || n < x.bn || K <= 64) return -1.0;
+    if (k_padded / x.splits < x.min_k && !group) return -1.0;   // the eight-wave kernel takes any K
     if (K != k_padded && !x.fn_tail[layout]) return -1.0;
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0) return -1.0;   // 16-byte direct loads and stores
     if (std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return -1.0;
-    if (x.group) return group_us(x.bm, x.bn, 1, layout, m, n, K, lda, ldb, ldc);
+    if (group) return group_us(x.bm, x.bn, 1, layout, m, n, K, lda, ldb, ldc);
     const int64_t tiles = ((m + x.bm - 1) / x.bm) * ((n + x.bn - 1) / x.bn), wgs = tiles * x.splits, rest = wgs % 256;
     const double rounds = (double)(wgs / 256) + (rest ? 0.76 + 0.24 * (double)rest / 256.0 : 0.0);
-    if (x.splits == 1 && x.bm * x.bn == 256 * 256) {
+    if (figures == Figures::Current && x.splits == 1 && x.bm * x.bn == 256 * 256) {
         // fitted by itself over 1 500 products of 4 to 600 GFLOP, the mean of operands in cache and from memory (residual 4 %; 8 %
         // with the split forms' figures, which were up to 25 % too much for K of one to four steps)
         static const double step[3] = {1.444, 1.333, 1.411};
@@ -406,11 +418,11 @@ static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64
 
 // The tile kernel without split-K (overlapping tiles and strips never touch the scratch area) of the smallest modelled time, if
 // that is below best.us.
-static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, BlockChoice& best) {
+static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, BlockChoice& best, Figures figures = Figures::Current) {
     bool found = false;
     for (int v = 1; v < edge_variant(); ++v) {
         if (variants()[v].splits > 1) continue;
-        const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
+        const double us = block_us(v, m, n, K, layout, lda, ldb, ldc, figures);
         if (us >= 0.0 && us < best.us) {
             best = BlockChoice{};
             best.tile = v;
@@ -418,6 +430,7 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
             found = true;
         }
     }
+    if (figures == Figures::Area) return found;
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
     // Near a tie the wave-K kernel stays: either model is good to 6 %, and where operands come from memory (12 MB and more) its
     // waves, eight chunks of a row in flight between them, suffer less (698 x 968 x 7144 NT: 35 us in cache, 40 from memory; 64 x 64
@@ -441,27 +454,28 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
 // against 53 on 256 x 256 tiles).  Near a tie it is the guarded kernel: of 2 400 sampled ragged products, half of them with K
 // of 72 to 768 and half with outputs of up to 500 MB, 9 then run more than 4 % (12 % at most) behind it or behind
 // whole tiles with guarded strips.
-static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc) {
+static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, Figures figures) {
     constexpr double kMargin = 0.93;
     BlockChoice guarded, best;
     guarded.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
     best.us = kMargin * guarded.us;
-    const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb);
+    const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb, figures == Figures::Area);
     if (wk.tile >= 0 && wk.us < best.us) {
         best.wavek = wk;
         best.us = wk.us;
     }
-    if (tiles_choice(m, n, K, layout, lda, ldb, ldc, best)) return best;
+    if (tiles_choice(m, n, K, layout, lda, ldb, ldc, best, figures)) return best;
     return best.wavek.tile < 0 ? guarded : best;
 }
 // The same for the block at (row0, col0) of the M x N product.  An edge strip of fewer than 16 rows or columns of
 // an MN-contiguous operand is too narrow for the wave-K kernel and would take the guarded one, element by element
 // (2048 x 8 over K = 4096: 60 us against 12); it takes the 16 last ones instead, some of which the launch over the
 // whole tiles, which comes first, has written before.
-static BlockChoice guarded_choice(int64_t row0, int64_t col0, int64_t m, int64_t n, int64_t M, int64_t N, int64_t K, int layout) {
+static BlockChoice guarded_choice(int64_t row0, int64_t col0, int64_t m, int64_t n, int64_t M, int64_t N, int64_t K, int layout,
+                                  Figures figures = Figures::Current) {
     const int lead_m = (layout == AXONN_TN && m < 16 && row0 >= 16) ? (int)(16 - m) : 0;
     const int lead_n = (layout != AXONN_NT && n < 16 && col0 >= 16) ? (int)(16 - n) : 0;
-    BlockChoice g = guarded_choice(m + lead_m, n + lead_n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N, N);
+    BlockChoice g = guarded_choice(m + lead_m, n + lead_n, K, layout, layout == AXONN_TN ? M : K, layout == AXONN_NT ? K : N, N, figures);
     if (g.tile < 0 && g.group.tile < 0 && g.wavek.tile >= 0) {
         g.lead_m = lead_m;
         g.lead_n = lead_n;
@@ -525,18 +539,30 @@ static bool ragged_may_split(int64_t M, int64_t N, int64_t mm, int64_t nm, int64
     return t < guarded(M, N) * kUnitsPerUs;
 }
 
+// Bytes of partial tiles that the variants of a block, or of a plan, exchange.
+static size_t split_bytes(const Part& p) {
+    const Variant& x = variants()[p.variant];
+    return x.splits == 1 ? 0 : (size_t)((p.m / x.bm) * (p.n / x.bn) * (x.splits - 1)) * x.bm * x.bn * sizeof(float);
+}
+
+static size_t split_bytes(const Plan& plan) {
+    size_t bytes = 0;
+    for (int i = 0; i < plan.parts; ++i) bytes = std::max(bytes, split_bytes(plan.part[i]));
+    return bytes;   // the launches of a plan run one after the other and share the area
+}
+
 // A launch over whole tiles of the M x N product, in microseconds.  The variants without a figure of their own count as
 // the 64-k kernel on the same tile: the 32-k ring on the large tile, and the resident workgroups, whose stores overlap
 // the next tile's loads (1 to 2 us a round less on 36 products, and 0.6 of what shared lines cost; below K = 384 only
 // where there are none).
-static double tiles_us(const Part& p, int64_t M, int64_t N, int64_t K, int layout) {
+static double tiles_us(const Part& p, int64_t M, int64_t N, int64_t K, int layout, Figures figures = Figures::Current) {
     const Variant& x = variants()[p.variant];
     const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
-    double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);
+    double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N, figures);
     for (int v = 1; us < 0.0 && v < edge_variant(); ++v) {
         const Variant& y = variants()[v];
         if (!y.k64 || y.bm != x.bm || y.bn != x.bn || y.splits != x.splits) continue;
-        us = block_us(v, p.m, p.n, K, layout, lda, ldb, N);
+        us = block_us(v, p.m, p.n, K, layout, lda, ldb, N, figures);
         if (us >= 0.0 && x.resident && (N % 64 == 0 || K >= 384)) {
             us -= 1.5 * std::max(0.0, (double)((p.m / x.bm) * (p.n / x.bn)) / x.resident - 1.0);
             us -= 0.4 * shared_lines_us(y, p.m, p.n, N);
@@ -565,19 +591,23 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
             const int v_tiles = select_variant(mm, nm, K, layout, split, &t_tiles);
             if (!is_guarded(v_tiles)) {
                 const Plan inner = make_plan(mm, nm, K, layout, split);
-                double t = 0.0;
-                for (int i = 0; i < inner.parts; ++i) t += tiles_us(inner.part[i], M, N, K, layout);
-                if (nm != N) t += guarded_choice(0, nm, mm, N - nm, M, N, K, layout).us;
-                if (mm != M) t += guarded_choice(mm, 0, M - mm, N, M, N, K, layout).us;
-                // One time model on both sides: of 1 230 sampled products, each measured in both forms, those whose modelled
+                // One time model on both sides.  Of 1 230 sampled products, each measured in both forms, those whose modelled
                 // times are within 5 % of each other took 0.97 (strips modelled shorter) and 1.00 (longer) of the one
                 // launch.  Many tiles over a long K keep their strips up to 1.2: the plans of such products
                 // (axonn_linear_plan) are relied on as whole tiles and strips, which costs 6-19 % there (2152 x 12296 x
                 // 4096 NT 195 us against 179).
                 // Below K = 512 the strips have to be clearly shorter: what shared lines cost the whole tiles is the larger
                 // part of the time there.
-                const double favour = (mm / 128) * (nm / 128) >= 1024 && K >= 4096 ? 1.2 : K < 512 ? 0.9 : 1.0;
-                if (t < favour * t_one / kUnitsPerUs) {
+                const double favour = (mm / 128) * (nm / 128) >= 1024 && K >= 4096 ? 1.2 : 1.0;
+                auto strips_pay = [&](Figures figures) {
+                    double t = 0.0;
+                    for (int i = 0; i < inner.parts; ++i) t += tiles_us(inner.part[i], M, N, K, layout, figures);
+                    if (nm != N) t += guarded_choice(0, nm, mm, N - nm, M, N, K, layout, figures).us;
+                    if (mm != M) t += guarded_choice(mm, 0, M - mm, N, M, N, K, layout, figures).us;
+                    if (figures == Figures::Area) return t < favour * guarded_choice(0, 0, M, N, M, N, K, layout, figures).us;
+                    return t < (K < 512 ? 0.9 : favour) * t_one / kUnitsPerUs;
+                };
+                if (strips_pay(Figures::Current) && (split_bytes(inner) == 0 || strips_pay(Figures::Area))) {
                     plan = inner;
                     if (nm != N) plan.part[plan.parts++] = Part{edge_variant(), mm, N - nm, 0, nm};
                     if (mm != M) plan.part[plan.parts++] = Part{edge_variant(), M - mm, N, mm, 0};
@@ -697,17 +727,6 @@ static void raise_lds_limits_once() {
         return;
     }
     std::call_once(g_attr_once[dev], raise_lds_limits);
-}
-
-static size_t split_bytes(const Part& p) {
-    const Variant& x = variants()[p.variant];
-    return x.splits == 1 ? 0 : (size_t)((p.m / x.bm) * (p.n / x.bn) * (x.splits - 1)) * x.bm * x.bn * sizeof(float);
-}
-
-static size_t split_bytes(const Plan& plan) {
-    size_t bytes = 0;
-    for (int i = 0; i < plan.parts; ++i) bytes = std::max(bytes, split_bytes(plan.part[i]));
-    return bytes;   // the launches of a plan run one after the other and share the area
 }
 
 // What the launches touch of it: nothing for a block planned with split-K that runs on a kernel without it.

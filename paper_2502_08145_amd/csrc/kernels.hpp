@@ -48,7 +48,8 @@ struct WaveKChoice {
     int tile = -1, waves = 0;   // tile < 0: the kernel does not take this block
     double us = 0.0;            // modelled time
 };
-WaveKChoice wavek_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb);
+// area_rule: by the figures that decide which plans use the scratch area
+WaveKChoice wavek_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, bool area_rule = false);
 void wavek_tile(const WaveKChoice& c, int* rows, int* cols);   // of its output tile
 bool wavek_short(const WaveKChoice& c, int layout, int64_t K);   // whether it runs on gemm_shortk_kernel
 void wavek_raise_lds_limit();

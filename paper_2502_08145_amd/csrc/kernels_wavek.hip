@@ -45,8 +45,15 @@ static const WaveKModel kModel[3] = {
     {2.70, 0.178, 0.0345, 0.0188, 0.0021, 0.160, 0.406, 0.191, 0.0263, 0.399, 0.271, 0.299, 1.18},   // NT
     {3.01, 0.194, 0.0307, 0.0238, 0.0, 0.206, 0.235, 0.271, 0.0417, 0.274, 0.184, 0.340, 0.83},      // TN
 };
-static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
-    const WaveKModel& m = kModel[layout];
+// The figures of the rule for the scratch area (Figures::Area in axonn_linear.hip): they decide which plans use it and do not
+// follow the kernel.
+constexpr double kAreaChosen = 1.10;
+static const WaveKModel kAreaModel[3] = {
+    {4.0, 0.110, 0.045, 0.029, 0.0, 0.30, 0.20, 0.153, 0.044, 0.0, 0.0, 0.0, 0.0},       // NN
+    {5.3, 0.141, 0.032, 0.010, 0.0076, 0.45, 0.14, 0.148, 0.038, 0.0, 0.0, 0.0, 0.0},    // NT
+    {4.0, 0.105, 0.044, 0.033, 0.0, 0.31, 0.21, 0.153, 0.044, 0.0, 0.0, 0.0, 0.0},       // TN
+};
+static double model_us(const WaveKModel& m, int mi, int ni, int waves, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
     const double area = mi * ni, tiles = (double)((M + 16 * mi - 1) / (16 * mi)) * (double)((N + 16 * ni - 1) / (16 * ni));
     const int64_t n_chunks = (K + WaveKCfg::KC - 1) / WaveKCfg::KC;
     auto more_lines = [&](int64_t ld) { return (ld % 64 ? m.off_line : 0.0) + (ld % 8 ? m.off_piece : 0.0); };
@@ -64,7 +71,8 @@ static double model_us(int layout, int mi, int ni, int waves, int64_t M, int64_t
     return m.fill + (waves > 1 ? m.add_up * area / 16.0 : 0.0) + std::cbrt(chain * chain * chain + unit * unit * unit + memory * memory * memory + staged * staged * staged);
 }
 
-WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, bool area_rule) {
+    const WaveKModel& model = (area_rule ? kAreaModel : kModel)[layout];
     WaveKChoice best;
     if (lda >= WaveKCfg::MAX_LD || ldb >= WaveKCfg::MAX_LD || (layout != 2 && K < 8)) return best;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
@@ -77,11 +85,11 @@ WaveKChoice wavek_choose(int layout, int64_t M, int64_t N, int64_t K, int64_t ld
         const int64_t tiles = ((M + tm - 1) / tm) * ((N + tn - 1) / tn);
         for (int w = 1; w <= WaveKCfg::max_waves(t.mi, t.ni) && (w == 1 || (int64_t)(w - 1) * WaveKCfg::KC < K); w *= 2) {
             if (tiles * 64 * w >= ((int64_t)1 << 32)) continue;   // threads of a launch
-            const double us = model_us(layout, t.mi, t.ni, w, M, N, K, lda, ldb);
+            const double us = model_us(model, t.mi, t.ni, w, M, N, K, lda, ldb);
             if (best.tile < 0 || us < best.us) best = WaveKChoice{i, w, us};
         }
     }
-    best.us *= kChosen;
+    best.us *= area_rule ? kAreaChosen : kChosen;
     return best;
 }
 
