@@ -646,7 +646,17 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
 // of their plan (geometric mean, operands in cache), the slowest 0.98 times.
 // A block planned without split-K also goes to whatever other tile kernel without it is modelled faster: the plans are made
 // with efficiencies from before the eight-wave kernel, which do not know its smaller tiles.  One planned with split-K
-// leaves it for the wave-K kernel only, and only where that is far ahead: callers bring a scratch area for it.
+// leaves it for the wave-K kernel only.
+// By the scratch area's own figures where those say so: such a block stays out of the area (56 products over K of 17 000 and more
+// that went back to split-K by the current figures alone took 1.31 times as long with operands in cache, 1.43 from memory; 384 x
+// 640 x 24064 NT 37 us and 52).  Else by the current ones, where they are far ahead: 120 sampled products 1.25 and 1.37 times as
+// fast, the slowest 1.03 (512 x 768 x 31872 NN 111 us and 72).  Not from four ranges in TN, where the wave-K model is short by up to
+// a half: ten products 0.71 to 0.98 times as fast (256 x 256 x 24576 48 us and 62), two 1.08 and 1.11.
+static bool leaves_split_k(const Part& p, int64_t K, int layout, int64_t lda, int64_t ldb, double us, const WaveKChoice& wk) {
+    if (wk.tile < 0) return false;
+    if (wavek_choose(layout, p.m, p.n, K, lda, ldb, true).us < 0.97 * us) return true;
+    return wk.us < 0.815 * us && !(layout == AXONN_TN && variants()[p.variant].splits >= 4);
+}
 static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
     const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
     for (int i = 0; i < plan.parts; ++i) {
@@ -654,18 +664,21 @@ static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout
         if (variants()[p.variant].edge) {
             p.how = guarded_choice(p.row0, p.col0, p.m, p.n, M, N, K, layout);
         } else if (p.variant > 0) {
-            const bool split = variants()[p.variant].splits > 1;
-            const double margin = split ? 0.815 : 0.98;
-            const double us = split ? block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N) : tiles_us(p, M, N, K, layout);
+            const WaveKChoice wk = wavek_choose(layout, p.m, p.n, K, lda, ldb);
+            if (variants()[p.variant].splits > 1) {
+                const double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);   // the same by either figures
+                if (us > 0.0 && leaves_split_k(p, K, layout, lda, ldb, us, wk)) p.how.wavek = wk;
+                continue;
+            }
+            const double us = tiles_us(p, M, N, K, layout);
             if (us <= 0.0) continue;
             BlockChoice best;
-            best.us = margin * us;
-            const WaveKChoice wk = wavek_choose(layout, p.m, p.n, K, lda, ldb);
+            best.us = 0.98 * us;
             if (wk.tile >= 0 && wk.us < best.us) {
                 best.wavek = wk;
                 best.us = wk.us;
             }
-            if (!split) tiles_choice(p.m, p.n, K, layout, lda, ldb, N, best);
+            tiles_choice(p.m, p.n, K, layout, lda, ldb, N, best);
             if (best.tile != p.variant) p.how = best;
         }
     }
