@@ -835,7 +835,7 @@ static int part_kernel_name(const Part& p, int64_t K, int layout, char* name, si
     if (p.how.wavek.tile >= 0) {
         int rows = 0, cols = 0;
         wavek_tile(p.how.wavek, &rows, &cols);
-        if (wavek_short(p.how.wavek, layout, K)) return std::snprintf(name, bytes, "wavek_%dx%d_k%d", rows, cols, K <= 32 ? 32 : 64);
+        if (wavek_short(p.how.wavek, layout, p.m + p.how.lead_m, p.n + p.how.lead_n, K)) return std::snprintf(name, bytes, "wavek_%dx%d_k%d", rows, cols, K <= 32 ? 32 : 64);
         return std::snprintf(name, bytes, "wavek_%dx%d_w%d", rows, cols, p.how.wavek.waves);
     }
     const char* const tail = planned.bm && K % 64 ? "_ktail" : "";

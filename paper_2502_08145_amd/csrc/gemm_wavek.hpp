@@ -318,7 +318,7 @@ __global__ __launch_bounds__(64 * WaveKCfg::max_waves(MI, NI)) void gemm_wavek_k
 
 // The weight gradient of a few tokens: two MN-contiguous operands over K <= 32 H (H = 1, 2), M >= 64, N >= 64.  All of K is one
 // chunk, so what counts is the output, written once, and how many waves are there to write it.  A workgroup of
-// four waves takes 64 rows and, SPAN times, 4 x 64 columns; a wave's region of LDS holds 32 H k-rows (wave-K kernel: 64 of
+// four waves takes 64 rows and, SPAN times, 4 x 64 columns (a wave whose columns would all be another's has no work); a wave's region of LDS holds 32 H k-rows (wave-K kernel: 64 of
 // both operands), the fragments of the rows stay in registers, the next columns' loads are in flight while 16 rows at a time
 // are multiplied, rounded and stored as whole lines.  Products and sums are the wave-K kernel's, to the bit.
 // What bounds it is the output's way to memory.  On the wave-K kernel eight waves fit a compute unit's LDS (18 KB each) and
@@ -340,6 +340,9 @@ __global__ __launch_bounds__(256, (H == 1 ? 4 : 3)) void gemm_shortk_kernel(cons
     const int spans = (tiles_n + span - 1) / span;   // tiles_n: steps of COLS columns
     const int tile_m = blockIdx.x / spans, first = (blockIdx.x - tile_m * spans) * span, last = min(first + span, tiles_n);
     const int64_t m0 = min((int64_t)tile_m * 64, M - 64);
+    // columns from N on are another wave's; there is no barrier in this kernel
+    const int mine = (int)min((int64_t)last, (N - 64 * wave + ShortKCfg::COLS - 1) / ShortKCfg::COLS);
+    if (first >= mine) return;
 
     // a load is 8 k-rows x 128 bytes; k-rows behind K: the last one again, dropped
     const int kr = lane >> 3, ch = lane & 7;
@@ -377,10 +380,10 @@ __global__ __launch_bounds__(256, (H == 1 ? 4 : 3)) void gemm_shortk_kernel(cons
     load(xb, B + column(first), ldb);
     stage(xa);
     fragments(fa);
-    for (int tile = first; tile < last; ++tile) {
+    for (int tile = first; tile < mine; ++tile) {
         const int64_t n0 = column(tile);
         stage(xb);
-        if (tile + 1 < last) load(xb, B + column(tile + 1), ldb);
+        if (tile + 1 < mine) load(xb, B + column(tile + 1), ldb);
         fragments(fb);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {

@@ -98,9 +98,16 @@ void wavek_tile(const WaveKChoice& c, int* rows, int* cols) {
     *cols = 16 * kTiles[c.tile].ni;
 }
 
-// One wave over all of K on the 64 x 64 tile of two MN-contiguous operands: all of K is one chunk there.
-bool wavek_short(const WaveKChoice& c, int layout, int64_t K) {
-    return layout == 2 && c.waves == 1 && kTiles[c.tile].mi == 4 && kTiles[c.tile].ni == 4 && K <= 64;
+// One wave over all of K on the 64 x 64 tile of two MN-contiguous operands: all of K is one chunk there.  900 sampled products on
+// both kernels (1 to 64 k, 64 to 262144 rows, 64 to 20000 columns; operands in cache and from memory): below K = 64 gemm_shortk_kernel
+// is 1.20 times as fast, but for 64 columns over more than 32 k, where one wave of a workgroup's four has work (65536 x 64 x 48
+// 6.9 us against 5.5).  At K = 64 the wave-K kernel's k-rows are all there, and it is ahead (0.73 to 0.98 over narrow outputs, 0.90 to 0.95
+// over rows off 128-byte lines, 9200 x 320 5.1 us against 6.4) until whole lines of 256 columns and more make nine tiles a compute
+// unit (from there 1.13 times).
+bool wavek_short(const WaveKChoice& c, int layout, int64_t m, int64_t n, int64_t K) {
+    if (layout != 2 || c.waves != 1 || kTiles[c.tile].mi != 4 || kTiles[c.tile].ni != 4 || K > 64) return false;
+    if (K < 64) return K <= 32 || n > 64;
+    return n % 64 == 0 && n >= 256 && (m + 63) / 64 * (n / 64) >= 9 * 256;
 }
 
 static int lds_bytes(int tile, int waves, int layout) {
@@ -118,7 +125,7 @@ void wavek_raise_lds_limit() {
 void wavek_launch(const WaveKChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                   int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const WaveKTile& t = kTiles[c.tile];
-    if (wavek_short(c, layout, K)) {
+    if (wavek_short(c, layout, m, n, K)) {
         const int64_t tm = (m + 63) / 64, tn = (n + ShortKCfg::COLS - 1) / ShortKCfg::COLS;
         // from three workgroups a compute unit on, each takes two steps of columns: 3000 x 5000 x 24 8.9 -> 8.6 us, 8192 x 8192 x 40 33.9 ->
         // 28.7; 600 x 16384 x 7 (640 steps) 6.4 -> 6.9.  Four steps: 14 % slower on 2048 x 8192 x 24.
