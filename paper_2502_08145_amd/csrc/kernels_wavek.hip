@@ -102,12 +102,12 @@ void wavek_tile(const WaveKChoice& c, int* rows, int* cols) {
 // both kernels (1 to 64 k, 64 to 262144 rows, 64 to 20000 columns; operands in cache and from memory): below K = 64 gemm_shortk_kernel
 // is 1.20 times as fast, but for 64 columns over more than 32 k, where one wave of a workgroup's four has work (65536 x 64 x 48
 // 6.9 us against 5.5).  At K = 64 the wave-K kernel's k-rows are all there, and it is ahead (0.73 to 0.98 over narrow outputs, 0.90 to 0.95
-// over rows off 128-byte lines, 9200 x 320 5.1 us against 6.4) until whole lines of 256 columns and more make nine tiles a compute
-// unit (from there 1.13 times).
+// over rows off 128-byte lines, 9200 x 320 5.1 us against 6.4) until there are nine tiles a compute unit and more than 192 columns: from
+// there whole lines run 1.13 times as fast on gemm_shortk_kernel, up to 512 columns off them 1.07 times, more columns off them 0.94.
 bool wavek_short(const WaveKChoice& c, int layout, int64_t m, int64_t n, int64_t K) {
     if (layout != 2 || c.waves != 1 || kTiles[c.tile].mi != 4 || kTiles[c.tile].ni != 4 || K > 64) return false;
     if (K < 64) return K <= 32 || n > 64;
-    return n % 64 == 0 && n >= 256 && (m + 63) / 64 * (n / 64) >= 9 * 256;
+    return n > 192 && (n % 64 == 0 || n <= 512) && (m + 63) / 64 * ((n + 63) / 64) >= 9 * 256;
 }
 
 static int lds_bytes(int tile, int waves, int layout) {
