@@ -418,7 +418,8 @@ static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64
 
 // The tile kernel without split-K (overlapping tiles and strips never touch the scratch area) of the smallest modelled time, if
 // that is below best.us.
-static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, BlockChoice& best, Figures figures = Figures::Current) {
+static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, BlockChoice& best, bool wavek_stays,
+                         Figures figures = Figures::Current) {
     bool found = false;
     for (int v = 1; v < edge_variant(); ++v) {
         if (variants()[v].splits > 1) continue;
@@ -432,11 +433,11 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
     }
     if (figures == Figures::Area) return found;
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
-    // Near a tie the wave-K kernel stays: either model is good to 6 %, and where operands come from memory (12 MB and more) its
+    // wavek_stays: near a tie.  Either model is good to 6 %, and where operands come from memory (12 MB and more) its
     // waves, eight chunks of a row in flight between them, suffer less (698 x 968 x 7144 NT: 35 us in cache, 40 from memory; 64 x 64
     // tiles 34 and 51).
     const GroupChoice g = group_choose(layout, m, n, K, lda, ldb, ldc);
-    const double near = best.wavek.tile < 0 ? 1.0 : m * K + K * n > (int64_t)6000000 ? 0.88 : 0.96;
+    const double near = best.wavek.tile < 0 || !wavek_stays ? 1.0 : m * K + K * n > (int64_t)6000000 ? 0.88 : 0.96;
     if (g.tile >= 0 && g.us < near * best.us) {
         best = BlockChoice{};
         best.group = g;
@@ -451,20 +452,24 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
 // wherever the output has few 128 x 128 tiles (by a factor of three and more for a few rows over a long K; it
 // loses from some 20 GFLOP on, where its 64 x 64 tiles load twice the bytes: 1930 x 7344 x 1832 NN 123 us against
 // 96 for the guarded kernel), the guarded one for large outputs over one or two steps of K (4160 x 11928 x 72 TN: 38 us
-// against 53 on 256 x 256 tiles).  Near a tie it is the guarded kernel: of 2 400 sampled ragged products, half of them with K
-// of 72 to 768 and half with outputs of up to 500 MB, 9 then run more than 4 % (12 % at most) behind it or behind
-// whole tiles with guarded strips.
+// against 53 on 256 x 256 tiles).
+// The guarded kernel has to be modelled 9 % shorter below K = 2048: its model is 5 to 11 % short there for rows of two K-contiguous
+// operands, the wave-K one 10 to 15 % long for launches of more than some 12 us (taken off up to two chunks of K).  At a tie it was the
+// wrong one by up to 1.7 times (8030 x 2081 x 460 NT 41 us on the wave-K kernel, 70 here; 262144 x 128 x 64 TN 18 and 27).  From K = 2048
+// on a tie is the guarded kernel's.  1 120 sampled ragged products on all three kernels (K of 8 to 6000, beyond K = 320 the contested
+// ones): what is chosen takes 1.005 times the best of the three on average, 1.29 at most; with ties to the guarded kernel 1.018 and 1.76.
 static BlockChoice guarded_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, Figures figures) {
-    constexpr double kMargin = 0.93;
+    const bool current = figures == Figures::Current;
     BlockChoice guarded, best;
     guarded.us = edge_us(m, n, K, lda % 8 == 0 && ldb % 8 == 0);
-    best.us = kMargin * guarded.us;
-    const WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb, figures == Figures::Area);
+    best.us = (current && K < 2048 ? 1.1 : 0.93) * guarded.us;
+    WaveKChoice wk = wavek_choose(layout, m, n, K, lda, ldb, !current);
+    if (current && K <= 2 * 64) wk.us -= 0.15 * std::max(0.0, wk.us - 5.0);
     if (wk.tile >= 0 && wk.us < best.us) {
         best.wavek = wk;
         best.us = wk.us;
     }
-    if (tiles_choice(m, n, K, layout, lda, ldb, ldc, best, figures)) return best;
+    if (tiles_choice(m, n, K, layout, lda, ldb, ldc, best, wk.us < 0.93 * guarded.us, figures)) return best;
     return best.wavek.tile < 0 ? guarded : best;
 }
 // The same for the block at (row0, col0) of the M x N product.  An edge strip of fewer than 16 rows or columns of
@@ -678,7 +683,7 @@ static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout
                 best.wavek = wk;
                 best.us = wk.us;
             }
-            tiles_choice(p.m, p.n, K, layout, lda, ldb, N, best);
+            tiles_choice(p.m, p.n, K, layout, lda, ldb, N, best, true);
             if (best.tile != p.variant) p.how = best;
         }
     }

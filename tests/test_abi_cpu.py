@@ -473,3 +473,12 @@ def test_a_second_round_of_wave_k_tiles_counts_whole(shape, layout, slower):
 ])
 def test_short_k_large_ragged_outputs_avoid_what_measured_slower(shape, layout, slower):
     assert not B.kernel_name(*shape, layout).startswith(slower)
+
+
+@pytest.mark.parametrize("shape,layout", [
+    # 41 to 288 us there, 1.3 to 1.8 times that on the guarded kernel (262144 x 128 x 64: 18 us and 27)
+    ((8030, 2081, 460), "NT"), ((1177, 13570, 495), "NT"), ((4467, 1824, 1142), "NT"), ((8784, 23504, 128), "NT"),
+    ((7128, 1179, 615), "NN"), ((26407, 922, 477), "NN"), ((4170, 28780, 526), "NT"), ((262144, 128, 64), "TN"),
+])
+def test_ragged_products_near_a_tie_with_the_guarded_kernel(shape, layout):
+    assert B.kernel_name(*shape, layout) == "wavek_64x64_w1"
