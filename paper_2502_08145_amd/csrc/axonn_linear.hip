@@ -835,12 +835,14 @@ static int plan_call(int64_t M, int64_t N, int64_t K, int layout, ScratchFrom fr
 
 // The kernel behind one launch, named as profile_summary.short() names its symbol (plus the number of K ranges
 // or of waves per tile, which are run-time arguments).  A plan names variants: what runs is more than that.
-static int part_kernel_name(const Part& p, int64_t K, int layout, char* name, size_t bytes) {
+static int part_kernel_name(const Part& p, int64_t N, int64_t K, int layout, char* name, size_t bytes) {
     const Variant& planned = variants()[p.variant];
     if (p.how.wavek.tile >= 0) {
         int rows = 0, cols = 0;
         wavek_tile(p.how.wavek, &rows, &cols);
-        if (wavek_short(p.how.wavek, layout, p.m + p.how.lead_m, p.n + p.how.lead_n, K)) return std::snprintf(name, bytes, "wavek_%dx%d_k%d", rows, cols, K <= 32 ? 32 : 64);
+        const ShortK short_k = wavek_short(p.how.wavek, layout, p.m + p.how.lead_m, p.n + p.how.lead_n, K, N);
+        if (short_k != ShortK::No)
+            return std::snprintf(name, bytes, "wavek_%dx%d_k%d%s", rows, cols, K <= 32 ? 32 : 64, short_k == ShortK::Chunks ? "_xcd" : "");
         return std::snprintf(name, bytes, "wavek_%dx%d_w%d", rows, cols, p.how.wavek.waves);
     }
     const char* const tail = planned.bm && K % 64 ? "_ktail" : "";
@@ -1135,7 +1137,7 @@ int axonn_linear_part_kernel(int64_t M, int64_t N, int64_t K, int layout, int no
         plan = axonn::cached_plan(M, N, K, layout, axonn::g_split_k_enabled.load(std::memory_order_relaxed) != 0);
     }
     if (part >= plan.parts) return AXONN_ERR_INVALID_ARG;
-    const int n = axonn::part_kernel_name(plan.part[part], K, layout, name, name_bytes);
+    const int n = axonn::part_kernel_name(plan.part[part], N, K, layout, name, name_bytes);
     return n > 0 && (size_t)n < name_bytes ? plan.parts : AXONN_ERR_INVALID_ARG;
 }
 

@@ -329,7 +329,7 @@ struct ShortKCfg {
     static constexpr int COLS = 4 * 64;                             // per workgroup and step
     static constexpr int wave_bytes(int H) { return 32 * H * ROWB + 16 * ROWB; }
 };
-template <int H>
+template <int H, bool CHUNKS>
 __global__ __launch_bounds__(256, (H == 1 ? 4 : 3)) void gemm_shortk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
                                                           int64_t M, int64_t N, int K, int64_t lda, int64_t ldb, int64_t ldc, int tiles_n, int span) {
     constexpr int ROWB = ShortKCfg::ROWB, NL = 4 * H;
@@ -338,7 +338,12 @@ __global__ __launch_bounds__(256, (H == 1 ? 4 : 3)) void gemm_shortk_kernel(cons
     uint8_t* const region = smem + wave * ShortKCfg::wave_bytes(H);
     uint8_t* const rows16 = region + 32 * H * ROWB;
     const int spans = (tiles_n + span - 1) / span;   // tiles_n: steps of COLS columns
-    const int tile_m = blockIdx.x / spans, first = (blockIdx.x - tile_m * spans) * span, last = min(first + span, tiles_n);
+    int id = blockIdx.x;
+    if constexpr (CHUNKS) {   // XCD x runs the workgroups x, x + 8, ...: a contiguous chunk of the sequence
+        const uint32_t x = blockIdx.x & 7, rem = gridDim.x & 7;
+        id = (int)(x * (gridDim.x >> 3) + min(x, rem) + (blockIdx.x >> 3));
+    }
+    const int tile_m = id / spans, first = (id - tile_m * spans) * span, last = min(first + span, tiles_n);
     const int64_t m0 = min((int64_t)tile_m * 64, M - 64);
     // columns from N on are another wave's; there is no barrier in this kernel
     const int mine = (int)min((int64_t)last, (N - 64 * wave + ShortKCfg::COLS - 1) / ShortKCfg::COLS);

@@ -51,7 +51,8 @@ struct WaveKChoice {
 // area_rule: by the figures that decide which plans use the scratch area
 WaveKChoice wavek_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, bool area_rule = false);
 void wavek_tile(const WaveKChoice& c, int* rows, int* cols);   // of its output tile
-bool wavek_short(const WaveKChoice& c, int layout, int64_t m, int64_t n, int64_t K);   // whether it runs on gemm_shortk_kernel
+enum class ShortK { No, Yes, Chunks };   // whether it runs on gemm_shortk_kernel, and in which order of its workgroups
+ShortK wavek_short(const WaveKChoice& c, int layout, int64_t m, int64_t n, int64_t K, int64_t ldc);
 void wavek_raise_lds_limit();
 void wavek_launch(const WaveKChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                   int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);

@@ -104,10 +104,15 @@ void wavek_tile(const WaveKChoice& c, int* rows, int* cols) {
 // 6.9 us against 5.5).  At K = 64 the wave-K kernel's k-rows are all there, and it is ahead (0.73 to 0.98 over narrow outputs, 0.90 to 0.95
 // over rows off 128-byte lines, 9200 x 320 5.1 us against 6.4) until there are nine tiles a compute unit and more than 192 columns: from
 // there whole lines run 1.13 times as fast on gemm_shortk_kernel, up to 512 columns off them 1.07 times, more columns off them 0.94.
-bool wavek_short(const WaveKChoice& c, int layout, int64_t m, int64_t n, int64_t K) {
-    if (layout != 2 || c.waves != 1 || kTiles[c.tile].mi != 4 || kTiles[c.tile].ni != 4 || K > 64) return false;
-    if (K < 64) return K <= 32 || n > 64;
-    return n > 192 && (n % 64 == 0 || n <= 512) && (m + 63) / 64 * ((n + 63) / 64) >= 9 * 256;
+// Outputs of more than 320 MB whose rows are no whole halves of a line: 42 products 0.87 times as fast on it (18336 x 21736 x 8 263 us and 178).
+//
+// Workgroups that write parts of one line run side by side behind one L2 (Chunks), where rows are no whole halves of a line: 1.06 to 1.10
+// times as fast from 8 MB of output on (163 products); below, and for whole rows, up to 4 % slower.
+ShortK wavek_short(const WaveKChoice& c, int layout, int64_t m, int64_t n, int64_t K, int64_t ldc) {
+    if (layout != 2 || c.waves != 1 || kTiles[c.tile].mi != 4 || kTiles[c.tile].ni != 4 || K > 64) return ShortK::No;
+    if (n % 32 != 0 && m * n > (int64_t)160 << 20) return ShortK::No;
+    const bool ahead = K < 64 ? K <= 32 || n > 64 : n > 192 && (n % 64 == 0 || n <= 512) && (m + 63) / 64 * ((n + 63) / 64) >= 9 * 256;
+    return !ahead ? ShortK::No : ldc % 32 != 0 && m * n >= (int64_t)4 << 20 ? ShortK::Chunks : ShortK::Yes;
 }
 
 static int lds_bytes(int tile, int waves, int layout) {
@@ -125,12 +130,16 @@ void wavek_raise_lds_limit() {
 void wavek_launch(const WaveKChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                   int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const WaveKTile& t = kTiles[c.tile];
-    if (wavek_short(c, layout, m, n, K)) {
+    const ShortK short_k = wavek_short(c, layout, m, n, K, ldc);
+    if (short_k != ShortK::No) {
         const int64_t tm = (m + 63) / 64, tn = (n + ShortKCfg::COLS - 1) / ShortKCfg::COLS;
         // from three workgroups a compute unit on, each takes two steps of columns: 3000 x 5000 x 24 8.9 -> 8.6 us, 8192 x 8192 x 40 33.9 ->
         // 28.7; 600 x 16384 x 7 (640 steps) 6.4 -> 6.9.  Four steps: 14 % slower on 2048 x 8192 x 24.
         const int64_t span = tm * tn >= 768 ? 2 : 1;
-        hipLaunchKernelGGL(K <= 32 ? gemm_shortk_kernel<1> : gemm_shortk_kernel<2>, dim3((unsigned)(tm * ((tn + span - 1) / span))), dim3(256), 0, s,
+        const bool chunks = short_k == ShortK::Chunks;
+        const auto kernel = K <= 32 ? (chunks ? gemm_shortk_kernel<1, true> : gemm_shortk_kernel<1, false>)
+                                    : (chunks ? gemm_shortk_kernel<2, true> : gemm_shortk_kernel<2, false>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(tm * ((tn + span - 1) / span))), dim3(256), 0, s,
                            A, B, C, m, n, (int)K, lda, ldb, ldc, (int)tn, (int)span);
         return;
     }

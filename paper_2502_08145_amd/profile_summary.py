@@ -55,9 +55,9 @@ def short(name: str) -> str:
     if m:
         akc, bkc, mi, ni = m.groups()
         return f"wavek_{16 * int(mi)}x{16 * int(ni)}/{_LAYOUT.get((akc, bkc), '??')}"
-    m = re.search(r"gemm_shortk_kernel<(\d)>", name)
+    m = re.search(rf"gemm_shortk_kernel<(\d), {_BOOL}>", name)
     if m:
-        return f"wavek_64x64_k{32 * int(m.group(1))}/TN"
+        return f"wavek_64x64_k{32 * int(m.group(1))}{'_xcd' if m.group(2) == 'true' else ''}/TN"
     m = re.search(rf"gemm_edge_kernel<{_BOOL}, {_BOOL}>", name)
     if m:
         return f"edge_128x128/{_LAYOUT.get(m.groups(), '??')}"
