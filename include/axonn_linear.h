@@ -143,9 +143,12 @@ size_t axonn_linear_static_scratch_bytes(void);
  * `stream` and returns.  AXONN_OK, AXONN_ERR_INVALID_ARG, AXONN_ERR_UNSUPPORTED or
  * AXONN_ERR_LAUNCH; nothing launched on error. */
 int axonn_transpose_bf16(int64_t rows, int64_t cols, const void *src, void *dst, void *stream);
-/* Name of the kernel that re-stores a matrix of this size, both buffers 16-byte aligned or not; NULL if the size is
- * refused.  Larger matrices whose output rows start off 128-byte lines run on the form of the tile kernels that follows those
- * lines, under the same names.  Host only. */
+/* Name of the kernel that re-stores a matrix of this size between these addresses (which are not read): "transpose_naive"
+ * (one element per thread), "transpose_tile" and "transpose_tile_bands" (64 x 64 tiles in two orders), "transpose_window"
+ * (larger matrices whose output rows start off 128-byte lines); NULL if the size is refused.  Host only. */
+const char *axonn_transpose_kernel_at(int64_t rows, int64_t cols, const void *src, const void *dst);
+/* The same for two buffers as an allocator gives them (on 128-byte lines), or, `aligned` = 0, two that start at an odd multiple
+ * of 2 bytes.  Host only. */
 const char *axonn_transpose_kernel(int64_t rows, int64_t cols, int aligned);
 
 /* Mode tuner (Sec. IV-C: time each product in the three modes during the first batch and keep the

@@ -27,7 +27,7 @@ EXPORTS = (
     "axonn_linear_plan", "axonn_linear_call_plan", "axonn_linear_part_kernel",
     "axonn_linear_force_variant",
     "axonn_linear_init", "axonn_linear_set_split_k", "axonn_linear_split_k_timeouts",
-    "axonn_linear_workspace_bytes", "axonn_linear_set_workspace", "axonn_transpose_bf16", "axonn_transpose_kernel",
+    "axonn_linear_workspace_bytes", "axonn_linear_set_workspace", "axonn_transpose_bf16", "axonn_transpose_kernel", "axonn_transpose_kernel_at",
     "axonn_linear_tune", "axonn_linear_tuned", "axonn_linear_tune_reset", "axonn_linear_tuned_set", "axonn_linear_tuned_call",
     "axonn_comm_group_bandwidths", "axonn_comm_layer_time", "axonn_comm_rank_grids",
 )
@@ -117,6 +117,8 @@ def lib() -> ctypes.CDLL:
         L.axonn_transpose_bf16.restype = ci
         L.axonn_transpose_kernel.argtypes = [i64, i64, ci]
         L.axonn_transpose_kernel.restype = ctypes.c_char_p
+        L.axonn_transpose_kernel_at.argtypes = [i64, i64, vp, vp]
+        L.axonn_transpose_kernel_at.restype = ctypes.c_char_p
         L.axonn_linear_tune.argtypes = [ci, i64, i64, i64, vp, vp, vp, vp, ctypes.c_size_t, vp,
                                         ctypes.POINTER(TuneResult)]
         L.axonn_linear_tune.restype = ci
@@ -347,6 +349,12 @@ def transpose_kernel(rows: int, cols: int, aligned: bool = True):
     """Name of the kernel behind axonn_transpose_bf16 for this size; None if it is refused."""
     name = lib().axonn_transpose_kernel(int(rows), int(cols), int(aligned))
     return name.decode() if name is not None else None
+
+
+def transpose_kernel_at(rows: int, cols: int, src: int, dst: int):
+    """The same between two addresses (integers, not read)."""
+    name = lib().axonn_transpose_kernel_at(int(rows), int(cols), int(src), int(dst))
+    return name.decode() if name else None
 
 
 def axonn_transpose_bf16(rows, cols, src, dst, stream=None, check=True):

@@ -1211,7 +1211,7 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     const uintptr_t s = reinterpret_cast<uintptr_t>(src), d = reinterpret_cast<uintptr_t>(dst);
     const uintptr_t bytes = (uintptr_t)rows * (uintptr_t)cols * 2;
     if (!src || !dst || (s & 1) || (d & 1) || (s < d + bytes && d < s + bytes)) return AXONN_ERR_INVALID_ARG;
-    const axonn::TrKernel kernel = axonn::tr_choose(rows, cols, !((s | d) & 15));
+    const axonn::TrKernel kernel = axonn::tr_choose(rows, cols, s, d);
     if (kernel == axonn::TrKernel::Refused) return AXONN_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint16_t* from = static_cast<const uint16_t*>(src);
@@ -1220,7 +1220,7 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     if (kernel == axonn::TrKernel::Element) {
         hipLaunchKernelGGL(axonn::transpose_naive_kernel, dim3((unsigned)((rows + 63) / 64), (unsigned)((cols + 3) / 4)), dim3(256), 0, st,
                            from, to, rows, cols);
-    } else if (axonn::tr_window(rows, cols, d)) {
+    } else if (kernel == axonn::TrKernel::Window) {
         const int64_t tiles_r = axonn::tr_windows(rows), tiles_c = axonn::tr_tiles(cols);
         hipLaunchKernelGGL(axonn::transpose_window_kernel, dim3((unsigned)(tiles_r * tiles_c)), dim3(axonn::TR_WINDOW_THREADS), 0, st,
                            from, to, rows, cols, (int)tiles_r, (int)tiles_c);
@@ -1232,14 +1232,20 @@ int axonn_transpose_bf16(int64_t rows, int64_t cols, const void* src, void* dst,
     return hipGetLastError() == hipSuccess ? AXONN_OK : AXONN_ERR_LAUNCH;
 }
 
-const char* axonn_transpose_kernel(int64_t rows, int64_t cols, int aligned) {
+const char* axonn_transpose_kernel_at(int64_t rows, int64_t cols, const void* src, const void* dst) {
     if (rows <= 0 || cols <= 0) return nullptr;
-    switch (axonn::tr_choose(rows, cols, aligned != 0)) {
+    switch (axonn::tr_choose(rows, cols, reinterpret_cast<uintptr_t>(src), reinterpret_cast<uintptr_t>(dst))) {
         case axonn::TrKernel::Element: return "transpose_naive";
         case axonn::TrKernel::Tile: return "transpose_tile";
         case axonn::TrKernel::TileBands: return "transpose_tile_bands";
+        case axonn::TrKernel::Window: return "transpose_window";
         default: return nullptr;
     }
+}
+
+const char* axonn_transpose_kernel(int64_t rows, int64_t cols, int aligned) {
+    const void* const at = reinterpret_cast<const void*>(static_cast<uintptr_t>(aligned ? 128 : 130));
+    return axonn_transpose_kernel_at(rows, cols, at, at);
 }
 
 static bool comm_args_ok(const int* grid, int g_node, double beta_inter, double bytes_per_element) {

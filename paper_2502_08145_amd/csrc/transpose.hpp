@@ -51,17 +51,7 @@ inline bool tr_bands(int64_t rows, int64_t cols, int64_t tiles, bool whole) {
 // against 3.0).
 constexpr int64_t tr_ragged_from(int64_t narrow) { return narrow < 256 ? 3 << 19 : 1 << 18; }
 inline int64_t tr_tiles(int64_t extent) { return (extent + TR_TILE - 1) / TR_TILE; }
-enum class TrKernel { Refused, Element, Tile, TileBands };
-// `aligned`: both pointers on 16-byte boundaries.
-inline TrKernel tr_choose(int64_t rows, int64_t cols, bool aligned) {
-    const bool whole = rows % TR_TILE == 0 && cols % TR_TILE == 0 && aligned;
-    if (!whole && (cols + 3) / 4 > 65535) return TrKernel::Refused;   // the element kernel's grid, whichever kernel runs
-    const int64_t tiles = tr_tiles(rows) * tr_tiles(cols);
-    // 256 threads a tile, and a launch holds fewer than 2^32 in one dimension: the element kernel has two
-    const bool ragged_tiles = std::min(rows, cols) >= TR_TILE && rows * cols >= tr_ragged_from(std::min(rows, cols)) && tiles < ((int64_t)1 << 24);
-    if (!whole && !ragged_tiles) return TrKernel::Element;
-    return tr_bands(rows, cols, tiles, whole) ? TrKernel::TileBands : TrKernel::Tile;
-}
+enum class TrKernel { Refused, Element, Tile, TileBands, Window };
 // Whether the tile kernels leave a matrix to transpose_window_kernel.  Where output rows start at odd addresses it is ahead from
 // some 600 tiles on (1001 x 3000, 752 tiles: 4.8 -> 4.2 us; 1001 x 2000, 512 tiles: 3.3 -> 3.7); where at even ones, from some 2500
 // on (2008 x 5000, 2528 tiles: 7.8 -> 7.5 us; 1608 x 4168, 1716 tiles: 5.4 -> 5.9).
@@ -69,6 +59,17 @@ inline TrKernel tr_choose(int64_t rows, int64_t cols, bool aligned) {
 inline bool tr_window(int64_t rows, int64_t cols, uintptr_t dst) {
     if ((rows % 64 == 0 && dst % 128 == 0) || tr_windows(rows) * tr_tiles(cols) >= ((int64_t)1 << 23)) return false;
     return tr_tiles(rows) * tr_tiles(cols) >= ((rows % 2 || dst % 4) ? 640 : 2560);
+}
+// The one decision on a matrix: what is launched and what is told of it.
+inline TrKernel tr_choose(int64_t rows, int64_t cols, uintptr_t src, uintptr_t dst) {
+    const bool whole = rows % TR_TILE == 0 && cols % TR_TILE == 0 && ((src | dst) & 15) == 0;
+    if (!whole && (cols + 3) / 4 > 65535) return TrKernel::Refused;   // the element kernel's grid, whichever kernel runs
+    const int64_t tiles = tr_tiles(rows) * tr_tiles(cols);
+    // 256 threads a tile, and a launch holds fewer than 2^32 in one dimension: the element kernel has two
+    const bool ragged_tiles = std::min(rows, cols) >= TR_TILE && rows * cols >= tr_ragged_from(std::min(rows, cols)) && tiles < ((int64_t)1 << 24);
+    if (!whole && !ragged_tiles) return TrKernel::Element;
+    if (tr_window(rows, cols, dst)) return TrKernel::Window;
+    return tr_bands(rows, cols, tiles, whole) ? TrKernel::TileBands : TrKernel::Tile;
 }
 constexpr int TR_LDS_STRIDE = 144;   // bytes per tile row in LDS (128 + 16)
 

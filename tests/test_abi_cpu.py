@@ -436,9 +436,9 @@ def test_a_block_on_the_wave_k_kernel_asks_for_no_scratch(shape):
 
 @pytest.mark.parametrize("rows,cols,aligned,kernel", [
     (64, 64, True, "transpose_tile"), (64, 64, False, "transpose_naive"), (63, 9000, True, "transpose_naive"),
-    (2049, 4100, True, "transpose_tile_bands"), (4096, 12288, True, "transpose_tile_bands"), (4096, 12224, True, "transpose_tile"),
+    (2049, 4100, True, "transpose_window"), (1160, 4100, True, "transpose_tile_bands"), (4096, 12288, True, "transpose_tile_bands"), (4096, 12224, True, "transpose_tile"),
     # 2^24 tiles and more would be 2^32 threads in one dimension, which no launch holds: the element kernel has two
-    (262139 * 64, 64 * 64, False, "transpose_tile_bands"), (2 ** 24, 64 * 64, False, "transpose_naive"),
+    (262139 * 64, 64 * 64, False, "transpose_window"), (262139 * 64, 64 * 64, True, "transpose_tile"), (2 ** 24, 64 * 64, False, "transpose_naive"),
     (2 ** 28 + 1, 256, True, "transpose_naive"), (262144 + 1, 262140, True, "transpose_naive"),
     (8, 262141, True, None), (2049, 300001, True, None), (64, 64 * 5000, True, "transpose_tile"),
 ])
@@ -448,6 +448,20 @@ def test_transpose_kernel_by_size(rows, cols, aligned, kernel):
     if got and got.startswith("transpose_tile"):
         tiles = -(-rows // 64) * -(-cols // 64)
         assert tiles * 256 < 2 ** 32
+
+
+@pytest.mark.parametrize("rows,cols,src,dst,kernel", [
+    # output rows off 128-byte lines: from 640 tiles on where they start at odd addresses, from 2560 where at even ones
+    (1001, 2540, 0, 0, "transpose_window"), (1001, 2496, 0, 0, "transpose_tile"), (2048, 5120, 0, 64, "transpose_window"), (2048, 5056, 0, 64, "transpose_tile"),
+    (2048, 5056, 0, 2, "transpose_window"), (2048, 5056, 0, 128, "transpose_tile"), (2048, 5056, 2, 128, "transpose_tile_bands"),
+    (2050, 4992, 0, 0, "transpose_window"), (2050, 4928, 0, 0, "transpose_tile_bands"), (2050, 4928, 0, 30, "transpose_window"),
+    # 512 threads a window and tile column
+    (16776895, 4096, 0, 0, "transpose_window"), (16777215, 4097, 0, 0, "transpose_naive"), (2 ** 23, 8192, 0, 128, "transpose_tile_bands"),
+])
+def test_transpose_kernel_by_address(rows, cols, src, dst, kernel):
+    assert B.transpose_kernel_at(rows, cols, src, dst) == kernel
+    if kernel == "transpose_window":
+        assert -(-(rows + 63) // 128) * -(-cols // 64) * 512 < 2 ** 32
 
 
 @pytest.mark.parametrize("shape,layout,slower", [
