@@ -315,16 +315,17 @@ int axonn_linear_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_pa
 int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_plan_part_t parts[AXONN_MAX_PLAN_PARTS]);
 /* A plan names the variants its blocks are planned with.  The block of a tile variant may run on another kernel that
  * needs no scratch area: the one that splits K over a workgroup's waves (a few dozen tiles of 128 x 128 and fewer), or,
- * where the variant is one without split-K, another tile without it.  A FORCED variant is always that very kernel (the last one: the guarded kernel with
+ * where the variant is one without split-K, another tile without it (down to 64 x 64).  A FORCED variant is always that very kernel (the last one: the guarded kernel with
  * 128 x 128 tiles).
  * axonn_linear_part_kernel tells what runs: it writes the name of the kernel behind launch `part` (0, 1, ...) to
  * `name` (HOST memory, `name_bytes` bytes, 64 are enough, zero-terminated) and returns the number of launches, or a
  * negative error code.  now = 0: of axonn_linear_plan; now = 1: of a call made now on the current device, a forced
- * variant included.  Names: a tile variant's, with "_ktail" behind it for a K that is no multiple of 64 (the
- * tiles of NT without split-K are "mfma16k64_128x128", "..._256x128" and "..._128x256" whatever the variant), or
- * "mfma16_64x128", "mfma16_128x64" and, with two groups of waves that halve K between them, "mfma16_128x128_g2" and
- * "wavek_64x64_g2"; "wavek_<rows>x<columns>_w<waves>" where the waves of a workgroup split K; "edge_128x128" for the guarded kernel; "naive".  Host logic, now = 1 plus one
- * hipGetDevice. */
+ * variant included.  Names: a tile variant's, with "_ktail" behind it for a K that is no multiple of 64;
+ * "mfma16k64g_<rows>x<columns>" for the eight-wave kernel, whatever variant stands for its tile ("_g2": with two groups of waves
+ * that halve K between them; "_ktail" as above); "mfma16k64_128x128_sk<ranges>" for NT on that tile with split-K;
+ * "wavek_<rows>x<columns>_w<waves>" where the waves of a workgroup split K; "wavek_64x64_k32" and "..._k64" for TN over a K of up to 32
+ * and 64 ("_xcd": with neighbouring workgroups on one XCD); "edge_128x128" for the guarded kernel; "naive".  Host logic, now = 1
+ * plus one hipGetDevice. */
 int axonn_linear_part_kernel(int64_t M, int64_t N, int64_t K, int layout, int now, int part, char *name, size_t name_bytes);
 /* Override the choice for all later calls in this process; -1 restores automatic selection.
  * Returns AXONN_OK or AXONN_ERR_INVALID_ARG.  For tests, tuning and the benchmark. */

@@ -646,9 +646,8 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, int layout, bool allow_sp
 }
 
 // Which kernels do the blocks of the guarded variant, and which of a tile variant's blocks are small enough for
-// the wave-K kernel: outputs of a few dozen 128 x 128 tiles (512 x 1024 x 2048 NT: 32 tiles, 15.6 us against 9.6; 640 x 640 x
-// 2048 TN 17 -> 10).  1 500 sampled products of 0.1 to 40 GFLOP that the rule gives it run 1.89 times as fast as the tile variant
-// of their plan (geometric mean, operands in cache), the slowest 0.98 times.
+// the wave-K kernel: outputs of a few dozen 128 x 128 tiles and fewer, over a K that is long for them (128 x 128 x 8192 NT planned in
+// four K ranges 19.4 us, 7.4 on it; 256 x 256 x 8192 21.0 and 8.1).
 // A block planned without split-K also goes to whatever other tile kernel without it is modelled faster: the plans are made
 // with efficiencies from before the eight-wave kernel, which do not know its smaller tiles.  One planned with split-K
 // leaves it for the wave-K kernel only.
@@ -847,15 +846,14 @@ static int part_kernel_name(const Part& p, int64_t N, int64_t K, int layout, cha
     }
     const char* const tail = planned.bm && K % 64 ? "_ktail" : "";
     if (p.how.group.tile >= 0) {
-        // two groups of waves on a 64 x 64 tile are K split over waves, like the wave-K kernel's tiles
         int rows = 0, cols = 0, groups = 0;
         group_tile(p.how.group, &rows, &cols, &groups);
-        return std::snprintf(name, bytes, "%s_%dx%d%s%s", rows * cols == 64 * 64 ? "wavek" : "mfma16", rows, cols, groups == 2 ? "_g2" : "", tail);
+        return std::snprintf(name, bytes, "mfma16k64g_%dx%d%s%s", rows, cols, groups == 2 ? "_g2" : "", tail);
     }
     if (planned.edge && p.how.tile < 0) return std::snprintf(name, bytes, "edge_%dx%d", planned.bm, planned.bn);
     const Variant& var = p.how.tile >= 0 ? variants()[p.how.tile] : planned;
-    // two K-contiguous operands (NT): one kernel behind the variants of a tile, under the 64-k one's name
-    if (layout == AXONN_NT && var.group) return std::snprintf(name, bytes, "mfma16k64_%dx%d%s", var.bm, var.bn, tail);
+    if (var.group) return std::snprintf(name, bytes, "mfma16k64g_%dx%d%s", var.bm, var.bn, tail);   // one kernel behind the variants of a tile
+    // 128 x 128 tiles of two K-contiguous operands (NT) with split-K: the 64-k kernel
     const bool k64_under_ring_name = layout == AXONN_NT && !var.k64 && var.bm == 128 && var.bn == 128;
     return std::snprintf(name, bytes, "%s%s%s", k64_under_ring_name ? "mfma16k64_" : "",
                          var.name + (k64_under_ring_name ? std::strlen("mfma16_") : 0), tail);

@@ -41,13 +41,7 @@ def short(name: str) -> str:
     m = re.search(rf"gemm_tile_kernel_k64g<(\d+), (\d+), (\d+), {_BOOL}, {_BOOL}, {_BOOL}>", name)
     if m:
         bm, bn, groups, akc, bkc, tail = m.groups()
-        lay = _LAYOUT.get((akc, bkc), "??")
-        if (bm, bn) == ("64", "64"):
-            family = "wavek_"
-        else:
-            family = "mfma16k64_" if lay == "NT" and "64" not in (bm, bn) else "mfma16_"
-        waves = "_w8" if (bm, bn) == ("128", "256") and lay != "NT" else ""   # beside the ring's four-wave kernel
-        return f"{family}{bm}x{bn}{waves}{'_g2' if groups == '2' else ''}{'_ktail' if tail == 'true' else ''}/{lay}"
+        return f"mfma16k64g_{bm}x{bn}{'_g2' if groups == '2' else ''}{'_ktail' if tail == 'true' else ''}/{_LAYOUT.get((akc, bkc), '??')}"
     m = re.search(rf"gemm_tile_kernel_k64p<{_BOOL}, {_BOOL}>", name)
     if m:
         return f"mfma16k64p_256x256_w8/{_LAYOUT.get(m.groups(), '??')}"

@@ -343,12 +343,12 @@ def test_planner_choices_that_the_design_notes_describe():
 
 # ------------------------------------------------------------------ what a call really runs
 @pytest.mark.parametrize("shape,layout,planned,runs", [
-    ((640, 640, 2048), "TN", "mfma16_128x128", "wavek_"),                              # few tiles: K split over the waves
-    ((128, 128, 8192), "NT", "mfma16_128x128_sk", "wavek_"),
-    ((1064, 4168, 1608), "NT", "mfma16_edge_128x128", "mfma16k64_128x256_ktail"),      # overlapping tiles, a K tail
-    ((1064, 4168, 1664), "NN", "mfma16_edge_128x128", "mfma16_128x256_w8"),            # overlapping tiles
+    ((640, 640, 2048), "TN", "mfma16_128x128", "mfma16k64g_64x64_g2"),                 # few tiles: 64 x 64 ones, K halved between groups of waves
+    ((128, 128, 8192), "NT", "mfma16_128x128_sk", "wavek_"),                            # fewer: K split over the waves
+    ((1064, 4168, 1608), "NT", "mfma16_edge_128x128", "mfma16k64g_128x256_ktail"),     # overlapping tiles, a K tail
+    ((1064, 4168, 1664), "NN", "mfma16_edge_128x128", "mfma16k64g_128x256"),           # overlapping tiles
     ((4099, 4099, 4099), "TN", "mfma16_edge_128x128", "edge_128x128"),
-    ((1024, 3072, 3072), "NT", "mfma16_128x128", "mfma16k64_128x128"),                  # the 64-k kernel under the ring's name
+    ((1024, 3072, 3072), "NT", "mfma16_128x128", "mfma16k64g_128x128"),               # the eight-wave kernel under the ring's name
     ((128, 128, 0), "NN", "naive", "naive"),
 ])
 def test_kernel_names_are_those_of_the_kernels_that_run(shape, layout, planned, runs):
@@ -356,6 +356,13 @@ def test_kernel_names_are_those_of_the_kernels_that_run(shape, layout, planned, 
     got = B.kernel_name(*shape, layout, now=True)
     assert got.startswith(runs) and ("_ktail" in got) == ("_ktail" in runs), got
     assert len(B.kernels(*shape, layout)) == len(B.plan(*shape, layout))
+
+
+def test_split_k_of_small_tiles_is_named_by_its_kernel():
+    """128 x 128 tiles with split-K are the 64-k kernel's for NT and the ring's for NN and TN, under one variant."""
+    for layout, kernel in (("NT", "mfma16k64_128x128_sk"), ("NN", "mfma16_128x128_sk"), ("TN", "mfma16_128x128_sk")):
+        assert B.plan_name(1024, 1024, 4096, layout).startswith("mfma16_128x128_sk")
+        assert B.kernel_name(1024, 1024, 4096, layout).startswith(kernel)
 
 
 def test_kernel_name_query_refuses_bad_arguments():
@@ -481,9 +488,9 @@ def test_a_second_round_of_wave_k_tiles_counts_whole(shape, layout, slower):
     ((4160, 11928, 72), "TN", "mfma16k64_256x256"), ((15960, 3088, 72), "TN", "mfma16k64_256x256"),
     ((9680, 3704, 112), "NT", "mfma16k64_256x256"), ((9808, 4176, 128), "NT", "mfma16k64_256x256"),
     ((2376, 9288, 128), "NN", "mfma16k64_256x256"), ((5904, 8080, 128), "TN", "mfma16k64_256x256"),
-    ((6512, 7576, 128), "NT", "mfma16k64_256x128+"), ((6928, 11312, 128), "TN", "mfma16k64p_256x256"),
+    ((6512, 7576, 128), "NT", "mfma16k64g_256x128+"), ((6928, 11312, 128), "TN", "mfma16k64p_256x256"),
     ((15192, 7912, 256), "TN", "mfma16k64p_256x256"), ((14944, 3544, 192), "NT", "mfma16k64_256x256"),
-    ((14272, 5576, 192), "NT", "mfma16k64_256x128+"), ((1256, 15760, 384), "NN", "mfma16_128x128+"),
+    ((14272, 5576, 192), "NT", "mfma16k64g_256x128+"), ((1256, 15760, 384), "NN", "mfma16k64g_128x128+"),
 ])
 def test_short_k_large_ragged_outputs_avoid_what_measured_slower(shape, layout, slower):
     assert not B.kernel_name(*shape, layout).startswith(slower)

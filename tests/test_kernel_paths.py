@@ -118,9 +118,9 @@ def small_tile_products(kernel, layout):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout", LAYOUTS)
-@pytest.mark.parametrize("kernel", ["wavek_64x64_g2", "mfma16_64x128", "mfma16_128x64", "mfma16_128x128_g2"])
+@pytest.mark.parametrize("kernel", ["mfma16k64g_64x64_g2", "mfma16k64g_64x128", "mfma16k64g_128x64", "mfma16k64g_128x128_g2"])
 def test_small_tiles_of_the_eight_wave_kernel(oracle_mod, layout, kernel):
-    if kernel == "mfma16_128x128_g2" and layout == "NT":
+    if kernel == "mfma16k64g_128x128_g2" and layout == "NT":
         pytest.skip("not built: one group is as fast there")
     B.register_workspace()
     shapes = small_tile_products(kernel, layout)
@@ -180,7 +180,7 @@ def test_strips_narrower_than_sixteen(oracle_mod, layout, shape):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("layout,shape,kernel", [("NN", (1024, 3072, 3072), "mfma16_128x128"), ("NT", (1024, 3072, 3072), "mfma16k64_128x128"),
+@pytest.mark.parametrize("layout,shape,kernel", [("NN", (1024, 3072, 3072), "mfma16k64g_128x128"), ("NT", (1024, 3072, 3072), "mfma16k64g_128x128"),
                                                  ("NN", (4099, 4099, 4099), "edge"), ("NN", (1000, 520, 1031), "wavek")])
 def test_same_inputs_same_bits_on_the_kernel_named(layout, shape, kernel):
     B.register_workspace()
