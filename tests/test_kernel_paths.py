@@ -130,6 +130,48 @@ def test_small_tiles_of_the_eight_wave_kernel(oracle_mod, layout, kernel):
         _check(oracle_mod, *shape, layout, [kernel])
 
 
+@lru_cache(maxsize=None)
+def eight_wave_products():
+    """{(kernel, layout): {64-k steps: the smallest sampled product of one launch on it}}, K a multiple of 64 or, for the "_ktail" forms,
+    not (any K for TN, multiples of 8 where an operand is K-contiguous)."""
+    rng = random.Random(16)
+    found = {}
+    for _ in range(60000):
+        layout, steps, step = rng.choice(LAYOUTS), rng.choice([2, 3, 4, 5, 6, 7, 8, 9, 24, 25, 33, 48, 65]), rng.choice([8, 8, 64])
+        M, N, K = _log_int(rng, 64, 6000, step), _log_int(rng, 64, 6000, step), 64 * steps
+        if rng.random() < 0.6:
+            K -= rng.randrange(1, 64) if layout == "TN" and rng.random() < 0.5 else 8 * rng.randrange(1, 8)
+        if M * N * K > 2e10:
+            continue
+        names = B.kernels(M, N, K, layout)
+        if len(names) == 1 and names[0].startswith("mfma16k64g"):
+            best = found.setdefault((names[0], layout), {})
+            if steps not in best or M * N < best[steps][0] * best[steps][1]:
+                best[steps] = (M, N, K)
+    return found
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("tail", ["", "_ktail"])
+@pytest.mark.parametrize("tile", ["64x64_g2", "64x128", "128x64", "128x128", "256x128", "128x256"])
+def test_every_length_of_k_on_the_eight_wave_kernel(oracle_mod, tile, tail, layout):
+    """The ring has three to five stages: a K that is shorter, exactly as long, and up to three steps longer (refills, window and
+    waits, either parity), and some dozens of steps, with a shorter last 64 k, which is staged first, and without."""
+    kernel = f"mfma16k64g_{tile}{tail}"
+    products = eight_wave_products()[(kernel, layout)]
+    assert len(set(products) & {2, 3, 4, 5, 6, 7, 8, 9}) >= 7 and max(products) >= 24, products
+    B.register_workspace()
+    for steps, shape in sorted(products.items()):
+        print(f"  {kernel} {layout} {shape}", flush=True)
+        _check(oracle_mod, *shape, layout, [kernel])
+
+
+@pytest.mark.gpu
+def test_a_ragged_layer_s_data_gradient(oracle_mod):
+    _check(oracle_mod, 1064, 1608, 4168, "NT", ["mfma16k64g_64x128_ktail"])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shape", [(2048, 8192, 24), (1024, 4096, 32), (1025, 4099, 31), (600, 16384, 7), (3000, 5000, 1), (16384, 1024, 33),
                                    (2001, 8191, 63), (2000, 8200, 40), (65, 40001, 9), (4099, 2303, 63), (9000, 900, 8), (2048, 8192, 64),
