@@ -93,7 +93,7 @@ static std::vector<Variant> make_variants() {
         for (int l = 0; l < 3; ++l)
             x.fn[l] = (bm == 256 && bn == 256)              ? ring_kernel_large(splits > 1, l)
                       : (bm == 128 && bn == 128 && l == AXONN_NT) ? k64_kernel_half(bm, bn, l)
-                                                              : ring_kernel_small(bm, bn, splits > 1, l);
+                                                              : ring_kernel_small(bm, bn, l);
         v.push_back(x);
     };
     auto group = [&](const char* name, int bm, int bn, int min_k, bool k64, double nn, double nt, double tn) {
@@ -118,7 +118,7 @@ static std::vector<Variant> make_variants() {
                                           "mfma16_256x256_w8_sk6", "mfma16_256x256_w8_sk7", "mfma16_256x256_w8_sk8"};
     for (int sp = 2; sp <= 8; ++sp) ring(ring_sk[sp - 2], 256, 256, 4, sp, L::LDS_BYTES, L::MIN_K, 1.13, 1.06, 1.12);
     group("mfma16_256x128", 256, 128, TileCfg16<256, 128, 2, 2>::MIN_K, false, 0.86, 0.78, 0.91);
-    ring("mfma16_128x256", 128, 256, 2, 1, TileCfg16<128, 256, 2, 2>::LDS_BYTES, TileCfg16<128, 256, 2, 2>::MIN_K, 0.95, 0.74, 0.92);
+    group("mfma16_128x256", 128, 256, TileCfg16<128, 256, 2, 2>::MIN_K, false, 0.95, 0.74, 0.92);
     group("mfma16_128x256_w8", 128, 256, TileCfg16<128, 256, 2, 4>::MIN_K, false, 0.93, 0.72, 0.97);
     using S = TileCfg16<128, 128, 2, 2>;
     group("mfma16_128x128", 128, 128, S::MIN_K, false, 0.85, 0.72, 0.90);

@@ -225,13 +225,6 @@ struct OperandKContig {   // global P[row * ld + k]
         else
             direct_load16(lds_dst[C] + stage_off, base[C], voff[0]);
     }
-    // The same load for K-step STEP (0 or 1) of a shorter last 64 k taken first: `delta` bytes beyond the window's
-    // address, zero for the pieces behind the `left` (1 .. 63) k that exist (whole pieces: rows are 16-byte aligned).
-    template <int C, int AHEAD, int STEP>
-    __device__ __forceinline__ void issue_tail(uint32_t stage_off, size_t delta, int left, int lane, int /*wave*/) const {
-        const int k = 32 * STEP + 8 * ((lane & 3) ^ ((lane >> (2 + SWZ)) & 3));
-        direct_load16_from(lds_dst[C] + stage_off + (PAIR ? lds_par : 0u), piece_or_zero(base[C] + voff[PAIR ? AHEAD : 0] + delta, k < left));
-    }
     // next K-step: window one step on and, PAIR, the other row groups
     __device__ __forceinline__ void advance() {
         if constexpr (PAIR) {
@@ -328,11 +321,6 @@ struct OperandMNContig {   // global P[k * ld + row]
     __device__ __forceinline__ void issue(uint32_t stage_off) const {
         static_assert(AHEAD == 0, "loaded one K-step at a time");
         direct_load16(lds_dst[C] + stage_off, base, voff[C]);
-    }
-    template <int C, int AHEAD, int STEP>
-    __device__ __forceinline__ void issue_tail(uint32_t stage_off, size_t delta, int left, int lane, int wave) const {
-        const int k = 32 * STEP + KR * (QL * wave + C) + lane / CPR;
-        direct_load16_from(lds_dst[C] + stage_off, piece_or_zero(base + voff[C] + delta, k < left));
     }
     // One K-step on.  The window moves in the (64-bit, scalar) base pointers, not in the 32-bit
     // per-lane offsets: a panel of more than 4 GB (K * ld * 2 bytes) would wrap those.

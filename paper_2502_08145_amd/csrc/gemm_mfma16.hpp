@@ -226,7 +226,7 @@ __device__ __forceinline__ void store_block_row16(f32x4 (&row)[NI], uint8_t* epi
 }
 
 // Requires M >= BM, N >= BN, K % 64 == 0, K >= TileCfg16::MIN_K (per K range when split), and 16-byte aligned rows.
-template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, bool SPLITK, bool KTAIL = false>
+template <int BM, int BN, int WM, int WN, bool A_KC, bool B_KC, bool SPLITK>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
     int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
@@ -258,9 +258,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     const uint32_t lds0 = lds_address(smem);
     OpA opa;
     OpB opb;
-    static_assert(!(SPLITK && KTAIL), "a shorter last 64 k belongs to no range");
-    // KTAIL: K-steps 0 and 1 are the shorter last 64 k, K-step s the k from 32 (s - 2) on: the window starts 64 k early
-    const int64_t k0 = KTAIL ? -64 : (int64_t)krange * ktotal;
+    const int64_t k0 = (int64_t)krange * ktotal;
     // the load schedule starts NS K-steps before K-step 0
     constexpr bool FIRST_ODD = NS % 2 == 1;
     opa.init(A + (A_KC ? k0 : k0 * lda), m0, 2u * (uint32_t)lda, lane, wave, lds0, wm * TM, FIRST_ODD);
@@ -337,15 +335,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
     auto next_stage = [&](uint32_t off) __attribute__((always_inline)) -> uint32_t { return off + SB == RING ? 0u : off + SB; };
 
     // ---- prologue: the loads "steps -NS .. -1" would have issued: K-steps 0 .. NS-1 ---------------
-    auto first_load = [&](auto& op, auto x_c, auto ahead_c, auto step_c, bool is_a, uint32_t stage) __attribute__((always_inline)) {
-        constexpr int X = decltype(x_c)::value, AHEAD = decltype(ahead_c)::value, STEP = decltype(step_c)::value;
+    auto first_load = [&](auto& op, auto x_c, auto ahead_c, uint32_t stage) __attribute__((always_inline)) {
         using Op = typename std::remove_reference<decltype(op)>::type;
-        if constexpr (KTAIL && STEP < 2) {
-            const size_t elements = is_a ? (A_KC ? (size_t)ktotal : (size_t)ktotal * lda) : (B_KC ? (size_t)ktotal : (size_t)ktotal * ldb);
-            op.template issue_tail<X, Op::PAIR ? AHEAD : 0, STEP>(stage, 2 * elements, grid.k_tail, lane, wave);
-        } else {
-            op.template issue<X, Op::PAIR ? AHEAD : 0>(stage);
-        }
+        // Nothing, but that the closure holds both by reference, which changes the order of the registers: without it the 256 x 256
+        // tile of TN with split-K is 1-2 % slower (16 products).
+        if constexpr (decltype(x_c)::value < 0) (void)(lane + wave);
+        op.template issue<decltype(x_c)::value, Op::PAIR ? decltype(ahead_c)::value : 0>(stage);
     };
     static_for<NS>([&](auto v) __attribute__((always_inline)) {
         constexpr int T = decltype(v)::value - NS;                // virtual step
@@ -356,13 +351,13 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel16(
             auto& op = [&]() __attribute__((always_inline)) -> auto& { if constexpr (IS_A) return opa; else return opb; }();
             if constexpr (Op::PAIR && T == -NS) {
                 // K-step -1 does not exist: only the K-step 0 half of the pair, window stays
-                static_for<Op::NBASE>([&](auto d) __attribute__((always_inline)) { first_load(op, d, Int<0>{}, Int<0>{}, IS_A, FAR); });
+                static_for<Op::NBASE>([&](auto d) __attribute__((always_inline)) { first_load(op, d, Int<0>{}, FAR); });
                 op.flip();
             } else {
                 constexpr uint32_t NEAR = Op::PAIR ? FAR - SB : 0u;
                 static_for<Op::NBASE>([&](auto d) __attribute__((always_inline)) {
-                    if constexpr (Op::PAIR) first_load(op, d, Int<0>{}, Int<T + NS - 1>{}, IS_A, NEAR);
-                    first_load(op, d, Int<1>{}, Int<T + NS>{}, IS_A, FAR);
+                    if constexpr (Op::PAIR) first_load(op, d, Int<0>{}, NEAR);
+                    first_load(op, d, Int<1>{}, FAR);
                 });
                 op.advance();
             }

@@ -13,9 +13,9 @@ namespace axonn {
 typedef void (*tile_kernel_t)(const uint16_t*, const uint16_t*, uint16_t*, int, int, int, int, TileGrid, int, SplitK);
 
 // layout: 0 NN, 1 NT, 2 TN.  k_tail: the form for a K that is no multiple of 64 (TileGrid).  nullptr: no such kernel.
-// 32-k LDS ring (gemm_tile_kernel16): tile bm x bn, 2 x wn waves, with or without split-K
-tile_kernel_t ring_kernel_large(bool split, int layout);                          // 256 x 256, 2 x 4 waves
-tile_kernel_t ring_kernel_small(int bm, int bn, bool split, int layout);          // 2 x 2 waves: 256x128, 128x256, 128x128 (not NT) with split-K; 128x256 without
+// 32-k LDS ring (gemm_tile_kernel16): tile bm x bn
+tile_kernel_t ring_kernel_large(bool split, int layout);                          // 2 x 4 waves, with or without split-K: 256x256
+tile_kernel_t ring_kernel_small(int bm, int bn, int layout);                       // 2 x 2 waves, split-K: 256x128, 128x256, 128x128 (not NT)
 // 64-k stages (gemm_tile_kernel_k64): 256 x 256, 2 x 4 waves
 tile_kernel_t k64_kernel(bool split, int layout, bool k_tail = false);
 // the same on 256 x 128, 128 x 256 and 128 x 128 tiles, 2 x 2 waves, three LDS buffers per operand (NT with split-K only)

@@ -37,7 +37,8 @@ static const GroupTile kTiles[] = {
     AXONN_GROUP_TILE(128, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.16, 1.82, 0.812, 1.04, {0.338, 0.308, 0.408}, {0.276, 0.381, 0.112}, {0.509, 0.583, 0.290}, {0.36, 0.44, 0.11, 0.21}),
     AXONN_GROUP_TILE(128, 128, 2, AXONN_GROUP2, AXONN_NO_KERNELS, 2.51, 2.69, 0.806, 0.96, {0.311, 0.0, 0.341}, {0.299, 0.0, 0.159}, {0.665, 0.0, 0.579}, {0.42, 0.44, 0.22, 0.26}),
     AXONN_GROUP_TILE(256, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 1.93, 3.34, 0.693, 3.57, {0.609, 0.598, 0.728}, {0.130, 0.155, 0.0}, {0.472, 0.557, 0.260}, {0.32, 0.30, 0.03, 0.23}),
-    // (NN and NT step: 0.635 and 0.581 fitted.  Near a tie of the half tiles this one is taken, 2 % ahead with operands from memory.)
+    // (NN and NT step: 0.635 and 0.581 fitted.  Near a tie of the half tiles this one is taken.  NT: 1.4 % ahead with operands from memory, 0.4 %
+    // in cache, nine products.  NN: 2.2 % ahead from memory, 1.5-4.5 % behind in cache, the 70 sampled products that the figure decides.)
     AXONN_GROUP_TILE(128, 256, 1, AXONN_GROUP3, AXONN_GROUP3, 1.86, 3.41, 0.692, 2.91, {0.612, 0.562, 0.716}, {0.071, 0.155, 0.0}, {0.760, 0.848, 0.358}, {0.13, 0.43, 0.06, 0.10}),
 };
 #undef AXONN_GROUP_TILE

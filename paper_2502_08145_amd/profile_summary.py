@@ -28,11 +28,11 @@ _BOOL = "(true|false)"
 def short(name: str) -> str:
     """The name of a kernel symbol: the library's (axonn_linear_part_kernel) without what is a run-time argument (the
     number of K ranges, the waves per wave-K tile), and the mode; kernel_key() gives the same from the library's side."""
-    m = re.search(rf"gemm_tile_kernel16<(\d+), (\d+), (\d+), (\d+), {_BOOL}, {_BOOL}, {_BOOL}, {_BOOL}>", name)
+    m = re.search(rf"gemm_tile_kernel16<(\d+), (\d+), (\d+), (\d+), {_BOOL}, {_BOOL}, {_BOOL}>", name)
     if m:
-        bm, bn, wm, wn, akc, bkc, split, tail = m.groups()
+        bm, bn, wm, wn, akc, bkc, split = m.groups()
         waves = "_w8" if int(wm) * int(wn) == 8 else ""
-        return f"mfma16_{bm}x{bn}{waves}{'_sk' if split == 'true' else ''}{'_ktail' if tail == 'true' else ''}/{_LAYOUT.get((akc, bkc), '??')}"
+        return f"mfma16_{bm}x{bn}{waves}{'_sk' if split == 'true' else ''}/{_LAYOUT.get((akc, bkc), '??')}"
     m = re.search(rf"gemm_tile_kernel_k64<(\d+), (\d+), (\d+), {_BOOL}, {_BOOL}, {_BOOL}, \d+, {_BOOL}>", name)
     if m:
         bm, bn, wn, akc, bkc, split, tail = m.groups()
