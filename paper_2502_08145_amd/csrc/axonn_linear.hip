@@ -77,7 +77,8 @@ struct Variant {
     tile_kernel_t fn_tail[3] = {nullptr, nullptr, nullptr};   // for a K that is no multiple of 64
     bool edge = false;               // the guarded MFMA kernel: any shape, launched through edge_kernel_launch
     int resident = 0;                // > 0: a grid of at most this many workgroups walks the tiles (one per compute unit)
-    bool group = false;              // the eight-wave kernel (gemm_tile_kernel_k64g), which has a time model of its own
+    bool group = false;              // the eight-wave kernel (gemm_tile_kernel_k64g)
+    bool group_model = false;        // ... and its time model (block_us)
 };
 
 // Kernel families: the 64-k-stage kernel (256 x 256, eight waves: the default wherever the output has
@@ -98,7 +99,7 @@ static std::vector<Variant> make_variants() {
     };
     auto group = [&](const char* name, int bm, int bn, int min_k, bool k64, double nn, double nt, double tn) {
         Variant x{name, bm, bn, 512, group_lds_bytes(bm, bn, 1), min_k, TileCfgK64::KS, 1, k64, {nn, nt, tn}, {nullptr, nullptr, nullptr}};
-        x.group = true;
+        x.group = x.group_model = true;
         for (int l = 0; l < 3; ++l)
             if (!k64 || l == AXONN_NT) {
                 x.fn[l] = group_kernel(bm, bn, 1, l, false);
@@ -118,7 +119,13 @@ static std::vector<Variant> make_variants() {
                                           "mfma16_256x256_w8_sk6", "mfma16_256x256_w8_sk7", "mfma16_256x256_w8_sk8"};
     for (int sp = 2; sp <= 8; ++sp) ring(ring_sk[sp - 2], 256, 256, 4, sp, L::LDS_BYTES, L::MIN_K, 1.13, 1.06, 1.12);
     group("mfma16_256x128", 256, 128, TileCfg16<256, 128, 2, 2>::MIN_K, false, 0.86, 0.78, 0.91);
+    // The variant that plans of 128 large tiles carry, in NN above all.  Its blocks, and plans with strips that have one, are priced with
+    // the ring's figures (us64): near a tie they then go to another tile or to one launch (settle_parts, make_plan).  Priced as the
+    // eight-wave kernel, 85 sampled ragged products that changed to strips took 1.05 times as long (1.25 the worst), 8064 x 2944 x 12800 NN
+    // 495 us for 428.
     group("mfma16_128x256", 128, 256, TileCfg16<128, 256, 2, 2>::MIN_K, false, 0.95, 0.74, 0.92);
+    v.back().group_model = false;
+    std::fill(v.back().fn_tail, v.back().fn_tail + 3, nullptr);
     group("mfma16_128x256_w8", 128, 256, TileCfg16<128, 256, 2, 4>::MIN_K, false, 0.93, 0.72, 0.97);
     using S = TileCfg16<128, 128, 2, 2>;
     group("mfma16_128x128", 128, 128, S::MIN_K, false, 0.85, 0.72, 0.90);
@@ -390,7 +397,7 @@ static double shared_lines_us(const Variant& x, int64_t m, int64_t n, int64_t ld
 // some of its bandwidth per tile.  Fitted over 36 000 sampled products, residual 3-8 %.
 static double block_us(int v, int64_t m, int64_t n, int64_t K, int layout, int64_t lda, int64_t ldb, int64_t ldc, Figures figures = Figures::Current) {
     const Variant& x = variants()[v];
-    const bool group = x.group && figures == Figures::Current;
+    const bool group = x.group_model && figures == Figures::Current;
     const int64_t k_padded = (K + 63) / 64 * 64;   // every tile kernel takes K 64 at a time
     if ((x.us64[layout] <= 0.0 && !group) || !x.fn[layout] || m < x.bm || n < x.bn || K <= 64) return -1.0;
     if (k_padded / x.splits < x.min_k && !group) return -1.0;   // the eight-wave kernel takes any K
