@@ -439,6 +439,16 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
         }
     }
     if (figures == Figures::Area) return found;
+    // The half tiles' model was fitted up to 80 GFLOP.  From 300 on they take 4 to 11 % more of it, beside the 256 x 256 tile's, than there (34
+    // products on both; 5768 x 9696 x 12544 NT 1240 us on 128 x 256 tiles, 1091 on 256 x 256).  Near a tie over a long K it is the 256 x 256 tile
+    // then: 77 ragged products that this moves run 1.12 times as fast, 82 of K below 6000 would run 1.00 times, 0.98 in NT.  The time
+    // stays the half tile's: it is what strips are compared with.
+    if (found && variants()[best.tile].group && K >= 6000 && 2.0 * (double)m * (double)n * (double)K > 300e9)
+        for (int v = 1; v < edge_variant(); ++v)
+            if (variants()[v].k64 && variants()[v].splits == 1 && variants()[v].bm * variants()[v].bn == 256 * 256) {
+                const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
+                if (us >= 0.0 && us < 1.06 * best.us) best.tile = v;
+            }
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
     // wavek_stays: near a tie.  Either model is good to 6 %, and where operands come from memory (12 MB and more) its
     // waves, eight chunks of a row in flight between them, suffer less (698 x 968 x 7144 NT: 35 us in cache, 40 from memory; 64 x 64
