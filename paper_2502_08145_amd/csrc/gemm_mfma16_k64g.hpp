@@ -8,7 +8,8 @@
 // little else may stand in a row with it:
 //
 //  * Two waves per SIMD, which cover each other's LDS reads, loads and waits, share one stage and one barrier per 64 k.
-//    (The 128 x 128 tile on four waves, one per SIMD, took 0.48-0.53 us per 64 k; here 0.40-0.47.)
+//    (The 128 x 128 tile on four waves, one per SIMD, took 0.53-0.56 us per 64 k, slope over K and operands in cache; here 0.31-0.41,
+//    and 0.45-0.47 with launch, fill and stores at K = 8192.)
 //  * At the barrier every wave has its last fragments of a stage in registers and the loads of the next stage have landed;
 //    after it the next stage is read and the released one refilled, NS - 1 iterations ahead of its use.  NS: three stages
 //    of the larger tiles are enough (a fourth and fifth gained nothing and lengthen the prologue); 64 x 128 has four (1024 x
