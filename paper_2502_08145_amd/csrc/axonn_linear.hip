@@ -443,11 +443,16 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
     // products on both; 5768 x 9696 x 12544 NT 1240 us on 128 x 256 tiles, 1091 on 256 x 256).  Near a tie over a long K it is the 256 x 256 tile
     // then: 77 ragged products that this moves run 1.12 times as fast, 82 of K below 6000 would run 1.00 times, 0.98 in NT.  The time
     // stays the half tile's: it is what strips are compared with.
-    if (found && variants()[best.tile].group && K >= 6000 && 2.0 * (double)m * (double)n * (double)K > 300e9)
+    // Likewise over two steps of K under whole lines of 32 MB of output and more: the models put the smaller tiles up to 1.14 times ahead there,
+    // and 36 sampled products ran 0.99 times as fast on them with operands in cache, 0.90 from memory (0.73 the worst, 7808 x 3200 x 128 NN 17.6 us
+    // and 24.0); over K of 192 to 512 35 ran 1.10 and 1.03 times.
+    const bool long_k = K >= 6000 && 2.0 * (double)m * (double)n * (double)K > 300e9;
+    const bool two_steps = K <= 2 * 64 && ldc % 64 == 0 && m * n >= (int64_t)16 << 20;
+    if (found && variants()[best.tile].group && (long_k || two_steps))
         for (int v = 1; v < edge_variant(); ++v)
             if (variants()[v].k64 && variants()[v].splits == 1 && variants()[v].bm * variants()[v].bn == 256 * 256) {
                 const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
-                if (us >= 0.0 && us < 1.06 * best.us) best.tile = v;
+                if (us >= 0.0 && us < (two_steps ? 1.15 : 1.06) * best.us) best.tile = v;
             }
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
     // wavek_stays: near a tie.  Either model is good to 6 %, and where operands come from memory (12 MB and more) its

@@ -510,3 +510,10 @@ def test_ragged_products_near_a_tie_with_the_guarded_kernel(shape, layout):
 def test_large_ragged_products_over_a_long_k_take_the_large_tile(shape, layout):
     """In one launch either way: 0.86 to 0.93 times as fast on 128 x 256 tiles, a few per cent shorter by their model."""
     assert B.kernels(*shape, layout) == ["mfma16k64_256x256_w8"]
+
+
+@pytest.mark.parametrize("shape,layout", [((3456, 11648, 128), "NN"), ((8320, 14208, 128), "NT"), ((9856, 10880, 128), "NT"), ((12672, 14848, 128), "NN"),
+                                          ((5632, 10112, 128), "NN"), ((4224, 8960, 128), "TN"), ((13184, 5248, 128), "TN")])
+def test_large_whole_outputs_over_two_steps_of_k_stay_on_the_large_tile(shape, layout):
+    """0.82 to 0.91 times as fast on half tiles, operands in cache and from memory together."""
+    assert "256x256_w8" in B.kernels(*shape, layout)[0]
