@@ -457,9 +457,11 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
     // wavek_stays: near a tie.  Either model is good to 6 %, and where operands come from memory (12 MB and more) its
     // waves, eight chunks of a row in flight between them, suffer less (698 x 968 x 7144 NT: 35 us in cache, 40 from memory; 64 x 64
-    // tiles 34 and 51).
+    // tiles 34 and 51).  In NN by lines (GroupKLines) from smaller operands too (within 12 %: 0.92 to 1.12 times as fast in cache, 0.78 to 0.92 from memory;
+    // 506 x 816 x 3112 12.4 us and 13.5, from memory 15.4 and 19.7).
     const GroupChoice g = group_choose(layout, m, n, K, lda, ldb, ldc);
-    const double near = best.wavek.tile < 0 || !wavek_stays ? 1.0 : m * K + K * n > (int64_t)6000000 ? 0.88 : 0.96;
+    const bool far = m * K + K * n > (int64_t)6000000 || (layout == AXONN_NN && K % 64 != 0 && K > 2 * kGroupLinesK);
+    const double near = best.wavek.tile < 0 || !wavek_stays ? 1.0 : far ? 0.88 : 0.96;
     if (g.tile >= 0 && g.us < near * best.us) {
         best = BlockChoice{};
         best.group = g;

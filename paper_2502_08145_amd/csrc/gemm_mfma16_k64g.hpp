@@ -31,6 +31,7 @@
 // MFMA order, accumulator layout and the XCD-aware tile order are those of gemm_tile_kernel16.
 #pragma once
 #include "gemm_mfma16.hpp"
+#include "kernels.hpp"
 
 namespace axonn {
 
@@ -38,7 +39,7 @@ namespace axonn {
 //   issue<X>(stage)           the X-th of this wave's QL direct loads, at the window, into the stage at `stage`
 //   issue_tail<X>(...)        the same for a shorter last 64 k
 //   advance()                 the window 64 k on
-//   cursor<H>(stage), read<I>() fragment of 16-row block I: the 32 k of this wave's group (H = 0), or the other half (H = 1)
+//   cursor<H>(stage, next), read<I>() fragment of 16-row block I: the 32 k of this wave's group (H = 0), or the other half (H = 1)
 template <int ROWS, int REGION, int NW, int NB>
 struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chunks swizzled by (row >> 1) & 7
     static constexpr int QL = ROWS / 8 / NW;   // a load is 8 rows x 128 bytes
@@ -77,11 +78,91 @@ struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chun
         uint32_t a;
     };
     template <int H>
-    __device__ __forceinline__ Cursor cursor(uint32_t stage) const { return Cursor{raddr[H] + stage}; }
+    __device__ __forceinline__ Cursor cursor(uint32_t stage, uint32_t) const { return Cursor{raddr[H] + stage}; }
     template <int I>
     __device__ __forceinline__ bf16x8 read(const Cursor& c) const {
         typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
         return __builtin_bit_cast(bf16x8, *reinterpret_cast<lds_u32x4*>(c.a + I * 2048u));
+    }
+};
+
+// The same for rows that start anywhere on 16 bytes (a K that is no multiple of 64): every load is still 8 whole lines.  Loaded by k,
+// each row's 128 bytes of a stage lie across two lines, each line is fetched for two stages, and a step takes up to twice as long.
+// Here a row that starts s pieces into its line has its last s pieces of every 64 k fetched one stage later, with the rest of
+// their line: stage l holds, at the place of piece c, the one of 64 k number l, or, where c + s >= 8, of number l - 1.  An iteration
+// reads its own stage and the next one; there is one more stage than iterations, of late pieces only.
+template <int ROWS, int REGION, int NW, int NB>
+struct GroupKLines {
+    static constexpr int QL = ROWS / 8 / NW;
+    static_assert(QL >= 1 && (QL == 1 || QL % 2 == 0), "loads per wave");
+    const uint8_t* base;     // uniform: 128 bytes before the wave's first row, at the window
+    uint32_t voff[QL];
+    uint32_t lds_dst;
+    uint32_t raddr[2];
+    uint32_t late[2];        // all ones where this lane reads half 0 (1) from the next stage
+    uint32_t late_load;      // bit x: this lane's piece of load x is a late one
+
+    __device__ __forceinline__ void init(const uint16_t* P, int64_t row0, uint32_t ld_bytes, int lane, int wave, int group,
+                                         uint32_t lds0, int wave_row) {
+        const uint8_t* const first = reinterpret_cast<const uint8_t*>(P) + (size_t)row0 * ld_bytes;
+        base = first + (size_t)(8 * QL * wave) * ld_bytes - 128;
+        // where a row starts in its line, in pieces: the same for rows 8 apart
+        const uint32_t s0 = (uint32_t)(reinterpret_cast<size_t>(first) >> 4), ld = ld_bytes >> 4;
+        const uint32_t s = (s0 + (lane >> 3) * ld) & 7u;
+        late_load = 0;
+#pragma unroll
+        for (int x = 0; x < QL; ++x) {
+            const uint32_t row = 8 * (QL * wave + x) + (lane >> 3), c = ((uint32_t)lane & 7u) ^ ((row >> 1) & 7u);
+            const bool l = c + s >= 8;
+            late_load |= l ? 1u << x : 0u;
+            voff[x] = (uint32_t)(8 * x + (lane >> 3)) * ld_bytes + (c << 4) + (l ? 0u : 128u);
+        }
+        lds_dst = lds0 + REGION + (uint32_t)(QL * wave) * 1024u;
+        const uint32_t r16 = lane & 15, quad = lane >> 4, s16 = (s0 + r16 * ld) & 7u;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t c = 4u * (group ^ h) + quad;
+            raddr[h] = lds0 + REGION + (uint32_t)(wave_row + r16) * 128u + ((c ^ (r16 >> 1)) << 4);
+            late[h] = c + s16 >= 8 ? ~0u : 0u;
+        }
+    }
+    template <int X>
+    __device__ __forceinline__ void issue(uint32_t stage) const {
+        direct_load16(lds_dst + stage + X * 1024u, base, voff[X]);
+    }
+    // Stages 0 and 1: the shorter 64 k come first.  `delta`: their bytes behind the row's first k.
+    template <int X>
+    __device__ __forceinline__ void issue_tail(uint32_t stage, size_t delta, int left, int lane, int wave) const {
+        const bool l = late_load >> X & 1;
+        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, !l && tail_k(X, lane, wave) < left));
+    }
+    template <int X>
+    __device__ __forceinline__ void issue_second(uint32_t stage, size_t delta, int left, int lane, int wave) const {
+        const bool l = late_load >> X & 1;
+        const uint8_t* const p = base + voff[X];
+        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(l ? p + 128 + delta : p, !l || tail_k(X, lane, wave) < left));
+    }
+    // the stage of late pieces only
+    template <int X>
+    __device__ __forceinline__ void issue_last(uint32_t stage) const {
+        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X], late_load >> X & 1));
+    }
+    __device__ __forceinline__ void advance() { base += 128; }
+    struct Cursor {
+        uint32_t a;
+    };
+    template <int H>
+    __device__ __forceinline__ Cursor cursor(uint32_t stage, uint32_t next) const { return Cursor{raddr[H] + stage + (late[H] & (next - stage))}; }
+    template <int I>
+    __device__ __forceinline__ bf16x8 read(const Cursor& c) const {
+        typedef __attribute__((address_space(3))) const u32x4 lds_u32x4;
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<lds_u32x4*>(c.a + I * 2048u));
+    }
+
+private:
+    __device__ __forceinline__ static int tail_k(int x, int lane, int wave) {
+        const uint32_t row = 8 * (QL * wave + x) + (lane >> 3);
+        return 8 * (int)((lane & 7) ^ ((row >> 1) & 7));
     }
 };
 
@@ -131,7 +212,7 @@ struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte ch
         uint32_t a;
     };
     template <int H>
-    __device__ __forceinline__ Cursor cursor(uint32_t stage) const { return Cursor{stage + H * 32u * ROWB}; }
+    __device__ __forceinline__ Cursor cursor(uint32_t stage, uint32_t) const { return Cursor{stage + H * 32u * ROWB}; }
     template <int I>
     __device__ __forceinline__ bf16x8 read(const Cursor& c) const {
         typedef short i16x4 __attribute__((ext_vector_type(4)));
@@ -143,12 +224,15 @@ struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte ch
     }
 };
 
-template <int BM, int BN, int G>
+// Not the half tiles: LDS has room for three stages of them, one too few for an iteration that reads two (0.83 to 1.02 times as fast).
+constexpr bool group_lines(int bm, int bn, bool a_kc, bool b_kc) { return bm + bn <= 256 && (a_kc || b_kc); }
+// LINES: an operand is loaded by lines (GroupKLines); an iteration then reads two stages, and one more is there for it where LDS has room
+template <int BM, int BN, int G, bool LINES = false>
 struct GroupCfg {
     static constexpr int NW = 8, NT = 512;
     static constexpr int WN = G == 2 || BM > BN || BN == 64 ? 2 : 4, WM = NW / G / WN;
     static constexpr int STAGE = (BM + BN) * 128;                // 64 k of both operands
-    static constexpr int NS = BM + BN <= 128 ? 5 : BM + BN <= 192 ? 4 : 3;
+    static constexpr int NS = BM + BN <= 128 ? 5 : BM + BN <= 192 ? 4 + LINES : BM + BN <= 256 ? 3 + LINES : 3;
     static constexpr int EXCHANGE = G == 2 ? BM * BN * 4 : 0;   // half of either group's fp32 tile
     static constexpr int LDS_BYTES = NS * STAGE > EXCHANGE ? NS * STAGE : EXCHANGE;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS per workgroup");
@@ -156,13 +240,14 @@ struct GroupCfg {
     static constexpr int WAVES_PER_SIMD = 2 * LDS_BYTES <= 160 * 1024 ? 4 : 2;
 };
 
-// Requires M >= BM, N >= BN, K % 64 == 0 (KTAIL: see TileGrid), and 16-byte aligned rows.
-template <int BM, int BN, int G, bool A_KC, bool B_KC, bool KTAIL = false>
-__global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void gemm_tile_kernel_k64g(
-    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
-    int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
-    using Cfg = GroupCfg<BM, BN, G>;
+// One tile.  LINES: its K-contiguous operands by lines; K > 64 NS.
+template <int BM, int BN, int G, bool A_KC, bool B_KC, bool KTAIL, bool LINES>
+__device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
+                                           int K, int lda, int ldb, int ldc, int64_t m0, int64_t n0, int k_tail) {
+    constexpr bool LINES_A = LINES && A_KC, LINES_B = LINES && B_KC;
+    using Cfg = GroupCfg<BM, BN, G, LINES>;
     constexpr int NW = Cfg::NW, NS = Cfg::NS;
+    constexpr int AHEAD = LINES ? 2 : 1;   // an iteration reads this many stages
     constexpr uint32_t STAGE = Cfg::STAGE;
     constexpr int TM = BM / Cfg::WM, TN = BN / Cfg::WN, MI = TM / 16, NI = TN / 16, NM = MI * NI;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -172,12 +257,12 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int group = G == 2 ? wave >> 2 : 0, wm = (G == 2 ? wave & 3 : wave) / Cfg::WN, wn = wave % Cfg::WN;
 
-    const TileWork work = map_workgroup<false, false>(blockIdx.x, gridDim.x, K, grid.tiles_m, grid.tiles_n, group_m, sk);
-    const int64_t m0 = min(work.tile_m * BM, grid.m_last), n0 = min(work.tile_n * BN, grid.n_last);
-
-    using OpA = typename std::conditional<A_KC, GroupKContig<BM, 0, NW, MI>, GroupMNContig<BM, 0, NW, MI>>::type;
-    using OpB = typename std::conditional<B_KC, GroupKContig<BN, BM * 128, NW, NI>, GroupMNContig<BN, BM * 128, NW, NI>>::type;
+    using OpA = typename std::conditional<LINES_A, GroupKLines<BM, 0, NW, MI>,
+                                          typename std::conditional<A_KC, GroupKContig<BM, 0, NW, MI>, GroupMNContig<BM, 0, NW, MI>>::type>::type;
+    using OpB = typename std::conditional<LINES_B, GroupKLines<BN, BM * 128, NW, NI>,
+                                          typename std::conditional<B_KC, GroupKContig<BN, BM * 128, NW, NI>, GroupMNContig<BN, BM * 128, NW, NI>>::type>::type;
     constexpr int QLA = OpA::QL, QLB = OpB::QL, QL = QLA + QLB;
+    constexpr int QX = (LINES_A ? QLA : 0) + (LINES_B ? QLB : 0);   // loads of the stage of late pieces
     const uint32_t lds0 = lds_address(smem);
     OpA opa;
     OpB opb;
@@ -201,11 +286,20 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
         opa.advance();
         opb.advance();
     };
-    auto read_range = [&](Frags& x, uint32_t stage, auto h_c, auto lo_c, auto hi_c) __attribute__((always_inline)) {
+    auto issue_last = [&](auto x_c, uint32_t stage) __attribute__((always_inline)) {
+        constexpr int X = decltype(x_c)::value;
+        if constexpr (X < QLA) {
+            if constexpr (LINES_A) opa.template issue_last<X>(stage);
+        } else {
+            if constexpr (LINES_B) opb.template issue_last<X - QLA>(stage);
+        }
+    };
+    // fragments of the iteration whose stage is `stage`; `after`: the stage behind it
+    auto read_range = [&](Frags& x, uint32_t stage, uint32_t after, auto h_c, auto lo_c, auto hi_c) __attribute__((always_inline)) {
         constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;
         constexpr int H = decltype(h_c)::value;
-        const auto ca = opa.template cursor<H>(stage);
-        const auto cb = opb.template cursor<H>(stage);
+        const auto ca = opa.template cursor<H>(stage, after);
+        const auto cb = opb.template cursor<H>(stage, after);
         static_for<HI - LO>([&](auto d) __attribute__((always_inline)) {
             constexpr int X = LO + decltype(d)::value;
             if constexpr (X < MI)
@@ -225,26 +319,39 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
 
     // ---- prologue: the first stages
     const int KI = K / 64;
-    const int fill = KI < NS ? KI : NS;
+    const int fill = LINES || KI > NS ? NS : KI;
     {
         int s = 0;
         if constexpr (KTAIL) {
             const size_t whole = (size_t)(K - 64);
             static_for<QLA>([&](auto x) __attribute__((always_inline)) {
-                opa.template issue_tail<decltype(x)::value>(0u, 2 * (A_KC ? whole : whole * lda), grid.k_tail, lane, wave);
+                opa.template issue_tail<decltype(x)::value>(0u, 2 * (A_KC ? whole : whole * lda), k_tail, lane, wave);
             });
             static_for<QLB>([&](auto x) __attribute__((always_inline)) {
-                opb.template issue_tail<decltype(x)::value>(0u, 2 * (B_KC ? whole : whole * ldb), grid.k_tail, lane, wave);
+                opb.template issue_tail<decltype(x)::value>(0u, 2 * (B_KC ? whole : whole * ldb), k_tail, lane, wave);
             });
             s = 1;
+            if constexpr (LINES) {
+                static_for<QLA>([&](auto x) __attribute__((always_inline)) {
+                    if constexpr (LINES_A) opa.template issue_second<decltype(x)::value>(STAGE, 2 * whole, k_tail, lane, wave);
+                    else opa.template issue<decltype(x)::value>(STAGE);
+                });
+                static_for<QLB>([&](auto x) __attribute__((always_inline)) {
+                    if constexpr (LINES_B) opb.template issue_second<decltype(x)::value>(STAGE, 2 * whole, k_tail, lane, wave);
+                    else opb.template issue<decltype(x)::value>(STAGE);
+                });
+                opa.advance();
+                opb.advance();
+                s = 2;
+            }
         }
         for (; s < fill; ++s) issue_stage(s * STAGE);
     }
-    if (KI < NS) {   // all of K is in LDS
+    if (!LINES && KI < NS) {   // all of K is in LDS
         asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         for (int i = 0; i < KI; ++i) {
             static_for<2 / G>([&](auto h) __attribute__((always_inline)) {
-                read_range(f[0], i * STAGE, h, Int<0>{}, Int<MI + NI>{});
+                read_range(f[0], i * STAGE, (i + 1) * STAGE, h, Int<0>{}, Int<MI + NI>{});
                 mfma_range(f[0], Int<0>{}, Int<NM>{});
             });
         }
@@ -255,10 +362,11 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
         uint32_t st = 0;                // stage of the running iteration
         auto next = [&](uint32_t s) __attribute__((always_inline)) { return s + STAGE == NS * STAGE ? 0u : s + STAGE; };
         // MFMAs on `cur`, among them the reads of `nxt` from half H of stage `from` and the loads LF .. LL-1 of a stage
-        // into `to`.  VM >= 0: a barrier first, at which this wave's fragments are in registers and all its loads but the
-        // last VM have landed.
-        auto substep = [&](const Frags& cur, Frags& nxt, auto vm_c, auto read_c, auto h_c, auto lf_c, auto ll_c, uint32_t from, uint32_t to) __attribute__((always_inline)) {
-            constexpr bool READ = decltype(read_c)::value;
+        // into `to` (LATE: of the stage of late pieces).  VM >= 0: a barrier first, at which this wave's fragments are in registers
+        // and all its loads but the last VM have landed.
+        auto substep = [&](const Frags& cur, Frags& nxt, auto vm_c, auto read_c, auto h_c, auto lf_c, auto ll_c, auto late_c, uint32_t from, uint32_t to) __attribute__((always_inline)) {
+            constexpr bool READ = decltype(read_c)::value, LATE = decltype(late_c)::value;
+            const uint32_t after = next(from);
             constexpr int VM = decltype(vm_c)::value, LF = decltype(lf_c)::value, NL = decltype(ll_c)::value - LF;
             AXONN_FENCE();
             mfma_range(cur, Int<0>{}, Int<P>{});
@@ -270,10 +378,12 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
             constexpr int R = NM - P;
             static_for<NC>([&](auto q_c) __attribute__((always_inline)) {
                 constexpr int Q = decltype(q_c)::value;
-                if constexpr (READ) read_range(nxt, from, h_c, Int<Q * (MI + NI) / NC>{}, Int<(Q + 1) * (MI + NI) / NC>{});
+                if constexpr (READ) read_range(nxt, from, after, h_c, Int<Q * (MI + NI) / NC>{}, Int<(Q + 1) * (MI + NI) / NC>{});
                 static_for<(Q + 1) * NL / NC - Q * NL / NC>([&](auto d) __attribute__((always_inline)) {
                     constexpr int X = LF + Q * NL / NC + decltype(d)::value;
-                    if constexpr (X < QLA)
+                    if constexpr (LATE)
+                        issue_last(Int<X>{}, to);
+                    else if constexpr (X < QLA)
                         opa.template issue<X>(to);
                     else
                         opb.template issue<X - QLA>(to);
@@ -287,15 +397,21 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
         };
         using Yes = std::true_type;
         using No = std::false_type;
-        wait_vmcnt<(NS - 1) * QL>();
+        wait_vmcnt<(NS - AHEAD) * QL>();
         __builtin_amdgcn_s_barrier();
         AXONN_FENCE();
-        constexpr int VM = (NS - 2) * QL;
+        // what may be in flight at the barrier of an iteration: the stages beyond those that the next one reads
+        constexpr int VM = (NS - 1 - AHEAD) * QL;
+        // at the J-th of the last NS ones; < 0: no barrier
+        constexpr auto vm_at_end = [](int j) {
+            const int stages = NS - 1 - AHEAD - j;   // whole ones
+            return j == NS - 1 ? -1 : (stages > 0 ? stages * QL : 0) + (LINES && j > 0 && stages >= 0 ? QX : 0);
+        };
         if constexpr (G == 2) {
             // one iteration: multiplies `cur`, reads the next iteration's fragments, refills the stage behind the barrier
-            auto step = [&](const Frags& cur, Frags& nxt, auto vm_c, auto read_c, auto load_c) __attribute__((always_inline)) {
+            auto step = [&](const Frags& cur, Frags& nxt, auto vm_c, auto read_c, auto load_c, auto late_c) __attribute__((always_inline)) {
                 const uint32_t ns = next(st);
-                substep(cur, nxt, vm_c, read_c, Int<0>{}, Int<0>{}, Int<decltype(load_c)::value ? QL : 0>{}, ns, st);
+                substep(cur, nxt, vm_c, read_c, Int<0>{}, Int<0>{}, Int<decltype(load_c)::value || decltype(late_c)::value ? QL : 0>{}, late_c, ns, st);
                 if constexpr (decltype(load_c)::value) {
                     opa.advance();
                     opb.advance();
@@ -304,50 +420,53 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
             };
             int n = KI - NS;   // iterations with a load; the register buffers alternate, and the ones without a load start on f[0]
             if (n & 1) {
-                read_range(f[1], 0u, Int<0>{}, Int<0>{}, Int<MI + NI>{});
-                step(f[1], f[0], Int<VM>{}, Yes{}, Yes{});
+                read_range(f[1], 0u, STAGE, Int<0>{}, Int<0>{}, Int<MI + NI>{});
+                step(f[1], f[0], Int<VM>{}, Yes{}, Yes{}, No{});
             } else {
-                read_range(f[0], 0u, Int<0>{}, Int<0>{}, Int<MI + NI>{});
+                read_range(f[0], 0u, STAGE, Int<0>{}, Int<0>{}, Int<MI + NI>{});
             }
             for (n >>= 1; n > 0; --n) {
-                step(f[0], f[1], Int<VM>{}, Yes{}, Yes{});
-                step(f[1], f[0], Int<VM>{}, Yes{}, Yes{});
+                step(f[0], f[1], Int<VM>{}, Yes{}, Yes{}, No{});
+                step(f[1], f[0], Int<VM>{}, Yes{}, Yes{}, No{});
             }
             static_for<NS>([&](auto j_c) __attribute__((always_inline)) {
                 constexpr int J = decltype(j_c)::value;
-                constexpr int V = J == NS - 1 ? -1 : J < NS - 2 ? (NS - 2 - J) * QL : 0;
-                step(f[J & 1], f[1 - (J & 1)], Int<V>{}, std::bool_constant<(J < NS - 1)>{}, No{});
+                step(f[J & 1], f[1 - (J & 1)], Int<vm_at_end(J)>{}, std::bool_constant<(J < NS - 1)>{}, No{}, std::bool_constant<(LINES && J == 0)>{});
             });
         } else {
             // one iteration: both halves.  The stage is released at the barrier in the second one; its loads go out there
             // and in the next iteration's first half.
             constexpr int QH = QL / 2;
             uint32_t to = 0;
+            // loads of the first and of the second substep: 0 none, 1 a stage's, 2 those of the stage of late pieces
             auto step = [&](auto vm_c, auto last_c, auto load0_c, auto load1_c) __attribute__((always_inline)) {
-                constexpr bool LAST = decltype(last_c)::value, L0 = decltype(load0_c)::value, L1 = decltype(load1_c)::value;
+                constexpr bool LAST = decltype(last_c)::value;
+                constexpr int L0 = decltype(load0_c)::value, L1 = decltype(load1_c)::value;
                 const uint32_t ns = next(st);
-                substep(f[0], f[1], Int<-1>{}, Yes{}, Int<1>{}, Int<QH>{}, Int<L0 ? QL : QH>{}, st, to);
-                if constexpr (L0) {
+                substep(f[0], f[1], Int<-1>{}, Yes{}, Int<1>{}, Int<QH>{}, Int<L0 ? QL : QH>{}, std::bool_constant<L0 == 2>{}, st, to);
+                if constexpr (L0 == 1) {
                     opa.advance();
                     opb.advance();
                 }
-                substep(f[1], f[0], vm_c, std::bool_constant<!LAST>{}, Int<0>{}, Int<0>{}, Int<L1 ? QH : 0>{}, ns, st);
+                substep(f[1], f[0], vm_c, std::bool_constant<!LAST>{}, Int<0>{}, Int<0>{}, Int<L1 ? QH : 0>{}, std::bool_constant<L1 == 2>{}, ns, st);
                 to = st;
                 st = ns;
             };
-            read_range(f[0], 0u, Int<0>{}, Int<0>{}, Int<MI + NI>{});
+            read_range(f[0], 0u, STAGE, Int<0>{}, Int<0>{}, Int<MI + NI>{});
             int n = KI - NS;
+            using L0 = Int<0>;
+            using L1 = Int<1>;
+            using L2 = Int<LINES ? 2 : 0>;
             if (n > 0) {
-                step(Int<VM>{}, No{}, No{}, Yes{});
-                for (; n > 1; --n) step(Int<VM>{}, No{}, Yes{}, Yes{});
-                step(Int<VM>{}, No{}, Yes{}, No{});
+                step(Int<VM>{}, No{}, L0{}, L1{});
+                for (; n > 1; --n) step(Int<VM>{}, No{}, L1{}, L1{});
+                step(Int<VM>{}, No{}, L1{}, L2{});
             } else {
-                step(Int<VM>{}, No{}, No{}, No{});
+                step(Int<VM>{}, No{}, L0{}, L2{});
             }
             static_for<NS - 1>([&](auto j_c) __attribute__((always_inline)) {
                 constexpr int J = decltype(j_c)::value + 1;
-                constexpr int V = J == NS - 1 ? -1 : J < NS - 2 ? (NS - 2 - J) * QL : 0;
-                step(Int<V>{}, std::bool_constant<(J == NS - 1)>{}, No{}, No{});
+                step(Int<vm_at_end(J)>{}, std::bool_constant<(J == NS - 1)>{}, Int<LINES && J == 1 ? 2 : 0>{}, L0{});
             });
         }
     }
@@ -389,6 +508,23 @@ __global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void ge
         for (int i = 0; i < MH; ++i) store_block_row16<TN, NI>(out[i], epi, pc + (int64_t)(16 * i) * ldc, ldc, lane);
     }
 #undef AXONN_FENCE
+}
+
+// Requires M >= BM, N >= BN, K % 64 == 0 (KTAIL: see TileGrid), and 16-byte aligned rows.
+template <int BM, int BN, int G, bool A_KC, bool B_KC, bool KTAIL = false>
+__global__ __launch_bounds__(512, (GroupCfg<BM, BN, G>::WAVES_PER_SIMD)) void gemm_tile_kernel_k64g(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
+    int K, int lda, int ldb, int ldc, TileGrid grid, int group_m, SplitK sk) {
+    const TileWork work = map_workgroup<false, false>(blockIdx.x, grid.tiles_m * grid.tiles_n, K, grid.tiles_m, grid.tiles_n, group_m, sk);
+    const int64_t m0 = min(work.tile_m * BM, grid.m_last), n0 = min(work.tile_n * BN, grid.n_last);
+    if constexpr (KTAIL && group_lines(BM, BN, A_KC, B_KC)) {
+        if (__builtin_expect(K <= kGroupLinesK, 1))
+            group_tile<BM, BN, G, A_KC, B_KC, true, false>(A, B, C, K, lda, ldb, ldc, m0, n0, grid.k_tail);
+        else
+            group_tile<BM, BN, G, A_KC, B_KC, true, true>(A, B, C, K, lda, ldb, ldc, m0, n0, grid.k_tail);
+    } else {
+        group_tile<BM, BN, G, A_KC, B_KC, KTAIL, false>(A, B, C, K, lda, ldb, ldc, m0, n0, grid.k_tail);
+    }
 }
 
 }  // namespace axonn

@@ -23,6 +23,11 @@ tile_kernel_t k64_kernel_half(int bm, int bn, int layout);
 // the same with one resident workgroup per compute unit walking a list of tiles (gemm_tile_kernel_k64p)
 tile_kernel_t k64p_kernel(int layout);
 
+// Where the eight-wave kernel loads the K-contiguous operands of a K that is no multiple of 64 by lines (GroupKLines): beyond this K.  Up to there
+// the stage more and the prologue cost what the lines save (operands in cache, from memory: 0.96 and 1.00 of the speed of the loads by k over
+// K of 256 to 520, 0.97 and 1.05 over 520 to 800; from 1000 on 1.01 and 1.12, from 2500 on 1.27 and 1.25).
+constexpr int kGroupLinesK = 768;
+
 // eight waves on tiles from 64 x 64 to 256 x 128 (gemm_tile_kernel_k64g), no split-K
 tile_kernel_t group_kernel(int bm, int bn, int groups, int layout, bool k_tail);
 int group_lds_bytes(int bm, int bn, int groups);

@@ -13,14 +13,17 @@ namespace axonn {
 //   as the operands outgrow the caches (16 MB and more: all of it): by `far`, and by `apart` times the share of a panel that the
 //   tiles behind one L2 do not have in common (one tile column or row over the whole chip: half of it; a square patch: a fifth);
 //   where the rows of an operand do not start on 128-byte lines: its loads then touch a line more (`lines`: of A K-contiguous, B
-//   K-contiguous, A MN-contiguous, B MN-contiguous, times its share of the tile).
+//   K-contiguous, A MN-contiguous, B MN-contiguous, times its share of the tile).  Where K-contiguous rows
+//   are loaded by lines (GroupKLines) a step of theirs takes `late_line` longer (B) or no longer (A), and a tile `late` steps more: a stage
+//   more is loaded and waited for.  (600 sampled products of K off 64, residual 7-11 %; what is chosen takes 1.004 times the best tile, 1.008
+//   with the figures of the loads by k.)
 // Outputs whose rows do not start on 128-byte lines pay for the lines that two workgroups write a part of.
 // Least squares on the logarithm over 6 000 sampled products of up to 80 GFLOP, the mean of operands in cache and operands
 // from memory, residual 5-8 %.  With the wave-K and the guarded kernel's models the choice is 0.8 % behind the best kernel measured
 // on average, 5 % at the 95th percentile.
 struct GroupTile {
     int bm, bn, groups, lds_bytes;
-    double launch, tile, last, shared_lines, us64[3], far[3], apart[3], lines[4];
+    double launch, tile, last, shared_lines, us64[3], far[3], apart[3], lines[4], late, late_line;
     tile_kernel_t fn[3], fn_tail[3];   // per layout; nullptr: not built
 };
 #define AXONN_GROUP3(BM, BN, G, ...) {gemm_tile_kernel_k64g<BM, BN, G, true, false, __VA_ARGS__>, gemm_tile_kernel_k64g<BM, BN, G, true, true, __VA_ARGS__>, \
@@ -29,17 +32,17 @@ struct GroupTile {
 // NN 3-7 % faster than one group, TN 8-11 %, NT +-1 %), and for whole K only
 #define AXONN_GROUP2(BM, BN, G, ...) {gemm_tile_kernel_k64g<BM, BN, G, true, false, __VA_ARGS__>, nullptr, gemm_tile_kernel_k64g<BM, BN, G, false, false, __VA_ARGS__>}
 #define AXONN_NO_KERNELS(...) {nullptr, nullptr, nullptr}
-#define AXONN_GROUP_TILE(BM, BN, G, KERNELS, TAIL_KERNELS, ...) {BM, BN, G, GroupCfg<BM, BN, G>::LDS_BYTES, __VA_ARGS__, KERNELS(BM, BN, G, false), TAIL_KERNELS(BM, BN, G, true)}
+#define AXONN_GROUP_TILE(BM, BN, G, KERNELS, TAIL_KERNELS, ...) {BM, BN, G, GroupCfg<BM, BN, G, group_lines(BM, BN, true, true)>::LDS_BYTES, __VA_ARGS__, KERNELS(BM, BN, G, false), TAIL_KERNELS(BM, BN, G, true)}
 static const GroupTile kTiles[] = {
-    AXONN_GROUP_TILE(64, 64, 2, AXONN_GROUP3, AXONN_GROUP3, 3.04, 0.48, 0.770, 0.09, {0.141, 0.124, 0.155}, {0.073, 0.131, 0.0}, {2.118, 2.712, 1.544}, {0.44, 0.51, 0.49, 0.60}),
-    AXONN_GROUP_TILE(64, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.22, 1.33, 0.789, 0.21, {0.229, 0.202, 0.258}, {0.209, 0.349, 0.036}, {1.099, 1.396, 1.135}, {0.47, 0.49, 0.35, 0.30}),
-    AXONN_GROUP_TILE(128, 64, 1, AXONN_GROUP3, AXONN_GROUP3, 2.25, 1.28, 0.814, 0.26, {0.224, 0.201, 0.255}, {0.314, 0.421, 0.130}, {0.791, 0.978, 0.611}, {0.43, 0.56, 0.19, 0.64}),
-    AXONN_GROUP_TILE(128, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.16, 1.82, 0.812, 1.04, {0.338, 0.308, 0.408}, {0.276, 0.381, 0.112}, {0.509, 0.583, 0.290}, {0.36, 0.44, 0.11, 0.21}),
-    AXONN_GROUP_TILE(128, 128, 2, AXONN_GROUP2, AXONN_NO_KERNELS, 2.51, 2.69, 0.806, 0.96, {0.311, 0.0, 0.341}, {0.299, 0.0, 0.159}, {0.665, 0.0, 0.579}, {0.42, 0.44, 0.22, 0.26}),
-    AXONN_GROUP_TILE(256, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 1.93, 3.34, 0.693, 3.57, {0.609, 0.598, 0.728}, {0.130, 0.155, 0.0}, {0.472, 0.557, 0.260}, {0.32, 0.30, 0.03, 0.23}),
+    AXONN_GROUP_TILE(64, 64, 2, AXONN_GROUP3, AXONN_GROUP3, 3.04, 0.48, 0.770, 0.09, {0.141, 0.124, 0.155}, {0.073, 0.131, 0.0}, {2.118, 2.712, 1.544}, {0.44, 0.51, 0.49, 0.60}, 1.8, 0.06),
+    AXONN_GROUP_TILE(64, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.22, 1.33, 0.789, 0.21, {0.229, 0.202, 0.258}, {0.209, 0.349, 0.036}, {1.099, 1.396, 1.135}, {0.47, 0.49, 0.35, 0.30}, 2.4, 0.03),
+    AXONN_GROUP_TILE(128, 64, 1, AXONN_GROUP3, AXONN_GROUP3, 2.25, 1.28, 0.814, 0.26, {0.224, 0.201, 0.255}, {0.314, 0.421, 0.130}, {0.791, 0.978, 0.611}, {0.43, 0.56, 0.19, 0.64}, 2.6, 0.06),
+    AXONN_GROUP_TILE(128, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.16, 1.82, 0.812, 1.04, {0.338, 0.308, 0.408}, {0.276, 0.381, 0.112}, {0.509, 0.583, 0.290}, {0.36, 0.44, 0.11, 0.21}, 1.8, 0.04),
+    AXONN_GROUP_TILE(128, 128, 2, AXONN_GROUP2, AXONN_NO_KERNELS, 2.51, 2.69, 0.806, 0.96, {0.311, 0.0, 0.341}, {0.299, 0.0, 0.159}, {0.665, 0.0, 0.579}, {0.42, 0.44, 0.22, 0.26}, 0.0, 0.0),
+    AXONN_GROUP_TILE(256, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 1.93, 3.34, 0.693, 3.57, {0.609, 0.598, 0.728}, {0.130, 0.155, 0.0}, {0.472, 0.557, 0.260}, {0.32, 0.30, 0.03, 0.23}, 0.0, 0.0),
     // (NN and NT step: 0.635 and 0.581 fitted.  Near a tie of the half tiles this one is taken.  NT: 1.4 % ahead with operands from memory, 0.4 %
     // in cache, nine products.  NN: 2.2 % ahead from memory, 1.5-4.5 % behind in cache, the 70 sampled products that the figure decides.)
-    AXONN_GROUP_TILE(128, 256, 1, AXONN_GROUP3, AXONN_GROUP3, 1.86, 3.41, 0.692, 2.91, {0.612, 0.562, 0.716}, {0.071, 0.155, 0.0}, {0.760, 0.848, 0.358}, {0.13, 0.43, 0.06, 0.10}),
+    AXONN_GROUP_TILE(128, 256, 1, AXONN_GROUP3, AXONN_GROUP3, 1.86, 3.41, 0.692, 2.91, {0.612, 0.562, 0.716}, {0.071, 0.155, 0.0}, {0.760, 0.848, 0.358}, {0.13, 0.43, 0.06, 0.10}, 0.0, 0.0),
 };
 #undef AXONN_GROUP_TILE
 #undef AXONN_GROUP3
@@ -66,8 +69,9 @@ static double model_us(const GroupTile& t, int layout, int64_t m, int64_t n, int
     if (!(K % 64 ? t.fn_tail : t.fn)[layout] || m < t.bm || n < t.bn || K <= 64) return -1.0;
     const int64_t wgs = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn), rest = wgs % 256;
     const double rounds = (double)(wgs / 256) + (rest ? t.last + (1.0 - t.last) * (double)rest / 256.0 : 0.0);
-    const double lines = 1.0 + (lda % 64 ? t.lines[layout == 2 ? 2 : 0] * t.bm / (t.bm + t.bn) : 0.0) +
-                         (ldb % 64 ? t.lines[layout == 1 ? 1 : 3] * t.bn / (t.bm + t.bn) : 0.0);
+    const bool late = K % 64 && K > kGroupLinesK && group_lines(t.bm, t.bn, layout != 2, layout == 1);
+    const double line_a = layout == 2 ? t.lines[2] : late ? 0.0 : t.lines[0], line_b = layout != 1 ? t.lines[3] : late ? t.late_line : t.lines[1];
+    const double lines = 1.0 + (lda % 64 ? line_a * t.bm / (t.bm + t.bn) : 0.0) + (ldb % 64 ? line_b * t.bn / (t.bm + t.bn) : 0.0);
     const double shared = ldc % 64 == 0 ? 0.0 : ldc % 32 == 0 ? 0.15 : 1.0;
     const double full = (double)wgs / 256.0 - 0.5;
     const double mb = 2e-6 * ((double)m * K + (double)K * n);
@@ -76,7 +80,8 @@ static double model_us(const GroupTile& t, int layout, int64_t m, int64_t n, int
     const double rows = std::min(std::min(tiles_m, 8.0), behind), cols = std::ceil(behind / rows);
     const double panels = (rows * t.bm + cols * t.bn) / (behind * (t.bm + t.bn));
     const double step = t.us64[layout] * lines * (1.0 + (t.far[layout] + t.apart[layout] * panels) * std::min(1.0, mb / 16.0));
-    return t.launch + rounds * ((double)((K + 63) / 64) * step + t.tile) + (full > 0.0 ? shared * t.shared_lines * full : 0.0);
+    const double steps = (double)((K + 63) / 64) + (late ? t.late : 0.0);
+    return t.launch + rounds * (steps * step + t.tile) + (full > 0.0 ? shared * t.shared_lines * full : 0.0);
 }
 
 double group_us(int bm, int bn, int groups, int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {

@@ -167,6 +167,41 @@ def test_every_length_of_k_on_the_eight_wave_kernel(oracle_mod, tile, tail, layo
         _check(oracle_mod, *shape, layout, [kernel])
 
 
+@lru_cache(maxsize=None)
+def by_lines_products():
+    """{(kernel, layout): {pieces of 8 beyond whole 64 k: the smallest sampled product of one launch on it}}, K beyond 768."""
+    rng = random.Random(17)
+    found = {}
+    for _ in range(60000):
+        layout, K = rng.choice(["NN", "NT"]), 8 * rng.randrange(97, 300)
+        M, N = _log_int(rng, 64, 4000, 8), _log_int(rng, 64, 4000, 8)
+        names = B.kernels(M, N, K, layout)
+        if K % 64 and len(names) == 1 and names[0].startswith("mfma16k64g"):
+            best, left = found.setdefault((names[0], layout), {}), K % 64 // 8
+            if left not in best or M * N * K < math.prod(best[left]):
+                best[left] = (M, N, K)
+    return found
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", ["NN", "NT"])
+@pytest.mark.parametrize("tile", ["64x64_g2", "64x128", "128x64", "128x128"])
+def test_k_contiguous_rows_loaded_by_lines(tile, layout):
+    """Rows that start on every 16 bytes of a line (each K modulo 64, buffers on every 16 bytes of one): integers, exact in any order."""
+    B.register_workspace()
+    products = by_lines_products()[(f"mfma16k64g_{tile}_ktail", layout)]
+    assert set(products) == set(range(1, 8)), products
+    for left, (M, N, K) in products.items():
+        for at_a, at_b in ((left, 0), (3, left), (0, 8 - left)):
+            print(f"  {tile} {layout} {(M, N, K)} {at_a} {at_b}", flush=True)
+            a = torch.randint(-4, 5, (8 * at_a + M * K,), device="cuda").to(torch.bfloat16)[8 * at_a:].view(M, K)
+            b = torch.randint(-4, 5, (8 * at_b + N * K,), device="cuda").to(torch.bfloat16)[8 * at_b:].view(*((N, K) if layout == "NT" else (K, N)))
+            c = torch.full((M + 2, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.axonn_linear_fwd(M, N, K, layout, a, b, c[:M])
+            ref = a.float() @ (b.float().t().contiguous() if layout == "NT" else b.float())
+            assert torch.equal(c[:M], ref.to(torch.bfloat16)) and bool(c[M:].isnan().all())
+
+
 @pytest.mark.gpu
 def test_a_ragged_layer_s_data_gradient(oracle_mod):
     _check(oracle_mod, 1064, 1608, 4168, "NT", ["mfma16k64g_64x128_ktail"])
