@@ -250,7 +250,8 @@ const char *axonn_status_string(int status);
 int axonn_linear_version(void);
 
 /* Caller-owned split-K scratch.  axonn_linear_workspace_bytes: what the variants that this problem is planned with
- * need (0: none; otherwise at least the 4 KiB + 256 KiB that axonn_linear_set_workspace accepts).  A block that
+ * need (0: none; otherwise at least the 4 KiB + 256 KiB that axonn_linear_set_workspace accepts).  In a
+ * larger area some run faster, in more K ranges (up to 4 KiB + 32 MiB per product, axonn_linear_part_kernel with now = 1).  A block that
  * runs on a kernel without scratch all the same (axonn_linear_part_kernel) touches none of it, registered or not.
  * axonn_linear_set_workspace: use `bytes` bytes at the
  * DEVICE pointer `dev_ptr` (256-byte aligned) as the current device's scratch area from now on; the
@@ -323,6 +324,8 @@ int axonn_linear_call_plan(int64_t M, int64_t N, int64_t K, int layout, axonn_pl
  * variant included.  Names: a tile variant's, with "_ktail" behind it for a K that is no multiple of 64;
  * "mfma16k64g_<rows>x<columns>" for the eight-wave kernel, whatever variant stands for its tile ("_g2": with two groups of waves
  * that halve K between them; "_ktail" as above); "mfma16k64_128x128_sk<ranges>" for NT on that tile with split-K;
+ * "mfma16k64g_<rows>x<columns>_sk<ranges>" for the eight-wave kernel with split-K (now = 1 only: it takes a larger area than
+ * axonn_linear_workspace_bytes asks for);
  * "wavek_<rows>x<columns>_w<waves>" where the waves of a workgroup split K; "wavek_64x64_k32" and "..._k64" for TN over a K of up to 32
  * and 64 ("_xcd": with neighbouring workgroups on one XCD); "edge_128x128" for the guarded kernel; "naive".  Host logic, now = 1
  * plus one hipGetDevice. */

@@ -373,7 +373,8 @@ enum class Figures { Current, Area };
 struct BlockChoice {
     int tile = -1;           // >= 0: this tile variant, its last tiles moved back to the block's edge (TileGrid)
     GroupChoice group{};     // else, .tile >= 0: one of the eight-wave kernel's small tiles
-    WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel; else what the part's variant says
+    WaveKChoice wavek{};     // else, .tile >= 0: the wave-K kernel
+    GroupSplitChoice split{};     // else, .tile >= 0: the eight-wave kernel in K ranges, where the scratch area has room; else what the part's variant says
     int lead_m = 0, lead_n = 0;   // rows and columns before the block that the launch covers as well
     double us = 0.0;         // modelled time
 };
@@ -685,6 +686,17 @@ static bool leaves_split_k(const Part& p, int64_t K, int layout, int64_t lda, in
     if (wavek_choose(layout, p.m, p.n, K, lda, ldb, true).us < 0.97 * us) return true;
     return wk.us < 0.815 * us && !(layout == AXONN_TN && variants()[p.variant].splits >= 4);
 }
+// A block planned with split-K on the eight-wave kernel's tiles and counts instead.  700 sampled products that are planned so, on all of
+// them (in cache, three sets in turn, from memory): 1.31, 1.31 and 1.53 times as fast as planned with 128 x 128 tiles (527, three of them 3-4 % slower),
+// half tiles 1.12 to 1.17 where the models put it 2 % ahead, 256 x 256 tiles in four and more ranges 1.16 to 1.27; in two and three ranges 0.78 to
+// 0.85, an output that has a round of large tiles nearly full.
+static GroupSplitChoice split_on_eight_waves(const Part& p, int64_t K, int layout, double us) {
+    const Variant& x = variants()[p.variant];
+    const int area = x.bm * x.bn;
+    if (us <= 0.0 || (area == 256 * 256 && x.splits < 4)) return GroupSplitChoice{};
+    const GroupSplitChoice c = group_split_choose(layout, p.m, p.n, K, kStaticSlots * kSlotBytes, kMaxFlags);
+    return c.tile >= 0 && c.us < (area <= 128 * 128 ? 1.1 : 0.98) * us ? c : GroupSplitChoice{};
+}
 static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
     const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
     for (int i = 0; i < plan.parts; ++i) {
@@ -696,6 +708,7 @@ static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout
             if (variants()[p.variant].splits > 1) {
                 const double us = block_us(p.variant, p.m, p.n, K, layout, lda, ldb, N);   // the same by either figures
                 if (us > 0.0 && leaves_split_k(p, K, layout, lda, ldb, us, wk)) p.how.wavek = wk;
+                else p.how.split = split_on_eight_waves(p, K, layout, us);
                 continue;
             }
             const double us = tiles_us(p, M, N, K, layout);
@@ -784,6 +797,11 @@ static int64_t part_workgroups(const Part& p) {
     return ((p.m + var.bm - 1) / var.bm) * ((p.n + var.bn - 1) / var.bn) * var.splits;
 }
 
+static uint32_t next_epoch() {
+    const uint32_t epoch = g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;
+    return epoch ? epoch : g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;   // flags start at 0
+}
+
 // A tile kernel over the m x n block that starts at A, B, C.
 static void launch_tiles(const Variant& var, int64_t m, int64_t n, int64_t K, int layout, const uint16_t* A, const uint16_t* B,
                          uint16_t* C, int64_t lda, int64_t ldb, int64_t ldc, const Scratch& scratch, hipStream_t s) {
@@ -792,8 +810,7 @@ static void launch_tiles(const Variant& var, int64_t m, int64_t n, int64_t K, in
     const int group_m = tiles_m < 8 ? tiles_m : 8;
     SplitK sk{nullptr, nullptr, nullptr, 0u, 1, 0};
     if (var.splits > 1) {
-        uint32_t epoch = g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;
-        if (epoch == 0) epoch = g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;   // flags start at 0
+        const uint32_t epoch = next_epoch();
         // one iteration less for every writer (measured on 2048 x 4096 x 4096 and x 16384 in two ranges: 64 k
         // takes 1-2 us off, 128 and more give it back)
         const int skew = (var.k64 && K / var.splits >= 1024) ? TileCfgK64::KS : 0;
@@ -824,6 +841,10 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
         group_launch(p.how.group, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc);
         return;
     }
+    if (p.how.split.tile >= 0) {
+        group_split_launch(p.how.split, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc, scratch.partials, scratch.flags, scratch.timeouts(), next_epoch());
+        return;
+    }
     if (var.edge && p.how.tile < 0) {
         const int tiles_n = (int)((p.n + var.bn - 1) / var.bn);
         edge_kernel_launch(layout, (unsigned)part_workgroups(p), s, A, B, C, p.m, p.n, K, lda, ldb, ldc, tiles_n);
@@ -852,6 +873,9 @@ static int plan_call(int64_t M, int64_t N, int64_t K, int layout, ScratchFrom fr
             if (forced >= 0) return AXONN_ERR_WORKSPACE;
             plan = cached_plan(M, N, K, layout, false);   // no area, or too small a one: the kernels that need none
         }
+        // the eight-wave kernel's partial sums may take more than the variant's: where the area is short of them, the variant itself
+        for (int i = 0; i < plan.parts; ++i)
+            if (group_split_bytes(plan.part[i].how.split, plan.part[i].m, plan.part[i].n) > scratch.partial_bytes) plan.part[i].how.split = GroupSplitChoice{};
     }
     return AXONN_OK;
 }
@@ -873,6 +897,11 @@ static int part_kernel_name(const Part& p, int64_t N, int64_t K, int layout, cha
         int rows = 0, cols = 0, groups = 0;
         group_tile(p.how.group, &rows, &cols, &groups);
         return std::snprintf(name, bytes, "mfma16k64g_%dx%d%s%s", rows, cols, groups == 2 ? "_g2" : "", tail);
+    }
+    if (p.how.split.tile >= 0) {
+        int rows = 0, cols = 0;
+        group_split_tile(p.how.split, &rows, &cols);
+        return std::snprintf(name, bytes, "mfma16k64g_%dx%d_sk%d", rows, cols, p.how.split.splits);
     }
     if (planned.edge && p.how.tile < 0) return std::snprintf(name, bytes, "edge_%dx%d", planned.bm, planned.bn);
     const Variant& var = p.how.tile >= 0 ? variants()[p.how.tile] : planned;
@@ -1157,6 +1186,8 @@ int axonn_linear_part_kernel(int64_t M, int64_t N, int64_t K, int layout, int no
         if (rc != AXONN_OK) return rc;
     } else {
         plan = axonn::cached_plan(M, N, K, layout, axonn::g_split_k_enabled.load(std::memory_order_relaxed) != 0);
+        // with the scratch area that axonn_linear_workspace_bytes asks for: the variants' own kernels
+        for (int i = 0; i < plan.parts; ++i) plan.part[i].how.split = axonn::GroupSplitChoice{};
     }
     if (part >= plan.parts) return AXONN_ERR_INVALID_ARG;
     const int n = axonn::part_kernel_name(plan.part[part], N, K, layout, name, name_bytes);

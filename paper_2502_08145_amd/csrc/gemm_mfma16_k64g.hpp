@@ -240,10 +240,102 @@ struct GroupCfg {
     static constexpr int WAVES_PER_SIMD = 2 * LDS_BYTES <= 160 * 1024 ? 4 : 2;
 };
 
-// One tile.  LINES: its K-contiguous operands by lines; K > 64 NS.
-template <int BM, int BN, int G, bool A_KC, bool B_KC, bool KTAIL, bool LINES>
+// ---- split-K: the sums of a tile's `splits` workgroups, every one of which adds up and stores a share of the blocks --------------
+//
+// Range r stores the blocks of its wave tiles that are another's, waits for the others of its tile, and adds up its own over the ranges,
+// in their order (the result depends neither on timing nor on who adds).  All of them move their share at once, where one
+// reader per tile takes splits - 1 whole ones while the others' compute units have gone idle.
+//
+// The workgroups of a tile follow one another in the order of dispatch, so they are there together, or will be as soon as the tiles
+// before have ended: at most 2 (splits - 1) of an XCD's 32 compute units hold a tile that is not complete.  (The wait is bounded all the same.)
+//
+// What it replaces: one reader per tile on the 32-k ring and the four-wave 64-k kernel, half the compute units idle at 120 tiles in two ranges.  us,
+// before and here: 1920 x 1024 x 16384 NT 101 -> 70;  640 x 1024 x 8832 NT 37.2 -> 23.2;  256 x 1024 x 12032 NN 30.0 -> 16.5 (six ranges).
+// With a counter per tile (a compare-and-swap, a poll and an addition one after the other) the exchange took 8 us longer, with fences 10.
+//
+// A flag per pair of ranges of a tile, valid when it equals the launch's epoch; the range that waits for it takes it back to 0, so that a
+// launch replayed from a captured graph does not find its own value.
+//
+// No fences: a device-scope release would write the whole L2 back and an acquire invalidate it, under the other tiles' K loops.  The sums
+// leave as device-scope stores that are acknowledged before the flags go out, and come as device-scope loads, past the L2.
+struct GroupSplit {
+    float* partials;      // [tiles][splits] slots of BM * BN floats: 16 x 16 block, wave, lane
+    uint32_t* flags;      // [tiles][splits: who waits][splits - 1]
+    uint32_t* timeouts;
+    uint32_t epoch;       // not 0
+    int splits;           // 2 .. 6, 8
+};
+
+// By the first wave: tell the tile's other ranges, and wait for them.
+__device__ __forceinline__ void group_split_meet(const GroupSplit& sp, uint32_t* flags, int range, int lane) {
+    const int others = sp.splits - 1;
+    if (lane < others) {
+        const int other = lane + (lane >= range ? 1 : 0);
+        uint32_t* const theirs = flags + other * others + (range - (range > other ? 1 : 0));
+        uint32_t* const ours = flags + range * others + lane;
+        __hip_atomic_store(theirs, sp.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t probes = 0; __hip_atomic_load(ours, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != sp.epoch;) {
+            if (++probes > kSplitSpinLimit) {
+                atomicAdd(sp.timeouts, 1u);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __hip_atomic_store(ours, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+// Device-scope load: from memory, past what this XCD's L2 holds, so that no cache has to be invalidated first.
+__device__ __forceinline__ f32x4 load_device_scope(const f32x4* p) {
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const uint64_t* const q = reinterpret_cast<const uint64_t*>(p);
+    const u64x2 v{__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+    return __builtin_bit_cast(f32x4, v);
+}
+
+template <int BM, int BN, int MI, int NI, int S>
+__device__ __forceinline__ void group_split_finish(f32x4 (&acc)[MI][NI], const GroupSplit& sp, int tile, int range, uint16_t* pc, int ldc,
+                                                   int wave, int lane, int t) {
+    constexpr int BLOCKS = MI * NI, NW = 8, SLOT = BM * BN / 4, OWN = (BLOCKS + S - 1) / S;   // SLOT: f32x4 of a slot
+    const int first = (range * BLOCKS + S - 1) / S, count = ((range + 1) * BLOCKS + S - 1) / S - first;   // this workgroup's blocks
+    f32x4* const slots = reinterpret_cast<f32x4*>(sp.partials) + (size_t)tile * S * SLOT + wave * 64 + lane;
+    f32x4* const mine = slots + (size_t)range * SLOT;
+#pragma unroll
+    for (int u = 0; u < BLOCKS; ++u)
+        if (u < first || u >= first + count)   // device-scope stores and the wait state behind them: see split_k_exchange16
+            asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(mine + u * (NW * 64)), "v"(acc[u / NI][u % NI]) : "memory");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // acknowledged: the compiler does not count stores issued from asm
+    __syncthreads();
+    if (wave == 0) group_split_meet(sp, sp.flags + tile * S * (S - 1), range, lane);
+    __syncthreads();
+    // all of the other ranges' sums in flight together
+    f32x4 v[OWN][S - 1];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+        if (i < count)
+#pragma unroll
+            for (int q = 0; q < S - 1; ++q)
+                v[i][q] = load_device_scope(slots + (size_t)(q + (q >= range ? 1 : 0)) * SLOT + (first + i) * (NW * 64));
+    __builtin_amdgcn_sched_barrier(0);
+    pc += (int64_t)(lane & 15) * ldc + 4 * (lane >> 4);
+#pragma unroll
+    for (int i = 0; i < OWN; ++i)
+        if (i < count) {
+            f32x4 sum;
+#pragma unroll
+            for (int u = 0; u < BLOCKS; ++u)
+                if (u == first + i) sum = acc[u / NI][u % NI];
+#pragma unroll
+            for (int q = 0; q < S - 1; ++q) sum += v[i][q];
+            const u32x2 w{pack2_bf16(sum[0], sum[1]), pack2_bf16(sum[2], sum[3])};
+            __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(pc + (int64_t)(16 * ((first + i) / NI)) * ldc + 16 * ((first + i) % NI)));
+        }
+}
+
+// One tile.  LINES: its K-contiguous operands by lines; K > 64 NS.  SPLITK: one of the K ranges of a tile.
+template <int BM, int BN, int G, bool A_KC, bool B_KC, bool KTAIL, bool LINES, bool SPLITK = false>
 __device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
-                                           int K, int lda, int ldb, int ldc, int64_t m0, int64_t n0, int k_tail) {
+                                           int K, int lda, int ldb, int ldc, int64_t m0, int64_t n0, int k_tail,
+                                           const GroupSplit& split = GroupSplit{}, int tile = 0, int range = 0) {
     constexpr bool LINES_A = LINES && A_KC, LINES_B = LINES && B_KC;
     using Cfg = GroupCfg<BM, BN, G, LINES>;
     constexpr int NW = Cfg::NW, NS = Cfg::NS;
@@ -470,9 +562,20 @@ __device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const
             });
         }
     }
-    __syncthreads();   // the stages are free
+    if constexpr (!SPLITK) __syncthreads();   // the stages are free
     asm volatile("" : "+v"(lane));   // see split_k_exchange16: keeps the epilogue's addresses out of the K loop's registers
-    if constexpr (G == 1) {
+    if constexpr (SPLITK) {
+        static_assert(G == 1, "the waves divide the tile");
+        uint16_t* const pc = C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN;
+        switch (split.splits) {
+            case 2: group_split_finish<BM, BN, MI, NI, 2>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+            case 3: group_split_finish<BM, BN, MI, NI, 3>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+            case 4: group_split_finish<BM, BN, MI, NI, 4>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+            case 5: group_split_finish<BM, BN, MI, NI, 5>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+            case 6: group_split_finish<BM, BN, MI, NI, 6>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+            default: group_split_finish<BM, BN, MI, NI, 8>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+        }
+    } else if constexpr (G == 1) {
         uint8_t* const epi = smem + wave * (32 * TN);
         uint16_t* const pc = C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN;
 #pragma unroll
@@ -508,6 +611,25 @@ __device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const
         for (int i = 0; i < MH; ++i) store_block_row16<TN, NI>(out[i], epi, pc + (int64_t)(16 * i) * ldc, ldc, lane);
     }
 #undef AXONN_FENCE
+}
+
+// The same over `split.splits` K ranges per tile, of K / 64 / splits or one more 64 k; whole tiles, K >= 64 splits.
+template <int BM, int BN, bool A_KC, bool B_KC>
+__global__ __launch_bounds__(512, (GroupCfg<BM, BN, 1>::WAVES_PER_SIMD)) void gemm_tile_kernel_k64gs(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C,
+    int K, int lda, int ldb, int ldc, int tiles_m, int tiles_n, int group_m, GroupSplit split) {
+    const int tiles = tiles_m * tiles_n, nwg = tiles * split.splits;
+    // XCD x runs the workgroups x, x + 8, ...: a contiguous chunk of the sequence (tile, range), see map_workgroup
+    const int x = blockIdx.x & 7, rem = nwg & 7;
+    const int id = x * (nwg >> 3) + (x < rem ? x : rem) + (blockIdx.x >> 3);
+    const int tile = id / split.splits, range = id - tile * split.splits;
+    const int group_sz = group_m * tiles_n, group = tile / group_sz, first_m = group * group_m;
+    const int gm = min(tiles_m - first_m, group_m), in_group = tile - group * group_sz;
+    const int64_t m0 = (int64_t)(first_m + in_group % gm) * BM, n0 = (int64_t)(in_group / gm) * BN;
+    const int steps = K / 64, each = steps / split.splits, more = steps - each * split.splits;
+    const int64_t k0 = 64 * (int64_t)(each * range + min(range, more));
+    group_tile<BM, BN, 1, A_KC, B_KC, false, false, true>(A + (A_KC ? k0 : k0 * lda), B + (B_KC ? k0 : k0 * ldb), C,
+                                                         64 * (each + (range < more ? 1 : 0)), lda, ldb, ldc, m0, n0, 0, split, tile, range);
 }
 
 // Requires M >= BM, N >= BN, K % 64 == 0 (KTAIL: see TileGrid), and 16-byte aligned rows.

@@ -43,6 +43,18 @@ void group_tile(const GroupChoice& c, int* rows, int* cols, int* groups);
 void group_launch(const GroupChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                   int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);
 
+// the same kernel in several K ranges per tile (gemm_tile_kernel_k64gs), for blocks of whole tiles; through the scratch area
+struct GroupSplitChoice {
+    int tile = -1, splits = 0;  // tile < 0: none takes this block within the limits
+    double us = 0.0;            // modelled time
+};
+GroupSplitChoice group_split_choose(int layout, int64_t m, int64_t n, int64_t K, size_t max_bytes, int64_t max_flags);
+size_t group_split_bytes(const GroupSplitChoice& c, int64_t m, int64_t n);   // of partial sums
+void group_split_tile(const GroupSplitChoice& c, int* rows, int* cols);
+// epoch: not 0, another one for every launch
+void group_split_launch(const GroupSplitChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C, int64_t m, int64_t n,
+                        int64_t K, int64_t lda, int64_t ldb, int64_t ldc, float* partials, uint32_t* flags, uint32_t* timeouts, uint32_t epoch);
+
 // guarded MFMA kernel (gemm_edge_kernel): any m, n, K >= 1 and any leading dimensions
 void edge_kernel_raise_lds_limit();
 void edge_kernel_launch(int layout, unsigned workgroups, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,

@@ -106,13 +106,6 @@ void group_tile(const GroupChoice& c, int* rows, int* cols, int* groups) {
     *groups = kTiles[c.tile].groups;
 }
 
-void group_raise_lds_limit() {
-    for (const GroupTile& t : kTiles)
-        for (int l = 0; l < 3; ++l)
-            for (const tile_kernel_t fn : {t.fn[l], t.fn_tail[l]})
-                if (fn) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, t.lds_bytes);
-}
-
 void group_launch(const GroupChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C,
                   int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const GroupTile& t = kTiles[c.tile];
@@ -120,6 +113,79 @@ void group_launch(const GroupChoice& c, int layout, hipStream_t s, const uint16_
     hipLaunchKernelGGL(k_tail ? t.fn_tail[layout] : t.fn[layout], dim3((unsigned)((int64_t)tiles_m * tiles_n)), dim3(512), t.lds_bytes, s, A, B, C,
                        (int)(K - k_tail + (k_tail ? 64 : 0)), (int)lda, (int)ldb, (int)ldc,
                        TileGrid{tiles_m, tiles_n, (int)(m - t.bm), (int)(n - t.bn), k_tail}, tiles_m < 8 ? tiles_m : 8, SplitK{});
+}
+
+// ---- split-K ----------------------------------------------------------------------------------------------------------------------
+// Modelled time: launch and exchange, plus for every round of 256 workgroups the 64-k steps of a range and what it costs beside them,
+// plus the bytes of partial sums that are written and read back (`moved`, per MB).  Least squares over 700 sampled products that are planned
+// with split-K, operands in cache, of three sets in turn, and from memory (residual 7-10 %); what is chosen takes 1.011 times the best of the
+// tiles and counts measured.
+struct GroupSplitTile {
+    int bm, bn, lds_bytes;
+    double launch, us64[3], apart, tile, moved, last;
+    void (*fn[3])(const uint16_t*, const uint16_t*, uint16_t*, int, int, int, int, int, int, int, GroupSplit);
+};
+#define AXONN_SPLIT_TILE(BM, BN, ...) {BM, BN, GroupCfg<BM, BN, 1>::LDS_BYTES, __VA_ARGS__, {gemm_tile_kernel_k64gs<BM, BN, true, false>, \
+                                       gemm_tile_kernel_k64gs<BM, BN, true, true>, gemm_tile_kernel_k64gs<BM, BN, false, false>}}
+static const GroupSplitTile kSplitTiles[] = {
+    AXONN_SPLIT_TILE(64, 128, 7.27, {0.203, 0.203, 0.213}, 1.263, 7.02, 0.317, 0.800),
+    AXONN_SPLIT_TILE(128, 128, 7.71, {0.376, 0.376, 0.381}, 0.577, 7.66, 0.365, 0.672),
+    AXONN_SPLIT_TILE(256, 128, 6.27, {0.561, 0.556, 0.548}, 0.865, 10.0, 0.792, 0.594),
+    AXONN_SPLIT_TILE(128, 256, 8.87, {0.690, 0.708, 0.722}, 0.0, 7.91, 0.556, 0.764),
+};
+#undef AXONN_SPLIT_TILE
+static const int kSplitCounts[] = {2, 3, 4, 5, 6, 8};   // the ones that group_tile has an exchange for
+
+size_t group_split_bytes(const GroupSplitChoice& c, int64_t m, int64_t n) {
+    return c.tile < 0 ? 0 : (size_t)(m * n * c.splits) * sizeof(float);   // whole tiles
+}
+
+GroupSplitChoice group_split_choose(int layout, int64_t m, int64_t n, int64_t K, size_t max_bytes, int64_t max_flags) {
+    GroupSplitChoice best;
+    if (K % 64 != 0) return best;
+    for (int i = 0; i < (int)(sizeof(kSplitTiles) / sizeof(kSplitTiles[0])); ++i) {
+        const GroupSplitTile& t = kSplitTiles[i];
+        if (m % t.bm != 0 || n % t.bn != 0) continue;
+        const int64_t tiles_m = m / t.bm, tiles = tiles_m * (n / t.bn);
+        for (const int splits : kSplitCounts) {
+            const int64_t wgs = tiles * splits, rest = wgs % 256;
+            // up to two rounds: more were not tried
+            if (wgs > 512 || K / 64 < splits || tiles * splits * (splits - 1) > max_flags) continue;
+            if (group_split_bytes(GroupSplitChoice{i, splits, 0.0}, m, n) > max_bytes) continue;
+            // the ranges of a tile run behind one L2, each over another K: fewer tiles there have a panel in common
+            const double behind = std::max(std::min(std::ceil((double)wgs / 8.0), 32.0) / splits, 1.0);
+            const double rows = std::min(std::min((double)tiles_m, 8.0), behind), cols = std::max(behind / rows, 1.0);
+            const double panels = (rows * t.bm + cols * t.bn) / (behind * (t.bm + t.bn));
+            const double step = t.us64[layout] * (1.0 + t.apart * panels * std::min(1.0, 2e-6 * (double)K * (double)(m + n) / 16.0));
+            const double rounds = (double)(wgs / 256) + (rest ? t.last + (1.0 - t.last) * (double)rest / 256.0 : 0.0);
+            const double moved = 8e-6 * (double)m * (double)n * (splits - 1) / splits;
+            const double us = t.launch + rounds * ((double)((K / 64 + splits - 1) / splits) * step + t.tile) + t.moved * moved;
+            if (best.tile < 0 || us < best.us) best = GroupSplitChoice{i, splits, us};
+        }
+    }
+    return best;
+}
+
+void group_split_tile(const GroupSplitChoice& c, int* rows, int* cols) {
+    *rows = kSplitTiles[c.tile].bm;
+    *cols = kSplitTiles[c.tile].bn;
+}
+
+void group_split_launch(const GroupSplitChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C, int64_t m, int64_t n,
+                        int64_t K, int64_t lda, int64_t ldb, int64_t ldc, float* partials, uint32_t* flags, uint32_t* timeouts, uint32_t epoch) {
+    const GroupSplitTile& t = kSplitTiles[c.tile];
+    const int tiles_m = (int)(m / t.bm), tiles_n = (int)(n / t.bn);
+    hipLaunchKernelGGL(t.fn[layout], dim3((unsigned)(tiles_m * tiles_n * c.splits)), dim3(512), t.lds_bytes, s, A, B, C, (int)K, (int)lda, (int)ldb, (int)ldc,
+                       tiles_m, tiles_n, tiles_m < 8 ? tiles_m : 8, GroupSplit{partials, flags, timeouts, epoch, c.splits});
+}
+
+void group_raise_lds_limit() {
+    for (const GroupTile& t : kTiles)
+        for (int l = 0; l < 3; ++l)
+            for (const tile_kernel_t fn : {t.fn[l], t.fn_tail[l]})
+                if (fn) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, t.lds_bytes);
+    for (const GroupSplitTile& t : kSplitTiles)
+        for (const auto fn : t.fn) (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, t.lds_bytes);
 }
 
 }  // namespace axonn

@@ -42,6 +42,10 @@ def short(name: str) -> str:
     if m:
         bm, bn, groups, akc, bkc, tail = m.groups()
         return f"mfma16k64g_{bm}x{bn}{'_g2' if groups == '2' else ''}{'_ktail' if tail == 'true' else ''}/{_LAYOUT.get((akc, bkc), '??')}"
+    m = re.search(rf"gemm_tile_kernel_k64gs<(\d+), (\d+), {_BOOL}, {_BOOL}>", name)
+    if m:
+        bm, bn, akc, bkc = m.groups()
+        return f"mfma16k64g_{bm}x{bn}_sk/{_LAYOUT.get((akc, bkc), '??')}"
     m = re.search(rf"gemm_tile_kernel_k64p<{_BOOL}, {_BOOL}>", name)
     if m:
         return f"mfma16k64p_256x256_w8/{_LAYOUT.get(m.groups(), '??')}"

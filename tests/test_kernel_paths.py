@@ -202,6 +202,71 @@ def test_k_contiguous_rows_loaded_by_lines(tile, layout):
             assert torch.equal(c[:M], ref.to(torch.bfloat16)) and bool(c[M:].isnan().all())
 
 
+@lru_cache(maxsize=None)
+def eight_wave_split_products():
+    """{(kernel, layout): the smallest sampled product of one launch on it} with the whole scratch area registered; ranges of equal length
+    and not, from a few 64 k to some dozens."""
+    rng = random.Random(18)
+    found = {}
+    for _ in range(30000):
+        layout, M, N, K = rng.choice(LAYOUTS), *(_log_int(rng, 128, 4096, 128) for _ in range(2)), _log_int(rng, 512, 24000, 64)
+        if M * N > 1 << 22 or M * N * K > 3e10:
+            continue
+        names = B.kernels(M, N, K, layout, now=True)
+        if len(names) == 1 and re.match(r"mfma16k64g_\d+x\d+_sk", names[0]):
+            best = found.setdefault((names[0], layout), (M, N, K))
+            if M * N * K < math.prod(best):
+                found[(names[0], layout)] = (M, N, K)
+    return found
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_split_k_on_the_eight_wave_kernel(oracle_mod, layout):
+    """Every tile and number of K ranges that the library picks: every element, the flags taken back, the same bits again, and from a
+    captured graph, which carries one epoch through its replays."""
+    area = B.register_workspace()
+    products = {name: shape for (name, lay), shape in eight_wave_split_products().items() if lay == layout}
+    assert {n.split("_sk")[0] for n in products} >= {"mfma16k64g_64x128", "mfma16k64g_128x128"}, products
+    assert {int(n.split("_sk")[1]) for n in products} >= {2, 3, 4, 5}, products
+    for name, (M, N, K) in sorted(products.items()):
+        print(f"  {name} {layout} {(M, N, K)}", flush=True)
+        _check(oracle_mod, M, N, K, layout, [name])
+    name, (M, N, K) = min(products.items(), key=lambda p: math.prod(p[1]))
+    x = torch.randn((K, M) if layout == "TN" else (M, K), device="cuda").to(torch.bfloat16)
+    y = torch.randn((N, K) if layout == "NT" else (K, N), device="cuda").to(torch.bfloat16)
+    want, c = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    B.axonn_linear_fwd(M, N, K, layout, x, y, want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(2):
+            B.axonn_linear_fwd(M, N, K, layout, x, y, c)
+    for _ in range(4):
+        c.zero_()
+        graph.replay()
+        B.axonn_linear_fwd(M, N, K, layout, x, y, want)
+        torch.cuda.synchronize()
+        assert torch.equal(c.view(torch.int16), want.view(torch.int16)), name
+    assert not area[:4096].any() and B.axonn_linear_split_k_timeouts() == 0
+
+
+@pytest.mark.gpu
+def test_an_area_of_the_advertised_size_runs_the_planned_variant(oracle_mod):
+    """The eight-wave kernel's partial sums take more than the variant's: without room for them the variant itself runs."""
+    shape = (1024, 1024, 4096, "NT")
+    B.register_workspace()
+    wide = B.kernels(*shape, now=True)
+    try:
+        exact = torch.zeros((B.axonn_linear_workspace_bytes(*shape),), dtype=torch.uint8, device="cuda")
+        B.axonn_linear_set_workspace(exact)
+        assert B.kernels(*shape, now=True) == B.kernels(*shape) != wide
+        _check(oracle_mod, *shape, B.kernels(*shape))
+        assert not exact[:4096].any()
+    finally:
+        B.register_workspace()
+
+
 @pytest.mark.gpu
 def test_a_ragged_layer_s_data_gradient(oracle_mod):
     _check(oracle_mod, 1064, 1608, 4168, "NT", ["mfma16k64g_64x128_ktail"])
