@@ -8,12 +8,15 @@ of a symbol fails loudly -- there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch  # noqa: F401  (imported before the library so both share one HIP runtime)
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "lib", "libaxonn_linear.so")
+MARSHAL_PATH = os.path.join(_HERE, "lib", "axonn_marshal.so")
 
 AXONN_NN, AXONN_NT, AXONN_TN = 0, 1, 2
 LAYOUTS = {"NN": AXONN_NN, "NT": AXONN_NT, "TN": AXONN_TN}
@@ -33,6 +36,11 @@ EXPORTS = (
 )
 
 _lib = None
+
+# The native marshalling of the calls on the hot path (csrc/marshal.cpp) and the addresses of their entry points, set by lib().  A call that it
+# answers with None, as all are before that, takes the general path below.
+_gemm = _tuned = _transpose = lambda *args: None
+_fwd_at = _bwd_data_at = _bwd_weight_at = _static_at = _tuned_at = _transpose_at = 0
 
 
 class PlanPart(ctypes.Structure):
@@ -145,8 +153,23 @@ def lib() -> ctypes.CDLL:
         L.axonn_linear_set_split_k.restype = ci
         L.axonn_linear_split_k_timeouts.argtypes = [ctypes.POINTER(ctypes.c_uint64)]
         L.axonn_linear_split_k_timeouts.restype = ci
+        _load_marshal(L)
         _lib = L
     return _lib
+
+
+def _load_marshal(L) -> None:
+    global _gemm, _tuned, _transpose, _fwd_at, _bwd_data_at, _bwd_weight_at, _static_at, _tuned_at, _transpose_at
+    if not os.path.exists(MARSHAL_PATH):
+        raise ImportError(f"{MARSHAL_PATH} is missing: build it with `python -m paper_2502_08145_amd.build`")
+    loader = importlib.machinery.ExtensionFileLoader("axonn_marshal", MARSHAL_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("axonn_marshal", loader))
+    loader.exec_module(module)
+    _fwd_at, _bwd_data_at, _bwd_weight_at, _static_at, _tuned_at, _transpose_at = (
+        ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in
+        ("axonn_linear_fwd", "axonn_linear_bwd_data", "axonn_linear_bwd_weight", "axonn_linear_gemm_static",
+         "axonn_linear_tuned_call", "axonn_transpose_bf16"))
+    _gemm, _tuned, _transpose = module.gemm, module.tuned, module.transpose
 
 
 def status_string(status: int) -> str:
@@ -313,9 +336,11 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
-def _call(name, M, N, K, layout, a, b, c, fp32_accumulate, stream, check):
-    rc = getattr(_lib or lib(), name)(int(M), int(N), int(K), _layout(layout), _ptr(a), _ptr(b), _ptr(c),
-                              int(fp32_accumulate), _stream(stream))
+def _call(name, rc, M, N, K, layout, a, b, c, fp32_accumulate, stream, check):
+    """The general path, for a call that has not run yet (rc: None), and what follows a status that is not AXONN_OK."""
+    if rc is None:
+        rc = getattr(_lib or lib(), name)(int(M), int(N), int(K), _layout(layout), _ptr(a), _ptr(b), _ptr(c),
+                                          int(fp32_accumulate), _stream(stream))
     if check and rc != AXONN_OK:
         raise AxonnError(rc, name)
     return rc
@@ -323,22 +348,34 @@ def _call(name, M, N, K, layout, a, b, c, fp32_accumulate, stream, check):
 
 def axonn_linear_fwd(M, N, K, layout, X, W, Y, fp32_accumulate=1, stream=None, check=True):
     """Y[M,N] = X * W (Algorithm 1 line 3); X, W stored as `layout` says; Y is written."""
-    return _call("axonn_linear_fwd", M, N, K, layout, X, W, Y, fp32_accumulate, stream, check)
+    rc = _gemm(_fwd_at, M, N, K, layout, X, W, Y, fp32_accumulate, stream)
+    if rc == AXONN_OK:
+        return rc
+    return _call("axonn_linear_fwd", rc, M, N, K, layout, X, W, Y, fp32_accumulate, stream, check)
 
 
 def axonn_linear_bwd_data(M, N, K, layout, dY, W, dX, fp32_accumulate=1, stream=None, check=True):
     """dX[M,N] = dY * W^T (Algorithm 1 line 11)."""
-    return _call("axonn_linear_bwd_data", M, N, K, layout, dY, W, dX, fp32_accumulate, stream, check)
+    rc = _gemm(_bwd_data_at, M, N, K, layout, dY, W, dX, fp32_accumulate, stream)
+    if rc == AXONN_OK:
+        return rc
+    return _call("axonn_linear_bwd_data", rc, M, N, K, layout, dY, W, dX, fp32_accumulate, stream, check)
 
 
 def axonn_linear_bwd_weight(M, N, K, layout, X, dY, dW, fp32_accumulate=1, stream=None, check=True):
     """dW[M,N] = X^T * dY (Algorithm 1 line 13)."""
-    return _call("axonn_linear_bwd_weight", M, N, K, layout, X, dY, dW, fp32_accumulate, stream, check)
+    rc = _gemm(_bwd_weight_at, M, N, K, layout, X, dY, dW, fp32_accumulate, stream)
+    if rc == AXONN_OK:
+        return rc
+    return _call("axonn_linear_bwd_weight", rc, M, N, K, layout, X, dY, dW, fp32_accumulate, stream, check)
 
 
 def axonn_linear_gemm_static(M, N, K, layout, first, second, out, fp32_accumulate=1, stream=None, check=True):
     """out[M,N] = the product, split-K through the library's static scratch array (no allocation anywhere)."""
-    return _call("axonn_linear_gemm_static", M, N, K, layout, first, second, out, fp32_accumulate, stream, check)
+    rc = _gemm(_static_at, M, N, K, layout, first, second, out, fp32_accumulate, stream)
+    if rc == AXONN_OK:
+        return rc
+    return _call("axonn_linear_gemm_static", rc, M, N, K, layout, first, second, out, fp32_accumulate, stream, check)
 
 
 def axonn_linear_static_scratch_bytes() -> int:
@@ -359,7 +396,9 @@ def transpose_kernel_at(rows: int, cols: int, src: int, dst: int):
 
 def axonn_transpose_bf16(rows, cols, src, dst, stream=None, check=True):
     """dst[cols, rows] = transpose of src[rows, cols] (bf16 tensors or raw device addresses)."""
-    rc = lib().axonn_transpose_bf16(rows, cols, _ptr(src), _ptr(dst), _stream(stream))
+    rc = _transpose(_transpose_at, rows, cols, src, dst, stream)
+    if rc is None:
+        rc = lib().axonn_transpose_bf16(rows, cols, _ptr(src), _ptr(dst), _stream(stream))
     if check and rc != 0:
         raise AxonnError(rc, "axonn_transpose_bf16")
     return rc
@@ -399,6 +438,12 @@ def axonn_linear_tuned_set(op, M, N, K, best_layout_all_in, best_layout=None) ->
 def axonn_linear_tuned_call(op, M, N, K, first, second, out, second_restored=None, scratch=None, fp32_accumulate=1,
                             stream=None, check=True):
     """Run the product in its tuned mode; returns the mode that ran (0 NN, 1 NT, 2 TN)."""
+    if scratch is None:
+        rc = _tuned(_tuned_at, op, M, N, K, first, second, out, second_restored, fp32_accumulate, stream)
+        if rc is not None:
+            if check and rc < 0:
+                raise AxonnError(rc, "axonn_linear_tuned_call")
+            return rc
     used = ctypes.c_int(-1)
     sp, sb = (0, 0) if scratch is None else (scratch.data_ptr(), scratch.numel() * scratch.element_size())
     rc = lib().axonn_linear_tuned_call(OP_INDEX[op] if isinstance(op, str) else int(op), M, N, K, _ptr(first), _ptr(second),

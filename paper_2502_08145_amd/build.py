@@ -16,6 +16,7 @@ UNITS = ["axonn_linear.hip", "kernels_k64.hip", "kernels_k64g.hip", "kernels_rin
 LIB_DIR = os.path.join(HERE, "lib")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(LIB_DIR, "libaxonn_linear.so")
+MARSHAL = os.path.join(LIB_DIR, "axonn_marshal.so")   # host code only: the Python extension that marshals binding.py's calls
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
@@ -65,8 +66,20 @@ def _run(cmd, verbose):
         print(err, file=sys.stderr)
 
 
+def marshal_command(out: str = MARSHAL):
+    """The host compiler's call for the extension: Python's and torch's headers, torch's libraries as they are loaded already."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+            "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+            "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc())), "include"),
+            os.path.join(CSRC, "marshal.cpp"), "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", out]
+
+
 def build(verbose: bool = False, extra=(), units=None, out: str = LIB) -> str:
-    """Compile every translation unit (in parallel) and link them into the shared library."""
+    """Compile every translation unit (in parallel) and link them into the shared library; the Python extension beside it."""
     from concurrent.futures import ThreadPoolExecutor
     os.makedirs(os.path.dirname(out), exist_ok=True)
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -74,6 +87,8 @@ def build(verbose: bool = False, extra=(), units=None, out: str = LIB) -> str:
     units = list(units or UNITS)
     objs = [os.path.join(OBJ_DIR, u.replace(".hip", ".o")) for u in units]
     cmds = [[cc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, u), "-o", o] for u, o in zip(units, objs)]
+    if out == LIB:
+        cmds.append(marshal_command())
     with ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as ex:
         list(ex.map(lambda c: _run(c, verbose), cmds))
     _run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", out], verbose)

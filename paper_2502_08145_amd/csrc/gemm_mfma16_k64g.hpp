@@ -242,8 +242,8 @@ struct GroupCfg {
 
 // ---- split-K: the sums of a tile's `splits` workgroups, every one of which adds up and stores a share of the blocks --------------
 //
-// Range r stores the blocks of its wave tiles that are another's, waits for the others of its tile, and adds up its own over the ranges,
-// in their order (the result depends neither on timing nor on who adds).  All of them move their share at once, where one
+// Range r stores the blocks of its wave tiles that are another's, waits for the others of its tile, and adds up its own: its own
+// sum, then the other ranges' in their order (the result does not depend on timing).  All of them move their share at once, where one
 // reader per tile takes splits - 1 whole ones while the others' compute units have gone idle.
 //
 // The workgroups of a tile follow one another in the order of dispatch, so they are there together, or will be as soon as the tiles
