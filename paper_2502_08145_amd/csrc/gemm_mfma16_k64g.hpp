@@ -327,7 +327,8 @@ __device__ __forceinline__ void group_split_finish(f32x4 (&acc)[MI][NI], const G
 #pragma unroll
             for (int q = 0; q < S - 1; ++q) sum += v[i][q];
             const u32x2 w{pack2_bf16(sum[0], sum[1]), pack2_bf16(sum[2], sum[3])};
-            __builtin_nontemporal_store(w, reinterpret_cast<u32x2*>(pc + (int64_t)(16 * ((first + i) / NI)) * ldc + 16 * ((first + i) % NI)));
+            // 32 bytes a row: left to the L2 to put together (non-temporal, each went to memory by itself: 640 x 1024 x 8832 NT 23.2 us, 22.6 so)
+            *reinterpret_cast<u32x2*>(pc + (int64_t)(16 * ((first + i) / NI)) * ldc + 16 * ((first + i) % NI)) = w;
         }
 }
 
