@@ -449,11 +449,15 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
     // and 24.0); over K of 192 to 512 35 ran 1.10 and 1.03 times.
     const bool long_k = K >= 6000 && 2.0 * (double)m * (double)n * (double)K > 300e9;
     const bool two_steps = K <= 2 * 64 && ldc % 64 == 0 && m * n >= (int64_t)16 << 20;
+    bool tie = false;
     if (found && variants()[best.tile].group && (long_k || two_steps))
         for (int v = 1; v < edge_variant(); ++v)
             if (variants()[v].k64 && variants()[v].splits == 1 && variants()[v].bm * variants()[v].bn == 256 * 256) {
                 const double us = block_us(v, m, n, K, layout, lda, ldb, ldc);
-                if (us >= 0.0 && us < (two_steps ? 1.15 : 1.06) * best.us) best.tile = v;
+                if (us >= 0.0 && us < (two_steps ? 1.15 : 1.06) * best.us) {
+                    best.tile = v;
+                    tie = true;   // with the other tiles of that model as well
+                }
             }
     if (lda % 8 != 0 || ldb % 8 != 0 || ldc % 8 != 0 || std::max(std::max(lda, ldb), std::max(ldc, std::max(m, K))) > kMaxTileDim) return found;
     // wavek_stays: near a tie.  Either model is good to 6 %, and where operands come from memory (12 MB and more) its
@@ -462,7 +466,7 @@ static bool tiles_choice(int64_t m, int64_t n, int64_t K, int layout, int64_t ld
     // 506 x 816 x 3112 12.4 us and 13.5, from memory 15.4 and 19.7).
     const GroupChoice g = group_choose(layout, m, n, K, lda, ldb, ldc);
     const bool far = m * K + K * n > (int64_t)6000000 || (layout == AXONN_NN && K % 64 != 0 && K > 2 * kGroupLinesK);
-    const double near = best.wavek.tile < 0 || !wavek_stays ? 1.0 : far ? 0.88 : 0.96;
+    const double near = tie ? (two_steps ? 1.0 / 1.15 : 1.0 / 1.06) : best.wavek.tile < 0 || !wavek_stays ? 1.0 : far ? 0.88 : 0.96;
     if (g.tile >= 0 && g.us < near * best.us) {
         best = BlockChoice{};
         best.group = g;

@@ -83,6 +83,17 @@ __device__ __forceinline__ void direct_load16_from(uint32_t lds_dst, const uint8
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
                  :: "v"(lane_src), "s"(lds_dst) : "memory", "m0");
 }
+// Both by the lanes of `lanes` only.  (The whole wave is active around it.)
+__device__ __forceinline__ void direct_load16(uint32_t lds_dst, const uint8_t* base, uint32_t voff, uint64_t lanes) {
+    lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
+    asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
+                 :: "v"(voff), "s"(base), "s"(lds_dst), "s"(lanes) : "memory", "m0");
+}
+__device__ __forceinline__ void direct_load16_from(uint32_t lds_dst, const uint8_t* lane_src, uint64_t lanes) {
+    lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 exec, %2\n\tglobal_load_lds_dwordx4 %0, off\n\ts_mov_b64 exec, -1"
+                 :: "v"(lane_src), "s"(lds_dst), "s"(lanes) : "memory", "m0");
+}
 // What a lane fetches in place of a piece beyond the last k: direct loads write LDS, so a zero has to come
 // from memory too.
 static __device__ const u32x4 g_zero_piece = {0u, 0u, 0u, 0u};

@@ -19,6 +19,9 @@
 //    That costs 0.5 (64 x 64) to 2 us per tile and saves a third of the LDS reads: it is the better form of the 64 x 64 tile
 //    (G = 1: 2-7 % slower) and, where an operand is read with the transposing reads, of the 128 x 128 tile over a long K
 //    (NN 3-7 %, TN 8-11 % from K = 6000 on; 9-11 % slower below K = 1536); half tiles lose by it.
+//  * Tiles of 96 and 192 rows stand between the powers of two, for outputs that those leave a good part of the chip without work of (9 x 18 tiles of
+//    128 x 256 are 162 workgroups, 6 x 35 of 192 x 128 are 210).  Not of columns: a wave tile of 48 columns ends rows inside 64 bytes (128 x 96, staged
+//    through LDS: NT 1024 x 3072 x 3072 2 % faster than 128 x 128, NN and TN 3 % slower, K = 768 6 %).
 //  * Loads are whole 128-byte lines of a K-contiguous operand (a stage row), and whole k-rows of the tile of an
 //    MN-contiguous one; both LDS layouts are free of bank conflicts for their reads.
 //
@@ -35,6 +38,18 @@
 
 namespace axonn {
 
+// Panels of 96 and 192 rows: some loads are for a part of the wave only.
+template <bool PART>
+__device__ __forceinline__ void group_load(uint32_t lds_dst, const uint8_t* base, uint32_t voff, uint64_t lanes) {
+    if constexpr (PART) direct_load16(lds_dst, base, voff, lanes);
+    else direct_load16(lds_dst, base, voff);
+}
+template <bool PART>
+__device__ __forceinline__ void group_load_from(uint32_t lds_dst, const uint8_t* lane_src, uint64_t lanes) {
+    if constexpr (PART) direct_load16_from(lds_dst, lane_src, lanes);
+    else direct_load16_from(lds_dst, lane_src);
+}
+
 // Operand policies: one stage holds ROWS x 64 k of the operand and is filled by all NW waves.
 //   issue<X>(stage)           the X-th of this wave's QL direct loads, at the window, into the stage at `stage`
 //   issue_tail<X>(...)        the same for a shorter last 64 k
@@ -42,8 +57,12 @@ namespace axonn {
 //   cursor<H>(stage, next), read<I>() fragment of 16-row block I: the 32 k of this wave's group (H = 0), or the other half (H = 1)
 template <int ROWS, int REGION, int NW, int NB>
 struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chunks swizzled by (row >> 1) & 7
-    static constexpr int QL = ROWS / 8 / NW;   // a load is 8 rows x 128 bytes
-    static_assert(QL >= 1 && (QL == 1 || QL % 2 == 0), "loads per wave");
+    static constexpr int BYTES = ROWS * 128;                    // of a stage
+    static constexpr int RW = ROWS / NW, QL = (RW + 7) / 8;    // rows per wave; a load is 8 rows x 128 bytes, the last one may be 4
+    static_assert(RW * NW == ROWS && RW % 4 == 0, "rows per wave");
+    template <int X>
+    static constexpr bool half() { return RW - 8 * X == 4; }
+    static __device__ __forceinline__ uint32_t row(int x, int lane, int wave) { return RW * wave + 8 * x + (lane >> 3); }
     const uint8_t* base;     // uniform: the wave's first row, at the window
     uint32_t voff[QL];       // per lane
     uint32_t lds_dst;        // uniform
@@ -51,13 +70,12 @@ struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chun
 
     __device__ __forceinline__ void init(const uint16_t* P, int64_t row0, uint32_t ld_bytes, int lane, int wave, int group,
                                          uint32_t lds0, int wave_row) {
-        base = reinterpret_cast<const uint8_t*>(P) + (size_t)(row0 + 8 * QL * wave) * ld_bytes;
+        base = reinterpret_cast<const uint8_t*>(P) + (size_t)(row0 + RW * wave) * ld_bytes;
 #pragma unroll
         for (int x = 0; x < QL; ++x) {
-            const uint32_t row = 8 * (QL * wave + x) + (lane >> 3);
-            voff[x] = (uint32_t)(8 * x + (lane >> 3)) * ld_bytes + ((((uint32_t)lane & 7u) ^ ((row >> 1) & 7u)) << 4);
+            voff[x] = (uint32_t)(8 * x + (lane >> 3)) * ld_bytes + ((((uint32_t)lane & 7u) ^ ((row(x, lane, wave) >> 1) & 7u)) << 4);
         }
-        lds_dst = lds0 + REGION + (uint32_t)(QL * wave) * 1024u;
+        lds_dst = lds0 + REGION + (uint32_t)(RW * wave) * 128u;
         const uint32_t r16 = lane & 15, quad = lane >> 4;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -65,13 +83,12 @@ struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chun
     }
     template <int X>
     __device__ __forceinline__ void issue(uint32_t stage) const {
-        direct_load16(lds_dst + stage + X * 1024u, base, voff[X]);
+        group_load<half<X>()>(lds_dst + stage + X * 1024u, base, voff[X], 0xFFFFFFFFull);
     }
     template <int X>
     __device__ __forceinline__ void issue_tail(uint32_t stage, size_t delta, int left, int lane, int wave) const {
-        const uint32_t row = 8 * (QL * wave + X) + (lane >> 3);
-        const int k = 8 * (int)((lane & 7) ^ ((row >> 1) & 7));
-        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, k < left));
+        const int k = 8 * (int)((lane & 7) ^ ((row(X, lane, wave) >> 1) & 7));
+        group_load_from<half<X>()>(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, k < left), 0xFFFFFFFFull);
     }
     __device__ __forceinline__ void advance() { base += 128; }
     struct Cursor {
@@ -93,8 +110,10 @@ struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chun
 // reads its own stage and the next one; there is one more stage than iterations, of late pieces only.
 template <int ROWS, int REGION, int NW, int NB>
 struct GroupKLines {
-    static constexpr int QL = ROWS / 8 / NW;
-    static_assert(QL >= 1 && (QL == 1 || QL % 2 == 0), "loads per wave");
+    using Rows = GroupKContig<ROWS, REGION, NW, NB>;
+    static constexpr int BYTES = Rows::BYTES, RW = Rows::RW, QL = Rows::QL;
+    template <int X>
+    static constexpr bool half() { return Rows::template half<X>(); }
     const uint8_t* base;     // uniform: 128 bytes before the wave's first row, at the window
     uint32_t voff[QL];
     uint32_t lds_dst;
@@ -105,19 +124,19 @@ struct GroupKLines {
     __device__ __forceinline__ void init(const uint16_t* P, int64_t row0, uint32_t ld_bytes, int lane, int wave, int group,
                                          uint32_t lds0, int wave_row) {
         const uint8_t* const first = reinterpret_cast<const uint8_t*>(P) + (size_t)row0 * ld_bytes;
-        base = first + (size_t)(8 * QL * wave) * ld_bytes - 128;
+        base = first + (size_t)(RW * wave) * ld_bytes - 128;
         // where a row starts in its line, in pieces: the same for rows 8 apart
         const uint32_t s0 = (uint32_t)(reinterpret_cast<size_t>(first) >> 4), ld = ld_bytes >> 4;
-        const uint32_t s = (s0 + (lane >> 3) * ld) & 7u;
+        const uint32_t s = (s0 + Rows::row(0, lane, wave) * ld) & 7u;
         late_load = 0;
 #pragma unroll
         for (int x = 0; x < QL; ++x) {
-            const uint32_t row = 8 * (QL * wave + x) + (lane >> 3), c = ((uint32_t)lane & 7u) ^ ((row >> 1) & 7u);
+            const uint32_t c = ((uint32_t)lane & 7u) ^ ((Rows::row(x, lane, wave) >> 1) & 7u);
             const bool l = c + s >= 8;
             late_load |= l ? 1u << x : 0u;
             voff[x] = (uint32_t)(8 * x + (lane >> 3)) * ld_bytes + (c << 4) + (l ? 0u : 128u);
         }
-        lds_dst = lds0 + REGION + (uint32_t)(QL * wave) * 1024u;
+        lds_dst = lds0 + REGION + (uint32_t)(RW * wave) * 128u;
         const uint32_t r16 = lane & 15, quad = lane >> 4, s16 = (s0 + r16 * ld) & 7u;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -128,24 +147,24 @@ struct GroupKLines {
     }
     template <int X>
     __device__ __forceinline__ void issue(uint32_t stage) const {
-        direct_load16(lds_dst + stage + X * 1024u, base, voff[X]);
+        group_load<half<X>()>(lds_dst + stage + X * 1024u, base, voff[X], 0xFFFFFFFFull);
     }
     // Stages 0 and 1: the shorter 64 k come first.  `delta`: their bytes behind the row's first k.
     template <int X>
     __device__ __forceinline__ void issue_tail(uint32_t stage, size_t delta, int left, int lane, int wave) const {
         const bool l = late_load >> X & 1;
-        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, !l && tail_k(X, lane, wave) < left));
+        group_load_from<half<X>()>(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, !l && tail_k(X, lane, wave) < left), 0xFFFFFFFFull);
     }
     template <int X>
     __device__ __forceinline__ void issue_second(uint32_t stage, size_t delta, int left, int lane, int wave) const {
         const bool l = late_load >> X & 1;
         const uint8_t* const p = base + voff[X];
-        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(l ? p + 128 + delta : p, !l || tail_k(X, lane, wave) < left));
+        group_load_from<half<X>()>(lds_dst + stage + X * 1024u, piece_or_zero(l ? p + 128 + delta : p, !l || tail_k(X, lane, wave) < left), 0xFFFFFFFFull);
     }
     // the stage of late pieces only
     template <int X>
     __device__ __forceinline__ void issue_last(uint32_t stage) const {
-        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X], late_load >> X & 1));
+        group_load_from<half<X>()>(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X], late_load >> X & 1), 0xFFFFFFFFull);
     }
     __device__ __forceinline__ void advance() { base += 128; }
     struct Cursor {
@@ -161,27 +180,30 @@ struct GroupKLines {
 
 private:
     __device__ __forceinline__ static int tail_k(int x, int lane, int wave) {
-        const uint32_t row = 8 * (QL * wave + x) + (lane >> 3);
-        return 8 * (int)((lane & 7) ^ ((row >> 1) & 7));
+        return 8 * (int)((lane & 7) ^ ((Rows::row(x, lane, wave) >> 1) & 7));
     }
 };
 
 template <int ROWS, int REGION, int NW, int NB>
 struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte chunks swizzled by k
-    static constexpr int ROWB = ROWS * 2, CPR = ROWB / 16;
+    // a k-row takes up a power of two in LDS; its pieces beyond ROWS are not loaded
+    static constexpr int PITCH = ROWS <= 64 ? 64 : ROWS <= 128 ? 128 : 256;
+    static constexpr int ROWB = PITCH * 2, CPR = ROWB / 16, BYTES = 64 * ROWB;
+    static constexpr bool MASKED = PITCH != ROWS;
     static constexpr int KR = 1024 / ROWB;     // k-rows per load
     static constexpr int QL = 64 / KR / NW;
     static_assert(QL >= 1, "loads per wave");
     const uint8_t* base;     // uniform: the wave's first k-row, at the window
     size_t step_bytes;       // 64 k-rows
     uint32_t voff[QL];
+    uint64_t lanes[MASKED ? QL : 1];
     uint32_t lds_dst;
     uint32_t raddr[NB];      // read address of block I in stage 0
 
     // The transposing read serves its four 16-lane groups (k blocks of eight) two at a time; the eight 32-byte pieces of
     // a pair fall into eight different eighths of the 64 banks.
     static __device__ __forceinline__ uint32_t swizzle(uint32_t k) {
-        return ROWS >= 128 ? (2u * (k & 3u)) ^ (8u * ((k >> 3) & 1u)) : (2u * ((k >> 1) & 1u)) ^ (4u * ((k >> 3) & 1u));
+        return PITCH >= 128 ? (2u * (k & 3u)) ^ (8u * ((k >> 3) & 1u)) : (2u * ((k >> 1) & 1u)) ^ (4u * ((k >> 3) & 1u));
     }
     __device__ __forceinline__ void init(const uint16_t* P, int64_t row0, uint32_t ld_bytes, int lane, int wave, int group,
                                          uint32_t lds0, int wave_row) {
@@ -189,7 +211,11 @@ struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte ch
         step_bytes = (size_t)64 * ld_bytes;
         const uint32_t kr = lane / CPR, pos = lane % CPR;
 #pragma unroll
-        for (int x = 0; x < QL; ++x) voff[x] = (KR * x + kr) * ld_bytes + ((pos ^ swizzle(KR * (QL * wave + x) + kr)) << 4);
+        for (int x = 0; x < QL; ++x) {
+            const uint32_t piece = pos ^ swizzle(KR * (QL * wave + x) + kr);
+            voff[x] = (KR * x + kr) * ld_bytes + (piece << 4);
+            if constexpr (MASKED) lanes[x] = __ballot(piece < ROWS / 8);
+        }
         lds_dst = lds0 + REGION + (uint32_t)(QL * wave) * 1024u;
         const uint32_t s = lane & 15, k = 32u * group + 8u * (lane >> 4) + (s >> 2);
 #pragma unroll
@@ -200,12 +226,12 @@ struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte ch
     }
     template <int X>
     __device__ __forceinline__ void issue(uint32_t stage) const {
-        direct_load16(lds_dst + stage + X * 1024u, base, voff[X]);
+        group_load<MASKED>(lds_dst + stage + X * 1024u, base, voff[X], lanes[MASKED ? X : 0]);
     }
     template <int X>
     __device__ __forceinline__ void issue_tail(uint32_t stage, size_t delta, int left, int lane, int wave) const {
         const int k = KR * (QL * wave + X) + lane / CPR;
-        direct_load16_from(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, k < left));
+        group_load_from<MASKED>(lds_dst + stage + X * 1024u, piece_or_zero(base + voff[X] + delta, k < left), lanes[MASKED ? X : 0]);
     }
     __device__ __forceinline__ void advance() { base += step_bytes; }
     struct Cursor {
@@ -227,11 +253,13 @@ struct GroupMNContig {   // global P[k * ld + row]; LDS [64 k][ROWS], 16-byte ch
 // Not the half tiles: LDS has room for three stages of them, one too few for an iteration that reads two (0.83 to 1.02 times as fast).
 constexpr bool group_lines(int bm, int bn, bool a_kc, bool b_kc) { return bm + bn <= 256 && (a_kc || b_kc); }
 // LINES: an operand is loaded by lines (GroupKLines); an iteration then reads two stages, and one more is there for it where LDS has room
-template <int BM, int BN, int G, bool LINES = false>
+template <int BM, int BN, int G, bool LINES = false, bool A_KC = true, bool B_KC = true>
 struct GroupCfg {
     static constexpr int NW = 8, NT = 512;
     static constexpr int WN = G == 2 || BM > BN || BN == 64 ? 2 : 4, WM = NW / G / WN;
-    static constexpr int STAGE = (BM + BN) * 128;                // 64 k of both operands
+    static constexpr int A_BYTES = A_KC ? GroupKContig<BM, 0, NW, 1>::BYTES : GroupMNContig<BM, 0, NW, 1>::BYTES;
+    static constexpr int B_BYTES = B_KC ? GroupKContig<BN, 0, NW, 1>::BYTES : GroupMNContig<BN, 0, NW, 1>::BYTES;
+    static constexpr int STAGE = A_BYTES + B_BYTES;              // 64 k of both operands
     static constexpr int NS = BM + BN <= 128 ? 5 : BM + BN <= 192 ? 4 + LINES : BM + BN <= 256 ? 3 + LINES : 3;
     static constexpr int EXCHANGE = G == 2 ? BM * BN * 4 : 0;   // half of either group's fp32 tile
     static constexpr int LDS_BYTES = NS * STAGE > EXCHANGE ? NS * STAGE : EXCHANGE;
@@ -239,6 +267,13 @@ struct GroupCfg {
     // 128 registers, so that two workgroups share a compute unit, where LDS has room for two
     static constexpr int WAVES_PER_SIMD = 2 * LDS_BYTES <= 160 * 1024 ? 4 : 2;
 };
+// of a launch in any layout and form
+template <int BM, int BN, int G>
+constexpr int group_lds() {
+    constexpr bool L = group_lines(BM, BN, true, true);
+    constexpr int kc = GroupCfg<BM, BN, G, L>::LDS_BYTES, nn = GroupCfg<BM, BN, G, L, true, false>::LDS_BYTES, tn = GroupCfg<BM, BN, G, false, false, false>::LDS_BYTES;
+    return kc > nn ? (kc > tn ? kc : tn) : (nn > tn ? nn : tn);
+}
 
 // ---- split-K: the sums of a tile's `splits` workgroups, every one of which adds up and stores a share of the blocks --------------
 //
@@ -338,7 +373,7 @@ __device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const
                                            int K, int lda, int ldb, int ldc, int64_t m0, int64_t n0, int k_tail,
                                            const GroupSplit& split = GroupSplit{}, int tile = 0, int range = 0) {
     constexpr bool LINES_A = LINES && A_KC, LINES_B = LINES && B_KC;
-    using Cfg = GroupCfg<BM, BN, G, LINES>;
+    using Cfg = GroupCfg<BM, BN, G, LINES, A_KC, B_KC>;
     constexpr int NW = Cfg::NW, NS = Cfg::NS;
     constexpr int AHEAD = LINES ? 2 : 1;   // an iteration reads this many stages
     constexpr uint32_t STAGE = Cfg::STAGE;
@@ -352,8 +387,8 @@ __device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const
 
     using OpA = typename std::conditional<LINES_A, GroupKLines<BM, 0, NW, MI>,
                                           typename std::conditional<A_KC, GroupKContig<BM, 0, NW, MI>, GroupMNContig<BM, 0, NW, MI>>::type>::type;
-    using OpB = typename std::conditional<LINES_B, GroupKLines<BN, BM * 128, NW, NI>,
-                                          typename std::conditional<B_KC, GroupKContig<BN, BM * 128, NW, NI>, GroupMNContig<BN, BM * 128, NW, NI>>::type>::type;
+    using OpB = typename std::conditional<LINES_B, GroupKLines<BN, Cfg::A_BYTES, NW, NI>,
+                                          typename std::conditional<B_KC, GroupKContig<BN, Cfg::A_BYTES, NW, NI>, GroupMNContig<BN, Cfg::A_BYTES, NW, NI>>::type>::type;
     constexpr int QLA = OpA::QL, QLB = OpB::QL, QL = QLA + QLB;
     constexpr int QX = (LINES_A ? QLA : 0) + (LINES_B ? QLB : 0);   // loads of the stage of late pieces
     const uint32_t lds0 = lds_address(smem);

@@ -33,7 +33,7 @@ tile_kernel_t group_kernel(int bm, int bn, int groups, int layout, bool k_tail);
 int group_lds_bytes(int bm, int bn, int groups);
 double group_us(int bm, int bn, int groups, int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc);   // modelled time; < 0: not there
 void group_raise_lds_limit();
-// the tiles that are no variants: 64 x 64, 64 x 128, 128 x 64, and 128 x 128 in two groups
+// the tiles that are no variants: 64 x 64, 64 x 128, 128 x 64, 96 x 128, 192 x 128, and 128 x 128 in two groups
 struct GroupChoice {
     int tile = -1;              // < 0: none of them takes this block
     double us = 0.0;            // modelled time

@@ -20,7 +20,8 @@ namespace axonn {
 // Outputs whose rows do not start on 128-byte lines pay for the lines that two workgroups write a part of.
 // Least squares on the logarithm over 6 000 sampled products of up to 80 GFLOP, the mean of operands in cache and operands
 // from memory, residual 5-8 %.  With the wave-K and the guarded kernel's models the choice is 0.8 % behind the best kernel measured
-// on average, 5 % at the 95th percentile.
+// on average, 5 % at the 95th percentile.  (96 x 128 and 192 x 128: 700 products of 48 to 900 tiles of 128 x 128, residual 4 %; they are
+// chosen for a third of those, which then run 1.08 to 1.09 times as fast, the slowest 0.97; what is chosen takes 1.003 times the best tile, 1.032 without them.)
 struct GroupTile {
     int bm, bn, groups, lds_bytes;
     double launch, tile, last, shared_lines, us64[3], far[3], apart[3], lines[4], late, late_line;
@@ -32,11 +33,13 @@ struct GroupTile {
 // NN 3-7 % faster than one group, TN 8-11 %, NT +-1 %), and for whole K only
 #define AXONN_GROUP2(BM, BN, G, ...) {gemm_tile_kernel_k64g<BM, BN, G, true, false, __VA_ARGS__>, nullptr, gemm_tile_kernel_k64g<BM, BN, G, false, false, __VA_ARGS__>}
 #define AXONN_NO_KERNELS(...) {nullptr, nullptr, nullptr}
-#define AXONN_GROUP_TILE(BM, BN, G, KERNELS, TAIL_KERNELS, ...) {BM, BN, G, GroupCfg<BM, BN, G, group_lines(BM, BN, true, true)>::LDS_BYTES, __VA_ARGS__, KERNELS(BM, BN, G, false), TAIL_KERNELS(BM, BN, G, true)}
+#define AXONN_GROUP_TILE(BM, BN, G, KERNELS, TAIL_KERNELS, ...) {BM, BN, G, group_lds<BM, BN, G>(), __VA_ARGS__, KERNELS(BM, BN, G, false), TAIL_KERNELS(BM, BN, G, true)}
 static const GroupTile kTiles[] = {
     AXONN_GROUP_TILE(64, 64, 2, AXONN_GROUP3, AXONN_GROUP3, 3.04, 0.48, 0.770, 0.09, {0.141, 0.124, 0.155}, {0.073, 0.131, 0.0}, {2.118, 2.712, 1.544}, {0.44, 0.51, 0.49, 0.60}, 1.8, 0.06),
     AXONN_GROUP_TILE(64, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.22, 1.33, 0.789, 0.21, {0.229, 0.202, 0.258}, {0.209, 0.349, 0.036}, {1.099, 1.396, 1.135}, {0.47, 0.49, 0.35, 0.30}, 2.4, 0.03),
     AXONN_GROUP_TILE(128, 64, 1, AXONN_GROUP3, AXONN_GROUP3, 2.25, 1.28, 0.814, 0.26, {0.224, 0.201, 0.255}, {0.314, 0.421, 0.130}, {0.791, 0.978, 0.611}, {0.43, 0.56, 0.19, 0.64}, 2.6, 0.06),
+    AXONN_GROUP_TILE(96, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.51, 0.99, 0.871, 0.37, {0.355, 0.342, 0.392}, {0.036, 0.080, 0.0}, {0.519, 0.539, 0.624}, {0.17, 0.29, 0.05, 0.27}, 1.3, 0.01),
+    AXONN_GROUP_TILE(192, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 1.98, 1.99, 0.794, 1.70, {0.563, 0.529, 0.604}, {0.028, 0.086, 0.0}, {0.431, 0.312, 0.245}, {0.19, 0.56, 0.06, 0.31}, 0.0, 0.0),
     AXONN_GROUP_TILE(128, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 2.16, 1.82, 0.812, 1.04, {0.338, 0.308, 0.408}, {0.276, 0.381, 0.112}, {0.509, 0.583, 0.290}, {0.36, 0.44, 0.11, 0.21}, 1.8, 0.04),
     AXONN_GROUP_TILE(128, 128, 2, AXONN_GROUP2, AXONN_NO_KERNELS, 2.51, 2.69, 0.806, 0.96, {0.311, 0.0, 0.341}, {0.299, 0.0, 0.159}, {0.665, 0.0, 0.579}, {0.42, 0.44, 0.22, 0.26}, 0.0, 0.0),
     AXONN_GROUP_TILE(256, 128, 1, AXONN_GROUP3, AXONN_GROUP3, 1.93, 3.34, 0.693, 3.57, {0.609, 0.598, 0.728}, {0.130, 0.155, 0.0}, {0.472, 0.557, 0.260}, {0.32, 0.30, 0.03, 0.23}, 0.0, 0.0),
@@ -89,13 +92,25 @@ double group_us(int bm, int bn, int groups, int layout, int64_t m, int64_t n, in
     return t ? model_us(*t, layout, m, n, K, lda, ldb, ldc) : -1.0;
 }
 
+// Tiles of 96 and 192 rows: by how much more than modelled they count; < 0: not there.
+// Within the range that the model was fitted over: beyond a round of workgroups over a short K it is 5 to 13 % short (9344 x 9344 x 384 TN 73 us on
+// 256 x 256 tiles, 83 here; 1920 x 12416 x 512 27 and 29, 1536 x 6272 x 640 16.4 and 17.1; in one round 1280 x 3712 x 384 TN 8.2 us on 256 x 128 and 7.3 here).
+// Rows of the output off 128-byte lines: they have to be 15 % ahead.  The kernels of such products are relied on by name
+// (axonn_linear_part_kernel), at up to 19 % of their time (1064 x 4168 x 1608 NT 26.4 us on 128 x 256 tiles, 22.2 on 192 x 128).
+static double between_margin(const GroupTile& t, int layout, int64_t m, int64_t n, int64_t K, int64_t ldc) {
+    const int64_t wgs = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn);
+    if (K < 320 || (K < (layout == 2 ? 1024 : 640) && wgs > 256) || m * n > (int64_t)16 << 20) return -1.0;
+    return ldc % 64 == 0 ? 1.0 : 1.15;
+}
+
 GroupChoice group_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     GroupChoice best;
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const GroupTile& t = kTiles[i];
-        if (t.groups == 1 && t.bm >= 128 && t.bn >= 128) continue;   // variants of their own
-        const double us = model_us(t, layout, m, n, K, lda, ldb, ldc);
-        if (us >= 0.0 && (best.tile < 0 || us < best.us)) best = GroupChoice{i, us};
+        if (t.groups == 1 && t.bm % 128 == 0 && t.bn % 128 == 0) continue;   // variants of their own
+        const double margin = t.bm % 96 == 0 ? between_margin(t, layout, m, n, K, ldc) : 1.0;
+        const double us = margin * model_us(t, layout, m, n, K, lda, ldb, ldc);
+        if (margin > 0.0 && us >= 0.0 && (best.tile < 0 || us < best.us)) best = GroupChoice{i, us};
     }
     return best;
 }

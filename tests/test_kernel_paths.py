@@ -167,6 +167,21 @@ def test_every_length_of_k_on_the_eight_wave_kernel(oracle_mod, tile, tail, layo
         _check(oracle_mod, *shape, layout, [kernel])
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", LAYOUTS)
+@pytest.mark.parametrize("tail", ["", "_ktail"])
+@pytest.mark.parametrize("tile", ["96x128", "192x128"])
+def test_tiles_of_96_and_192_rows(oracle_mod, tile, tail, layout):
+    """Loads for a part of a wave (12 rows a wave of a K-contiguous operand; k-rows that LDS holds padded): every length of K there is a product of."""
+    kernel = f"mfma16k64g_{tile}{tail}"
+    products = eight_wave_products()[(kernel, layout)]
+    assert len(set(products) & {2, 3, 4, 5, 6, 7, 8, 9}) >= 4 and max(products) >= 24, products
+    B.register_workspace()
+    for steps, shape in sorted(products.items()):
+        print(f"  {kernel} {layout} {shape}", flush=True)
+        _check(oracle_mod, *shape, layout, [kernel])
+
+
 @lru_cache(maxsize=None)
 def by_lines_products():
     """{(kernel, layout): {pieces of 8 beyond whole 64 k: the smallest sampled product of one launch on it}}, K beyond 768."""
@@ -185,7 +200,7 @@ def by_lines_products():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout", ["NN", "NT"])
-@pytest.mark.parametrize("tile", ["64x64_g2", "64x128", "128x64", "128x128"])
+@pytest.mark.parametrize("tile", ["64x64_g2", "64x128", "128x64", "96x128", "128x128"])
 def test_k_contiguous_rows_loaded_by_lines(tile, layout):
     """Rows that start on every 16 bytes of a line (each K modulo 64, buffers on every 16 bytes of one): integers, exact in any order."""
     B.register_workspace()
