@@ -693,13 +693,18 @@ static bool leaves_split_k(const Part& p, int64_t K, int layout, int64_t lda, in
 // A block planned with split-K on the eight-wave kernel's tiles and counts instead.  700 sampled products that are planned so, on all of
 // them (in cache, three sets in turn, from memory): 1.31, 1.31 and 1.53 times as fast as planned with 128 x 128 tiles (527, three of them 3-4 % slower),
 // half tiles 1.12 to 1.17 where the models put it 2 % ahead, 256 x 256 tiles in four and more ranges 1.16 to 1.27; in two and three ranges 0.78 to
-// 0.85, an output that has a round of large tiles nearly full.
+// 0.85, an output that has a round of large tiles nearly full.  Nor where NT would keep its 256 x 128 tiles in two ranges: the exchange saves least
+// there and the ranges are long, over which the four-wave tile is 2 to 7 % ahead in all of the 12 sampled (256 x 14080 x 15488 132 us and 142), while three
+// ranges gain 1.01 to 1.04.
 static GroupSplitChoice split_on_eight_waves(const Part& p, int64_t K, int layout, double us) {
     const Variant& x = variants()[p.variant];
     const int area = x.bm * x.bn;
     if (us <= 0.0 || (area == 256 * 256 && x.splits < 4)) return GroupSplitChoice{};
     const GroupSplitChoice c = group_split_choose(layout, p.m, p.n, K, kStaticSlots * kSlotBytes, kMaxFlags);
-    return c.tile >= 0 && c.us < (area <= 128 * 128 ? 1.1 : 0.98) * us ? c : GroupSplitChoice{};
+    if (c.tile < 0 || c.us >= (area <= 128 * 128 ? 1.1 : 0.98) * us) return GroupSplitChoice{};
+    int rows = 0, cols = 0;
+    group_split_tile(c, &rows, &cols);
+    return layout == AXONN_NT && area == 256 * 128 && rows * cols == area && x.splits == 2 && c.splits == 2 ? GroupSplitChoice{} : c;
 }
 static void settle_parts(Plan& plan, int64_t M, int64_t N, int64_t K, int layout) {
     const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N;
