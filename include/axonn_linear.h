@@ -276,9 +276,16 @@ int axonn_linear_set_split_k(int enable);
 
 /* Diagnostics: how many times, in the scratch area now registered on the current device and in its
  * static array together, a split-K workgroup gave up waiting for a partial tile (it waits about a
- * second; this cannot happen unless another workgroup of the same launch died).  Synchronous
+ * second; this cannot happen unless another workgroup of the same launch died: what it waits for never waits itself
+ * and is dispatched first.  On the eight-wave kernel no workgroup depends on a wait, and nothing is counted).  Synchronous
  * device-to-host copies.  *count is 0 when neither has been used. */
 int axonn_linear_split_k_timeouts(uint64_t *count);
+/* For tests and tuning: a product as axonn_linear_fwd runs it now, where at least one of its launches is the eight-wave kernel with
+ * split-K ("mfma16k64g_..._sk<ranges>"; else AXONN_ERR_UNSUPPORTED).  The K ranges of one of its tiles each finish a share of the tile;
+ * one that has not found the others after `probes` more looks, about a microsecond each, hands its share on to one that comes later.
+ * The result is the same to the bit. */
+int axonn_linear_gemm_split_probes(int64_t M, int64_t N, int64_t K, int layout, const void *first, const void *second, void *out,
+                                   uint32_t probes, void *stream);
 
 /* Kernel variants.  Variant 0 is the guarded one-thread-per-element kernel that accepts any
  * shape (the library itself uses it for K == 0 only); the last one ("mfma16_edge_128x128") takes

@@ -29,7 +29,7 @@ EXPORTS = (
     "axonn_linear_variant_name", "axonn_linear_variant_supports", "axonn_linear_select_variant",
     "axonn_linear_plan", "axonn_linear_call_plan", "axonn_linear_part_kernel",
     "axonn_linear_force_variant",
-    "axonn_linear_init", "axonn_linear_set_split_k", "axonn_linear_split_k_timeouts",
+    "axonn_linear_init", "axonn_linear_set_split_k", "axonn_linear_split_k_timeouts", "axonn_linear_gemm_split_probes",
     "axonn_linear_workspace_bytes", "axonn_linear_set_workspace", "axonn_transpose_bf16", "axonn_transpose_kernel", "axonn_transpose_kernel_at",
     "axonn_linear_tune", "axonn_linear_tuned", "axonn_linear_tune_reset", "axonn_linear_tuned_set", "axonn_linear_tuned_call",
     "axonn_comm_group_bandwidths", "axonn_comm_layer_time", "axonn_comm_rank_grids",
@@ -153,6 +153,8 @@ def lib() -> ctypes.CDLL:
         L.axonn_linear_set_split_k.restype = ci
         L.axonn_linear_split_k_timeouts.argtypes = [ctypes.POINTER(ctypes.c_uint64)]
         L.axonn_linear_split_k_timeouts.restype = ci
+        L.axonn_linear_gemm_split_probes.argtypes = [i64, i64, i64, ci, vp, vp, vp, ctypes.c_uint32, vp]
+        L.axonn_linear_gemm_split_probes.restype = ci
         _load_marshal(L)
         _lib = L
     return _lib
@@ -311,6 +313,13 @@ def axonn_linear_split_k_timeouts() -> int:
     if rc != 0:
         raise AxonnError(rc, "axonn_linear_split_k_timeouts")
     return int(n.value)
+
+
+def axonn_linear_gemm_split_probes(M, N, K, layout, first, second, out, probes, stream=None) -> None:
+    """A product whose K ranges look `probes` times more for one another before they hand their shares on (for tests and tuning)."""
+    rc = lib().axonn_linear_gemm_split_probes(M, N, K, _layout(layout), _ptr(first), _ptr(second), _ptr(out), probes, _stream(stream))
+    if rc != AXONN_OK:
+        raise AxonnError(rc, "axonn_linear_gemm_split_probes")
 
 
 def _layout(layout) -> int:

@@ -807,8 +807,10 @@ static int64_t part_workgroups(const Part& p) {
 }
 
 static uint32_t next_epoch() {
-    const uint32_t epoch = g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;
-    return epoch ? epoch : g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;   // flags start at 0
+    for (;;) {
+        const uint32_t epoch = g_epoch.fetch_add(1, std::memory_order_relaxed) + 1;
+        if (epoch != 0 && epoch != ~0u) return epoch;   // flags start at 0; ~epoch: see split_exchange.hpp
+    }
 }
 
 // A tile kernel over the m x n block that starts at A, B, C.
@@ -834,7 +836,7 @@ static void launch_tiles(const Variant& var, int64_t m, int64_t n, int64_t K, in
 
 // One kernel launch over the block `p` of the M x N output.
 static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layout, const uint16_t* A, const uint16_t* B,
-                        uint16_t* C, const Scratch& scratch, hipStream_t s) {
+                        uint16_t* C, const Scratch& scratch, uint32_t probes, hipStream_t s) {
     const Variant& var = variants()[p.variant];
     const int64_t lda = layout == AXONN_TN ? M : K, ldb = layout == AXONN_NT ? K : N, ldc = N;
     A += layout == AXONN_TN ? p.row0 : p.row0 * K;
@@ -851,7 +853,7 @@ static void launch_part(const Part& p, int64_t M, int64_t N, int64_t K, int layo
         return;
     }
     if (p.how.split.tile >= 0) {
-        group_split_launch(p.how.split, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc, scratch.partials, scratch.flags, scratch.timeouts(), next_epoch());
+        group_split_launch(p.how.split, layout, s, A, B, C, p.m, p.n, K, lda, ldb, ldc, scratch.partials, scratch.flags, next_epoch(), probes);
         return;
     }
     if (var.edge && p.how.tile < 0) {
@@ -922,7 +924,7 @@ static int part_kernel_name(const Part& p, int64_t N, int64_t K, int layout, cha
 }
 
 static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, const void* b, void* c,
-                  int fp32_accumulate, void* stream, ScratchFrom from = ScratchFrom::Registered) {
+                  int fp32_accumulate, void* stream, ScratchFrom from = ScratchFrom::Registered, uint32_t probes = kGroupSplitProbes) {
     const int rc = check_args(M, N, K, layout, a, b, c, fp32_accumulate);
     if (rc != AXONN_OK) return rc;
     if (M == 0 || N == 0) return AXONN_OK;
@@ -949,7 +951,7 @@ static int launch(int64_t M, int64_t N, int64_t K, int layout, const void* a, co
         raise_lds_limits_once();
         for (int i = 0; i < plan.parts; ++i)
             if (part_workgroups(plan.part[i]) >= ((int64_t)1 << 31)) return AXONN_ERR_UNSUPPORTED;
-        for (int i = 0; i < plan.parts; ++i) launch_part(plan.part[i], M, N, K, layout, A, B, C, scratch, s);
+        for (int i = 0; i < plan.parts; ++i) launch_part(plan.part[i], M, N, K, layout, A, B, C, scratch, probes, s);
     }
     return hipGetLastError() == hipSuccess ? AXONN_OK : AXONN_ERR_LAUNCH;
 }
@@ -1135,6 +1137,20 @@ int axonn_linear_bwd_weight(int64_t M, int64_t N, int64_t K, int layout, const v
 int axonn_linear_gemm_static(int64_t M, int64_t N, int64_t K, int layout, const void* first, const void* second, void* out,
                              int fp32_accumulate, void* stream) {
     return axonn::launch(M, N, K, layout, first, second, out, fp32_accumulate, stream, axonn::ScratchFrom::Static);
+}
+
+int axonn_linear_gemm_split_probes(int64_t M, int64_t N, int64_t K, int layout, const void* first, const void* second, void* out,
+                                   uint32_t probes, void* stream) {
+    const int rc = axonn::check_args(M, N, K, layout, first, second, out, 1);
+    if (rc != AXONN_OK) return rc;
+    if (M == 0 || N == 0) return AXONN_ERR_UNSUPPORTED;
+    axonn::Plan plan;
+    axonn::Scratch scratch;
+    const int planned = axonn::plan_call(M, N, K, layout, axonn::ScratchFrom::Registered, plan, scratch);
+    if (planned != AXONN_OK) return planned;
+    for (int i = 0; i < plan.parts; ++i)
+        if (plan.part[i].how.split.tile >= 0) return axonn::launch(M, N, K, layout, first, second, out, 1, stream, axonn::ScratchFrom::Registered, probes);
+    return AXONN_ERR_UNSUPPORTED;
 }
 
 size_t axonn_linear_static_scratch_bytes(void) { return axonn::kStaticBytes; }

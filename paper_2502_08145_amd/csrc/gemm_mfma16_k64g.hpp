@@ -35,6 +35,7 @@
 #pragma once
 #include "gemm_mfma16.hpp"
 #include "kernels.hpp"
+#include "split_exchange.hpp"
 
 namespace axonn {
 
@@ -281,44 +282,35 @@ constexpr int group_lds() {
 // sum, then the other ranges' in their order (the result does not depend on timing).  All of them move their share at once, where one
 // reader per tile takes splits - 1 whole ones while the others' compute units have gone idle.
 //
-// The workgroups of a tile follow one another in the order of dispatch, so they are there together, or will be as soon as the tiles
-// before have ended: at most 2 (splits - 1) of an XCD's 32 compute units hold a tile that is not complete.  (The wait is bounded all the same.)
+// The workgroups of a tile follow one another in the order of dispatch, and on an idle chip they are there together, or will be as soon as
+// the tiles before have ended.  Where they are not (compute units held by other kernels, a stream with a mask of them), a range does not wait for
+// long: it hands its share on to one that comes later (split_exchange.hpp), and every workgroup ends whatever else runs.
 //
 // What it replaces: one reader per tile on the 32-k ring and the four-wave 64-k kernel, half the compute units idle at 120 tiles in two ranges.  us,
 // before and here: 1920 x 1024 x 16384 NT 101 -> 70;  640 x 1024 x 8832 NT 37.2 -> 23.2;  256 x 1024 x 12032 NN 30.0 -> 16.5 (six ranges).
 // With a counter per tile (a compare-and-swap, a poll and an addition one after the other) the exchange took 8 us longer, with fences 10.
 //
-// A flag per pair of ranges of a tile, valid when it equals the launch's epoch; the range that waits for it takes it back to 0, so that a
-// launch replayed from a captured graph does not find its own value.
-//
 // No fences: a device-scope release would write the whole L2 back and an acquire invalidate it, under the other tiles' K loops.  The sums
 // leave as device-scope stores that are acknowledged before the flags go out, and come as device-scope loads, past the L2.
 struct GroupSplit {
     float* partials;      // [tiles][splits] slots of BM * BN floats: 16 x 16 block, wave, lane
-    uint32_t* flags;      // [tiles][splits: who waits][splits - 1]
-    uint32_t* timeouts;
-    uint32_t epoch;       // not 0
+    uint32_t* flags;      // [tiles][splits * (splits - 1)], see split_exchange.hpp
+    uint32_t epoch;       // neither 0 nor ~0
+    uint32_t probes;      // how often a range looks again for the others before it hands its share on
     int splits;           // 2 .. 6, 8
 };
 
-// By the first wave: tell the tile's other ranges, and wait for them.
-__device__ __forceinline__ void group_split_meet(const GroupSplit& sp, uint32_t* flags, int range, int lane) {
-    const int others = sp.splits - 1;
-    if (lane < others) {
-        const int other = lane + (lane >= range ? 1 : 0);
-        uint32_t* const theirs = flags + other * others + (range - (range > other ? 1 : 0));
-        uint32_t* const ours = flags + range * others + lane;
-        __hip_atomic_store(theirs, sp.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (uint32_t probes = 0; __hip_atomic_load(ours, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != sp.epoch;) {
-            if (++probes > kSplitSpinLimit) {
-                atomicAdd(sp.timeouts, 1u);
-                break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-        }
-        __hip_atomic_store(ours, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+struct GroupSplitWave {
+    int lane;
+    __device__ __forceinline__ uint32_t load(const uint32_t* p) const { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ void store(uint32_t* p, uint32_t v) const { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ uint32_t exchange(uint32_t* p, uint32_t v) const { return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ bool compare_exchange(uint32_t* p, uint32_t seen, uint32_t v) const {
+        return __hip_atomic_compare_exchange_strong(p, &seen, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-}
+    __device__ __forceinline__ uint64_t ballot(bool b) const { return __ballot(b); }
+    __device__ __forceinline__ void pause() const { __builtin_amdgcn_s_sleep(1); }
+};
 // Device-scope load: from memory, past what this XCD's L2 holds, so that no cache has to be invalidated first.
 __device__ __forceinline__ f32x4 load_device_scope(const f32x4* p) {
     typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
@@ -327,21 +319,45 @@ __device__ __forceinline__ f32x4 load_device_scope(const f32x4* p) {
     return __builtin_bit_cast(f32x4, v);
 }
 
-template <int BM, int BN, int MI, int NI, int S>
-__device__ __forceinline__ void group_split_finish(f32x4 (&acc)[MI][NI], const GroupSplit& sp, int tile, int range, uint16_t* pc, int ldc,
-                                                   int wave, int lane, int t) {
-    constexpr int BLOCKS = MI * NI, NW = 8, SLOT = BM * BN / 4, OWN = (BLOCKS + S - 1) / S;   // SLOT: f32x4 of a slot
-    const int first = (range * BLOCKS + S - 1) / S, count = ((range + 1) * BLOCKS + S - 1) / S - first;   // this workgroup's blocks
-    f32x4* const slots = reinterpret_cast<f32x4*>(sp.partials) + (size_t)tile * S * SLOT + wave * 64 + lane;
+// The 16 x 16 blocks of a wave tile that are a share.
+__device__ __forceinline__ int group_split_first(int share, int blocks, int splits) { return (share * blocks + splits - 1) / splits; }
+
+// device-scope stores and the wait state behind them: see split_k_exchange16
+__device__ __forceinline__ void store_device_scope(f32x4* p, const f32x4& v) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(p), "v"(v) : "memory");
+}
+// 32 bytes a row: left to the L2 to put together (non-temporal, each went to memory by itself: 640 x 1024 x 8832 NT 23.2 us, 22.6 so)
+__device__ __forceinline__ void group_split_store(uint16_t* pc, int ldc, int row_block, int col_block, const f32x4& sum) {
+    const u32x2 w{pack2_bf16(sum[0], sum[1]), pack2_bf16(sum[2], sum[3])};
+    *reinterpret_cast<u32x2*>(pc + (int64_t)(16 * row_block) * ldc + 16 * col_block) = w;
+}
+
+// Returns the shares that are still this workgroup's to settle; its sums of them are in their slots (this wave's, by now).  `pc`, `slots`: this lane's.
+template <int MI, int NI, int S, int SLOT>
+__device__ __forceinline__ uint32_t group_split_finish(f32x4 (&acc)[MI][NI], const GroupSplit& sp, f32x4* slots, uint32_t* flags, int range, uint16_t* pc, int ldc,
+                                                       int wave, int lane, uint32_t* word) {
+    constexpr int BLOCKS = MI * NI, NW = 8, OWN = (BLOCKS + S - 1) / S;
+    const int first = group_split_first(range, BLOCKS, S), count = group_split_first(range + 1, BLOCKS, S) - first;   // this workgroup's blocks
     f32x4* const mine = slots + (size_t)range * SLOT;
 #pragma unroll
     for (int u = 0; u < BLOCKS; ++u)
-        if (u < first || u >= first + count)   // device-scope stores and the wait state behind them: see split_k_exchange16
-            asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" ::"v"(mine + u * (NW * 64)), "v"(acc[u / NI][u % NI]) : "memory");
+        if (u < first || u >= first + count) store_device_scope(mine + u * (NW * 64), acc[u / NI][u % NI]);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // acknowledged: the compiler does not count stores issued from asm
     __syncthreads();
-    if (wave == 0) group_split_meet(sp, sp.flags + tile * S * (S - 1), range, lane);
+    if (wave == 0) {
+        bool complete;
+        const uint32_t held = split_meet(GroupSplitWave{lane}, flags, S, range, sp.epoch, sp.probes, &complete);
+        if (lane == 0) *word = held;
+    }
     __syncthreads();
+    const uint32_t held = __builtin_amdgcn_readfirstlane(*word);
+    if (held >> range & 1) {
+#pragma unroll
+        for (int u = 0; u < BLOCKS; ++u)
+            if (u >= first && u < first + count) store_device_scope(mine + u * (NW * 64), acc[u / NI][u % NI]);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return held;
+    }
     // all of the other ranges' sums in flight together
     f32x4 v[OWN][S - 1];
 #pragma unroll
@@ -351,7 +367,6 @@ __device__ __forceinline__ void group_split_finish(f32x4 (&acc)[MI][NI], const G
             for (int q = 0; q < S - 1; ++q)
                 v[i][q] = load_device_scope(slots + (size_t)(q + (q >= range ? 1 : 0)) * SLOT + (first + i) * (NW * 64));
     __builtin_amdgcn_sched_barrier(0);
-    pc += (int64_t)(lane & 15) * ldc + 4 * (lane >> 4);
 #pragma unroll
     for (int i = 0; i < OWN; ++i)
         if (i < count) {
@@ -361,10 +376,33 @@ __device__ __forceinline__ void group_split_finish(f32x4 (&acc)[MI][NI], const G
                 if (u == first + i) sum = acc[u / NI][u % NI];
 #pragma unroll
             for (int q = 0; q < S - 1; ++q) sum += v[i][q];
-            const u32x2 w{pack2_bf16(sum[0], sum[1]), pack2_bf16(sum[2], sum[3])};
-            // 32 bytes a row: left to the L2 to put together (non-temporal, each went to memory by itself: 640 x 1024 x 8832 NT 23.2 us, 22.6 so)
-            *reinterpret_cast<u32x2*>(pc + (int64_t)(16 * ((first + i) / NI)) * ldc + 16 * ((first + i) % NI)) = w;
+            group_split_store(pc, ldc, (first + i) / NI, (first + i) % NI, sum);
         }
+    return held;
+}
+// The shares that were handed on: rare, and off the path above.  The sums are added in the same order, the share's own range's first.
+template <int MI, int NI, int SLOT>
+__device__ __forceinline__ void group_split_settle(uint32_t held, const GroupSplit& sp, const f32x4* slots, uint32_t* flags, uint16_t* pc, int ldc, int wave, int lane, uint32_t* word) {
+    constexpr int BLOCKS = MI * NI, NW = 8;
+    while (held) {
+        const int share = __builtin_ctz(held);
+        held &= held - 1;
+        __syncthreads();   // every wave's sums are in memory, and every wave has read the word
+        if (wave == 0) {
+            const bool all = split_settle(GroupSplitWave{lane}, flags, sp.splits, share, sp.epoch);
+            if (lane == 0) *word = all;
+        }
+        __syncthreads();
+        if (!__builtin_amdgcn_readfirstlane(*word)) continue;
+        const int end = group_split_first(share + 1, BLOCKS, sp.splits);
+        for (int u = group_split_first(share, BLOCKS, sp.splits); u < end; ++u) {
+            const f32x4* const p = slots + u * (NW * 64);
+            f32x4 sum = load_device_scope(p + (size_t)share * SLOT);
+            for (int q = 0; q < sp.splits; ++q)
+                if (q != share) sum += load_device_scope(p + (size_t)q * SLOT);
+            group_split_store(pc, ldc, u / NI, u % NI, sum);
+        }
+    }
 }
 
 // One tile.  LINES: its K-contiguous operands by lines; K > 64 NS.  SPLITK: one of the K ranges of a tile.
@@ -603,14 +641,21 @@ __device__ __forceinline__ void group_tile(const uint16_t* __restrict__ A, const
     if constexpr (SPLITK) {
         static_assert(G == 1, "the waves divide the tile");
         uint16_t* const pc = C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN;
+        constexpr int SLOT = BM * BN / 4;   // f32x4 of a slot
+        f32x4* const slots = reinterpret_cast<f32x4*>(split.partials) + (size_t)tile * split.splits * SLOT + wave * 64 + lane;
+        uint32_t* const flags = split.flags + tile * split.splits * (split.splits - 1);
+        uint16_t* const mine = pc + (int64_t)(lane & 15) * ldc + 4 * (lane >> 4);
+        uint32_t* const word = reinterpret_cast<uint32_t*>(smem);   // behind the barriers of the exchange the stages are free
+        uint32_t held = 0;
         switch (split.splits) {
-            case 2: group_split_finish<BM, BN, MI, NI, 2>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
-            case 3: group_split_finish<BM, BN, MI, NI, 3>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
-            case 4: group_split_finish<BM, BN, MI, NI, 4>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
-            case 5: group_split_finish<BM, BN, MI, NI, 5>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
-            case 6: group_split_finish<BM, BN, MI, NI, 6>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
-            default: group_split_finish<BM, BN, MI, NI, 8>(acc, split, tile, range, pc, ldc, wave, lane, t); break;
+            case 2: held = group_split_finish<MI, NI, 2, SLOT>(acc, split, slots, flags, range, mine, ldc, wave, lane, word); break;
+            case 3: held = group_split_finish<MI, NI, 3, SLOT>(acc, split, slots, flags, range, mine, ldc, wave, lane, word); break;
+            case 4: held = group_split_finish<MI, NI, 4, SLOT>(acc, split, slots, flags, range, mine, ldc, wave, lane, word); break;
+            case 5: held = group_split_finish<MI, NI, 5, SLOT>(acc, split, slots, flags, range, mine, ldc, wave, lane, word); break;
+            case 6: held = group_split_finish<MI, NI, 6, SLOT>(acc, split, slots, flags, range, mine, ldc, wave, lane, word); break;
+            default: held = group_split_finish<MI, NI, 8, SLOT>(acc, split, slots, flags, range, mine, ldc, wave, lane, word); break;
         }
+        if (__builtin_expect(held != 0, 0)) group_split_settle<MI, NI, SLOT>(held, split, slots, flags, mine, ldc, wave, lane, word);
     } else if constexpr (G == 1) {
         uint8_t* const epi = smem + wave * (32 * TN);
         uint16_t* const pc = C + (m0 + wm * TM) * (int64_t)ldc + n0 + wn * TN;

@@ -189,11 +189,11 @@ void group_split_tile(const GroupSplitChoice& c, int* rows, int* cols) {
 }
 
 void group_split_launch(const GroupSplitChoice& c, int layout, hipStream_t s, const uint16_t* A, const uint16_t* B, uint16_t* C, int64_t m, int64_t n,
-                        int64_t K, int64_t lda, int64_t ldb, int64_t ldc, float* partials, uint32_t* flags, uint32_t* timeouts, uint32_t epoch) {
+                        int64_t K, int64_t lda, int64_t ldb, int64_t ldc, float* partials, uint32_t* flags, uint32_t epoch, uint32_t probes) {
     const GroupSplitTile& t = kSplitTiles[c.tile];
     const int tiles_m = (int)(m / t.bm), tiles_n = (int)(n / t.bn);
     hipLaunchKernelGGL(t.fn[layout], dim3((unsigned)(tiles_m * tiles_n * c.splits)), dim3(512), t.lds_bytes, s, A, B, C, (int)K, (int)lda, (int)ldb, (int)ldc,
-                       tiles_m, tiles_n, tiles_m < 8 ? tiles_m : 8, GroupSplit{partials, flags, timeouts, epoch, c.splits});
+                       tiles_m, tiles_n, tiles_m < 8 ? tiles_m : 8, GroupSplit{partials, flags, epoch, probes, c.splits});
 }
 
 void group_raise_lds_limit() {

@@ -267,6 +267,43 @@ def test_split_k_on_the_eight_wave_kernel(oracle_mod, layout):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("layout", LAYOUTS)
+def test_ranges_that_do_not_wait_for_one_another(layout):
+    """A range that looks once (0), a few times (3) or for long for the others of its tile: shares are handed on or not, with the same bits, the flags
+    taken back, and in replays of a captured graph."""
+    area = B.register_workspace()
+    products = {name: shape for (name, lay), shape in eight_wave_split_products().items() if lay == layout}
+    for name, (M, N, K) in sorted(products.items()):
+        print(f"  {name} {layout} {(M, N, K)}", flush=True)
+        x = torch.randn((K, M) if layout == "TN" else (M, K), device="cuda").to(torch.bfloat16)
+        y = torch.randn((N, K) if layout == "NT" else (K, N), device="cuda").to(torch.bfloat16)
+        want = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+        c = torch.empty_like(want)
+        B.axonn_linear_gemm_split_probes(M, N, K, layout, x, y, want, 1 << 19)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(2):
+                B.axonn_linear_gemm_split_probes(M, N, K, layout, x, y, c, 0)
+        runs = [lambda p=p: B.axonn_linear_gemm_split_probes(M, N, K, layout, x, y, c, p) for p in (0, 0, 3)]
+        for run in runs + [graph.replay] * 3 + [lambda: B.axonn_linear_fwd(M, N, K, layout, x, y, c)]:
+            c.fill_(float("nan"))
+            run()
+            torch.cuda.synchronize()
+            assert torch.equal(c.view(torch.int16), want.view(torch.int16)), name
+            assert not area[:4096].any(), name
+
+
+def test_the_entry_point_with_probes_refuses_other_kernels():
+    at = 0x1000   # nothing is launched
+    for args in ((256, 256, 256), (0, 256, 256)):
+        with pytest.raises(B.AxonnError):
+            B.axonn_linear_gemm_split_probes(*args, "NN", at, at, at, 0, stream=0)
+    with pytest.raises(B.AxonnError):
+        B.axonn_linear_gemm_split_probes(1024, 1024, 4096, "NT", at, at + 2, at, 0, stream=0)
+
+
+@pytest.mark.gpu
 def test_an_area_of_the_advertised_size_runs_the_planned_variant(oracle_mod):
     """The eight-wave kernel's partial sums take more than the variant's: without room for them the variant itself runs."""
     shape = (1024, 1024, 4096, "NT")
