@@ -12,6 +12,7 @@
 
 #include <climits>
 #include <cstdint>
+#include <exception>
 
 namespace {
 
@@ -73,72 +74,82 @@ bool current_or_handle(PyObject* o, void** s) {
     return true;
 }
 
-// What the tensors and torch throw goes the general way too, and is thrown again there.
+// Whether the arguments are all of the kinds above.  What the tensors and torch throw about them goes the general way too, and is thrown again there.
 template <class F>
-PyObject* or_none(F&& f) {
+bool taken(F&& f) {
     try {
         return f();
     } catch (...) {
         PyErr_Clear();
-        Py_RETURN_NONE;
+        return false;
     }
 }
 
 // As ctypes does: other threads run while the call may wait for room in the queue.
+struct OthersRun {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~OthersRun() { PyEval_RestoreThread(state); }
+};
+
+// The call itself.  It has run, whatever comes out of it: never the general way a second time.
 template <class F>
 PyObject* status(F&& f) {
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = f();
-    Py_END_ALLOW_THREADS
+    try {
+        OthersRun others;
+        rc = f();
+    } catch (const std::exception& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
     return PyLong_FromLong(rc);
 }
 
 // (entry point, M, N, K, layout, first, second, out, fp32_accumulate, stream) -> status
 PyObject* gemm(PyObject*, PyObject* const* v, Py_ssize_t n) {
-    return or_none([&]() -> PyObject* {
-        gemm_t f;
-        int64_t M, N, K;
-        int layout, fp32;
-        void *a, *b, *c, *s;
-        if (n != 10 || !address(v[0], &f) || !integer(v[1], &M) || !integer(v[2], &N) || !integer(v[3], &K) || !choice(v[4], kModes, &layout) ||
-            !tensor(v[5], &a) || !tensor(v[6], &b) || !tensor(v[7], &c) || !small_integer(v[8], &fp32) || !current_or_handle(v[9], &s))
-            Py_RETURN_NONE;
-        return status([&] { return f(M, N, K, layout, a, b, c, fp32, s); });
-    });
+    gemm_t f;
+    int64_t M, N, K;
+    int layout, fp32;
+    void *a, *b, *c, *s;
+    if (!taken([&] {
+            return n == 10 && address(v[0], &f) && integer(v[1], &M) && integer(v[2], &N) && integer(v[3], &K) && choice(v[4], kModes, &layout) &&
+                   tensor(v[5], &a) && tensor(v[6], &b) && tensor(v[7], &c) && small_integer(v[8], &fp32) && current_or_handle(v[9], &s);
+        }))
+        Py_RETURN_NONE;
+    return status([&] { return f(M, N, K, layout, a, b, c, fp32, s); });
 }
 
 // (entry point, op, M, N, K, first, second, out, second_restored or None, fp32_accumulate, stream) -> the mode that ran, or a status below 0.
 // Without scratch memory.
 PyObject* tuned(PyObject*, PyObject* const* v, Py_ssize_t n) {
-    return or_none([&]() -> PyObject* {
-        tuned_t f;
-        int64_t M, N, K;
-        int op, fp32;
-        void *a, *b, *c, *restored = nullptr, *s;
-        if (n != 11 || !address(v[0], &f) || !choice(v[1], kOps, &op) || !integer(v[2], &M) || !integer(v[3], &N) || !integer(v[4], &K) || !tensor(v[5], &a) ||
-            !tensor(v[6], &b) || !tensor(v[7], &c) || (v[8] != Py_None && !tensor(v[8], &restored)) || !small_integer(v[9], &fp32) ||
-            !current_or_handle(v[10], &s))
-            Py_RETURN_NONE;
-        return status([&] {
-            int used = -1;
-            const int rc = f(op, M, N, K, a, b, c, restored, nullptr, 0, fp32, s, &used);
-            return rc == 0 ? used : rc;
-        });
+    tuned_t f;
+    int64_t M, N, K;
+    int op, fp32;
+    void *a, *b, *c, *restored = nullptr, *s;
+    if (!taken([&] {
+            return n == 11 && address(v[0], &f) && choice(v[1], kOps, &op) && integer(v[2], &M) && integer(v[3], &N) && integer(v[4], &K) && tensor(v[5], &a) &&
+                   tensor(v[6], &b) && tensor(v[7], &c) && (v[8] == Py_None || tensor(v[8], &restored)) && small_integer(v[9], &fp32) &&
+                   current_or_handle(v[10], &s);
+        }))
+        Py_RETURN_NONE;
+    return status([&] {
+        int used = -1;
+        const int rc = f(op, M, N, K, a, b, c, restored, nullptr, 0, fp32, s, &used);
+        return rc == 0 ? used : rc;
     });
 }
 
 // (entry point, rows, cols, src, dst, stream) -> status
 PyObject* transpose(PyObject*, PyObject* const* v, Py_ssize_t n) {
-    return or_none([&]() -> PyObject* {
-        transpose_t f;
-        int64_t rows, cols;
-        void *src, *dst, *s;
-        if (n != 6 || !address(v[0], &f) || !integer(v[1], &rows) || !integer(v[2], &cols) || !tensor(v[3], &src) || !tensor(v[4], &dst) ||
-            !current_or_handle(v[5], &s))
-            Py_RETURN_NONE;
-        return status([&] { return f(rows, cols, src, dst, s); });
-    });
+    transpose_t f;
+    int64_t rows, cols;
+    void *src, *dst, *s;
+    if (!taken([&] {
+            return n == 6 && address(v[0], &f) && integer(v[1], &rows) && integer(v[2], &cols) && tensor(v[3], &src) && tensor(v[4], &dst) &&
+                   current_or_handle(v[5], &s);
+        }))
+        Py_RETURN_NONE;
+    return status([&] { return f(rows, cols, src, dst, s); });
 }
 
 template <class F>

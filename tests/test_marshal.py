@@ -1,4 +1,7 @@
 """The native marshalling of binding.py's calls: what it takes runs as the general path does, anything else is left to that."""
+import ctypes
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -23,6 +26,21 @@ def test_other_arguments_are_left_to_the_general_path(at, value):
     args[at] = value
     assert _is_left(B._gemm, *args) and _is_left(B._gemm, *args[:-1]) and _is_left(B._gemm, *args, 0)
     assert _is_left(B._transpose, B._transpose_at, 8, 8, cpu, cpu, 0) and _is_left(B._tuned, B._tuned_at, "fwd", 8, 8, 8, cpu, cpu, cpu, None, 1, 0)
+
+
+@pytest.mark.gpu
+def test_an_exception_out_of_the_entry_point_is_raised_once(tmp_path):
+    """It becomes a Python error, with the interpreter held again, and the call does not go the general way a second time."""
+    src, so = tmp_path / "throws.cpp", str(tmp_path / "throws.so")
+    src.write_text('#include <stdexcept>\n#include <stdint.h>\nstatic int n = 0;\nextern "C" int calls() { return n; }\n'
+                   'extern "C" int gemm(int64_t, int64_t, int64_t, int, const void*, const void*, void*, int, void*) { ++n; throw std::runtime_error("no room"); }\n')
+    subprocess.run(["g++", "-shared", "-fPIC", str(src), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    t = torch.zeros(3, 8, 8, dtype=torch.bfloat16, device="cuda")
+    B.lib()
+    with pytest.raises(RuntimeError, match="no room"):
+        B._gemm(ctypes.cast(lib.gemm, ctypes.c_void_p).value, 8, 8, 8, "NN", t[0], t[1], t[2], 1, 0)
+    assert lib.calls() == 1
 
 
 def _operands():
