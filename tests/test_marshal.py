@@ -11,21 +11,67 @@ from paper_2502_08145_amd import binding as B
 M, N, K = 96, 72, 136
 
 
-def _is_left(call, *args):
+I64, INT, PTR = ctypes.c_int64, ctypes.c_int, ctypes.c_void_p
+GEMM_T = ctypes.CFUNCTYPE(INT, I64, I64, I64, INT, PTR, PTR, PTR, INT, PTR)
+TUNED_T = ctypes.CFUNCTYPE(INT, INT, I64, I64, I64, PTR, PTR, PTR, PTR, PTR, ctypes.c_size_t, INT, PTR, ctypes.POINTER(INT))
+TRANSPOSE_T = ctypes.CFUNCTYPE(INT, I64, I64, PTR, PTR, PTR)
+# what one place takes no other of: (place's kind, values that are left to the general path)
+LEFT = {"entry": [0, None, 1.0], "size": [8.0, np.int64(8), True, 1 << 70, "8"], "name": ["XX", b"NN", 1 << 40, None, 1.0],
+        "flag": [True, 1.0, 1 << 40], "stream": ["stream", 1 << 80, True, 1.0]}
+
+
+def test_tensors_off_the_device_are_left_to_the_general_path():
+    """Nothing runs: the entry points' addresses are not followed."""
     B.lib()
-    return call(*args) is None
-
-
-@pytest.mark.parametrize("at,value", [(0, 0), (0, None), (1, 8.0), (1, np.int64(8)), (1, True), (1, 1 << 70), (4, "XX"), (4, b"NN"), (4, 1 << 40),
-                                      (5, None), (5, 4096), (5, torch.zeros(8, 8)), (5, torch.zeros(8, 8, dtype=torch.bfloat16)),
-                                      (5, torch.nn.Parameter(torch.zeros(8, 8, dtype=torch.bfloat16))), (8, True), (8, 1.0), (9, "stream"), (9, 1 << 80)])
-def test_other_arguments_are_left_to_the_general_path(at, value):
-    """Nothing runs: the entry point's address is not followed (the tensors are not on a device)."""
     cpu = torch.zeros(8, 8, dtype=torch.bfloat16)
-    args = [B._fwd_at, 8, 8, 8, "NN", cpu, cpu, cpu, 1, 0]
-    args[at] = value
-    assert _is_left(B._gemm, *args) and _is_left(B._gemm, *args[:-1]) and _is_left(B._gemm, *args, 0)
-    assert _is_left(B._transpose, B._transpose_at, 8, 8, cpu, cpu, 0) and _is_left(B._tuned, B._tuned_at, "fwd", 8, 8, 8, cpu, cpu, cpu, None, 1, 0)
+    assert B._gemm(B._fwd_at, 8, 8, 8, "NN", cpu, cpu, cpu, 1, 0) is None
+    assert B._tuned(B._tuned_at, "fwd", 8, 8, 8, cpu, cpu, cpu, None, 1, 0) is None
+    assert B._transpose(B._transpose_at, 8, 8, cpu, cpu, 0) is None
+
+
+class Tagged(torch.Tensor):
+    pass
+
+
+def _calls(t, entry):
+    """(function, its C type, arguments that it takes, the kind of each, what the entry point then gets)."""
+    x, y, z = (t[i] for i in range(3))
+    p, q, r = (i.data_ptr() for i in (x, y, z))
+    return [(B._gemm, GEMM_T, [entry, 8, 9, 10, "NT", x, y, z, 1, 77], "entry size size size name tensor tensor tensor flag stream", (8, 9, 10, 1, p, q, r, 1, 77)),
+            (B._tuned, TUNED_T, [entry, "bwd_weight", 8, 9, 10, x, y, z, x, 1, 77], "entry name size size size tensor tensor tensor tensor flag stream",
+             (2, 8, 9, 10, p, q, r, p, None, 0, 1, 77)),
+            (B._transpose, TRANSPOSE_T, [entry, 8, 9, x, y, 77], "entry size size tensor tensor stream", (8, 9, p, q, 77))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", [0, 1, 2])
+def test_only_plain_arguments_reach_the_entry_point(which):
+    """With an entry point that records its calls: the arguments as they stand reach it, and not with any one of them of another kind."""
+    B.lib()
+    seen = []
+    t = torch.zeros(3, 8, 8, dtype=torch.bfloat16, device="cuda")
+    _, ctype, *_ = _calls(t, 1)[which]
+    record = ctype(lambda *args: seen.append(args) or -7)
+    call, _, args, kinds, want = _calls(t, ctypes.cast(record, PTR).value)[which]
+    assert call(*args) == -7 and len(seen) == 1 and seen[0][:len(want)] == want
+    left = {**LEFT, "tensor": [4096, t[0].cpu(), t[0].float(), t[0].as_subclass(Tagged), t[0].t()[:, :4], "x"] + ([] if which == 1 else [None])}
+    for i, kind in enumerate(kinds.split()):
+        for value in left[kind]:
+            assert call(*args[:i], value, *args[i + 1:]) is None, (i, value)
+    assert call(*args[:-1]) is None and call(*args, 0) is None
+    if which == 1:
+        for i in (5, 6, 7):
+            assert call(*args[:i], None, *args[i + 1:]) is None
+    assert len(seen) == 1
+    i = kinds.split().index("tensor")   # a parameter is a plain tensor
+    assert call(*args[:i], torch.nn.Parameter(args[i]), *args[i + 1:]) == -7 and seen[-1][:len(want)] == want
+    # no stream: the current one.  Names and numbers are the same.
+    assert call(*args[:-1], None) == -7 and (seen[-1][8 if which == 0 else 11 if which == 1 else 4] or 0) == torch.cuda.current_stream().cuda_stream
+    if which < 2:
+        i = kinds.split().index("name")
+        assert call(*args[:i], want[3 if which == 0 else 0], *args[i + 1:]) == -7 and seen[-1][:len(want)] == want
+    if which == 1:   # the re-stored operand is optional
+        assert call(*args[:8], None, *args[9:]) == -7 and seen[-1][7] is None
 
 
 @pytest.mark.gpu
@@ -39,7 +85,7 @@ def test_an_exception_out_of_the_entry_point_is_raised_once(tmp_path):
     t = torch.zeros(3, 8, 8, dtype=torch.bfloat16, device="cuda")
     B.lib()
     with pytest.raises(RuntimeError, match="no room"):
-        B._gemm(ctypes.cast(lib.gemm, ctypes.c_void_p).value, 8, 8, 8, "NN", t[0], t[1], t[2], 1, 0)
+        B._gemm(ctypes.cast(lib.gemm, PTR).value, 8, 8, 8, "NN", t[0], t[1], t[2], 1, 0)
     assert lib.calls() == 1
 
 
