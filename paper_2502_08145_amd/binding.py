@@ -11,6 +11,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch  # noqa: F401  (imported before the library so both share one HIP runtime)
 
@@ -161,12 +162,18 @@ def lib() -> ctypes.CDLL:
 
 
 def _load_marshal(L) -> None:
+    """The extension only saves host time, so without it every call takes the general path, and says so: it is built against one torch."""
     global _gemm, _tuned, _transpose, _fwd_at, _bwd_data_at, _bwd_weight_at, _static_at, _tuned_at, _transpose_at
-    if not os.path.exists(MARSHAL_PATH):
-        raise ImportError(f"{MARSHAL_PATH} is missing: build it with `python -m paper_2502_08145_amd.build`")
-    loader = importlib.machinery.ExtensionFileLoader("axonn_marshal", MARSHAL_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("axonn_marshal", loader))
-    loader.exec_module(module)
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("axonn_marshal", MARSHAL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("axonn_marshal", loader))
+        loader.exec_module(module)
+        built_for = getattr(module, "torch_version", None)
+        if built_for != torch.__version__:
+            raise ImportError(f"{MARSHAL_PATH} was built for torch {built_for}, this is {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"calls are marshalled in Python, 1.4 us more each: {e}; build the extension with `python -m paper_2502_08145_amd.build`", RuntimeWarning)
+        return
     _fwd_at, _bwd_data_at, _bwd_weight_at, _static_at, _tuned_at, _transpose_at = (
         ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in
         ("axonn_linear_fwd", "axonn_linear_bwd_data", "axonn_linear_bwd_weight", "axonn_linear_gemm_static",

@@ -72,6 +72,7 @@ def marshal_command(out: str = MARSHAL):
     import torch
     root = os.path.dirname(torch.__file__)
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DAXONN_TORCH_VERSION="{torch.__version__}"',
             "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
             "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
             "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc())), "include"),
@@ -87,11 +88,12 @@ def build(verbose: bool = False, extra=(), units=None, out: str = LIB) -> str:
     units = list(units or UNITS)
     objs = [os.path.join(OBJ_DIR, u.replace(".hip", ".o")) for u in units]
     cmds = [[cc, *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, u), "-o", o] for u, o in zip(units, objs)]
-    if out == LIB:
-        cmds.append(marshal_command())
-    with ThreadPoolExecutor(max_workers=min(len(cmds), os.cpu_count() or 1)) as ex:
+    with ThreadPoolExecutor(max_workers=min(len(cmds) + 1, os.cpu_count() or 1)) as ex:
+        marshal = ex.submit(lambda: _run(marshal_command(), verbose)) if out == LIB else None
         list(ex.map(lambda c: _run(c, verbose), cmds))
     _run([cc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", out], verbose)
+    if marshal:
+        marshal.result()   # the library does not need it
     return out
 
 

@@ -162,4 +162,12 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "axonn_marshal", nullptr, -1, kMet
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_axonn_marshal() { return PyModule_Create(&kModule); }
+PyMODINIT_FUNC PyInit_axonn_marshal() {
+    PyObject* const m = PyModule_Create(&kModule);
+    // torch's classes are read by the layout that they had here
+    if (m && PyModule_AddStringConstant(m, "torch_version", AXONN_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,5 +1,6 @@
 """The native marshalling of binding.py's calls: what it takes runs as the general path does, anything else is left to that."""
 import ctypes
+import importlib.util
 import subprocess
 
 import numpy as np
@@ -156,3 +157,30 @@ def test_tuned_calls_and_transposes():
     finally:
         B.axonn_linear_tune_reset()
     assert B.axonn_linear_tuned_call("fwd", M, -1, K, x, y, c, check=False) == B.AXONN_ERR_INVALID_ARG
+
+
+def test_the_extension_is_there():
+    B.lib()
+    assert type(B._gemm) is type(B._tuned) is type(B._transpose) is type(len)
+
+
+@pytest.mark.parametrize("why", ["missing", "unreadable", "another torch"])
+def test_without_the_extension_every_call_takes_the_general_path(why, tmp_path, monkeypatch):
+    """Queries, addresses and errors as with it, and a warning."""
+    spec = importlib.util.spec_from_file_location("binding_alone", B.__file__)
+    alone = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(alone)
+    if why == "another torch":
+        monkeypatch.setattr(torch, "__version__", "0.0")
+    else:
+        alone.MARSHAL_PATH = str(tmp_path / "axonn_marshal.so")
+    if why == "unreadable":
+        (tmp_path / "axonn_marshal.so").write_bytes(b"not a library")
+    with pytest.warns(RuntimeWarning, match="in Python"):
+        alone.lib()
+    assert alone.kernel_name(1024, 3072, 3072, "NT") == B.kernel_name(1024, 3072, 3072, "NT")
+    assert alone.axonn_linear_fwd(0, 8, 8, "NT", 0, 0, 0, stream=0) == B.AXONN_OK
+    with pytest.raises(alone.AxonnError):
+        alone.axonn_linear_fwd(8, 8, 8, "NN", 0, 0, 0, stream=0)
+    with pytest.raises(TypeError):
+        alone.axonn_linear_fwd(8, 8, 8, "NN", torch.zeros(8, 8), 0, 0, stream=0)
