@@ -251,7 +251,8 @@ int axonn_linear_version(void);
 
 /* Caller-owned split-K scratch.  axonn_linear_workspace_bytes: what the variants that this problem is planned with
  * need (0: none; otherwise at least the 4 KiB + 256 KiB that axonn_linear_set_workspace accepts).  In a
- * larger area some run faster, in more K ranges (up to 4 KiB + 32 MiB per product, axonn_linear_part_kernel with now = 1).  A block that
+ * larger area some run faster, in more K ranges (axonn_linear_part_kernel with now = 1): one that holds every product's own need and
+ * axonn_linear_static_scratch_bytes() is enough for all of them.  A block that
  * runs on a kernel without scratch all the same (axonn_linear_part_kernel) touches none of it, registered or not.
  * axonn_linear_set_workspace: use `bytes` bytes at the
  * DEVICE pointer `dev_ptr` (256-byte aligned) as the current device's scratch area from now on; the

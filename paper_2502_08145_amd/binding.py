@@ -172,7 +172,7 @@ def _load_marshal(L) -> None:
         if built_for != torch.__version__:
             raise ImportError(f"{MARSHAL_PATH} was built for torch {built_for}, this is {torch.__version__}")
     except ImportError as e:
-        warnings.warn(f"calls are marshalled in Python, 1.4 us more each: {e}; build the extension with `python -m paper_2502_08145_amd.build`", RuntimeWarning)
+        warnings.warn(f"calls are marshalled in Python, 2 us more each: {e}; build the extension with `python -m paper_2502_08145_amd.build`", RuntimeWarning)
         return
     _fwd_at, _bwd_data_at, _bwd_weight_at, _static_at, _tuned_at, _transpose_at = (
         ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in

@@ -365,6 +365,7 @@ struct OperandMNContig {   // global P[k * ld + row]
 // slots to its own accumulators in range order and writes C, so the result does not depend on timing.
 // Writers never wait and have the lower workgroup ids on every XCD, so they are dispatched before the
 // readers that depend on them and a reader's wait always ends; the wait is bounded anyway.
+// (The eight-wave kernel has an exchange of its own, in which nothing depends on a wait: split_exchange.hpp.)
 struct SplitK {
     float* partials;      // [(splits-1) * tiles] slots of BM*BN floats, in accumulator order
     uint32_t* flags;      // [(splits-1) * tiles]; a slot is valid when its flag equals `epoch`; the reader resets it to 0

@@ -105,7 +105,7 @@ struct GroupKContig {   // global P[row * ld + k]; LDS [row][64 k], 16-byte chun
 };
 
 // The same for rows that start anywhere on 16 bytes (a K that is no multiple of 64): every load is still 8 whole lines.  Loaded by k,
-// each row's 128 bytes of a stage lie across two lines, each line is fetched for two stages, and a step takes up to twice as long.
+// each row's 128 bytes of a stage lie across two lines, each line is fetched for two stages, and a step takes up to 1.6 times as long.
 // Here a row that starts s pieces into its line has its last s pieces of every 64 k fetched one stage later, with the rest of
 // their line: stage l holds, at the place of piece c, the one of 64 k number l, or, where c + s >= 8, of number l - 1.  An iteration
 // reads its own stage and the next one; there is one more stage than iterations, of late pieces only.

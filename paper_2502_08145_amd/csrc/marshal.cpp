@@ -1,9 +1,10 @@
 // The marshalling of binding.py's calls on the hot path, natively: exact Python ints, bf16 device tensors, mode names and the current stream
-// to the arguments of the C entry points.  Whatever else a caller may pass (a tensor subclass, a raw address, a stream object, a numpy integer, a tensor
+// to the arguments of the C entry points.  Whatever else a caller may pass (a tensor subclass other than a parameter, a raw address, a stream object, a numpy integer, a tensor
 // that is refused) is answered with None, and binding.py takes its general path, which raises what there is to raise.
 //
-// What it is for: the launch itself takes 2.8 us on the host, the same marshalling in Python and ctypes took 2.6 more, 0.25 of it per
-// tensor and 0.37 for the stream; a product of less than 6 us on the GPU was bound by it.
+// What it is for: the launch itself takes 2.8 us on the host, the same marshalling in Python and ctypes takes 2.6 more, 0.25 of it per
+// tensor and 0.37 for the stream; a product of less than 6 us on the GPU is bound by it.  The three products of a layer of 256 tokens, 512 -> 512:
+// 18.6 us the general way, 12.7 here; of 1024 tokens, 512 -> 2048, where the kernels take 6 us each, 17.9 and 17.6.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>

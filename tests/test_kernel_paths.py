@@ -320,6 +320,25 @@ def test_an_area_of_the_advertised_size_runs_the_planned_variant(oracle_mod):
 
 
 @pytest.mark.gpu
+def test_an_area_of_the_static_one_s_size_is_enough_for_the_eight_wave_kernel():
+    B.register_workspace()
+    products = [(*shape, layout) for (_, layout), shape in eight_wave_split_products().items()]
+    rng = random.Random(19)   # large ones as well: names alone
+    products += [(_log_int(rng, 128, 4096, 128), _log_int(rng, 128, 16384, 128), _log_int(rng, 512, 32000, 64), rng.choice(LAYOUTS)) for _ in range(2000)]
+    wide = {p: B.kernels(*p, now=True) for p in products}
+    try:
+        need = max([B.axonn_linear_workspace_bytes(*p) for p in products] + [B.axonn_linear_static_scratch_bytes()])
+        for size in (B.axonn_linear_static_scratch_bytes(), need):
+            area = torch.zeros((size,), dtype=torch.uint8, device="cuda")
+            B.axonn_linear_set_workspace(area)
+            for p in products:
+                if B.axonn_linear_workspace_bytes(*p) <= size:
+                    assert B.kernels(*p, now=True) == wide[p], p
+    finally:
+        B.register_workspace()
+
+
+@pytest.mark.gpu
 def test_a_ragged_layer_s_data_gradient(oracle_mod):
     _check(oracle_mod, 1064, 1608, 4168, "NT", ["mfma16k64g_64x128_ktail"])
 
