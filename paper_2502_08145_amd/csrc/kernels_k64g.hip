@@ -92,16 +92,19 @@ double group_us(int bm, int bn, int groups, int layout, int64_t m, int64_t n, in
     return t ? model_us(*t, layout, m, n, K, lda, ldb, ldc) : -1.0;
 }
 
-// Where tiles of 96 and 192 rows are there: within the range that the model was fitted over.  Beyond a round of workgroups over a short K it is 5 to
+// Tiles of 96 and 192 rows: by how much more than modelled they count; < 0: not there.  Within the range that the model was fitted over.  Beyond a round of workgroups over a short K it is 5 to
 // 13 % short (9344 x 9344 x 384 TN 73 us on 256 x 256 tiles, 83 here; 1920 x 12416 x 512 27 and 29, 1536 x 6272 x 640 16.4 and 17.1; in one round
 // 1280 x 3712 x 384 TN 8.2 us on 256 x 128 and 7.3 here).
 // TN in more than one round: not there.  256 x 256 tiles read an eighth less in their two rounds (23 such products: 0.988 here, 1152 x 7680 x 1152 26.2 us
 // there and 27.6 here), while in one round 62 TN products run 1.07 to 1.14 times as fast.
-// Rows of the output off 128-byte lines make no difference: 750 products that go to these tiles by up to 15 % of modelled time run 1.06 (NN), 1.10 (NT)
-// and 1.07 (TN) times as fast here, 1.03 to 1.08 those within 2 % of a tie (1064 x 4168 x 1608 NT 26.4 us on 128 x 256 tiles, 22.2 on 192 x 128).
-static bool between_fits(const GroupTile& t, int layout, int64_t m, int64_t n, int64_t K) {
+// Rows of the output off 128-byte lines make no difference in one round: 750 products that go to these tiles by up to 15 % of modelled time run 1.06 (NN),
+// 1.10 (NT) and 1.07 (TN) times as fast here, 1.03 to 1.08 those within 2 % of a tie (1064 x 4168 x 1608 NT 26.4 us on 128 x 256 tiles, 22.2 on 192 x 128).
+// In NT beyond a round 192 x 128 has to be 15 % ahead there: eleven such products on 256 x 256 tiles run 1.06 times as fast here with operands in
+// cache and 0.91 times from memory (3859 x 2888 x 5760 124 and 116 us, from memory 111 and 123).
+static double between_margin(const GroupTile& t, int layout, int64_t m, int64_t n, int64_t K, int64_t ldc) {
     const int64_t wgs = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn);
-    return K >= 320 && (wgs <= 256 || (K >= 640 && layout != 2)) && m * n <= (int64_t)16 << 20;
+    if (K < 320 || (wgs > 256 && (K < 640 || layout == 2)) || m * n > (int64_t)16 << 20) return -1.0;
+    return wgs > 256 && layout == 1 && t.bm == 192 && ldc % 64 != 0 ? 1.15 : 1.0;
 }
 
 GroupChoice group_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
@@ -109,9 +112,9 @@ GroupChoice group_choose(int layout, int64_t m, int64_t n, int64_t K, int64_t ld
     for (int i = 0; i < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++i) {
         const GroupTile& t = kTiles[i];
         if (t.groups == 1 && t.bm % 128 == 0 && t.bn % 128 == 0) continue;   // variants of their own
-        if (t.bm % 96 == 0 && !between_fits(t, layout, m, n, K)) continue;
-        const double us = model_us(t, layout, m, n, K, lda, ldb, ldc);
-        if (us >= 0.0 && (best.tile < 0 || us < best.us)) best = GroupChoice{i, us};
+        const double margin = t.bm % 96 == 0 ? between_margin(t, layout, m, n, K, ldc) : 1.0;
+        const double us = margin * model_us(t, layout, m, n, K, lda, ldb, ldc);
+        if (margin > 0.0 && us >= 0.0 && (best.tile < 0 || us < best.us)) best = GroupChoice{i, us};
     }
     return best;
 }
